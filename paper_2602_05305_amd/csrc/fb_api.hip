@@ -47,6 +47,29 @@ float eff_scale(const fb_shape* s) { return s->scale > 0.f ? s->scale : 1.0f / s
 
 long long rows_of(const fb_shape* s) { return (long long)s->batch * s->n_q_heads * s->block_len; }
 
+// Scratch memory of fb_external_partial_builtin_ws: the split partials of one call.  One copy per GPU the
+// library runs on, held until the process ends.
+constexpr size_t kBuiltinWsBytes = (size_t)20 * 1024 * 1024;
+
+// Splits of the fp32 passes: workgroups of f32_row_tile rows, one per CU (their K/V stages take most of the LDS), so as
+// many splits as keep the workgroup count within 256 (one round); a split is at least one tile.  The split partials are
+// kept within the built-in scratch array, so that more splits than a shape used to have never make it too large for
+// fb_external_partial_builtin_ws.  per_head: the passes whose workgroups belong to one query head.
+int f32_splits(const fb_shape* s, bool per_head) {
+  const int tiles = (s->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile;
+  const long long nrows = per_head ? s->block_len : (long long)(s->n_q_heads / s->n_kv_heads) * s->block_len;
+  const long long rt = fb::f32_row_tile(nrows);
+  const long long groups = (long long)s->batch * (per_head ? s->n_q_heads : s->n_kv_heads) * ((nrows + rt - 1) / rt);
+  long long ns = 256 / groups;
+  const long long split_bytes = rows_of(s) * (s->head_dim + 2) * (long long)sizeof(float);
+  const long long fit = (long long)(kBuiltinWsBytes - 4096) / split_bytes - 1;    // + the block-internal set; alignment
+  if (ns > fit) ns = fit;
+  if (ns > tiles) ns = tiles;
+  if (ns > FB_MAX_SPLITS) ns = FB_MAX_SPLITS;
+  if (ns < 1) ns = 1;
+  return (int)ns;
+}
+
 int auto_splits(const fb_shape* s, int active_heads = 0) {
   const int tiles = (s->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile;
   if (s->dtype == FB_BF16 && active_heads > 0 && active_heads < s->n_q_heads) {
@@ -88,17 +111,16 @@ int auto_splits(const fb_shape* s, int active_heads = 0) {
     if (ns < 1) ns = 1;
     return (int)ns;
   }
-  const long long groups =
-      (long long)s->batch * s->n_q_heads * ((s->block_len + fb::kRowsPerWgF32 - 1) / fb::kRowsPerWgF32);
-  long long ns = (1024 + groups - 1) / groups;
-  if (ns > tiles) ns = tiles;
-  if (ns > FB_MAX_SPLITS) ns = FB_MAX_SPLITS;
-  if (ns < 1) ns = 1;
-  return (int)ns;
+  return f32_splits(s, false);
 }
 
 // Split counts of the sparse passes (bf16): one workgroup per CU in both modes - 8 wavefronts in
 // the reuse pass, 4 wavefronts with two accumulator sets in the refresh pass.
+// Splits of the per-head refresh: the fp32 pass runs one query head per workgroup.
+int heads_splits(const fb_shape* s, int active_heads) {
+  return s->dtype == FB_BF16 ? auto_splits(s, active_heads) : f32_splits(s, true);
+}
+
 // Splits of the plain dense external pass.  KV groups above 128 rows run 256-row, 8-wavefront workgroups, one per
 // CU: as many splits as keep the workgroup count within the 256 CUs (one round), each with at least 8 tiles.
 int dense_splits(const fb_shape* s) {
@@ -116,7 +138,7 @@ int dense_splits(const fb_shape* s) {
 
 int sparse_splits(const fb_shape* s, bool refresh) {
   (void)refresh;
-  if (s->dtype != FB_BF16) return auto_splits(s);
+  if (s->dtype != FB_BF16) return f32_splits(s, true);
   const int tiles = (s->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile;
   const int G = s->n_q_heads / s->n_kv_heads;
   const long long groups =
@@ -266,7 +288,7 @@ int32_t fb_paged_splits(const fb_shape* shape) {
 size_t fb_workspace_bytes(const fb_shape* shape, int32_t key_block, int32_t topk, int32_t n_splits) {
   if (check_shape(shape) != FB_OK) return 0;
   if (n_splits < 0 || n_splits > FB_MAX_SPLITS) return 0;
-  const int ns = n_splits > 0 ? n_splits : std::max(auto_splits(shape), dense_splits(shape));
+  const int ns = n_splits > 0 ? n_splits : std::max({auto_splits(shape), dense_splits(shape), heads_splits(shape, 0)});
   size_t t = ws_layout(shape, ns, 2, 0, 1).total;   // + one block-internal partial for fb_refresh_step
   if (key_block != 0) {
     int nblk = 0;
@@ -311,7 +333,7 @@ fb_status external_partial_impl(const fb_shape* shape, const void* q, const void
   if (n_active_heads < 0) return FB_ERR_SHAPE;
   const int ns = n_splits > 0 ? n_splits
                              : (paged ? paged_splits(shape)
-                                      : use_head_mask ? auto_splits(shape, n_active_heads) : dense_splits(shape));
+                                      : use_head_mask ? heads_splits(shape, n_active_heads) : dense_splits(shape));
   const WsLayout w = ws_layout(shape, ns, 1, 0);
   if (!workspace || workspace_bytes < w.total) return FB_ERR_WORKSPACE;
 
@@ -373,7 +395,7 @@ fb_status fb_external_partial_prof(const fb_shape* shape, const void* q, const v
 
 int32_t fb_external_heads_splits(const fb_shape* shape, int32_t n_active_heads) {
   if (check_shape(shape) != FB_OK || n_active_heads < 0) return 0;
-  return auto_splits(shape, n_active_heads);
+  return heads_splits(shape, n_active_heads);
 }
 
 fb_status fb_external_partial_heads(const fb_shape* shape, const void* q, const void* k_prefix,
@@ -411,9 +433,6 @@ fb_status fb_external_partial(const fb_shape* shape, const void* q, const void* 
 
 namespace {
 
-// Scratch memory of fb_external_partial_builtin_ws: the split partials of one call.  One copy per GPU the
-// library runs on, held until the process ends.
-constexpr size_t kBuiltinWsBytes = (size_t)20 * 1024 * 1024;
 static __device__ __align__(256) unsigned char scratch[kBuiltinWsBytes];
 
 constexpr int kMaxDevices = 16;
@@ -506,11 +525,13 @@ fb_status fb_refresh_step_prof(const fb_shape* shape, const void* q, const void*
   // block's own keys are not streamed by the attention kernel at all (plain dense pass, with its split
   // count); one fold kernel (4 rows per workgroup) folds the splits, computes the rows' block-internal
   // attention and merges.
-  const bool small_block = shape->block_len <= fb::kMaxInlineBlock && shape->block_len % fb::kFoldRows == 0 &&
-                           dense_splits(shape) >= 8;
-  const int ns = small_block ? dense_splits(shape) : auto_splits(shape);
+  // (fp32: the block's own keys are one more workgroup of the pass, which then needs a place in the single round)
+  const bool small_block = shape->dtype == FB_BF16 && shape->block_len <= fb::kMaxInlineBlock &&
+                           shape->block_len % fb::kFoldRows == 0 && dense_splits(shape) >= 8;
+  const int ns = small_block ? dense_splits(shape) : std::max(1, auto_splits(shape) - (shape->dtype == FB_F32 ? 1 : 0));
   const WsLayout w = ws_layout(shape, ns, 2, 0, 1);
-  if (!workspace || workspace_bytes < w.total) return FB_ERR_WORKSPACE;
+  const size_t need = shape->dtype == FB_F32 ? fb_workspace_bytes(shape, 0, 0, 0) : w.total;
+  if (!workspace || workspace_bytes < need) return FB_ERR_WORKSPACE;
 
   hipStream_t stream = (hipStream_t)hip_stream;
   char* ws = (char*)workspace;

@@ -1,241 +1,416 @@
-// fp32 attention pass for gfx950: plain-FMA scores, wavefront-shuffle softmax statistics.
+// fp32 attention pass for gfx950: fp32 matrix instructions, wavefront-shuffle softmax statistics.
 //
-// Computes the per-row statistics of Eq. 3-4/6 (arxiv 2602.05305, Section 4.2) over a key
-// range, for storage type float.  This is the exactness path (max-abs 1e-5 against a float64
-// reference): scores are fp32 FMA chains, the running maximum is exact, and every reduction
-// has a fixed order, so results are bit-reproducible.
+// Computes the per-row statistics of Eq. 3-4/6 (arxiv 2602.05305, Section 4.2) over a key range, for storage
+// type float.  This is the exactness path (max-abs 1e-5 against a float64 reference): products and sums are fp32
+// (v_mfma_f32_16x16x4_f32), the running maximum is exact, and every reduction has a fixed order, so results are
+// bit-reproducible.
 //
-// Work decomposition: one workgroup = 4 wavefronts = 4 consecutive query rows of one query
-// head; grid = (row chunks, batch*Hq, splits).  Per 64-key tile the workgroup stages K in LDS
-// (row stride D+4 floats: conflict-free 128-bit reads), lane j of each wavefront scores key j
-// against its wavefront's query row, max/sum go through 6-step xor shuffles, and the value
-// accumulation has lanes own output columns (lane, lane+64) with p_j broadcast by readlane
-// while V rows are read coalesced from global memory (L1/L2 serve the 4 rows' re-reads).
+// What bounds it: the fp32 matrix rate (64 flop per clock and SIMD; 2 x 64 x 16 x D x 2 flop per 16 rows and tile), at
+// the smallest shapes the launch and one memory round trip.  Before this form the pass gave every query row a
+// wavefront and accumulated values by shuffle broadcasts: 32 x 128 rows against 4111 keys, head_dim 128, took 353 us.
+//
+// Work decomposition: one workgroup = WR x 4 wavefronts = WR*RB*16 rows x one range of 64-key tiles.  Wavefront
+// (wr, wk) owns rows [16 RB wr, +16 RB) and keys [16 wk, +16) of every tile; the four key quarters meet through LDS
+// after the last tile, each wavefront finishing a quarter of the output columns.  Four wavefronts along the keys keep
+// the smallest shapes (16 rows) as short as a tile of 64 keys allows; RB = 2 lets every K / V operand feed two MFMAs.
+// Rows are group-flattened (all query heads of a KV head share the K/V stream), except in the passes that select per
+// query head (per-head refresh, sparse), where a workgroup belongs to one query head and skips what the head skips:
+// an unselected key block is then never touched, whatever values it holds.
+// Per tile: S^T = K Q^T (A = K rows from LDS, B = Q^T in registers; lane l holds row l%16 and keys 4(l/16)..+3),
+//   O^T += V^T P^T with the lane's own probabilities as the B operand: the contraction index of a k-step is the key
+//   4(l/16) + r, so nothing moves between lanes.
+// Tiles go straight from global memory into two LDS stages (direct-to-LDS loads); the 16-byte chunks of a row are
+//   rotated on the global-address side (K: by the row, V: by the row rounded down to 4) so that both read patterns hit
+//   all 64 banks.
 #include "fb_kernels.h"
 
 namespace fb {
 namespace {
 
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
-  return x;
-}
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
 __device__ __forceinline__ float wave_sum(float x) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
   return x;
 }
 
-template <int NACC>
-struct RowState {
-  float m, l;
-  float acc[NACC];
+constexpr bool f32_per_head(int mode) {
+  return mode == kPassDenseHeads || mode == kPassSparseRefresh || mode == kPassSparseReuse;
+}
+
+template <int D, int RB, int WR>
+struct FCfg {
+  static constexpr int NW = 4 * WR, THREADS = 64 * NW;
+  static constexpr int ROWS = 16 * RB * WR;             // query rows of a workgroup
+  static constexpr int ROWB = D * 4, CPR = ROWB / 16;   // bytes and 16-byte chunks of a key row
+  static constexpr int OPB = kKeyTile * ROWB, STAGE = 2 * OPB;
+  static constexpr int NLOAD = OPB / (THREADS * 16);    // direct-to-LDS loads per lane, operand and tile
+  static constexpr int NQ = D / 16;                     // float4 query registers per row block
+  static constexpr int NDB = D / 16, NDBK = NDB / 4;    // 16-wide output column blocks; per finishing wavefront
+  static constexpr int RING = 2 * STAGE;
+  static constexpr int MERGE = NW * RB * (NDB * 1024 + 512);
+  static constexpr int LDS = RING > MERGE ? RING : MERGE;
+  static_assert(LDS <= 160 * 1024 && 2 * NLOAD <= 63, "LDS size and load counter");
+  __device__ static __forceinline__ int rot_k(int row) { return row; }
+  __device__ static __forceinline__ int rot_v(int row) { return row & ~3; }
+};
+
+// Running softmax state of a wavefront: RB blocks of 16 rows (row = lane%16; m is shared by the row's four lanes, l is
+// the lane's own share of the row sum), O^T with lane (row, g = lane/16) holding columns 16 db + 4 g .. +3.
+template <int RB, int NDB>
+struct FState {
+  float m[RB], l[RB];
+  f32x4 o[RB][NDB];
   __device__ __forceinline__ void init() {
-    m = -INFINITY;
-    l = 0.f;
 #pragma unroll
-    for (int i = 0; i < NACC; ++i) acc[i] = 0.f;
+    for (int rb = 0; rb < RB; ++rb) {
+      m[rb] = -INFINITY;
+      l[rb] = 0.f;
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) o[rb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
   }
 };
 
-// One online-softmax update of a row's state with the 64 scores held one per lane
-// (log2 domain; -inf marks keys outside the set).
-template <int D, int NACC>
-__device__ __forceinline__ void row_update(RowState<NACC>& st, float s, const float* __restrict__ V,
-                                           int k0, int nvalid, int lane) {
-  const float tmax = wave_max(s);
-  const float m_new = fmaxf(st.m, tmax);
-  const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-  const float p = exp2f(s - m_use);
-  const float alpha = exp2f(st.m - m_use);
-  st.l = st.l * alpha + wave_sum(p);
+template <int D, int RB, int WR>
+__device__ __forceinline__ void f32_tile(FState<RB, D / 16>& st, const f32x4 (&q)[RB][D / 16],
+                                         const unsigned char* __restrict__ stage, const uint32_t (&kaddr)[D / 16],
+                                         const uint32_t (&vaddr)[D / 16], float scale_log2, int key0, int nvalid) {
+  using C = FCfg<D, RB, WR>;
+  f32x4 s[RB];
 #pragma unroll
-  for (int i = 0; i < NACC; ++i) st.acc[i] *= alpha;
-  const float* vrow = V + (size_t)k0 * D + lane;
-  for (int j = 0; j < nvalid; ++j) {
-    const float pj = __shfl(p, j, 64);
+  for (int rb = 0; rb < RB; ++rb) s[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < NACC; ++i) st.acc[i] = fmaf(pj, vrow[(size_t)j * D + 64 * i], st.acc[i]);
+  for (int j = 0; j < C::NQ; ++j) {
+    const f32x4 a = *(const f32x4*)(stage + kaddr[j]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) s[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], q[rb][j][i], s[rb], 0, 0, 0);
   }
-  st.m = m_new;
+  // s[rb][r] = raw dot product of row lane%16 with key key0 + r of the tile (key0 includes the lane's 4 (lane/16))
+  if (nvalid < kKeyTile) {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (key0 + r >= nvalid) s[rb][r] = -INFINITY;
+  }
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    float tmax = fmaxf(fmaxf(s[rb][0], s[rb][1]), fmaxf(s[rb][2], s[rb][3])) * scale_log2;
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+    const float m_new = fmaxf(st.m[rb], tmax);
+    const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
+    const float alpha = __builtin_amdgcn_exp2f(st.m[rb] - m_use);
+    float lsum = 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      s[rb][r] = __builtin_amdgcn_exp2f(fmaf(s[rb][r], scale_log2, -m_use));
+      lsum += s[rb][r];
+    }
+    st.l[rb] = st.l[rb] * alpha + lsum;
+    st.m[rb] = m_new;
+    if (__any(alpha != 1.f)) {
+#pragma unroll
+      for (int db = 0; db < C::NDB; ++db)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) st.o[rb][db][r] *= alpha;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int db = 0; db < C::NDB; ++db) {
+      const float a = *(const float*)(stage + C::OPB + vaddr[db] + r * C::ROWB);
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+        st.o[rb][db] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, s[rb][r], st.o[rb][db], 0, 0, 0);
+    }
 }
 
-template <int D, int MODE>
-__global__ __launch_bounds__(256) void attn_f32_kernel(const PassParams p) {
-  constexpr int KSTR = D + 4;
-  constexpr int NACC = D / 64;
-  __shared__ __align__(16) float Ks[kKeyTile * KSTR];
-  __shared__ __align__(16) float Qs[4 * D];
+template <int D, int MODE, int RB, int WR>
+__global__ __launch_bounds__(256 * WR, 1) void attn_f32_kernel(const PassParams p) {
+  using C = FCfg<D, RB, WR>;
+  constexpr bool kPerHead = f32_per_head(MODE);
+  constexpr int NSETS = (MODE == kPassSparseRefresh) ? 2 : 1;
+  constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
+  extern __shared__ __align__(16) unsigned char ring[];
+  const int lane = threadIdx.x & 63, l16 = lane & 15, g4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int wk = wave & 3, wr = wave >> 2;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int chunk = blockIdx.x;
-  const int bh = blockIdx.y;
-  int b = bh / p.Hq;
-  const int h = bh % p.Hq;
+  // ---- workgroup -> (row tile, split, head, batch); each XCD gets a contiguous range so that row tiles and heads that
+  // share K/V share an L2 (ragged paged sequences are dealt round-robin instead)
+  int rt;
+  uint32_t rest;
   if constexpr (MODE == kPassDensePaged) {
-    if (p.seq_order != nullptr) b = p.seq_order[b];
+    const uint32_t j = blockIdx.x >> 3, xcd = blockIdx.x & 7;
+    const uint32_t jq = fastdiv(j, p.div_rowtiles);
+    rt = (int)(j - jq * p.div_rowtiles.d);
+    rest = jq * 8 + xcd;
+    if (rest >= (uint32_t)(p.B * p.Hkv * p.nsplit)) return;   // workgroup-uniform
+  } else {
+    const int bid = blockIdx.x, q8 = gridDim.x / 8, r8 = gridDim.x % 8, xcd = bid % 8;
+    const int w = (xcd < r8 ? xcd * (q8 + 1) : r8 * (q8 + 1) + (xcd - r8) * q8) + bid / 8;
+    rest = fastdiv((uint32_t)w, p.div_rowtiles);
+    rt = w - (int)(rest * p.div_rowtiles.d);
   }
-  const int kvh = h / p.G, g = h % p.G;
-  const int split = blockIdx.z;
-  const int row = chunk * 4 + wave;
-  const bool valid = row < p.Bq;
+  const uint32_t r2 = fastdiv(rest, p.div_nsplit);            // divisor: splits (+ 1 in the fused pass: the block's keys)
+  const int split = (int)(rest - r2 * p.div_nsplit.d);
+  int b = (int)fastdiv(r2, p.div_hkv);                        // divisor: query heads (per-head passes) or KV heads
+  const int unit_h = (int)(r2 - (uint32_t)b * p.div_hkv.d);
+  if constexpr (MODE == kPassDensePaged) {
+    if (p.seq_order != nullptr) b = sload(p.seq_order, b);
+  }
+  const int kvh = kPerHead ? unit_h / p.G : unit_h;
+  const int nrows = kPerHead ? p.Bq : p.G * p.Bq;
+  const size_t grow_base = (size_t)(b * p.Hq + (kPerHead ? unit_h : unit_h * p.G)) * p.Bq;
   if constexpr (MODE == kPassDenseHeads) {
-    if (p.head_on[bh] == 0) return;     // workgroup-uniform: this head keeps its cached partial
+    if (p.head_on[b * p.Hq + unit_h] == 0) return;            // this head keeps its cached partial
   }
-  int nkeys = p.nkeys;
-  if constexpr (MODE == kPassDensePaged) nkeys = min(p.nkeys, max(0, p.prefix_lens[b]));   // this sequence's prefix
   const int bk = b * p.Hkv + kvh;
-  // fused refresh pass: the workgroups of split index nsplit take the block's own keys
   const bool own_block = (MODE == kPassRefreshFused) && (split == p.nsplit);
-  if (own_block) nkeys = p.Bq;
+  int nkeys = own_block ? p.Bq : p.nkeys;
+  if constexpr (MODE == kPassDensePaged) nkeys = min(p.nkeys, max(0, sload(p.prefix_lens, b)));   // this sequence's prefix
 
-  const float* __restrict__ Q = (const float*)p.q + (size_t)(b * p.Hq + h) * p.Bq * D;
   // contiguous cache: this KV head's [nkeys, D] slab; paged cache: the pool (tiles add their page offset)
-  const float* __restrict__ K = (const float*)p.k + ((MODE == kPassDensePaged) ? (size_t)0 : (size_t)bk * nkeys * D);
-  const float* __restrict__ V = (const float*)p.v + ((MODE == kPassDensePaged) ? (size_t)0 : (size_t)bk * nkeys * D);
-  if (own_block) {
-    K = (const float*)p.k2 + (size_t)bk * nkeys * D;
-    V = (const float*)p.v2 + (size_t)bk * nkeys * D;
-  }
+  const size_t slab = (MODE == kPassDensePaged) ? (size_t)0 : (size_t)bk * nkeys * C::ROWB;
+  const unsigned char* __restrict__ Kg = (const unsigned char*)(own_block ? p.k2 : p.k) + slab;
+  const unsigned char* __restrict__ Vg = (const unsigned char*)(own_block ? p.v2 : p.v) + slab;
 
-  for (int i = tid; i < 4 * D; i += 256) {
-    const int r = chunk * 4 + i / D;
-    Qs[i] = (r < p.Bq) ? Q[(size_t)r * D + (i % D)] : 0.f;
-  }
-
-  // tile list of this workgroup
+  // ---- tile list; tiles that this workgroup's head sits out are never fetched
   int tpb = 1, total;
   if constexpr (MODE == kPassSparseReuse) {
     tpb = p.key_block / kKeyTile;
-    total = p.union_cnt[bk] * tpb;
+    total = sload(p.union_cnt, bk) * tpb;
   } else {
     total = (nkeys + kKeyTile - 1) / kKeyTile;
   }
-  TileRange tr = split_range(total, p.nsplit, split);
-  if (own_block) tr = TileRange{0, total};
-
-  RowState<NACC> sel, res;   // res only used by the sparse refresh pass
-  sel.init();
-  res.init();
-
-  for (int e = tr.begin; e < tr.end; ++e) {
+  TileRange tr = {0, total};
+  if (MODE != kPassInternal && !own_block) tr = split_range(total, p.nsplit, split);
+  struct Tile {
     int k0;
-    bool is_sel = true;
-    if constexpr (MODE == kPassSparseReuse) {
-      const int blk = p.union_list[(size_t)bk * p.nblk + e / tpb];
-      k0 = blk * p.key_block + kKeyTile * (e % tpb);
-      is_sel = (p.blk_mask[(size_t)bk * p.nblk + blk] >> g) & 1u;
-      if (!is_sel || k0 >= nkeys) continue;   // uniform over the workgroup
-    } else {
-      k0 = e * kKeyTile;
-      if constexpr (MODE == kPassSparseRefresh)
-        is_sel = (p.blk_mask[(size_t)bk * p.nblk + k0 / p.key_block] >> g) & 1u;
-    }
-    const float* Kt = K;
-    const float* Vt = V;
-    if constexpr (MODE == kPassDensePaged) {
-      // rebase so that key index k0 + r addresses row (k0 % page_size) + r of this head's slab of the page
-      const long long page = min(max(p.block_table[(size_t)b * p.max_pages + k0 / p.page_size], 0), p.num_pages - 1);
-      const long long off = ((page * p.Hkv + kvh) * p.page_size + (k0 % p.page_size) - k0) * D;
-      Kt = K + off;
-      Vt = V + off;
-    }
-    __syncthreads();   // all wavefronts are done with the previous K tile (and Qs is written)
-    for (int c = tid; c < kKeyTile * (D / 4); c += 256) {
-      const int r = c / (D / 4), c4 = c % (D / 4);
-      const int key = k0 + r;
-      float4 val = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (key < nkeys) val = *(const float4*)(Kt + (size_t)key * D + c4 * 4);
-      *(float4*)(Ks + r * KSTR + c4 * 4) = val;
-    }
-    __syncthreads();
-    if (valid) {
-      const float4* kr = (const float4*)(Ks + lane * KSTR);
-      const float4* qr = (const float4*)(Qs + wave * D);
-      float s = 0.f;
-#pragma unroll 8
-      for (int i = 0; i < D / 4; ++i) {
-        const float4 a = kr[i], c = qr[i];
-        s = fmaf(a.x, c.x, s);
-        s = fmaf(a.y, c.y, s);
-        s = fmaf(a.z, c.z, s);
-        s = fmaf(a.w, c.w, s);
+    bool is_sel;
+    size_t off;      // bytes from Kg / Vg
+  };
+  int e_next = tr.begin;
+  auto next_tile = [&](Tile& t) -> bool {
+    for (; e_next < tr.end; ++e_next) {
+      t.is_sel = true;
+      if constexpr (MODE == kPassSparseReuse) {
+        const int blk = sload(p.union_list + (size_t)bk * p.nblk, e_next / tpb);
+        t.k0 = blk * p.key_block + kKeyTile * (e_next % tpb);
+        const uint32_t mask = (uint32_t)sload(p.blk_mask + (size_t)bk * p.nblk, blk);
+        if (!((mask >> (unit_h - kvh * p.G)) & 1u) || t.k0 >= nkeys) continue;
+      } else {
+        t.k0 = e_next * kKeyTile;
+        if constexpr (MODE == kPassSparseRefresh) {
+          const uint32_t mask = (uint32_t)sload(p.blk_mask + (size_t)bk * p.nblk, t.k0 / p.key_block);
+          t.is_sel = ((mask >> (unit_h - kvh * p.G)) & 1u) != 0u;
+        }
       }
-      s *= p.scale_log2;
-      if (k0 + lane >= nkeys) s = -INFINITY;
-      const int nvalid = min(kKeyTile, nkeys - k0);
-      if (MODE == kPassSparseRefresh && !is_sel)
-        row_update<D, NACC>(res, s, Vt, k0, nvalid, lane);
-      else
-        row_update<D, NACC>(sel, s, Vt, k0, nvalid, lane);
+      if constexpr (MODE == kPassDensePaged) {
+        const int slot = (int)fastdiv((uint32_t)t.k0, p.div_page);
+        const int page = min(max(sload(p.block_table + (size_t)b * p.max_pages, slot), 0), p.num_pages - 1);
+        t.off = (((size_t)page * p.Hkv + kvh) * p.page_size + (t.k0 - slot * (int)p.div_page.d)) * C::ROWB;
+      } else {
+        t.off = (size_t)t.k0 * C::ROWB;
+      }
+      ++e_next;
+      return true;
     }
+    return false;
+  };
+
+  // ---- direct-to-LDS load slots: operand chunk (j*NW + wave)*64 + lane lives at LDS row chunk / CPR, position chunk % CPR
+  const uint32_t ring_base = (uint32_t)(uintptr_t)ring;
+  auto issue = [&](const Tile& t, int stage_i) {
+    const uint32_t base = ring_base + (uint32_t)stage_i * C::STAGE + wave * 1024;
+    const int last = min(kKeyTile, nkeys - t.k0) - 1;         // rows past the end read the last key (masked below)
+#pragma unroll
+    for (int j = 0; j < C::NLOAD; ++j) {
+      const int chunk = (j * C::NW + wave) * 64 + lane, r = chunk / C::CPR, pc = chunk % C::CPR;
+      dma16(Kg + t.off, (uint32_t)(min(r, last) * C::ROWB + ((pc - C::rot_k(r)) & (C::CPR - 1)) * 16),
+            base + j * C::NW * 1024);
+    }
+#pragma unroll
+    for (int j = 0; j < C::NLOAD; ++j) {
+      const int chunk = (j * C::NW + wave) * 64 + lane, r = chunk / C::CPR, pc = chunk % C::CPR;
+      dma16(Vg + t.off, (uint32_t)(min(r, last) * C::ROWB + ((pc - C::rot_v(r)) & (C::CPR - 1)) * 16),
+            base + C::OPB + j * C::NW * 1024);
+    }
+  };
+
+  Tile t0 = {0, true, 0}, t1 = {0, true, 0}, t2 = {0, true, 0};
+  bool have0 = next_tile(t0);
+  if (have0) issue(t0, 0);
+  // queries: rows past the end read the group's last row; what they compute is never stored
+  const int row0 = rt * C::ROWS + wr * 16 * RB;
+  f32x4 q[RB][C::NQ];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const float* qr = (const float*)p.q + (grow_base + min(row0 + 16 * rb + l16, nrows - 1)) * D + 4 * g4;
+#pragma unroll
+    for (int j = 0; j < C::NQ; ++j) q[rb][j] = *(const f32x4*)(qr + 16 * j);
+  }
+  // the wait for the queries belongs here: in the loop it would also wait for the tiles in flight
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int j = 0; j < C::NQ; ++j) asm volatile("" ::"v"(q[rb][j]));
+  bool have1 = have0 && next_tile(t1);
+  if (have1) issue(t1, 1);
+
+  // per-lane LDS read addresses inside a stage
+  uint32_t kaddr[C::NQ], vaddr[C::NDB];
+  {
+    const int krow = 16 * wk + l16, vrow = 16 * wk + 4 * g4;
+#pragma unroll
+    for (int j = 0; j < C::NQ; ++j) kaddr[j] = (uint32_t)(krow * C::ROWB + ((4 * j + g4 + C::rot_k(krow)) & (C::CPR - 1)) * 16);
+#pragma unroll
+    for (int db = 0; db < C::NDB; ++db)
+      vaddr[db] = (uint32_t)(vrow * C::ROWB + ((4 * db + (l16 >> 2) + C::rot_v(vrow)) & (C::CPR - 1)) * 16 + (l16 & 3) * 4);
   }
 
-  if (!valid) return;
-  const size_t grow = (size_t)(b * p.Hq + h) * p.Bq + row;
-  if constexpr (MODE == kPassInternal) {
-    // Eq. 8-9 with the cached pair expressed through (o, m, lse): A_out e^{L_out-M} = o e^{m-M}.
-    constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
-    float me2 = -INFINITY, le = 0.f;
-    if (p.ext_o != nullptr) {
-      const float me = p.ext_m[grow], lse = p.ext_lse[grow];
-      if (lse != -INFINITY) {
-        me2 = me * kLog2e;
-        le = exp2f((lse - me) * kLog2e);
+  FState<RB, C::NDB> sets[NSETS];
+#pragma unroll
+  for (int i = 0; i < NSETS; ++i) sets[i].init();
+
+  for (int t = 0; have0; ++t) {
+    if (have1) wait_vm<2 * C::NLOAD>();
+    else wait_vm<0>();
+    __syncthreads();
+    unsigned char* stage = ring + (t & 1) * C::STAGE;
+    const int nvalid = min(kKeyTile, nkeys - t0.k0);
+    if (nvalid < kKeyTile) {
+      // value rows past the end: a weight of 0 must not meet an infinity or NaN of the duplicated last key
+      for (int c = nvalid * C::CPR + (int)threadIdx.x; c < kKeyTile * C::CPR; c += C::THREADS)
+        *(f32x4*)(stage + C::OPB + c * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
+      __syncthreads();
+    }
+    const int key0 = 16 * wk + 4 * g4;
+    if (NSETS > 1 && !t0.is_sel)
+      f32_tile<D, RB, WR>(sets[NSETS - 1], q, stage, kaddr, vaddr, p.scale_log2, key0, nvalid);
+    else
+      f32_tile<D, RB, WR>(sets[0], q, stage, kaddr, vaddr, p.scale_log2, key0, nvalid);
+    const bool have2 = have1 && next_tile(t2);                // workgroup-uniform
+    if (have2) {
+      __syncthreads();                                        // every wavefront has left this stage
+      issue(t2, t & 1);
+    }
+    t0 = t1;
+    t1 = t2;
+    have0 = have1;
+    have1 = have2;
+  }
+
+  // ---- the four key quarters of a row block meet in LDS: records [wavefront][row block][column block][lane], then
+  // (m, l) per lane; wavefront wk finishes column blocks [wk*NDBK, +NDBK), folding the quarters in order
+#pragma unroll
+  for (int i = 0; i < NSETS; ++i) {
+    __syncthreads();
+    f32x4* rec_o = (f32x4*)ring;
+    float2* rec_ml = (float2*)(ring + C::NW * RB * C::NDB * 1024);
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      float l = sets[i].l[rb];
+      l += __shfl_xor(l, 16, 64);
+      l += __shfl_xor(l, 32, 64);
+#pragma unroll
+      for (int db = 0; db < C::NDB; ++db) rec_o[((wave * RB + rb) * C::NDB + db) * 64 + lane] = sets[i].o[rb][db];
+      rec_ml[(wave * RB + rb) * 64 + lane] = make_float2(sets[i].m[rb], l);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const int row = row0 + 16 * rb + l16;
+      const bool row_ok = row < nrows;
+      const size_t grow = grow_base + row;
+      float mq[4], lq[4], M = -INFINITY;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const float2 ml = rec_ml[((wr * 4 + w) * RB + rb) * 64 + lane];
+        mq[w] = ml.x;
+        lq[w] = ml.y;
+        M = fmaxf(M, ml.x);
       }
-    }
-    const float M2 = fmaxf(me2, sel.m);
-    const float Mu = (M2 == -INFINITY) ? 0.f : M2;
-    const float we = exp2f(me2 - Mu), wi = exp2f(sel.m - Mu);
-    const float den = le * we + sel.l * wi;
-    const float inv = den > 0.f ? 1.f / den : 0.f;
-    float* out = (float*)p.out + grow * D;
+      const float Mu = (M == -INFINITY) ? 0.f : M;
+      float l = 0.f;
+      f32x4 o[C::NDBK];
 #pragma unroll
-    for (int i = 0; i < NACC; ++i) {
-      float num = sel.acc[i] * wi;
-      if (le > 0.f) num = fmaf(p.ext_o[grow * D + lane + 64 * i], we, num);
-      out[lane + 64 * i] = num * inv;
-    }
-    if (p.lse_out != nullptr && lane == 0)
-      p.lse_out[grow] = den > 0.f ? (M2 + log2f(den)) * kLn2 : -INFINITY;
-  } else {
-    if constexpr (MODE == kPassDense || MODE == kPassDenseHeads || MODE == kPassDensePaged) {
-      if (p.direct) {
-        // single split: this is the final partial; same unit conversion as the split combine
-        constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
-        float m_nat = -INFINITY, L = -INFINITY, adj = 0.f;
-        if (sel.l > 0.f) {
-          m_nat = sel.m * kLn2;
-          adj = exp2f(sel.m - m_nat * kLog2e);
-          L = (sel.m + log2f(sel.l)) * kLn2;
-        }
+      for (int d = 0; d < C::NDBK; ++d) o[d] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < NACC; ++i) p.ws_o[grow * D + lane + 64 * i] = sel.acc[i] * adj;
-        if (lane == 0) {
-          p.ws_m[grow] = m_nat;
-          p.ws_l[grow] = L;
+      for (int w = 0; w < 4; ++w) {
+        const float wgt = __builtin_amdgcn_exp2f(mq[w] - Mu);
+        l = fmaf(lq[w], wgt, l);
+#pragma unroll
+        for (int d = 0; d < C::NDBK; ++d) {
+          const f32x4 x = rec_o[(((wr * 4 + w) * RB + rb) * C::NDB + wk * C::NDBK + d) * 64 + lane];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) o[d][r] = fmaf(x[r], wgt, o[d][r]);
         }
-        return;
       }
-    }
-    const size_t rows_total = (size_t)p.B * p.Hq * p.Bq;
-    const size_t wrow = (own_block ? (size_t)0 : (size_t)split * rows_total) + grow;
-    float* __restrict__ w_o = own_block ? p.ws_o2 : p.ws_o;
-    float* __restrict__ w_m = own_block ? p.ws_m2 : p.ws_m;
-    float* __restrict__ w_l = own_block ? p.ws_l2 : p.ws_l;
+      if (!row_ok) continue;
+      const int d0 = wk * C::NDBK * 16 + 4 * g4;              // first column of o[0]; o[d] is 16 d further
+      const bool writes_ml = (wk == 0 && g4 == 0);
+      if constexpr (MODE == kPassInternal) {
+        // Eq. 8-9 with the cached pair expressed through (o, m, lse): A_out e^{L_out-M} = o e^{m-M}.
+        float me2 = -INFINITY, le = 0.f;
+        if (p.ext_o != nullptr) {
+          const float me = p.ext_m[grow], lse = p.ext_lse[grow];
+          if (lse != -INFINITY) {
+            me2 = me * kLog2e;
+            le = exp2f((lse - me) * kLog2e);
+          }
+        }
+        const float M2 = fmaxf(me2, M);
+        const float M2u = (M2 == -INFINITY) ? 0.f : M2;
+        const float we = exp2f(me2 - M2u), wi = exp2f(M - M2u);
+        const float den = le * we + l * wi;
+        const float inv = den > 0.f ? 1.f / den : 0.f;
 #pragma unroll
-    for (int i = 0; i < NACC; ++i) w_o[wrow * D + lane + 64 * i] = sel.acc[i];
-    if (lane == 0) {
-      w_m[wrow] = sel.m;
-      w_l[wrow] = sel.l;
-    }
-    if constexpr (MODE == kPassSparseRefresh) {
+        for (int d = 0; d < C::NDBK; ++d) {
+          f32x4 num = o[d] * wi;
+          if (le > 0.f) {
+            const f32x4 x = *(const f32x4*)(p.ext_o + grow * D + d0 + 16 * d);
 #pragma unroll
-      for (int i = 0; i < NACC; ++i) p.ws_o2[wrow * D + lane + 64 * i] = res.acc[i];
-      if (lane == 0) {
-        p.ws_m2[wrow] = res.m;
-        p.ws_l2[wrow] = res.l;
+            for (int r = 0; r < 4; ++r) num[r] = fmaf(x[r], we, num[r]);
+          }
+          *(f32x4*)((float*)p.out + grow * D + d0 + 16 * d) = num * inv;
+        }
+        if (p.lse_out != nullptr && writes_ml) p.lse_out[grow] = den > 0.f ? (M2 + log2f(den)) * kLn2 : -INFINITY;
+      } else {
+        if (p.direct) {
+          // single split: this is the final partial; same unit conversion as the split combine
+          float m_nat = -INFINITY, L = -INFINITY, adj = 0.f;
+          if (l > 0.f) {
+            m_nat = M * kLn2;
+            adj = exp2f(M - m_nat * kLog2e);
+            L = (M + log2f(l)) * kLn2;
+          }
+#pragma unroll
+          for (int d = 0; d < C::NDBK; ++d) *(f32x4*)(p.ws_o + grow * D + d0 + 16 * d) = o[d] * adj;
+          if (writes_ml) {
+            p.ws_m[grow] = m_nat;
+            p.ws_l[grow] = L;
+          }
+        } else {
+          const bool set1 = own_block || i == 1;              // residual keys, or the block's own keys
+          const size_t rows_total = (size_t)p.B * p.Hq * p.Bq;
+          const size_t wrow = (own_block ? (size_t)0 : (size_t)split * rows_total) + grow;
+          float* __restrict__ w_o = set1 ? p.ws_o2 : p.ws_o;
+          float* __restrict__ w_m = set1 ? p.ws_m2 : p.ws_m;
+          float* __restrict__ w_l = set1 ? p.ws_l2 : p.ws_l;
+#pragma unroll
+          for (int d = 0; d < C::NDBK; ++d) *(f32x4*)(w_o + wrow * D + d0 + 16 * d) = o[d];
+          if (writes_ml) {
+            w_m[wrow] = M;
+            w_l[wrow] = l;
+          }
+        }
       }
     }
   }
@@ -298,20 +473,52 @@ __global__ __launch_bounds__(256) void block_mass_f32_kernel(const MassParams p)
   }
 }
 
+template <int D, int MODE, int RB, int WR>
+hipError_t launch_f32(const PassParams& p, hipStream_t s) {
+  using C = FCfg<D, RB, WR>;
+  auto kern = attn_f32_kernel<D, MODE, RB, WR>;
+  static LdsLimit lim;
+  hipError_t e = raise_lds_limit(kern, C::LDS, lim, C::LDS);
+  if (e != hipSuccess) return e;
+  constexpr bool per_head = f32_per_head(MODE);
+  const int heads = per_head ? p.Hq : p.Hkv, nrows = per_head ? p.Bq : p.G * p.Bq;
+  const int rowtiles = (nrows + C::ROWS - 1) / C::ROWS;
+  const int nsplit = p.nsplit + (MODE == kPassRefreshFused ? 1 : 0);
+  long long units = (long long)p.B * heads * nsplit;
+  if (MODE == kPassDensePaged) units = (units + 7) / 8 * 8;
+  if (units * rowtiles >= (1ll << 31)) return hipErrorInvalidValue;
+  PassParams q = p;
+  if (MODE == kPassDensePaged) q.div_page = make_fastdiv((uint32_t)p.page_size);
+  q.div_rowtiles = make_fastdiv((uint32_t)rowtiles);
+  q.div_nsplit = make_fastdiv((uint32_t)nsplit);
+  q.div_hkv = make_fastdiv((uint32_t)heads);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(units * rowtiles)), dim3(C::THREADS), C::LDS, s, q);
+  return hipGetLastError();
+}
+
+template <int D, int MODE>
+hipError_t launch_f32_rows(const PassParams& p, hipStream_t s) {
+  const int nrows = f32_per_head(MODE) ? p.Bq : p.G * p.Bq;
+  int tile = f32_row_tile(nrows);
+  // the internal pass has no splits to fill the chip with: 16-row workgroups until 64-row ones do
+  if (MODE == kPassInternal && (long long)p.B * p.Hkv * ((nrows + 63) / 64) < 256) tile = 16;
+  if (tile == 16) return launch_f32<D, MODE, 1, 1>(p, s);
+  if (tile == 32) return launch_f32<D, MODE, 2, 1>(p, s);
+  return launch_f32<D, MODE, 2, 2>(p, s);
+}
+
 template <int D>
 hipError_t launch_d(const PassParams& p, PassMode mode, hipStream_t s) {
-  const dim3 grid((p.Bq + kRowsPerWgF32 - 1) / kRowsPerWgF32, p.B * p.Hq, p.nsplit + (mode == kPassRefreshFused ? 1 : 0));
-  const dim3 block(256);
   switch (mode) {
-    case kPassDense: hipLaunchKernelGGL((attn_f32_kernel<D, kPassDense>), grid, block, 0, s, p); break;
-    case kPassInternal: hipLaunchKernelGGL((attn_f32_kernel<D, kPassInternal>), grid, block, 0, s, p); break;
-    case kPassSparseRefresh: hipLaunchKernelGGL((attn_f32_kernel<D, kPassSparseRefresh>), grid, block, 0, s, p); break;
-    case kPassSparseReuse: hipLaunchKernelGGL((attn_f32_kernel<D, kPassSparseReuse>), grid, block, 0, s, p); break;
-    case kPassDenseHeads: hipLaunchKernelGGL((attn_f32_kernel<D, kPassDenseHeads>), grid, block, 0, s, p); break;
-    case kPassDensePaged: hipLaunchKernelGGL((attn_f32_kernel<D, kPassDensePaged>), grid, block, 0, s, p); break;
-    case kPassRefreshFused: hipLaunchKernelGGL((attn_f32_kernel<D, kPassRefreshFused>), grid, block, 0, s, p); break;
+    case kPassDense: return launch_f32_rows<D, kPassDense>(p, s);
+    case kPassInternal: return launch_f32_rows<D, kPassInternal>(p, s);
+    case kPassSparseRefresh: return launch_f32_rows<D, kPassSparseRefresh>(p, s);
+    case kPassSparseReuse: return launch_f32_rows<D, kPassSparseReuse>(p, s);
+    case kPassDenseHeads: return launch_f32_rows<D, kPassDenseHeads>(p, s);
+    case kPassDensePaged: return launch_f32_rows<D, kPassDensePaged>(p, s);
+    case kPassRefreshFused: return launch_f32_rows<D, kPassRefreshFused>(p, s);
   }
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 }  // namespace

@@ -207,7 +207,10 @@ hipError_t launch_head_similarity(const float* o_a, const float* o_b, float* sim
 
 // Row tiles (workgroups along the group-flattened row axis) per KV group, per kernel family.
 constexpr int kRowsPerWgBf16 = 128;  // 4 waves x 32 rows
-constexpr int kRowsPerWgF32 = 4;     // 4 waves x 1 row
+constexpr int kRowsPerWgF32 = 4;     // fp32 mass kernel: 4 waves x 1 row
+// fp32 attention pass: rows of a workgroup, by the rows that share a K/V stream.  Shared by the split heuristic and the
+// launcher.
+inline int f32_row_tile(long long nrows) { return nrows <= 16 ? 16 : nrows <= 32 ? 32 : 64; }
 // bf16 dense external pass: KV groups of more than 128 rows run row-pair workgroups (8 wavefronts, 256 rows, one
 // shared tile stream), so every K/V tile is staged once per 256 rows.  At head_dim 64 that measures the same as
 // 128-row workgroups (32.6 vs 33.8 us at 256 rows, 32K keys) but leaves twice the splits to fold, so there only
@@ -217,6 +220,37 @@ inline bool dense_row_pairs(int nrows, int head_dim) {
 }
 
 // ---- device helpers shared by the attention kernels -------------------------------------
+// One 16-byte direct-to-LDS load per lane: lane l's chunk lands at LDS byte lds_base + 16 l.  Global address =
+// base (wavefront-uniform) + off (per lane, unsigned 32-bit).
+__device__ __forceinline__ void dma16(const void* base, uint32_t off, uint32_t lds_base) {
+  // base and lds_base are wavefront-uniform by construction; readfirstlane says so to the compiler, which
+  // otherwise may hand the "s" operands over in vector registers (not encodable here)
+  // (the builtin returns int: each half goes through uint32_t so that nothing is sign-extended)
+  const uint64_t b = (uint64_t)(uintptr_t)base;
+  const uint32_t b_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+  const uint32_t b_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+  const uint64_t bu = ((uint64_t)b_hi << 32) | (uint64_t)b_lo;
+  const uint32_t lu = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_base);
+  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
+               :
+               : "v"(off), "s"(bu), "s"(lu)
+               : "memory", "m0");
+}
+
+// Wavefront-uniform table lookup as a scalar load (constant address space).  The tables were written by earlier
+// kernels, so they are constant here; without this the compiler, which sees the inline assembly's memory
+// clobber, falls back to vector loads, and its wait for them (vmcnt(0)) would also drain every direct-to-LDS
+// load in flight.
+__device__ __forceinline__ int32_t sload(const void* table, int idx) {
+  typedef const __attribute__((address_space(4))) int32_t* cptr;
+  return ((cptr)(uintptr_t)table)[__builtin_amdgcn_readfirstlane(idx)];
+}
+
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
 // Tile schedule of one workgroup: which 64-key tiles it visits.
 struct TileRange {
   int begin, end;   // entries [begin, end) of the pass's tile list

@@ -83,37 +83,6 @@ struct SCfg {
   __device__ static __forceinline__ int rot_v(int row) { return D == 128 ? 4 * row : 4 * (row >> 1); }
 };
 
-// One 16-byte direct-to-LDS load per lane: lane l's chunk lands at LDS byte lds_base + 16 l.  Global address =
-// base (wavefront-uniform) + off (per lane, unsigned 32-bit).
-__device__ __forceinline__ void dma16(const void* base, uint32_t off, uint32_t lds_base) {
-  // base and lds_base are wavefront-uniform by construction; readfirstlane says so to the compiler, which
-  // otherwise may hand the "s" operands over in vector registers (not encodable here)
-  // (the builtin returns int: each half goes through uint32_t so that nothing is sign-extended)
-  const uint64_t b = (uint64_t)(uintptr_t)base;
-  const uint32_t b_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
-  const uint32_t b_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
-  const uint64_t bu = ((uint64_t)b_hi << 32) | (uint64_t)b_lo;
-  const uint32_t lu = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_base);
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
-               :
-               : "v"(off), "s"(bu), "s"(lu)
-               : "memory", "m0");
-}
-
-// Wavefront-uniform table lookup as a scalar load (constant address space).  The tables were written by earlier
-// kernels, so they are constant here; without this the compiler, which sees the inline assembly's memory
-// clobber, falls back to vector loads, and its wait for them (vmcnt(0)) would also drain every direct-to-LDS
-// load in flight.
-__device__ __forceinline__ int32_t sload(const void* table, int idx) {
-  typedef const __attribute__((address_space(4))) int32_t* cptr;
-  return ((cptr)(uintptr_t)table)[__builtin_amdgcn_readfirstlane(idx)];
-}
-
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
 // wait until at most `tiles` tiles' worth of this lane's direct-to-LDS loads are outstanding
 // (the counter has 6 bits: counts above 63 cannot be asked for, and no ring here keeps that many loads in flight)
 template <int LPT>
