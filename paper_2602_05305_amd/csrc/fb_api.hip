@@ -70,6 +70,8 @@ int f32_splits(const fb_shape* s, bool per_head) {
   return (int)ns;
 }
 
+size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+
 int auto_splits(const fb_shape* s, int active_heads = 0) {
   const int tiles = (s->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile;
   if (s->dtype == FB_BF16 && active_heads > 0 && active_heads < s->n_q_heads) {
@@ -116,11 +118,6 @@ int auto_splits(const fb_shape* s, int active_heads = 0) {
 
 // Split counts of the sparse passes (bf16): one workgroup per CU in both modes - 8 wavefronts in
 // the reuse pass, 4 wavefronts with two accumulator sets in the refresh pass.
-// Splits of the per-head refresh: the fp32 pass runs one query head per workgroup.
-int heads_splits(const fb_shape* s, int active_heads) {
-  return s->dtype == FB_BF16 ? auto_splits(s, active_heads) : f32_splits(s, true);
-}
-
 // Splits of the plain dense external pass.  KV groups above 128 rows run 256-row, 8-wavefront workgroups, one per
 // CU: as many splits as keep the workgroup count within the 256 CUs (one round), each with at least 8 tiles.
 int dense_splits(const fb_shape* s) {
@@ -134,6 +131,44 @@ int dense_splits(const fb_shape* s) {
   if (ns > FB_MAX_SPLITS) ns = FB_MAX_SPLITS;
   if (ns < 1) ns = 1;
   return (int)ns;
+}
+
+// Splits of the per-head refresh.  fp32: one query head per workgroup.
+int heads_splits(const fb_shape* s, int active_heads) {
+  return s->dtype == FB_BF16 ? auto_splits(s, active_heads) : f32_splits(s, true);
+}
+
+// Per-head refresh over KV groups of more than 128 rows (bf16) with a hint: 256-row workgroups as in the dense pass,
+// counted over the KV groups that the flagged heads can belong to.  Their split partials are stored densely by rank among
+// the flagged groups, so that there is room for more splits than for all heads (cap groups per batch element; groups
+// beyond it are streamed unsplit).  Of the two split counts around 256 / groups the one with the shorter critical path
+// (rounds of 256 workgroups x tiles per split), at least 8 tiles per split.  (3 of 12 heads, 4680 rows against 37440
+// keys: 4 splits of 57 row tiles.)  ns = 0: the hint says nothing, or the shape is another one's.
+struct HeadsPlan {
+  int ns, cap;
+  size_t o, m, l, total;      // workspace offsets
+};
+
+HeadsPlan heads_plan(const fb_shape* s, int active_heads) {
+  HeadsPlan h = {0, 0, 0, 0, 0, 0};
+  const long long nrows = (long long)(s->n_q_heads / s->n_kv_heads) * s->block_len;
+  if (s->dtype != FB_BF16 || active_heads <= 0 || active_heads >= s->n_q_heads) return h;
+  if (!fb::dense_row_pairs((int)std::min<long long>(nrows, 1 << 30), s->head_dim)) return h;
+  const int tiles = (s->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile;
+  h.cap = std::min(active_heads, s->n_kv_heads);
+  const long long groups = (long long)s->batch * h.cap * ((nrows + 2 * fb::kRowsPerWgBf16 - 1) / (2 * fb::kRowsPerWgBf16));
+  long long best_cost = -1;
+  const long long lo = std::max(std::min(256 / groups, tiles / 8ll), 1ll);
+  for (long long ns = lo; ns <= lo + 1; ++ns) {
+    if (tiles < 8 * ns || ns > FB_MAX_SPLITS) continue;
+    const long long cost = ((groups * ns + 255) / 256) * ((tiles + ns - 1) / ns);
+    if (best_cost < 0 || cost < best_cost) { h.ns = (int)ns; best_cost = cost; }
+  }
+  const size_t n = (size_t)h.ns * s->batch * h.cap * nrows;
+  h.m = align256(n * s->head_dim * sizeof(float));
+  h.l = h.m + align256(n * sizeof(float));
+  h.total = h.l + align256(n * sizeof(float));
+  return h;
 }
 
 int sparse_splits(const fb_shape* s, bool refresh) {
@@ -167,8 +202,6 @@ int paged_splits(const fb_shape* s) {
   if (ns < 1) ns = 1;
   return (int)ns;
 }
-
-size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct WsLayout {
   size_t o[2], m[2], l[2], mask, ulist, umask, ucnt, order, total;
@@ -331,7 +364,7 @@ fb_status external_partial_impl(const fb_shape* shape, const void* q, const void
       !aligned16(m_part) || !aligned16(lse_part) || !aligned16(workspace))
     return FB_ERR_ALIGN;
   if (n_active_heads < 0) return FB_ERR_SHAPE;
-  const int ns = n_splits > 0 ? n_splits
+  int ns = n_splits > 0 ? n_splits
                              : (paged ? paged_splits(shape)
                                       : use_head_mask ? heads_splits(shape, n_active_heads) : dense_splits(shape));
   const WsLayout w = ws_layout(shape, ns, 1, 0);
@@ -343,6 +376,15 @@ fb_status external_partial_impl(const fb_shape* shape, const void* q, const void
   p.ws_o = (float*)(ws + w.o[0]); p.ws_m = (float*)(ws + w.m[0]); p.ws_l = (float*)(ws + w.l[0]);
   p.head_on = use_head_mask ? head_mask : nullptr;
   fb::PassMode mode = use_head_mask ? fb::kPassDenseHeads : fb::kPassDense;
+  if (use_head_mask) {
+    const HeadsPlan h = heads_plan(shape, n_active_heads);
+    if (h.ns > 0 && h.total <= w.total) {
+      ns = p.nsplit = h.ns;
+      p.heads_cap = h.cap;
+      p.ws_o = (float*)ws; p.ws_m = (float*)(ws + h.m); p.ws_l = (float*)(ws + h.l);
+      p.o_final = o_part; p.m_final = m_part; p.l_final = lse_part;
+    }
+  }
   if (paged) {
     mode = fb::kPassDensePaged;
     p.block_table = paged->block_table; p.prefix_lens = paged->prefix_lens;
@@ -370,6 +412,8 @@ fb_status external_partial_impl(const fb_shape* shape, const void* q, const void
     c.ws_o = p.ws_o; c.ws_m = p.ws_m; c.ws_l = p.ws_l;
     c.o = o_part; c.m = m_part; c.lse = lse_part;
     c.head_on = p.head_on; c.Bq = shape->block_len;
+    c.heads_cap = p.heads_cap;
+    c.Hq = shape->n_q_heads; c.Hkv = shape->n_kv_heads; c.G = shape->n_q_heads / shape->n_kv_heads;
     if (fold_out) {
       *fold_out = c;
     } else {
@@ -508,6 +552,49 @@ fb_status fb_internal_merge(const fb_shape* shape, const void* q, const void* k_
   return FB_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// A refresh step as an external pass over the prefix (contiguous, or paged if kv is given) followed by the split fold and
+// the block-internal pass.  The block's tensors and outputs have been checked by the caller.
+fb_status refresh_in_passes(const fb_shape* shape, const void* q, const void* k_prefix, const void* v_prefix,
+                            const fb_paged_kv* kv, const void* k_block, const void* v_block, float* o_part, float* m_part,
+                            float* lse_part, void* out, float* lse_out, int32_t n_splits, void* workspace,
+                            size_t workspace_bytes, void* ev_begin, void* ev_attn_end, void* ev_end, void* hip_stream) {
+  // With several splits and a small block the split fold, the block-internal attention and the merge are one kernel;
+  // with one split the external pass writes the partial itself and the internal pass follows; otherwise combine + internal
+  // pass.
+  // (the fold kernel runs 4 rows per workgroup and is a latency chain: beyond a few thousand rows the plain
+  // combine and the MFMA internal pass are faster, measured 219 vs ~165 us per step at batch 32, block 32)
+  const bool fold_kernel = shape->block_len <= fb::kMaxInlineBlock && shape->block_len % fb::kFoldRows == 0 &&
+                           rows_of(shape) <= kFoldKernelMaxRows;
+  fb::CombineParams c;
+  fb_status st = external_partial_impl(shape, q, k_prefix, v_prefix, kv, nullptr, false, 0, o_part, m_part, lse_part, n_splits,
+                                       workspace, workspace_bytes, ev_begin, ev_attn_end, nullptr, hip_stream,
+                                       fold_kernel ? &c : nullptr);
+  if (st != FB_OK) return st;
+  hipError_t e = hipSuccess;
+  if (fold_kernel && c.nsplit > 0) {
+    c.fin_out = out; c.fin_lse = lse_out; c.fin_bf16 = shape->dtype == FB_BF16;
+    c.blk_q = q; c.blk_k = k_block; c.blk_v = v_block;
+    c.Hq = shape->n_q_heads; c.Hkv = shape->n_kv_heads; c.G = shape->n_q_heads / shape->n_kv_heads;
+    c.scale_log2 = eff_scale(shape) * kLog2e;
+    e = fb::launch_refresh_fold(c, (hipStream_t)hip_stream);
+  } else {
+    fb::PassParams p = base_pass(shape, q, k_block, v_block, shape->block_len, 1);
+    p.ext_o = o_part; p.ext_m = m_part; p.ext_lse = lse_part;
+    p.out = out; p.lse_out = lse_out;
+    e = launch_attn(shape, p, fb::kPassInternal, (hipStream_t)hip_stream);
+  }
+  if (e == hipSuccess && ev_end) e = hipEventRecord((hipEvent_t)ev_end, (hipStream_t)hip_stream);
+  return e == hipSuccess ? FB_OK : hip_fail(e);
+}
+
+}  // namespace
+
+extern "C" {
+
 fb_status fb_refresh_step_prof(const fb_shape* shape, const void* q, const void* k_prefix, const void* v_prefix,
                                const void* k_block, const void* v_block, float* o_part, float* m_part,
                                float* lse_part, void* out, float* lse_out, void* workspace,
@@ -532,6 +619,16 @@ fb_status fb_refresh_step_prof(const fb_shape* shape, const void* q, const void*
   const WsLayout w = ws_layout(shape, ns, 2, 0, 1);
   const size_t need = shape->dtype == FB_F32 ? fb_workspace_bytes(shape, 0, 0, 0) : w.total;
   if (!workspace || workspace_bytes < need) return FB_ERR_WORKSPACE;
+  if (shape->dtype == FB_BF16 && !small_block) {
+    // Many rows per KV head: the streaming kernel's external pass (which writes the partial itself when unsplit), then the
+    // internal pass, against the register-staged pass over prefix and block and the combine: video shape, a refresh and
+    // a reuse step 1423 -> 1347 us
+    const fb::PassParams d = base_pass(shape, q, k_prefix, v_prefix, shape->prefix_len, dense_splits(shape));
+    if (fb::dense_row_pairs(d.G * d.Bq, shape->head_dim) && fb::stream_bf16_covers(d, shape->head_dim, fb::kPassDense) &&
+        workspace_bytes >= ws_layout(shape, dense_splits(shape), 1, 0).total)
+      return refresh_in_passes(shape, q, k_prefix, v_prefix, nullptr, k_block, v_block, o_part, m_part, lse_part, out, lse_out,
+                               0, workspace, workspace_bytes, ev_begin, ev_attn_end, ev_end, hip_stream);
+  }
 
   hipStream_t stream = (hipStream_t)hip_stream;
   char* ws = (char*)workspace;
@@ -578,27 +675,8 @@ fb_status fb_refresh_step_paged(const fb_shape* shape, const void* q, const fb_p
   if (st != FB_OK) return st;
   if (!k_block || !v_block || !out) return FB_ERR_NULL;
   if (!aligned16(k_block) || !aligned16(v_block) || !aligned16(out) || !aligned16(lse_out)) return FB_ERR_ALIGN;
-  // With several splits and a small block the split fold, the block-internal attention and the merge are one
-  // kernel (as in fb_refresh_step); with one split the paged pass writes the partial itself and the internal pass
-  // follows; otherwise combine + internal pass.
-  // (the fold kernel runs 4 rows per workgroup and is a latency chain: beyond a few thousand rows the plain
-  // combine and the MFMA internal pass are faster, measured 219 vs ~165 us per step at batch 32, block 32)
-  const bool fold_kernel = shape->block_len <= fb::kMaxInlineBlock && shape->block_len % fb::kFoldRows == 0 &&
-                           rows_of(shape) <= kFoldKernelMaxRows;
-  fb::CombineParams c;
-  st = external_partial_impl(shape, q, nullptr, nullptr, kv, nullptr, false, 0, o_part, m_part, lse_part, n_splits,
-                             workspace, workspace_bytes, nullptr, nullptr, nullptr, hip_stream, fold_kernel ? &c : nullptr);
-  if (st != FB_OK) return st;
-  if (fold_kernel && c.nsplit > 0) {
-    c.fin_out = out; c.fin_lse = lse_out; c.fin_bf16 = shape->dtype == FB_BF16;
-    c.blk_q = q; c.blk_k = k_block; c.blk_v = v_block;
-    c.Hq = shape->n_q_heads; c.Hkv = shape->n_kv_heads; c.G = shape->n_q_heads / shape->n_kv_heads;
-    c.scale_log2 = eff_scale(shape) * kLog2e;
-    hipError_t e = fb::launch_refresh_fold(c, (hipStream_t)hip_stream);
-    if (e != hipSuccess) return hip_fail(e);
-    return FB_OK;
-  }
-  return fb_internal_merge(shape, q, k_block, v_block, o_part, m_part, lse_part, out, lse_out, hip_stream);
+  return refresh_in_passes(shape, q, nullptr, nullptr, kv, k_block, v_block, o_part, m_part, lse_part, out, lse_out, n_splits,
+                           workspace, workspace_bytes, nullptr, nullptr, nullptr, hip_stream);
 }
 
 fb_status fb_refresh_step(const fb_shape* shape, const void* q, const void* k_prefix, const void* v_prefix,

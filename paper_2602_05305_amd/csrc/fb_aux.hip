@@ -158,6 +158,29 @@ __device__ __forceinline__ Folded fold_strided(const float* __restrict__ ws_o, c
   return f;
 }
 
+// Where the split partials of a row are: `rows` rows per split, this one at `row`.  False: the row is not to be folded (its
+// head is not flagged, or its KV group ran unsplit).
+struct FoldRow {
+  size_t rows, row;
+};
+__device__ __forceinline__ bool fold_row(const CombineParams& p, size_t row, FoldRow& f) {
+  f.rows = p.rows;
+  f.row = row;
+  if (p.head_on == nullptr) return true;
+  const int bh = (int)(row / p.Bq);
+  if (p.head_on[bh] == 0) return false;
+  if (p.heads_cap > 0) {
+    const int b = bh / p.Hq, kvh = (bh - b * p.Hq) / p.G;
+    int rank = 0;
+    for (int g = 0; g < kvh; ++g) rank += group_flagged(p.head_on, b, p.Hq, p.G, g) ? 1 : 0;
+    if (rank >= p.heads_cap) return false;
+    const size_t nrows = (size_t)p.G * p.Bq;
+    f.rows = (size_t)(p.rows / (p.Hq * p.Bq)) * p.heads_cap * nrows;
+    f.row = ((size_t)b * p.heads_cap + rank) * nrows + (row - (size_t)(b * p.Hq + kvh * p.G) * p.Bq);
+  }
+  return true;
+}
+
 // Few splits: one thread per (row, 4 columns) walks the splits.
 __global__ __launch_bounds__(256) void combine_kernel(const CombineParams p) {
   const int per_row = p.D / 4;
@@ -165,12 +188,13 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineParams p) {
   if (idx >= (size_t)p.rows * per_row) return;
   const size_t row = idx / per_row;
   const int c4 = (int)(idx % per_row);
-  if (p.head_on != nullptr && p.head_on[row / p.Bq] == 0) return;
+  FoldRow f;
+  if (!fold_row(p, row, f)) return;
   Folded sel = empty_folded(), res = empty_folded();
   // chunks of four splits with all loads in flight (one memory round trip for up to four splits)
-  if (p.ws_o != nullptr && p.nsplit > 0) sel = fold_strided(p.ws_o, p.ws_m, p.ws_l, p.nsplit, p.rows, row, p.D, c4, 0, 1);
+  if (p.ws_o != nullptr && p.nsplit > 0) sel = fold_strided(p.ws_o, p.ws_m, p.ws_l, p.nsplit, f.rows, f.row, p.D, c4, 0, 1);
   const bool have_res_set = p.ws_o2 != nullptr;
-  if (have_res_set) res = fold_strided(p.ws_o2, p.ws_m2, p.ws_l2, p.nsplit, p.rows, row, p.D, c4, 0, 1);
+  if (have_res_set) res = fold_strided(p.ws_o2, p.ws_m2, p.ws_l2, p.nsplit, f.rows, f.row, p.D, c4, 0, 1);
   finish_row(p, sel, res, have_res_set, row, c4);
 }
 
@@ -181,10 +205,11 @@ __global__ __launch_bounds__(256) void combine_wide_kernel(const CombineParams p
   const int per_row = p.D / 4, nsl = 256 / per_row;
   const int tid = threadIdx.x, sl = tid / per_row, c4 = tid % per_row;
   const size_t row = xcd_contiguous(blockIdx.x, gridDim.x);
-  if (p.head_on != nullptr && p.head_on[row / p.Bq] == 0) return;   // workgroup-uniform
+  FoldRow f;
+  if (!fold_row(p, row, f)) return;                                 // workgroup-uniform
   const bool have_res_set = p.ws_o2 != nullptr;
-  sh[0][tid] = fold_strided(p.ws_o, p.ws_m, p.ws_l, p.nsplit, p.rows, row, p.D, c4, sl, nsl);
-  if (have_res_set) sh[1][tid] = fold_strided(p.ws_o2, p.ws_m2, p.ws_l2, p.nsplit, p.rows, row, p.D, c4, sl, nsl);
+  sh[0][tid] = fold_strided(p.ws_o, p.ws_m, p.ws_l, p.nsplit, f.rows, f.row, p.D, c4, sl, nsl);
+  if (have_res_set) sh[1][tid] = fold_strided(p.ws_o2, p.ws_m2, p.ws_l2, p.nsplit, f.rows, f.row, p.D, c4, sl, nsl);
   __syncthreads();
   if (sl != 0) return;
   Folded sel = sh[0][c4], res = empty_folded();

@@ -116,6 +116,10 @@ struct PassParams {
   const int32_t* union_cnt;   // [B,Hkv]
   int key_block, nblk;
   const uint8_t* head_on;     // [B,Hq] per-head refresh flags (kPassDenseHeads), else null
+  // per-head refresh, row-pair kernel, heads_cap > 0: split partials are stored by rank among the flagged KV groups,
+  // [split][B][heads_cap][G*Bq] rows; groups of a higher rank run unsplit and write the final partial
+  int heads_cap;
+  float* o_final; float* m_final; float* l_final;
   // paged pass: k/v point at the pools [num_pages, Hkv, page_size, D]
   const int32_t* block_table; // [B, max_pages] page ids
   const int32_t* prefix_lens; // [B] keys per sequence (<= nkeys)
@@ -145,6 +149,7 @@ struct CombineParams {
   float* res_out_o; float* res_out_m; float* res_out_lse;                  // residual out (refresh) or null
   float* o; float* m; float* lse;                                          // total out
   const uint8_t* head_on; int Bq;   // if head_on != null: rows of heads with a zero flag are left untouched
+  int heads_cap;                    // > 0: split partials stored by rank among the flagged KV groups (PassParams)
   // fused refresh step: block-internal partial (one split, log2 domain) merged with the total by Eq. 8-9 into
   // the normalised output (storage type) and its log-normaliser; null = no final output
   const float* blk_o; const float* blk_m; const float* blk_l;
@@ -235,6 +240,13 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t off, uint32_t l
                :
                : "v"(off), "s"(bu), "s"(lu)
                : "memory", "m0");
+}
+
+// Per-head refresh: whether any query head of KV group `kvh` of batch element b is flagged.
+__device__ __forceinline__ bool group_flagged(const uint8_t* head_on, int b, int Hq, int G, int kvh) {
+  uint32_t any = 0;
+  for (int g = 0; g < G; ++g) any |= head_on[b * Hq + kvh * G + g];
+  return any != 0;
 }
 
 // Wavefront-uniform table lookup as a scalar load (constant address space).  The tables were written by earlier

@@ -345,6 +345,32 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
     head_active = row_ok && p.head_on[b * p.Hq + kvh * p.G + row / p.Bq] != 0;
     if (!__syncthreads_or(head_active ? 1 : 0)) return;
   }
+  bool direct = p.direct != 0;                               // this workgroup writes the final partial
+  int rank = kvh, ranks = p.Hkv;                             // where the KV group's split partials go
+  float* __restrict__ fin_o = p.ws_o;
+  float* __restrict__ fin_m = p.ws_m;
+  float* __restrict__ fin_l = p.ws_l;
+  if constexpr (MODE == kPassDenseHeads) {
+    if (p.heads_cap > 0) {
+      rank = 0;
+      for (int g0 = 0; g0 < kvh; g0 += C::THREADS) {
+        const int g = g0 + (int)threadIdx.x;
+        rank += __syncthreads_count(g < kvh && group_flagged(p.head_on, b, p.Hq, p.G, g));
+      }
+      rank = __builtin_amdgcn_readfirstlane(rank);
+      ranks = p.heads_cap;
+      if (rank >= ranks) {                                   // more flagged groups than the hint said
+        if (split != 0) return;
+        direct = true;
+      }
+      if (direct || p.nsplit == 1) {
+        direct = true;
+        fin_o = p.o_final;
+        fin_m = p.m_final;
+        fin_l = p.l_final;
+      }
+    }
+  }
 
   // contiguous cache: this KV head's [nkeys, D] slab; paged cache: the pool (tiles add their page offset)
   const unsigned char* __restrict__ Kg =
@@ -362,7 +388,7 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
   } else {
     total = (nkeys + C::KT - 1) / C::KT;
   }
-  const TileRange tr = (MODE == kPassInternal) ? TileRange{0, total}
+  const TileRange tr = (MODE == kPassInternal || (MODE == kPassDenseHeads && direct)) ? TileRange{0, total}
                        : p.xcd_bias ? biased_range(total, p.nsplit, split) : split_range(total, p.div_nsplit, split);
   const int ntiles = tr.end - tr.begin;
   const uint32_t rsrc = (p.div_rowtiles.d == 1) ? blockIdx.x : unit;
@@ -559,6 +585,9 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
     // two tiles per barrier; the prologue put tiles 0 .. AHEAD-1 in flight, iteration t adds tiles t+AHEAD, t+AHEAD+1
     // into the stages of tiles t-2, t-1 (or the query stages), which every wavefront left before this barrier
     static_assert(!kListed, "row-pair layout: dense passes only");
+    // per-head refresh: a wavefront computes its rows if any of them is of a flagged head (rows of the others are
+    // computed along and not stored)
+    const bool wave_on = (MODE != kPassDenseHeads) || __any(head_active);
     for (int t = 0; t < ntiles; t += 2) {
       wait_tiles<C::LPT>(min(AHEAD - 2, max(ntiles - 2 - t, 0)));   // tiles issued after tile t+1 so far
       __syncthreads();
@@ -574,6 +603,7 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
         if (t + u < ntiles) {
           const unsigned char* stage = ring + ((t + u) % C::NS) * C::STAGE;
           const int nvalid = min(C::KT, nkeys - qk0[u]);
+          if (!wave_on) continue;
           f32x16 s[C::NKB];
           tile_scores<D, C::NKB>(s, qreg, stage, kaddr, kb0);
           tile_softmax_pv<D, C::NKB>(acc, s, stage, vaddr, kb0, p.scale_log2, true, nvalid, h);
@@ -700,7 +730,7 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
     if (p.lse_out != nullptr && h == 0) p.lse_out[grow] = den > 0.f ? (M2 + log2f(den)) * kLn2 : -INFINITY;
     return;
   } else {
-    if (p.direct) {
+    if (direct) {
       // single split: this is the final partial.  Same conversion as the split combine: m is rounded when
       // converted to natural-log units, o is rescaled to the reference consumers recover from it.
       if (!(row_ok && head_active)) return;
@@ -717,17 +747,16 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
           const int d0 = 32 * (db_keep + db) + 8 * q4 + 4 * h;
           f32x4 o4 = {acc.o[db][4 * q4] * adj, acc.o[db][4 * q4 + 1] * adj, acc.o[db][4 * q4 + 2] * adj,
                       acc.o[db][4 * q4 + 3] * adj};
-          *(f32x4*)(p.ws_o + grow * D + d0) = o4;
+          *(f32x4*)(fin_o + grow * D + d0) = o4;
         }
       if (h == 0 && kb0 == 0) {
-        p.ws_m[grow] = m_nat;
-        p.ws_l[grow] = L;
+        fin_m[grow] = m_nat;
+        fin_l[grow] = L;
       }
       return;
     }
     if (!row_ok) return;
-    const size_t rows_total = (size_t)p.B * p.Hq * p.Bq;
-    const size_t wrow = (size_t)split * rows_total + grow;
+    const size_t wrow = ((size_t)(split * p.B + b) * ranks + rank) * nrows + row;
 #pragma unroll
     for (int i = 0; i < NSETS; ++i) {
       float* __restrict__ w_o = i ? p.ws_o2 : p.ws_o;
@@ -797,7 +826,11 @@ hipError_t launch_stream_d(const PassParams& p, PassMode mode, hipStream_t s) {
     case kPassDense:
       if (dense_row_pairs(nrows, D)) return launch_stream<D, kPassDense, kRowPair>(p, s);
       return launch_key_split<D, kPassDense>(p, s);
-    case kPassDenseHeads: return launch_key_split<D, kPassDenseHeads>(p, s);
+    case kPassDenseHeads:
+      // many rows per KV head: as in the dense pass (3 of 12 heads of 4680 rows against 37440 keys: 354 us by the
+      // register-staged kernel in 2 splits, 284 us here in 4)
+      if (dense_row_pairs(nrows, D)) return launch_stream<D, kPassDenseHeads, kRowPair>(p, s);
+      return launch_key_split<D, kPassDenseHeads>(p, s);
     case kPassDensePaged: return launch_key_split<D, kPassDensePaged>(p, s);
     case kPassSparseReuse: return launch_key_split<D, kPassSparseReuse>(p, s);
     case kPassSparseRefresh: return launch_key_split<D, kPassSparseRefresh>(p, s);
@@ -815,9 +848,8 @@ bool stream_bf16_covers(const PassParams& p, int D, PassMode mode) {
   const int tiles = (p.nkeys + kKeyTile - 1) / kKeyTile;
   switch (mode) {
     case kPassDense:
-      if (dense_row_pairs(nrows, D)) return tiles >= 8 * p.nsplit;
-      return nrows <= 128 && tiles >= 8 * p.nsplit;
     case kPassDenseHeads:
+      return (nrows <= 128 || dense_row_pairs(nrows, D)) && tiles >= 8 * p.nsplit;
     case kPassDensePaged:
     case kPassSparseReuse:
     case kPassSparseRefresh:
