@@ -107,7 +107,8 @@ int32_t fb_external_splits(const fb_shape* shape);
 /* Name (as a profiler's kernel trace prints it, without the namespace) of the streaming attention
  * kernel fb_external_partial launches for this shape with the library's own split count: the
  * kernel whose duration the roofline of the external pass is about.  Host only.  Host string owned
- * by the library, valid until the next call on the same thread; "" on an invalid shape. */
+ * by the library, valid until the next call on the same thread; "" on an invalid shape.  (fp32: without the template
+ * arguments of the workgroup's row tile.) */
 const char* fb_external_kernel_name(const fb_shape* shape);
 
 /* Bytes of device workspace one call needs on this shape.  n_splits = 0 sizes for the

@@ -16,6 +16,7 @@
 //              Sparse refresh pass: the same layout with two accumulator sets per wavefront (selected /
 //              residual key blocks); a tile's scores are computed once and go to the set the row's head routes
 //              the tile's key block to, so the eight wavefronts stay evenly loaded whatever the selection.
+//              At head_dim 64 (except the paged pass) half h takes every other tile instead, two tiles per barrier.
 //   kRowPair   256 rows, wavefront w owns rows [32 w, +32) and whole tiles (many rows per KV head: a staged
 //              tile serves twice the rows).  Two tiles per barrier: inside an iteration the two wavefronts of a SIMD
 //              are free to drift apart by a tile, so that one's softmax can run under the other's MFMAs.
@@ -51,9 +52,18 @@ constexpr float kLn2 = 0.6931471805599453f;
 
 enum StreamLayout : int { kKeySplit = 0, kRowPair = 2 };
 
+// Whole tiles for the two wavefronts of a row group (half h takes every other tile, two tiles per barrier) instead of
+// half of every tile: at head_dim 64, where a tile's fixed cost (barrier, refill, the softmax's cross-lane step) is large
+// against its 16 KB: batch 4, 64K keys, 32 rows per KV head 118 -> 103 us a refresh and a reuse step, 128K keys 64.4 ->
+// 61.2, a sparse block at 64K 209 -> 189 us.  Not at head_dim 128, where pairs of tiles leave 64 KB in flight instead
+// of 96 (128K keys: 1 % slower) and the two accumulator sets of the sparse refresh do not fit the registers; not in the
+// paged pass, whose weights are rounded against the reference of the tiles a wavefront meets first and stay as they were.
+constexpr bool whole_tiles(int D, int mode) { return D == 64 && mode != kPassDensePaged; }
+
+
 // NRG: 32-row groups of a key-split workgroup (4: 128 rows, 8 wavefronts; 2: 64 rows, 4 wavefronts; 1: 32 rows, 2
 // wavefronts: the small blocks of 4- and 8-token diffusion steps, where more row groups would compute padding rows)
-template <int D, int LAYOUT, int NSETS = 1, int NRG = 4>
+template <int D, int LAYOUT, int NSETS = 1, int NRG = 4, bool WT = false>
 struct SCfg {
   static constexpr int NW = (LAYOUT == kRowPair) ? 8 : 2 * NRG;   // wavefronts per workgroup
   static constexpr int THREADS = 64 * NW;
@@ -65,14 +75,14 @@ struct SCfg {
   static constexpr int NLOAD = OPB / (THREADS * 16);  // direct-to-LDS loads per lane, operand and tile
   static constexpr int LSTEP = NW * 1024;             // LDS bytes one load of every wavefront covers
   static constexpr int LPT = 2 * NLOAD;               // loads per lane and tile
-  static constexpr int NS = (D == 128) ? 4 : 6;       // ring stages
+  static constexpr int NS = (D == 128) ? 4 : WT ? 8 : 6;       // ring stages
   static constexpr int NKS = D / 16;                  // MFMA k-steps of the score product
   static constexpr int NDB = D / 32;                  // 32-wide output column blocks
   static constexpr int ROWS = (LAYOUT == kRowPair) ? 256 : 32 * NRG;
-  static constexpr int NKB = (LAYOUT == kKeySplit) ? 1 : 2;    // 32-key blocks of a tile one wavefront computes
+  static constexpr int NKB = (LAYOUT == kKeySplit && !WT) ? 1 : 2;    // 32-key blocks of a tile one wavefront computes
   static constexpr int QPARTS = (ROWS + 63) / 64;             // the query rows are loaded 64 at a time, like a K operand
   static constexpr int QSTAGES = (QPARTS * OPB + STAGE - 1) / STAGE;   // ring stages they pass through at start
-  static constexpr int MERGE = (LAYOUT == kKeySplit) ? NSETS * NRG * 2 * (NDB / 2 * 16 + 2) * 64 * 4 : 0;   // key-half exchange
+  static constexpr int MERGE = (LAYOUT != kRowPair) ? NSETS * NRG * 2 * (NDB / 2 * 16 + 2) * 64 * 4 : 0;   // key-half exchange
   static constexpr int RING = NS * STAGE;
   static constexpr int FIFO = RING > MERGE ? RING : MERGE;
   static constexpr int LDS = FIFO;
@@ -252,16 +262,18 @@ struct TileDesc {
 template <int D, int MODE, int LAYOUT, int NRG>
 __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void attn_stream_kernel(const PassParams p) {
   constexpr int NSETS = (MODE == kPassSparseRefresh) ? 2 : 1;
-  using C = SCfg<D, LAYOUT, NSETS, NRG>;
+  constexpr bool kWhole = LAYOUT == kKeySplit && whole_tiles(D, MODE);
+  using C = SCfg<D, LAYOUT, NSETS, NRG, kWhole>;
   static_assert(MODE == kPassDense || MODE == kPassDenseHeads || MODE == kPassDensePaged || MODE == kPassSparseReuse ||
                     MODE == kPassSparseRefresh || MODE == kPassInternal, "modes of the streaming kernel");
-  static_assert(MODE != kPassSparseRefresh || LAYOUT == kKeySplit, "two accumulator sets: key-split layout");
+  static_assert(MODE != kPassSparseRefresh || LAYOUT != kRowPair, "two accumulator sets: key halves");
   static_assert(MODE != kPassInternal || LAYOUT == kRowPair, "internal pass: row-pair layout");
   // Row-pair layout: two tiles per barrier (tiles t, t+1 are computed while t+2, t+3 are in flight), measured 2 % faster
-  // at the video shape than one tile per barrier; every other layout: one tile per barrier, NS - 1 tiles in flight.
-  constexpr bool kPairs = LAYOUT == kRowPair;
+  // at the video shape than one tile per barrier; whole tiles of the key split the same; halves of tiles: one tile per barrier, NS - 1 in flight.
+  constexpr bool kPairs = LAYOUT == kRowPair || kWhole;
+  constexpr bool kHalves = LAYOUT != kRowPair;       // two wavefronts per row group, each with half of the keys
   constexpr int AHEAD = kPairs ? C::NS - 2 : C::NS - 1;
-  static_assert(!kPairs || (C::NS == 4 || C::NS == 6), "pairs of tiles: an even number of stages");
+  static_assert(!kPairs || C::NS % 2 == 0, "pairs of tiles: an even number of stages");
   // passes whose tiles come from a table (paged, sparse): the lookups are made one iteration ahead of the tile's
   // issue, and (first key, mask) travel to the tile's compute in a register queue
   constexpr bool kListed = (MODE == kPassDensePaged || MODE == kPassSparseReuse || MODE == kPassSparseRefresh);
@@ -269,7 +281,8 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
   const int lane = threadIdx.x & 63, l32 = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));     // wavefront-uniform (scalar)
   const int rg = (LAYOUT == kRowPair) ? wave : (wave % NRG);     // 32-row group
-  const int kb0 = (LAYOUT == kKeySplit) ? (wave / NRG) : 0;      // first 32-key block of every tile
+  const int half = kHalves ? (wave / NRG) : 0;                   // keys of this wavefront: half of every tile, or every other tile
+  const int kb0 = (kHalves && !kWhole) ? half : 0;              // first 32-key block of a tile
 
   // ---- workgroup -> (row tile, batch, KV head, split).  Hardware deals consecutive workgroup ids round-robin
   // to the 8 XCDs; each XCD gets a contiguous range of units so that row tiles sharing K/V share an L2.
@@ -529,9 +542,13 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
       }
   }
   // table words of the next tile to be issued, fetched one iteration ahead (lookups off the critical path)
-  TileRaw rnext;
-  rnext.e = 0; rnext.word = 0; rnext.mask = 0u;
-  if (AHEAD < ntiles) rnext = tile_raw(AHEAD);
+  constexpr int NNEXT = kPairs ? 2 : 1;
+  TileRaw rnext[NNEXT];
+#pragma unroll
+  for (int u = 0; u < NNEXT; ++u) {
+    rnext[u].e = 0; rnext[u].word = 0; rnext[u].mask = 0u;
+    if (AHEAD + u < ntiles) rnext[u] = tile_raw(AHEAD + u);
+  }
 
   // per-lane LDS read addresses inside a stage
   uint32_t kaddr[C::NKS], vaddr[C::NDB];
@@ -562,26 +579,48 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
     else return true;
   };
   constexpr bool kMasked = (MODE == kPassDenseHeads || MODE == kPassSparseReuse || MODE == kPassSparseRefresh);
-  // issue of tile t + AHEAD (into a stage every wavefront has left for good), then the lookups of the tile after it;
-  // the queue then holds tiles t .. t + AHEAD
-  auto refill = [&](int t) {
-    if (t + AHEAD < ntiles) {
-      const TileDesc d = tile_desc(rnext);
-      issue_tile(t + AHEAD, d);
-      qk0[AHEAD] = d.k0;
-      qmask[AHEAD] = d.mask;
-      if (t + AHEAD + 1 < ntiles) rnext = tile_raw(t + AHEAD + 1);
+  // issue of tile t + AHEAD + u (into a stage every wavefront has left for good), then the lookups of the tile that
+  // follows in this slot; the queue then holds tiles t .. t + AHEAD + u
+  auto refill = [&](int t, int u) {
+    if (t + AHEAD + u < ntiles) {
+      const TileDesc d = tile_desc(rnext[u]);
+      issue_tile(t + AHEAD + u, d);
+      qk0[AHEAD + u] = d.k0;
+      qmask[AHEAD + u] = d.mask;
+      if (t + AHEAD + u + NNEXT < ntiles) rnext[u] = tile_raw(t + AHEAD + u + NNEXT);
     }
   };
   auto advance = [&]() {
 #pragma unroll
-    for (int i = 0; i + 1 < C::NS; ++i) {
-      qk0[i] = qk0[i + 1];
-      qmask[i] = qmask[i + 1];
+    for (int i = 0; i + NNEXT < C::NS; ++i) {
+      qk0[i] = qk0[i + NNEXT];
+      qmask[i] = qmask[i + NNEXT];
+    }
+  };
+  // one tile of a wavefront whose row group is shared by two (key halves)
+  auto half_tile = [&](const unsigned char* stage, int k0, uint32_t mask) __attribute__((always_inline)) {
+    const int nvalid = min(C::KT, nkeys - k0);
+    if constexpr (MODE == kPassSparseReuse) {
+      if (nvalid <= 0) return;                               // a list entry past the end of the keys
+    }
+    bool on[NSETS];
+    bool any_on = false;
+#pragma unroll
+    for (int i = 0; i < NSETS; ++i) {
+      on[i] = lane_on_of(mask, i);
+      any_on = any_on || on[i];
+    }
+    if (kMasked && !__any(any_on)) return;
+    f32x16 s[C::NKB];
+    tile_scores<D, C::NKB>(s, qreg, stage, kaddr, kb0);
+#pragma unroll
+    for (int i = 0; i < NSETS; ++i) {
+      if (NSETS > 1 && !__any(on[i])) continue;
+      tile_softmax_pv<D, C::NKB>(accs[i], s, stage, vaddr, kb0, p.scale_log2, on[i], nvalid, h);
     }
   };
 
-  if constexpr (kPairs) {
+  if constexpr (LAYOUT == kRowPair) {
     // two tiles per barrier; the prologue put tiles 0 .. AHEAD-1 in flight, iteration t adds tiles t+AHEAD, t+AHEAD+1
     // into the stages of tiles t-2, t-1 (or the query stages), which every wavefront left before this barrier
     static_assert(!kListed, "row-pair layout: dense passes only");
@@ -592,12 +631,7 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
       wait_tiles<C::LPT>(min(AHEAD - 2, max(ntiles - 2 - t, 0)));   // tiles issued after tile t+1 so far
       __syncthreads();
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
-        if (t + AHEAD + u < ntiles) {
-          const TileDesc d = tile_desc(tile_raw(t + AHEAD + u));
-          issue_tile(t + AHEAD + u, d);
-          qk0[AHEAD + u] = d.k0;
-        }
+      for (int u = 0; u < 2; ++u) refill(t, u);
 #pragma unroll
       for (int u = 0; u < 2; ++u)
         if (t + u < ntiles) {
@@ -608,59 +642,50 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
           tile_scores<D, C::NKB>(s, qreg, stage, kaddr, kb0);
           tile_softmax_pv<D, C::NKB>(acc, s, stage, vaddr, kb0, p.scale_log2, true, nvalid, h);
         }
+      advance();
+    }
+  } else if constexpr (kWhole) {
+    for (int t = 0; t < ntiles; t += 2) {
+      wait_tiles<C::LPT>(min(AHEAD - 2, max(ntiles - 2 - t, 0)));   // tiles issued after tile t+1 so far
+      __syncthreads();
 #pragma unroll
-      for (int i = 0; i + 2 < C::NS; ++i) qk0[i] = qk0[i + 2];
+      for (int u = 0; u < 2; ++u) refill(t, u);
+      const int k0 = half ? qk0[1] : qk0[0];
+      const uint32_t mask = half ? qmask[1] : qmask[0];
+      advance();
+      if (t + half < ntiles) half_tile(ring + ((t + half) % C::NS) * C::STAGE, k0, mask);
     }
   } else {
     for (int t = 0; t < ntiles; ++t) {
       wait_tiles<C::LPT>(min(AHEAD - 1, ntiles - 1 - t));      // tiles issued after tile t so far
       __syncthreads();
-      refill(t);
-      const unsigned char* stage = ring + (t % C::NS) * C::STAGE;
+      refill(t, 0);
       const int k0 = qk0[0];
       const uint32_t mask = qmask[0];
       advance();
-      const int nvalid = min(C::KT, nkeys - k0);
-      if constexpr (MODE == kPassSparseReuse) {
-        if (nvalid <= 0) continue;                             // a list entry past the end of the keys
-      }
-      bool on[NSETS];
-      bool any_on = false;
-#pragma unroll
-      for (int i = 0; i < NSETS; ++i) {
-        on[i] = lane_on_of(mask, i);
-        any_on = any_on || on[i];
-      }
-      if (kMasked && !__any(any_on)) continue;
-      f32x16 s[C::NKB];
-      tile_scores<D, C::NKB>(s, qreg, stage, kaddr, kb0);
-#pragma unroll
-      for (int i = 0; i < NSETS; ++i) {
-        if (NSETS > 1 && !__any(on[i])) continue;
-        tile_softmax_pv<D, C::NKB>(accs[i], s, stage, vaddr, kb0, p.scale_log2, on[i], nvalid, h);
-      }
+      half_tile(ring + (t % C::NS) * C::STAGE, k0, mask);
     }
   }
 
   // Output column blocks this wavefront finishes and stores.  Row-pair layout: all of them.  Key-split layout: the two
   // wavefronts of a row group exchange halves, so that both take part in the merge and in the stores (the wavefront of
   // key half 0 keeps the lower column blocks, the other one the upper ones).
-  constexpr int NDBK = (LAYOUT == kKeySplit) ? C::NDB / 2 : C::NDB;
-  const int db_keep = (LAYOUT == kKeySplit) ? kb0 * NDBK : 0;
-  if constexpr (LAYOUT == kKeySplit) {
+  constexpr int NDBK = (kHalves) ? C::NDB / 2 : C::NDB;
+  const int db_keep = (kHalves) ? half * NDBK : 0;
+  if constexpr (kHalves) {
     // ---- merge the two key halves through LDS.  Record per (set, row group, key half): the NDBK column blocks the
     // wavefront gives away, then its m and l; [register][lane] so that neighbouring lanes hit neighbouring banks.
     constexpr int REC = NDBK * 16 + 2;
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < NSETS; ++i) {
-      float* mine = (float*)ring + (((size_t)i * NRG + rg) * 2 + kb0) * REC * 64 + lane;
+      float* mine = (float*)ring + (((size_t)i * NRG + rg) * 2 + half) * REC * 64 + lane;
 #pragma unroll
       for (int db = 0; db < NDBK; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          // static register indices: select between the two halves instead of indexing by kb0
-          mine[(db * 16 + r) * 64] = kb0 ? accs[i].o[db][r] : accs[i].o[NDBK + db][r];
+          // static register indices: select between the two halves instead of indexing by half
+          mine[(db * 16 + r) * 64] = half ? accs[i].o[db][r] : accs[i].o[NDBK + db][r];
         }
       mine[(NDBK * 16) * 64] = accs[i].m;
       mine[(NDBK * 16 + 1) * 64] = accs[i].l;
@@ -668,24 +693,24 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < NSETS; ++i) {
-      const float* other = (const float*)ring + (((size_t)i * NRG + rg) * 2 + (kb0 ^ 1)) * REC * 64 + lane;
+      const float* other = (const float*)ring + (((size_t)i * NRG + rg) * 2 + (half ^ 1)) * REC * 64 + lane;
       WaveAcc<C::NDB>& a = accs[i];
       const float mo = other[(NDBK * 16) * 64], lo = other[(NDBK * 16 + 1) * 64];
       // both wavefronts of the pair evaluate the same expressions on (key half 0, key half 1) in that order
-      const float m0 = kb0 ? mo : a.m, m1 = kb0 ? a.m : mo;
-      const float l0 = kb0 ? lo : a.l, l1 = kb0 ? a.l : lo;
+      const float m0 = half ? mo : a.m, m1 = half ? a.m : mo;
+      const float l0 = half ? lo : a.l, l1 = half ? a.l : lo;
       const float M = fmaxf(m0, m1);
       const float Mu = (M == -INFINITY) ? 0.f : M;
       const float w0 = __builtin_amdgcn_exp2f(m0 - Mu), w1 = __builtin_amdgcn_exp2f(m1 - Mu);
-      const float ws = kb0 ? w1 : w0, wo = kb0 ? w0 : w1;
+      const float ws = half ? w1 : w0, wo = half ? w0 : w1;
 #pragma unroll
       for (int db = 0; db < NDBK; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const float x = other[(db * 16 + r) * 64];
           // kept block = lower ones for key half 0, upper ones for key half 1; result parked in o[db]
-          const float own = kb0 ? a.o[NDBK + db][r] : a.o[db][r];
-          a.o[db][r] = kb0 ? (x * wo + own * ws) : (own * ws + x * wo);
+          const float own = half ? a.o[NDBK + db][r] : a.o[db][r];
+          a.o[db][r] = half ? (x * wo + own * ws) : (own * ws + x * wo);
         }
       a.l = l0 * w0 + l1 * w1;
       a.m = M;
@@ -749,7 +774,7 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
                       acc.o[db][4 * q4 + 3] * adj};
           *(f32x4*)(fin_o + grow * D + d0) = o4;
         }
-      if (h == 0 && kb0 == 0) {
+      if (h == 0 && half == 0) {
         fin_m[grow] = m_nat;
         fin_l[grow] = L;
       }
@@ -774,7 +799,7 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
           // the rows through LDS for whole-row stores, and faster than write-back stores)
           __builtin_nontemporal_store(o4, (f32x4*)(w_o + wrow * D + d0));
         }
-      if (h == 0 && kb0 == 0) {
+      if (h == 0 && half == 0) {
         w_m[wrow] = a.m;
         w_l[wrow] = l_i;
       }
@@ -784,7 +809,7 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
 
 template <int D, int MODE, int LAYOUT, int NRG = 4>
 hipError_t launch_stream(const PassParams& p, hipStream_t s) {
-  using C = SCfg<D, LAYOUT, (MODE == kPassSparseRefresh) ? 2 : 1, NRG>;
+  using C = SCfg<D, LAYOUT, (MODE == kPassSparseRefresh) ? 2 : 1, NRG, LAYOUT == kKeySplit && whole_tiles(D, MODE)>;
   auto kern = attn_stream_kernel<D, MODE, LAYOUT, NRG>;
   static LdsLimit lim;
   hipError_t e = raise_lds_limit(kern, C::LDS, lim, C::LDS);
@@ -827,8 +852,6 @@ hipError_t launch_stream_d(const PassParams& p, PassMode mode, hipStream_t s) {
       if (dense_row_pairs(nrows, D)) return launch_stream<D, kPassDense, kRowPair>(p, s);
       return launch_key_split<D, kPassDense>(p, s);
     case kPassDenseHeads:
-      // many rows per KV head: as in the dense pass (3 of 12 heads of 4680 rows against 37440 keys: 354 us by the
-      // register-staged kernel in 2 splits, 284 us here in 4)
       if (dense_row_pairs(nrows, D)) return launch_stream<D, kPassDenseHeads, kRowPair>(p, s);
       return launch_key_split<D, kPassDenseHeads>(p, s);
     case kPassDensePaged: return launch_key_split<D, kPassDensePaged>(p, s);
