@@ -138,12 +138,11 @@ int heads_splits(const fb_shape* s, int active_heads) {
   return s->dtype == FB_BF16 ? auto_splits(s, active_heads) : f32_splits(s, true);
 }
 
-// Per-head refresh over KV groups of more than 128 rows (bf16) with a hint: 256-row workgroups as in the dense pass,
-// counted over the KV groups that the flagged heads can belong to.  Their split partials are stored densely by rank among
-// the flagged groups, so that there is room for more splits than for all heads (cap groups per batch element; groups
-// beyond it are streamed unsplit).  Of the two split counts around 256 / groups the one with the shorter critical path
-// (rounds of 256 workgroups x tiles per split), at least 8 tiles per split.  (3 of 12 heads, 4680 rows against 37440
-// keys: 4 splits of 57 row tiles.)  ns = 0: the hint says nothing, or the shape is another one's.
+// Per-head refresh over KV groups of more than 128 rows (bf16) with a hint: 256-row workgroups, each split of
+// auto_splits as two, its even and its odd tiles, so that the flagged groups fill the CUs that 128-row workgroups with two
+// tile streams each would.  The split partials are stored densely by rank among the flagged KV groups (cap groups per batch
+// element; groups beyond it are streamed unsplit), which is what the workspace has room for.  ns = 0: the hint says nothing,
+// or the shape is another kernel's.
 struct HeadsPlan {
   int ns, cap;
   size_t o, m, l, total;      // workspace offsets
@@ -154,16 +153,10 @@ HeadsPlan heads_plan(const fb_shape* s, int active_heads) {
   const long long nrows = (long long)(s->n_q_heads / s->n_kv_heads) * s->block_len;
   if (s->dtype != FB_BF16 || active_heads <= 0 || active_heads >= s->n_q_heads) return h;
   if (!fb::dense_row_pairs((int)std::min<long long>(nrows, 1 << 30), s->head_dim)) return h;
-  const int tiles = (s->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile;
+  const int tiles = (s->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile, ns = auto_splits(s, active_heads);
+  if (tiles < 8 * ns || 2 * ns > FB_MAX_SPLITS) return h;
+  h.ns = 2 * ns;
   h.cap = std::min(active_heads, s->n_kv_heads);
-  const long long groups = (long long)s->batch * h.cap * ((nrows + 2 * fb::kRowsPerWgBf16 - 1) / (2 * fb::kRowsPerWgBf16));
-  long long best_cost = -1;
-  const long long lo = std::max(std::min(256 / groups, tiles / 8ll), 1ll);
-  for (long long ns = lo; ns <= lo + 1; ++ns) {
-    if (tiles < 8 * ns || ns > FB_MAX_SPLITS) continue;
-    const long long cost = ((groups * ns + 255) / 256) * ((tiles + ns - 1) / ns);
-    if (best_cost < 0 || cost < best_cost) { h.ns = (int)ns; best_cost = cost; }
-  }
   const size_t n = (size_t)h.ns * s->batch * h.cap * nrows;
   h.m = align256(n * s->head_dim * sizeof(float));
   h.l = h.m + align256(n * sizeof(float));
@@ -378,7 +371,7 @@ fb_status external_partial_impl(const fb_shape* shape, const void* q, const void
   fb::PassMode mode = use_head_mask ? fb::kPassDenseHeads : fb::kPassDense;
   if (use_head_mask) {
     const HeadsPlan h = heads_plan(shape, n_active_heads);
-    if (h.ns > 0 && h.total <= w.total) {
+    if (h.ns > 0 && h.total <= workspace_bytes) {
       ns = p.nsplit = h.ns;
       p.heads_cap = h.cap;
       p.ws_o = (float*)ws; p.ws_m = (float*)(ws + h.m); p.ws_l = (float*)(ws + h.l);
@@ -552,49 +545,6 @@ fb_status fb_internal_merge(const fb_shape* shape, const void* q, const void* k_
   return FB_OK;
 }
 
-}  // extern "C"
-
-namespace {
-
-// A refresh step as an external pass over the prefix (contiguous, or paged if kv is given) followed by the split fold and
-// the block-internal pass.  The block's tensors and outputs have been checked by the caller.
-fb_status refresh_in_passes(const fb_shape* shape, const void* q, const void* k_prefix, const void* v_prefix,
-                            const fb_paged_kv* kv, const void* k_block, const void* v_block, float* o_part, float* m_part,
-                            float* lse_part, void* out, float* lse_out, int32_t n_splits, void* workspace,
-                            size_t workspace_bytes, void* ev_begin, void* ev_attn_end, void* ev_end, void* hip_stream) {
-  // With several splits and a small block the split fold, the block-internal attention and the merge are one kernel;
-  // with one split the external pass writes the partial itself and the internal pass follows; otherwise combine + internal
-  // pass.
-  // (the fold kernel runs 4 rows per workgroup and is a latency chain: beyond a few thousand rows the plain
-  // combine and the MFMA internal pass are faster, measured 219 vs ~165 us per step at batch 32, block 32)
-  const bool fold_kernel = shape->block_len <= fb::kMaxInlineBlock && shape->block_len % fb::kFoldRows == 0 &&
-                           rows_of(shape) <= kFoldKernelMaxRows;
-  fb::CombineParams c;
-  fb_status st = external_partial_impl(shape, q, k_prefix, v_prefix, kv, nullptr, false, 0, o_part, m_part, lse_part, n_splits,
-                                       workspace, workspace_bytes, ev_begin, ev_attn_end, nullptr, hip_stream,
-                                       fold_kernel ? &c : nullptr);
-  if (st != FB_OK) return st;
-  hipError_t e = hipSuccess;
-  if (fold_kernel && c.nsplit > 0) {
-    c.fin_out = out; c.fin_lse = lse_out; c.fin_bf16 = shape->dtype == FB_BF16;
-    c.blk_q = q; c.blk_k = k_block; c.blk_v = v_block;
-    c.Hq = shape->n_q_heads; c.Hkv = shape->n_kv_heads; c.G = shape->n_q_heads / shape->n_kv_heads;
-    c.scale_log2 = eff_scale(shape) * kLog2e;
-    e = fb::launch_refresh_fold(c, (hipStream_t)hip_stream);
-  } else {
-    fb::PassParams p = base_pass(shape, q, k_block, v_block, shape->block_len, 1);
-    p.ext_o = o_part; p.ext_m = m_part; p.ext_lse = lse_part;
-    p.out = out; p.lse_out = lse_out;
-    e = launch_attn(shape, p, fb::kPassInternal, (hipStream_t)hip_stream);
-  }
-  if (e == hipSuccess && ev_end) e = hipEventRecord((hipEvent_t)ev_end, (hipStream_t)hip_stream);
-  return e == hipSuccess ? FB_OK : hip_fail(e);
-}
-
-}  // namespace
-
-extern "C" {
-
 fb_status fb_refresh_step_prof(const fb_shape* shape, const void* q, const void* k_prefix, const void* v_prefix,
                                const void* k_block, const void* v_block, float* o_part, float* m_part,
                                float* lse_part, void* out, float* lse_out, void* workspace,
@@ -619,15 +569,24 @@ fb_status fb_refresh_step_prof(const fb_shape* shape, const void* q, const void*
   const WsLayout w = ws_layout(shape, ns, 2, 0, 1);
   const size_t need = shape->dtype == FB_F32 ? fb_workspace_bytes(shape, 0, 0, 0) : w.total;
   if (!workspace || workspace_bytes < need) return FB_ERR_WORKSPACE;
-  if (shape->dtype == FB_BF16 && !small_block) {
-    // Many rows per KV head: the streaming kernel's external pass (which writes the partial itself when unsplit), then the
-    // internal pass, against the register-staged pass over prefix and block and the combine: video shape, a refresh and
-    // a reuse step 1423 -> 1347 us
-    const fb::PassParams d = base_pass(shape, q, k_prefix, v_prefix, shape->prefix_len, dense_splits(shape));
+  if (shape->dtype == FB_BF16 && !small_block && ns == 1) {
+    // Many rows per KV head, unsplit: the row-pair streaming kernel, once over the prefix (it writes the partial itself) and
+    // once over the block, against the register-staged pass over both and the combine (video shape, a refresh and a reuse
+    // step: 1380 -> 1320 us)
+    const fb::PassParams d = base_pass(shape, q, k_prefix, v_prefix, shape->prefix_len, 1);
+    fb::PassParams in = base_pass(shape, q, k_block, v_block, shape->block_len, 1);
     if (fb::dense_row_pairs(d.G * d.Bq, shape->head_dim) && fb::stream_bf16_covers(d, shape->head_dim, fb::kPassDense) &&
-        workspace_bytes >= ws_layout(shape, dense_splits(shape), 1, 0).total)
-      return refresh_in_passes(shape, q, k_prefix, v_prefix, nullptr, k_block, v_block, o_part, m_part, lse_part, out, lse_out,
-                               0, workspace, workspace_bytes, ev_begin, ev_attn_end, ev_end, hip_stream);
+        fb::stream_bf16_covers(in, shape->head_dim, fb::kPassInternal)) {
+      st = external_partial_impl(shape, q, k_prefix, v_prefix, nullptr, nullptr, false, 0, o_part, m_part, lse_part, 1, workspace,
+                                 workspace_bytes, ev_begin, ev_attn_end, nullptr, hip_stream);
+      if (st != FB_OK) return st;
+      in.ext_o = o_part; in.ext_m = m_part; in.ext_lse = lse_part;
+      in.out = out; in.lse_out = lse_out;
+      in.rotate = 1;
+      hipError_t e = launch_attn(shape, in, fb::kPassInternal, (hipStream_t)hip_stream);
+      if (e == hipSuccess && ev_end) e = hipEventRecord((hipEvent_t)ev_end, (hipStream_t)hip_stream);
+      return e == hipSuccess ? FB_OK : hip_fail(e);
+    }
   }
 
   hipStream_t stream = (hipStream_t)hip_stream;
@@ -640,9 +599,20 @@ fb_status fb_refresh_step_prof(const fb_shape* shape, const void* q, const void*
     const int btiles = (shape->block_len + fb::kKeyTile - 1) / fb::kKeyTile;
     p.blk_cost = ns > 1 ? std::min(2 + btiles, tiles / ns / 2) : 0;
   }
+  // Few splits, up to 128 rows per KV head and a block of one tile: the streaming kernel over the prefix, then the internal
+  // pass folds the splits, against the register-staged pass over both and the combine (a refresh and a reuse step, head_dim
+  // 128: batch 6, 31 rows, 9000 keys 90.8 -> 83.3 us; batch 8, 32 rows, 20000 keys 146 -> 138; head_dim 64: batch 16, 24
+  // rows, 30000 keys 118 -> 107, but 5003 keys, 20 tiles per split, 30.9 -> 32.1: from 32 tiles per split on)
+  fb::PassParams in = base_pass(shape, q, k_block, v_block, shape->block_len, 1);
+  in.fold_ns = ns;
+  const bool fold_internal = shape->dtype == FB_BF16 && !small_block && ns > 1 && p.G * p.Bq <= 128 &&
+                             p.Bq <= fb::kKeyTile && fb::stream_bf16_covers(p, shape->head_dim, fb::kPassDense) &&
+                             (shape->head_dim == 128 || shape->prefix_len >= 32 * fb::kKeyTile * ns) &&
+                             fb::internal_fold_covers(in, shape->head_dim);
+  p.whole_tiles = fold_internal ? 1 : 0;
   p.ws_o = (float*)(ws + w.o[0]); p.ws_m = (float*)(ws + w.m[0]); p.ws_l = (float*)(ws + w.l[0]);
   p.ws_o2 = (float*)(ws + w.o[1]); p.ws_m2 = (float*)(ws + w.m[1]); p.ws_l2 = (float*)(ws + w.l[1]);
-  hipError_t e = timed_attn(shape, p, small_block ? fb::kPassDense : fb::kPassRefreshFused, stream, ev_begin, ev_attn_end);
+  hipError_t e = timed_attn(shape, p, small_block || fold_internal ? fb::kPassDense : fb::kPassRefreshFused, stream, ev_begin, ev_attn_end);
   if (e != hipSuccess) return hip_fail(e);
 
   fb::CombineParams c;
@@ -652,7 +622,12 @@ fb_status fb_refresh_step_prof(const fb_shape* shape, const void* q, const void*
   c.o = o_part; c.m = m_part; c.lse = lse_part;
   c.Bq = shape->block_len;
   c.fin_out = out; c.fin_lse = lse_out; c.fin_bf16 = shape->dtype == FB_BF16;
-  if (small_block) {
+  if (fold_internal) {
+    in.ws_o = p.ws_o; in.ws_m = p.ws_m; in.ws_l = p.ws_l;
+    in.o_final = o_part; in.m_final = m_part; in.l_final = lse_part;
+    in.out = out; in.lse_out = lse_out;
+    e = launch_attn(shape, in, fb::kPassInternal, stream);
+  } else if (small_block) {
     c.blk_q = q; c.blk_k = k_block; c.blk_v = v_block;
     c.Hq = shape->n_q_heads; c.Hkv = shape->n_kv_heads; c.G = shape->n_q_heads / shape->n_kv_heads;
     c.scale_log2 = p.scale_log2;
@@ -675,8 +650,40 @@ fb_status fb_refresh_step_paged(const fb_shape* shape, const void* q, const fb_p
   if (st != FB_OK) return st;
   if (!k_block || !v_block || !out) return FB_ERR_NULL;
   if (!aligned16(k_block) || !aligned16(v_block) || !aligned16(out) || !aligned16(lse_out)) return FB_ERR_ALIGN;
-  return refresh_in_passes(shape, q, nullptr, nullptr, kv, k_block, v_block, o_part, m_part, lse_part, out, lse_out, n_splits,
-                           workspace, workspace_bytes, nullptr, nullptr, nullptr, hip_stream);
+  // One split: the paged pass writes the partial itself and the internal pass follows.  Several splits and a small block of
+  // few rows: one kernel of 4 rows per workgroup folds, computes the rows' block-internal attention and merges (as in
+  // fb_refresh_step; beyond a few thousand rows that latency chain loses: 219 vs ~165 us per step at batch 32, block 32).
+  // Few splits otherwise (bf16): the internal pass folds them (batch 8,
+  // 32 rows, up to 8000 keys 61.2 -> 58.5 us a refresh and a reuse step; batch 32 162.2 -> 159.7).  Else combine + internal pass.
+  fb::PassParams in = base_pass(shape, q, k_block, v_block, shape->block_len, 1);
+  in.out = out; in.lse_out = lse_out;
+  in.fold_ns = n_splits > 0 ? n_splits : paged_splits(shape);
+  const bool fold_kernel = shape->block_len <= fb::kMaxInlineBlock && shape->block_len % fb::kFoldRows == 0 &&
+                           rows_of(shape) <= kFoldKernelMaxRows;
+  const bool fold_internal = !fold_kernel && shape->dtype == FB_BF16 && in.fold_ns > 1 &&
+                             fb::internal_fold_covers(in, shape->head_dim);
+  fb::CombineParams c;
+  st = external_partial_impl(shape, q, nullptr, nullptr, kv, nullptr, false, 0, o_part, m_part, lse_part, n_splits,
+                             workspace, workspace_bytes, nullptr, nullptr, nullptr, hip_stream,
+                             fold_kernel || fold_internal ? &c : nullptr);
+  if (st != FB_OK) return st;
+  hipError_t e = hipSuccess;
+  if (fold_kernel && c.nsplit > 0) {
+    c.fin_out = out; c.fin_lse = lse_out; c.fin_bf16 = shape->dtype == FB_BF16;
+    c.blk_q = q; c.blk_k = k_block; c.blk_v = v_block;
+    c.scale_log2 = eff_scale(shape) * kLog2e;
+    e = fb::launch_refresh_fold(c, (hipStream_t)hip_stream);
+  } else {
+    if (fold_internal) {
+      in.ws_o = (float*)c.ws_o; in.ws_m = (float*)c.ws_m; in.ws_l = (float*)c.ws_l;
+      in.o_final = o_part; in.m_final = m_part; in.l_final = lse_part;
+    } else {
+      in.fold_ns = 0;
+      in.ext_o = o_part; in.ext_m = m_part; in.ext_lse = lse_part;
+    }
+    e = launch_attn(shape, in, fb::kPassInternal, (hipStream_t)hip_stream);
+  }
+  return e == hipSuccess ? FB_OK : hip_fail(e);
 }
 
 fb_status fb_refresh_step(const fb_shape* shape, const void* q, const void* k_prefix, const void* v_prefix,

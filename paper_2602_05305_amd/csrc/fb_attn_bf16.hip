@@ -310,7 +310,7 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
 // own pair of LDS stages, and group 1 hands its statistics to group 0 through LDS at the end.
 // Same wavefronts per CU as two 4-wave workgroups, half as many split partials to write and fold.
 template <int D, int MODE, int KT, int WS, int NG, int VAR = 0>
-__global__ __launch_bounds__(256 * NG, (NG > 1 || (MODE == kPassInternal && WS > 1) || MODE == kPassSparseRefresh) ? 1 : 2) void attn_bf16_kernel(const PassParams p) {
+__global__ __launch_bounds__(256 * NG, (VAR & 4) ? 2 : (NG > 1 || (MODE == kPassInternal && WS > 1) || MODE == kPassSparseRefresh) ? 1 : 2) void attn_bf16_kernel(const PassParams p) {
   using C = Cfg<D, KT>;
   extern __shared__ __align__(16) unsigned char smem_all[];
   // Sparse refresh with NG = 2: the two wavefront groups are specialised by accumulator set
@@ -319,6 +319,8 @@ __global__ __launch_bounds__(256 * NG, (NG > 1 || (MODE == kPassInternal && WS >
   // head routes it to its set, and every wavefront keeps ONE set: two wavefronts per SIMD
   // instead of the one that two sets in a single wavefront allow.
   constexpr bool RP = (VAR & 1) != 0;
+  constexpr bool kFold = (VAR & 4) != 0;          // internal pass that also folds the external pass's split partials
+  static_assert(!kFold || (MODE == kPassInternal && NG == 1), "fold variant");
   constexpr bool kSetSplit = (MODE == kPassSparseRefresh && NG == 2);
   // RP ("row pair", compute-bound passes with many rows): the two wavefront groups own DIFFERENT rows (256 per
   // workgroup) and share one tile stream and its LDS stages, so a staged tile serves twice the rows.
@@ -545,11 +547,19 @@ __global__ __launch_bounds__(256 * NG, (NG > 1 || (MODE == kPassInternal && WS >
     // makes the compiler wait for the loads right there, in front of the first tile.
     f32x4 eo[NEO];
     float ext_m_v = -INFINITY, ext_lse_v = -INFINITY;
-    const bool has_ext = (MODE == kPassInternal) && (p.ext_o != nullptr);     // workgroup-uniform
+    const bool has_ext = (MODE == kPassInternal) && (kFold || p.ext_o != nullptr);     // workgroup-uniform
+    constexpr int FST = D + 4;                               // folded row in LDS: o, m, log-normaliser
+    float* const fold_s = (float*)(smem_all + C::LDS);
     auto load_ext = [&]() {
       typedef const __attribute__((address_space(1))) f32x4* gptr_f4;
       typedef const __attribute__((address_space(1))) float* gptr_f;
-      if (has_ext) {
+      if constexpr (kFold) {
+        const float* fr = fold_s + ((wave / WS) * 32 + l32) * FST;
+        ext_m_v = fr[D];
+        ext_lse_v = fr[D + 1];
+#pragma unroll
+        for (int i = 0; i < NEO; ++i) eo[i] = *(const f32x4*)(fr + 32 * (db_base + i / 4) + 8 * (i % 4) + 4 * h);
+      } else if (has_ext) {
         const size_t er = row_ok ? grow : grow_last;   // rows past the end read the group's last row; never stored
         ext_m_v = *((gptr_f)p.ext_m + er);
         ext_lse_v = *((gptr_f)p.ext_lse + er);
@@ -560,7 +570,92 @@ __global__ __launch_bounds__(256 * NG, (NG > 1 || (MODE == kPassInternal && WS >
             eo[db * 4 + q4] = *(gptr_f4)(p.ext_o + er * D + 32 * (db_base + db) + 8 * q4 + 4 * h);
       }
     };
-    if constexpr (MODE == kPassInternal && kExtEarly) { if (ntiles == 0) load_ext(); }
+    if constexpr (kFold) {
+      // Eq. 5 over the splits in order, in chunks of two whose loads are independent (four spill, or take the registers of a
+      // second workgroup per CU).  Thread = 4 columns of NPT rows: whole rows are
+      // read and written, and the accumulator layout picks its share out of LDS in the epilogue (read straight into that
+      // layout, 16 bytes of 32 different rows per instruction, the pass took 27 us instead of 13 + 12 for combine and
+      // internal pass at batch 32, 128 rows per KV head, 2 splits).
+      constexpr int CH = 2, CPR = D / 4, NPT = ROWS * CPR / 256;
+      const size_t rows = (size_t)p.B * p.Hq * p.Bq, grow0 = grow_last - (nrows - 1);
+      const int c4 = tid % CPR;
+      size_t fr[NPT];
+      f32x4 fo[NPT];
+      float m2[NPT], l[NPT];
+#pragma unroll
+      for (int i = 0; i < NPT; ++i) {
+        fr[i] = grow0 + min(rt * ROWS + (tid + 256 * i) / CPR, nrows - 1);
+        fo[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        m2[i] = -INFINITY;
+        l[i] = 0.f;
+      }
+      for (int s0 = 0; s0 < p.fold_ns; s0 += CH) {
+        float mv[NPT][CH], lv[NPT][CH];
+        f32x4 ov[NPT][CH];
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+          if (s0 + c < p.fold_ns) {                      // workgroup-uniform
+#pragma unroll
+            for (int i = 0; i < NPT; ++i) {
+              const size_t r = (size_t)(s0 + c) * rows + fr[i];
+              mv[i][c] = p.ws_m[r];
+              lv[i][c] = p.ws_l[r];
+              ov[i][c] = *(const f32x4*)(p.ws_o + r * D + c4 * 4);
+            }
+          } else {
+#pragma unroll
+            for (int i = 0; i < NPT; ++i) {
+              mv[i][c] = -INFINITY;
+              lv[i][c] = 0.f;
+              ov[i][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+          }
+#pragma unroll
+        for (int i = 0; i < NPT; ++i) {
+          float cm = mv[i][0];
+#pragma unroll
+          for (int c = 1; c < CH; ++c) cm = fmaxf(cm, mv[i][c]);
+          const float Mn = fmaxf(m2[i], cm);
+          const float Mu = (Mn == -INFINITY) ? 0.f : Mn;
+          const float a = __builtin_amdgcn_exp2f(m2[i] - Mu);
+          l[i] *= a;
+          fo[i] = fo[i] * a;
+#pragma unroll
+          for (int c = 0; c < CH; ++c) {
+            const float w = __builtin_amdgcn_exp2f(mv[i][c] - Mu);
+            l[i] = fmaf(lv[i][c], w, l[i]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) fo[i][k] = fmaf(ov[i][c][k], w, fo[i][k]);
+          }
+          m2[i] = Mn;
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < NPT; ++i) {
+        // natural-log units; o is rescaled to the reference that consumers recover from the rounded m
+        float m_nat = -INFINITY, L = -INFINITY;
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+        if (l[i] > 0.f) {
+          m_nat = m2[i] * kLn2;
+          v = fo[i] * __builtin_amdgcn_exp2f(m2[i] - m_nat * kLog2e);
+          L = (m2[i] + log2f(l[i])) * kLn2;
+        }
+        const int lr = (tid + 256 * i) / CPR;            // row of the workgroup
+        *(f32x4*)(fold_s + lr * FST + c4 * 4) = v;
+        if (c4 == 0) {
+          fold_s[lr * FST + D] = m_nat;
+          fold_s[lr * FST + D + 1] = L;
+        }
+        if (rt * ROWS + lr < nrows) {
+          *(f32x4*)(p.o_final + fr[i] * D + c4 * 4) = v;
+          if (c4 == 0) {
+            p.m_final[fr[i]] = m_nat;
+            p.l_final[fr[i]] = L;
+          }
+        }
+      }
+    }
+    if constexpr (MODE == kPassInternal && kExtEarly && !kFold) { if (ntiles == 0) load_ext(); }
     WaveState<NDBL> sel;
     sel.init();
     WaveState<(MODE == kPassSparseRefresh && !kSetSplit) ? NDBL : 1> res;
@@ -647,7 +742,7 @@ __global__ __launch_bounds__(256 * NG, (NG > 1 || (MODE == kPassInternal && WS >
       // for the next tile's prefetch
 #pragma unroll
       for (int ks = 0; ks < C::NKS; ++ks) asm volatile("" ::"v"(qreg[ks]));
-      if constexpr (MODE == kPassInternal && kExtEarly) load_ext();   // in flight under the attention work
+      if constexpr (MODE == kPassInternal && kExtEarly && !kFold) load_ext();   // in flight under the attention work
       for (int i = 0; i < common - 1; ++i) {       // steady state: one barrier per tile
         if (i + 2 < mine) k0_nn = entry_k0(tile_entry(i + 2), mask_nn);
         load_tile(k0_next, mask_next);
@@ -701,7 +796,7 @@ __global__ __launch_bounds__(256 * NG, (NG > 1 || (MODE == kPassInternal && WS >
     // ---------------------------------------------------------------- epilogue
     const float l_sel = sel.l + __shfl_xor(sel.l, 32, 64);
     if constexpr (MODE == kPassInternal) {
-      if constexpr (!kExtEarly) load_ext();
+      if constexpr (!kExtEarly || kFold) load_ext();
       if (!row_ok) return;
       // keep the use of the cached statistics down here: hoisted into the prologue, it would make the
       // first tile wait for the cached partial's loads
@@ -898,7 +993,8 @@ hipError_t launch_one(const PassParams& p, hipStream_t s) {
   static LdsLimit lim;
   constexpr bool RP = (VAR & 1) != 0;
   auto kern = attn_bf16_kernel<D, MODE, KT, WS, NG, VAR>;
-  constexpr int lds = Cfg<D, KT>::LDS * ((MODE == kPassSparseRefresh || RP) ? 1 : NG);
+  constexpr int lds = Cfg<D, KT>::LDS * ((MODE == kPassSparseRefresh || RP) ? 1 : NG) +
+                      ((VAR & 4) ? kRowsPerWgBf16 / WS * (D + 4) * 4 : 0);
   {
     hipError_t e = raise_lds_limit(kern, lds, lim, lds);
     if (e != hipSuccess) return e;
@@ -976,12 +1072,19 @@ hipError_t launch_d(const PassParams& p, PassMode mode, hipStream_t s) {
       return launch_one<D, kPassDense, kKeyTile, 1, 1>(p, s);
     }
     case kPassInternal: {
+      const long long wgs = (long long)p.B * p.Hkv * ((p.G * p.Bq + kRowsPerWgBf16 - 1) / kRowsPerWgBf16);
+      if (p.fold_ns > 0) {
+        // (the caller has checked internal_fold_covers)
+        if (p.nkeys <= 32) return launch_one<D, kPassInternal, 32, WSMAX, 1, 4>(p, s);
+        return launch_one<D, kPassInternal, kKeyTile, WSMAX, 1, 4>(p, s);
+      }
       // Few rows (an LLM-sized block): the pass is one wavefront's run-once instruction stream.
       // Spread each 32-row group over WSMAX wavefronts (columns split) and, for a block of at
       // most 32 keys, use the 32-key tile: both shorten that stream.
       if (use_row_pairs(p)) return launch_one<D, kPassInternal, kKeyTile, 1, 2, 1>(p, s);
-      const long long wgs = (long long)p.B * p.Hkv * ((p.G * p.Bq + kRowsPerWgBf16 - 1) / kRowsPerWgBf16);
-      if (wgs < 128) {
+      // (or a KV group has at most 32 rows, where a 128-row workgroup computes padding: batch 128, blocks of 4 tokens,
+      // 16 rows per KV head 11.2 -> 8.8 us, blocks of 8 12.6 -> 11.4)
+      if (p.G * p.Bq <= 32 || wgs < 128) {
         if (p.nkeys <= 32) return launch_one<D, kPassInternal, 32, WSMAX, 1>(p, s);
         return launch_one<D, kPassInternal, kKeyTile, WSMAX, 1>(p, s);
       }
@@ -1028,6 +1131,10 @@ hipError_t launch_block_mass_bf16(const MassParams& p, int D, hipStream_t s) {
   if (D == 64) hipLaunchKernelGGL(block_mass_bf16_kernel<64>, grid, dim3(256), 0, s, p);
   else hipLaunchKernelGGL(block_mass_bf16_kernel<128>, grid, dim3(256), 0, s, p);
   return hipGetLastError();
+}
+
+bool internal_fold_covers(const PassParams& p, int D) {
+  return p.fold_ns > 0 && p.fold_ns < 8 && !use_row_pairs(p) && !stream_bf16_covers(p, D, kPassInternal);
 }
 
 int attn_bf16_dense_name(const PassParams& p, int D, char* buf, size_t n) {

@@ -116,10 +116,17 @@ struct PassParams {
   const int32_t* union_cnt;   // [B,Hkv]
   int key_block, nblk;
   const uint8_t* head_on;     // [B,Hq] per-head refresh flags (kPassDenseHeads), else null
-  // per-head refresh, row-pair kernel, heads_cap > 0: split partials are stored by rank among the flagged KV groups,
-  // [split][B][heads_cap][G*Bq] rows; groups of a higher rank run unsplit and write the final partial
+  // per-head refresh, heads_cap > 0 (row-pair kernel): an even number of splits, 2i and 2i + 1 with the even and the odd
+  // tiles of the i-th range; their partials are stored by rank among the flagged KV groups, [split][B][heads_cap][G*Bq] rows;
+  // groups of a higher rank run unsplit and write the final partial
   int heads_cap;
   float* o_final; float* m_final; float* l_final;
+  // internal pass, fold_ns > 0: the external statistics are fold_ns split partials in ws_o / ws_m / ws_l, which the pass
+  // folds, writes to o_final / m_final / l_final (natural-log units) and merges
+  int fold_ns;
+  // streaming kernel: whole tiles for the two wavefronts of a row group, splits cut with blk_cost (refresh step); and the
+  // internal pass visits its tiles in rotated order
+  int whole_tiles, rotate;
   // paged pass: k/v point at the pools [num_pages, Hkv, page_size, D]
   const int32_t* block_table; // [B, max_pages] page ids
   const int32_t* prefix_lens; // [B] keys per sequence (<= nkeys)
@@ -195,6 +202,8 @@ hipError_t launch_attn_bf16(const PassParams& p, int D, PassMode mode, hipStream
 bool stream_bf16_covers(const PassParams& p, int D, PassMode mode);
 hipError_t launch_stream_bf16(const PassParams& p, int D, PassMode mode, hipStream_t s);
 int stream_bf16_name(const PassParams& p, int D, PassMode mode, char* buf, size_t n);
+// Whether the internal pass of p can fold p.fold_ns split partials itself (few splits; not the row-pair kernels).
+bool internal_fold_covers(const PassParams& p, int D);
 // Name of the kernel launch_attn_bf16 runs for the dense external pass of p (profiler spelling, no namespace).
 int attn_bf16_dense_name(const PassParams& p, int D, char* buf, size_t n);
 hipError_t launch_combine(const CombineParams& p, hipStream_t s);

@@ -16,7 +16,8 @@
 //              Sparse refresh pass: the same layout with two accumulator sets per wavefront (selected /
 //              residual key blocks); a tile's scores are computed once and go to the set the row's head routes
 //              the tile's key block to, so the eight wavefronts stay evenly loaded whatever the selection.
-//              At head_dim 64 (except the paged pass) half h takes every other tile instead, two tiles per barrier.
+//              At head_dim 64 two tiles per barrier.
+//   kTileSplit the same with whole tiles: half h takes every other tile, two tiles per barrier.
 //   kRowPair   256 rows, wavefront w owns rows [32 w, +32) and whole tiles (many rows per KV head: a staged
 //              tile serves twice the rows).  Two tiles per barrier: inside an iteration the two wavefronts of a SIMD
 //              are free to drift apart by a tile, so that one's softmax can run under the other's MFMAs.
@@ -50,20 +51,17 @@ typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
-enum StreamLayout : int { kKeySplit = 0, kRowPair = 2 };
+enum StreamLayout : int { kKeySplit = 0, kTileSplit = 1, kRowPair = 2 };
 
-// Whole tiles for the two wavefronts of a row group (half h takes every other tile, two tiles per barrier) instead of
-// half of every tile: at head_dim 64, where a tile's fixed cost (barrier, refill, the softmax's cross-lane step) is large
-// against its 16 KB: batch 4, 64K keys, 32 rows per KV head 118 -> 103 us a refresh and a reuse step, 128K keys 64.4 ->
-// 61.2, a sparse block at 64K 209 -> 189 us.  Not at head_dim 128, where pairs of tiles leave 64 KB in flight instead
-// of 96 (128K keys: 1 % slower) and the two accumulator sets of the sparse refresh do not fit the registers; not in the
-// paged pass, whose weights are rounded against the reference of the tiles a wavefront meets first and stay as they were.
-constexpr bool whole_tiles(int D, int mode) { return D == 64 && mode != kPassDensePaged; }
-
+// Key split at head_dim 64: two tiles per barrier, their scores and weights computed together, because a tile's fixed cost
+// (barrier, refill, the softmax's cross-lane step) is large against its 16 KB: batch 4, 64K keys, 32 rows
+// per KV head 118 -> 101 us a refresh and a reuse step, 128K keys 64.6 -> 60.7, a sparse block at 64K 209 -> 201.  Not at
+// head_dim 128, where pairs of tiles leave 64 KB in flight instead of 96 (128K keys: 1 % slower).
+constexpr bool paired_halves(int D, int layout) { return D == 64 && layout == kKeySplit; }
 
 // NRG: 32-row groups of a key-split workgroup (4: 128 rows, 8 wavefronts; 2: 64 rows, 4 wavefronts; 1: 32 rows, 2
 // wavefronts: the small blocks of 4- and 8-token diffusion steps, where more row groups would compute padding rows)
-template <int D, int LAYOUT, int NSETS = 1, int NRG = 4, bool WT = false>
+template <int D, int LAYOUT, int NSETS = 1, int NRG = 4>
 struct SCfg {
   static constexpr int NW = (LAYOUT == kRowPair) ? 8 : 2 * NRG;   // wavefronts per workgroup
   static constexpr int THREADS = 64 * NW;
@@ -75,11 +73,11 @@ struct SCfg {
   static constexpr int NLOAD = OPB / (THREADS * 16);  // direct-to-LDS loads per lane, operand and tile
   static constexpr int LSTEP = NW * 1024;             // LDS bytes one load of every wavefront covers
   static constexpr int LPT = 2 * NLOAD;               // loads per lane and tile
-  static constexpr int NS = (D == 128) ? 4 : WT ? 8 : 6;       // ring stages
+  static constexpr int NS = (D == 128) ? 4 : (LAYOUT == kRowPair) ? 6 : 8;       // ring stages
   static constexpr int NKS = D / 16;                  // MFMA k-steps of the score product
   static constexpr int NDB = D / 32;                  // 32-wide output column blocks
   static constexpr int ROWS = (LAYOUT == kRowPair) ? 256 : 32 * NRG;
-  static constexpr int NKB = (LAYOUT == kKeySplit && !WT) ? 1 : 2;    // 32-key blocks of a tile one wavefront computes
+  static constexpr int NKB = (LAYOUT == kKeySplit) ? 1 : 2;    // 32-key blocks of a tile one wavefront computes
   static constexpr int QPARTS = (ROWS + 63) / 64;             // the query rows are loaded 64 at a time, like a K operand
   static constexpr int QSTAGES = (QPARTS * OPB + STAGE - 1) / STAGE;   // ring stages they pass through at start
   static constexpr int MERGE = (LAYOUT != kRowPair) ? NSETS * NRG * 2 * (NDB / 2 * 16 + 2) * 64 * 4 : 0;   // key-half exchange
@@ -244,6 +242,88 @@ __device__ __forceinline__ void tile_softmax_pv(WaveAcc<D / 32>& st, f32x16 (&s)
   tile_pv<D, NKB>(st, pb, stage, vaddr, kb0);
 }
 
+// The same for one 32-key block of each of two tiles, whose accumulator chains alternate.
+template <int D>
+__device__ __forceinline__ void two_scores(f32x16 (&s)[2], const bf16x8 (&qreg)[D / 16], const unsigned char* __restrict__ stage_a,
+                                           const unsigned char* __restrict__ stage_b, const uint32_t (&kaddr)[D / 16], int kb0) {
+  constexpr int NKS = D / 16, ROWB = D * 2;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[i][r] = 0.f;
+#pragma unroll
+  for (int ks = 0; ks < NKS; ++ks) {
+    const bf16x8 a = *(const bf16x8*)(stage_a + kaddr[ks] + kb0 * 32 * ROWB);
+    const bf16x8 b = *(const bf16x8*)(stage_b + kaddr[ks] + kb0 * 32 * ROWB);
+    s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qreg[ks], s[0], 0, 0, 0);
+    s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, qreg[ks], s[1], 0, 0, 0);
+  }
+}
+
+// Softmax update and value product of the two blocks.  Each tile moves the reference by the rule of tile_softmax, one
+// after the other; unless the second moves it (rare), both tiles' weights are taken against the same reference and
+// computed together, else one after the other.
+template <int D>
+__device__ __forceinline__ void two_softmax_pv(WaveAcc<D / 32>& st, f32x16 (&s)[2], const unsigned char* __restrict__ stage_a,
+                                               const unsigned char* __restrict__ stage_b, const uint32_t (&vaddr)[D / 32],
+                                               int kb0, float scale_log2, bool on_a, bool on_b, int nva, int nvb, int h) {
+  constexpr int NDB = D / 32;
+  constexpr float kLazy = 8.f;
+  const bool on[2] = {on_a, on_b};
+  const int nv[2] = {nva, nvb};
+  float tmax[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    if (nv[i] < 64) {
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int key = kb0 * 32 + 8 * (r / 4) + 4 * h + (r % 4);
+        if (key >= nv[i]) s[i][r] = -INFINITY;
+      }
+    }
+    tmax[i] = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) tmax[i] = fmaxf(tmax[i], s[i][r]);
+    tmax[i] = on[i] ? tmax[i] * scale_log2 : -INFINITY;
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) tmax[i] = fmaxf(tmax[i], __shfl_xor(tmax[i], 32, 64));
+  const float m_a = (tmax[0] > st.m + kLazy) ? tmax[0] : st.m;
+  const float m_b = (tmax[1] > m_a + kLazy) ? tmax[1] : m_a;
+  if (__any(m_b != m_a)) {
+    f32x16 one[1] = {s[0]};
+    tile_softmax_pv<D, 1>(st, one, stage_a, vaddr, kb0, scale_log2, on_a, nva, h);
+    one[0] = s[1];
+    tile_softmax_pv<D, 1>(st, one, stage_b, vaddr, kb0, scale_log2, on_b, nvb, h);
+    return;
+  }
+  const float m_use = (m_a == -INFINITY) ? 0.f : m_a;
+  const float alpha = __builtin_amdgcn_exp2f(st.m - m_use);
+  bf16x8 pa[2], pb[2];
+  float lsum[2] = {0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      float pf = __builtin_amdgcn_exp2f(fmaf(s[i][r], scale_log2, -m_use));
+      if (!on[i]) pf = 0.f;
+      lsum[i] += pf;
+      if (i == 0) pa[r / 8][r % 8] = (__bf16)pf;
+      else pb[r / 8][r % 8] = (__bf16)pf;
+    }
+  st.l = (st.l * alpha + lsum[0]) + lsum[1];
+  st.m = m_a;
+  if (__any(alpha != 1.f)) {
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) st.o[db][r] *= alpha;
+  }
+  tile_pv<D, 1>(st, pa, stage_a, vaddr, kb0);
+  tile_pv<D, 1>(st, pb, stage_b, vaddr, kb0);
+}
+
 // A tile of the stream (all wavefront-uniform).  TileRaw is what the table lookups deliver (fetched one iteration
 // before the tile is issued, with no arithmetic on the loaded words, so that the wait for them falls into the
 // next iteration); TileDesc adds the addresses.
@@ -262,15 +342,14 @@ struct TileDesc {
 template <int D, int MODE, int LAYOUT, int NRG>
 __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void attn_stream_kernel(const PassParams p) {
   constexpr int NSETS = (MODE == kPassSparseRefresh) ? 2 : 1;
-  constexpr bool kWhole = LAYOUT == kKeySplit && whole_tiles(D, MODE);
-  using C = SCfg<D, LAYOUT, NSETS, NRG, kWhole>;
+  using C = SCfg<D, LAYOUT, NSETS, NRG>;
   static_assert(MODE == kPassDense || MODE == kPassDenseHeads || MODE == kPassDensePaged || MODE == kPassSparseReuse ||
                     MODE == kPassSparseRefresh || MODE == kPassInternal, "modes of the streaming kernel");
   static_assert(MODE != kPassSparseRefresh || LAYOUT != kRowPair, "two accumulator sets: key halves");
   static_assert(MODE != kPassInternal || LAYOUT == kRowPair, "internal pass: row-pair layout");
   // Row-pair layout: two tiles per barrier (tiles t, t+1 are computed while t+2, t+3 are in flight), measured 2 % faster
-  // at the video shape than one tile per barrier; whole tiles of the key split the same; halves of tiles: one tile per barrier, NS - 1 in flight.
-  constexpr bool kPairs = LAYOUT == kRowPair || kWhole;
+  // at the video shape than one tile per barrier; tile split and head_dim 64 the same; key split at 128: one tile per barrier, NS - 1 in flight.
+  constexpr bool kPairs = LAYOUT != kKeySplit || paired_halves(D, LAYOUT);
   constexpr bool kHalves = LAYOUT != kRowPair;       // two wavefronts per row group, each with half of the keys
   constexpr int AHEAD = kPairs ? C::NS - 2 : C::NS - 1;
   static_assert(!kPairs || C::NS % 2 == 0, "pairs of tiles: an even number of stages");
@@ -282,7 +361,7 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));     // wavefront-uniform (scalar)
   const int rg = (LAYOUT == kRowPair) ? wave : (wave % NRG);     // 32-row group
   const int half = kHalves ? (wave / NRG) : 0;                   // keys of this wavefront: half of every tile, or every other tile
-  const int kb0 = (kHalves && !kWhole) ? half : 0;              // first 32-key block of a tile
+  const int kb0 = (LAYOUT == kKeySplit) ? half : 0;              // first 32-key block of a tile
 
   // ---- workgroup -> (row tile, batch, KV head, split).  Hardware deals consecutive workgroup ids round-robin
   // to the 8 XCDs; each XCD gets a contiguous range of units so that row tiles sharing K/V share an L2.
@@ -376,8 +455,7 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
         if (split != 0) return;
         direct = true;
       }
-      if (direct || p.nsplit == 1) {
-        direct = true;
+      if (direct) {
         fin_o = p.o_final;
         fin_m = p.m_final;
         fin_l = p.l_final;
@@ -401,17 +479,38 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
   } else {
     total = (nkeys + C::KT - 1) / C::KT;
   }
-  const TileRange tr = (MODE == kPassInternal || (MODE == kPassDenseHeads && direct)) ? TileRange{0, total}
-                       : p.xcd_bias ? biased_range(total, p.nsplit, split) : split_range(total, p.div_nsplit, split);
-  const int ntiles = tr.end - tr.begin;
-  const uint32_t rsrc = (p.div_rowtiles.d == 1) ? blockIdx.x : unit;
-  const int rot = (MODE == kPassInternal || ntiles <= 0) ? 0 : (int)((rsrc * 13u + (rsrc >> 5) * 7u) % (unsigned)ntiles);
+  TileRange tr = (MODE == kPassInternal) ? TileRange{0, total}
+                 : p.xcd_bias ? biased_range(total, p.nsplit, split) : split_range(total, p.div_nsplit, split);
+  // per-head refresh, partials by rank: splits 2i and 2i + 1 take the even and the odd tiles of the same range
+  constexpr bool kByRank = MODE == kPassDenseHeads && LAYOUT == kRowPair;
+  int stride = 1, first = 0;
+  uint32_t rsrc = (p.div_rowtiles.d == 1) ? blockIdx.x : unit;
+  if constexpr (kByRank) {
+    if (direct) {
+      tr = TileRange{0, total};
+    } else {
+      const int pairs = p.nsplit / 2;
+      tr = split_range(total, pairs, split >> 1);
+      stride = 2;
+      first = split & 1;
+      rsrc = (uint32_t)((b * p.Hkv + kvh) * pairs + (split >> 1));
+    }
+  }
+  if constexpr (LAYOUT == kTileSplit) {
+    // as the register-staged refresh pass cuts them: the last split is blk_cost tiles shorter
+    tr = split_range(total + p.blk_cost, p.div_nsplit, split);
+    tr.begin = min(tr.begin, total);
+    tr.end = min(tr.end, total);
+  }
+  const int range = tr.end - tr.begin;
+  const int ntiles = kByRank ? (range - first + stride - 1) / stride : range;
+  const int rot = ((MODE == kPassInternal && !p.rotate) || range <= 0) ? 0 : (int)((rsrc * 13u + (rsrc >> 5) * 7u) % (unsigned)range);
   const uint32_t* __restrict__ bmask = p.blk_mask ? p.blk_mask + (size_t)bk * p.nblk : nullptr;
   const int32_t* __restrict__ ulist = p.union_list ? p.union_list + (size_t)bk * p.nblk : nullptr;
   const uint32_t* __restrict__ umask = p.union_mask ? p.union_mask + (size_t)bk * p.nblk : nullptr;
   auto tile_raw = [&](int i) -> TileRaw {        // i-th tile of this workgroup: table lookups only
-    int j = i + rot;
-    if (j >= ntiles) j -= ntiles;
+    int j = (kByRank ? stride * i + first : i) + rot;
+    if (j >= range) j -= range;
     TileRaw r;
     r.e = tr.begin + j;
     r.word = 0;
@@ -620,6 +719,42 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
     }
   };
 
+  // two tiles whose key halves this wavefront owns: as half_tile for one and then the other, with the same results bit for
+  // bit, but the scores, the cross-lane maxima and the weights of both in one go
+  auto two_tiles = [&](const unsigned char* stage_a, int k0a, uint32_t mask_a, const unsigned char* stage_b, int k0b,
+                       uint32_t mask_b) __attribute__((always_inline)) {
+    const int nva = min(C::KT, nkeys - k0a), nvb = min(C::KT, nkeys - k0b);
+    bool ona[NSETS], onb[NSETS];
+    bool any_a = false, any_b = false;
+#pragma unroll
+    for (int i = 0; i < NSETS; ++i) {
+      ona[i] = lane_on_of(mask_a, i);
+      onb[i] = lane_on_of(mask_b, i);
+      any_a = any_a || ona[i];
+      any_b = any_b || onb[i];
+    }
+    const bool need_a = (!kMasked || __any(any_a)) && (MODE != kPassSparseReuse || nva > 0);
+    const bool need_b = (!kMasked || __any(any_b)) && (MODE != kPassSparseReuse || nvb > 0);
+    if (!(need_a && need_b)) {
+      if (need_a) half_tile(stage_a, k0a, mask_a);
+      if (need_b) half_tile(stage_b, k0b, mask_b);
+      return;
+    }
+    f32x16 s[2];
+    two_scores<D>(s, qreg, stage_a, stage_b, kaddr, kb0);
+#pragma unroll
+    for (int i = 0; i < NSETS; ++i) {
+      const bool set_a = NSETS == 1 || __any(ona[i]), set_b = NSETS == 1 || __any(onb[i]);
+      if (set_a && set_b) {
+        two_softmax_pv<D>(accs[i], s, stage_a, stage_b, vaddr, kb0, p.scale_log2, ona[i], onb[i], nva, nvb, h);
+      } else if (set_a || set_b) {
+        f32x16 s1[1] = {set_a ? s[0] : s[1]};
+        tile_softmax_pv<D, 1>(accs[i], s1, set_a ? stage_a : stage_b, vaddr, kb0, p.scale_log2, set_a ? ona[i] : onb[i],
+                              set_a ? nva : nvb, h);
+      }
+    }
+  };
+
   if constexpr (LAYOUT == kRowPair) {
     // two tiles per barrier; the prologue put tiles 0 .. AHEAD-1 in flight, iteration t adds tiles t+AHEAD, t+AHEAD+1
     // into the stages of tiles t-2, t-1 (or the query stages), which every wavefront left before this barrier
@@ -644,7 +779,7 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
         }
       advance();
     }
-  } else if constexpr (kWhole) {
+  } else if constexpr (LAYOUT == kTileSplit) {
     for (int t = 0; t < ntiles; t += 2) {
       wait_tiles<C::LPT>(min(AHEAD - 2, max(ntiles - 2 - t, 0)));   // tiles issued after tile t+1 so far
       __syncthreads();
@@ -654,6 +789,20 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
       const uint32_t mask = half ? qmask[1] : qmask[0];
       advance();
       if (t + half < ntiles) half_tile(ring + ((t + half) % C::NS) * C::STAGE, k0, mask);
+    }
+  } else if constexpr (kPairs) {
+    for (int t = 0; t < ntiles; t += 2) {
+      wait_tiles<C::LPT>(min(AHEAD - 2, max(ntiles - 2 - t, 0)));
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < 2; ++u) refill(t, u);
+      const int k0a = qk0[0], k0b = qk0[1];
+      const uint32_t mask_a = qmask[0], mask_b = qmask[1];
+      advance();
+      const unsigned char* stage_a = ring + (t % C::NS) * C::STAGE;
+      const unsigned char* stage_b = ring + ((t + 1) % C::NS) * C::STAGE;
+      if (t + 1 < ntiles) two_tiles(stage_a, k0a, mask_a, stage_b, k0b, mask_b);
+      else half_tile(stage_a, k0a, mask_a);
     }
   } else {
     for (int t = 0; t < ntiles; ++t) {
@@ -809,7 +958,7 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
 
 template <int D, int MODE, int LAYOUT, int NRG = 4>
 hipError_t launch_stream(const PassParams& p, hipStream_t s) {
-  using C = SCfg<D, LAYOUT, (MODE == kPassSparseRefresh) ? 2 : 1, NRG, LAYOUT == kKeySplit && whole_tiles(D, MODE)>;
+  using C = SCfg<D, LAYOUT, (MODE == kPassSparseRefresh) ? 2 : 1, NRG>;
   auto kern = attn_stream_kernel<D, MODE, LAYOUT, NRG>;
   static LdsLimit lim;
   hipError_t e = raise_lds_limit(kern, C::LDS, lim, C::LDS);
@@ -825,7 +974,7 @@ hipError_t launch_stream(const PassParams& p, hipStream_t s) {
   {
     // long streams only: below 64 tiles per split a 1/64 bias rounds away
     const int tiles = (p.nkeys + kKeyTile - 1) / kKeyTile;
-    q.xcd_bias = ((MODE == kPassDense || MODE == kPassSparseRefresh) && ntile_rows == 1 && p.nsplit % 2 == 0 &&
+    q.xcd_bias = (LAYOUT == kKeySplit && (MODE == kPassDense || MODE == kPassSparseRefresh) && ntile_rows == 1 && p.nsplit % 2 == 0 &&
                   nwg % 8 == 0 && tiles >= 64 * p.nsplit) ? 1 : 0;
   }
   q.div_rowtiles = make_fastdiv((uint32_t)ntile_rows);
@@ -850,9 +999,16 @@ hipError_t launch_stream_d(const PassParams& p, PassMode mode, hipStream_t s) {
   switch (mode) {
     case kPassDense:
       if (dense_row_pairs(nrows, D)) return launch_stream<D, kPassDense, kRowPair>(p, s);
+      if (p.whole_tiles) {
+        if (nrows <= 32) return launch_stream<D, kPassDense, kTileSplit, 1>(p, s);
+        if (nrows <= 64) return launch_stream<D, kPassDense, kTileSplit, 2>(p, s);
+        return launch_stream<D, kPassDense, kTileSplit, 4>(p, s);
+      }
       return launch_key_split<D, kPassDense>(p, s);
     case kPassDenseHeads:
-      if (dense_row_pairs(nrows, D)) return launch_stream<D, kPassDenseHeads, kRowPair>(p, s);
+      // many rows per KV head, with a hint: 3 of 12 heads of 4680 rows against 37440 keys 354 us by the register-staged
+      // kernel in 2 splits, 284 us here in 4
+      if (p.heads_cap > 0) return launch_stream<D, kPassDenseHeads, kRowPair>(p, s);
       return launch_key_split<D, kPassDenseHeads>(p, s);
     case kPassDensePaged: return launch_key_split<D, kPassDensePaged>(p, s);
     case kPassSparseReuse: return launch_key_split<D, kPassSparseReuse>(p, s);
@@ -871,8 +1027,10 @@ bool stream_bf16_covers(const PassParams& p, int D, PassMode mode) {
   const int tiles = (p.nkeys + kKeyTile - 1) / kKeyTile;
   switch (mode) {
     case kPassDense:
-    case kPassDenseHeads:
       return (nrows <= 128 || dense_row_pairs(nrows, D)) && tiles >= 8 * p.nsplit;
+    case kPassDenseHeads:
+      if (p.heads_cap > 0) return true;
+      return nrows <= 128 && tiles >= 8 * p.nsplit;
     case kPassDensePaged:
     case kPassSparseReuse:
     case kPassSparseRefresh:

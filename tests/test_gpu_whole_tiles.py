@@ -2,8 +2,10 @@
 counts around the ring's length, ragged last tiles, every row-group count, dense and sparse, against the numpy float64
 oracle.  Tolerances: those of bf16 storage (fb_testlib)."""
 import pytest
+import torch
 
 from oracle import flashblock_oracle as orc
+from paper_2602_05305_amd import flashblock as fb
 from paper_2602_05305_amd import workloads as wl
 
 import fb_testlib as T
@@ -33,3 +35,30 @@ def test_sparse(P, key_block, topk):
         T.assert_close(g["out"], o["out"], "bf16", w.name + " out")
         T.check_partial(g["ext"], o["ext"], "bf16", w.name + " sel(+)res")
         T.check_partial(g["residual"], o["residual"], "bf16", w.name + " residual")
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,P,Bq", [
+    (6, 16, 8, 128, 2700, 31),       # odd block: streaming pass by whole tiles, splits folded by the internal pass
+    (16, 8, 4, 128, 3000, 9),        # 18 rows per KV head
+    (10, 8, 4, 128, 4100, 64),       # 128 rows, a block of one whole tile
+    (16, 8, 4, 64, 9000, 24),        # head_dim 64, more than 32 tiles per split
+    (40, 8, 4, 128, 700, 40),        # too short for the streaming kernel: register-staged, as before
+])
+def test_refresh_step_with_few_splits(B, Hq, Hkv, d, P, Bq):
+    w = wl.Workload(f"fs_{B}_{d}_{P}_{Bq}", B, Hq, Hkv, d, P, Bq, 2, 2, "bf16", 1.0)
+    Kp, Vp = wl.make_prefix(w, 505)
+    steps = wl.make_block_steps(w, 505)
+    ora = orc.run_block_dense(Kp, Vp, steps, 2)
+    shape, ext, ws = T.shape_of(w), T.Partial(w), T.workspace(T.shape_of(w))
+    kp, vp = T.to_dev(Kp, "bf16"), T.to_dev(Vp, "bf16")
+    for t, step in enumerate(steps):
+        q, kb, vb = (T.to_dev(x, "bf16") for x in step)
+        out, lse = torch.empty_like(q), torch.empty(q.shape[:3], device=T.DEV)
+        if t == 0:
+            fb.fb_refresh_step(shape, q, kp, vp, kb, vb, ext.o, ext.m, ext.lse, out, lse, ws)
+        else:
+            fb.fb_internal_merge(shape, q, kb, vb, ext.o, ext.m, ext.lse, out, lse)
+        torch.cuda.synchronize()
+        T.assert_close(out.double().cpu().numpy(), ora[t]["out"], "bf16", f"{w.name} step {t} out")
+        T.assert_close(lse.double().cpu().numpy(), ora[t]["lse"], "bf16", f"{w.name} step {t} lse", lse=True)
+    T.check_partial(ext.numpy(), ora[0]["ext"], "bf16", w.name + " ext")
