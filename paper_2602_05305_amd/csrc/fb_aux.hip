@@ -870,7 +870,8 @@ hipError_t launch_head_similarity(const float* o_a, const float* o_b, float* sim
 hipError_t launch_combine(const CombineParams& p, hipStream_t s) {
   const size_t n = (size_t)p.rows * (p.D / 4);
   if (n == 0) return hipSuccess;
-  if (p.nsplit >= 8 && p.ws_o != nullptr)
+  // (one workgroup per row: not for the per-head refresh of many rows, most of whose rows are left alone)
+  if (p.nsplit >= 8 && p.ws_o != nullptr && p.heads_cap == 0)
     hipLaunchKernelGGL(combine_wide_kernel, dim3((unsigned)p.rows), dim3(256), 0, s, p);
   else
     hipLaunchKernelGGL(combine_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p);

@@ -51,7 +51,9 @@ typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
-enum StreamLayout : int { kKeySplit = 0, kTileSplit = 1, kRowPair = 2 };
+// (kKeySplitSingle: the key split with one tile per barrier at head_dim 64 as well)
+enum StreamLayout : int { kKeySplit = 0, kTileSplit = 1, kRowPair = 2, kKeySplitSingle = 3 };
+constexpr bool key_split(int layout) { return layout == kKeySplit || layout == kKeySplitSingle; }
 
 // Key split at head_dim 64: two tiles per barrier, their scores and weights computed together, because a tile's fixed cost
 // (barrier, refill, the softmax's cross-lane step) is large against its 16 KB: batch 4, 64K keys, 32 rows
@@ -73,11 +75,11 @@ struct SCfg {
   static constexpr int NLOAD = OPB / (THREADS * 16);  // direct-to-LDS loads per lane, operand and tile
   static constexpr int LSTEP = NW * 1024;             // LDS bytes one load of every wavefront covers
   static constexpr int LPT = 2 * NLOAD;               // loads per lane and tile
-  static constexpr int NS = (D == 128) ? 4 : (LAYOUT == kRowPair) ? 6 : 8;       // ring stages
+  static constexpr int NS = (D == 128) ? 4 : (LAYOUT == kRowPair || LAYOUT == kKeySplitSingle) ? 6 : 8;       // ring stages
   static constexpr int NKS = D / 16;                  // MFMA k-steps of the score product
   static constexpr int NDB = D / 32;                  // 32-wide output column blocks
   static constexpr int ROWS = (LAYOUT == kRowPair) ? 256 : 32 * NRG;
-  static constexpr int NKB = (LAYOUT == kKeySplit) ? 1 : 2;    // 32-key blocks of a tile one wavefront computes
+  static constexpr int NKB = key_split(LAYOUT) ? 1 : 2;    // 32-key blocks of a tile one wavefront computes
   static constexpr int QPARTS = (ROWS + 63) / 64;             // the query rows are loaded 64 at a time, like a K operand
   static constexpr int QSTAGES = (QPARTS * OPB + STAGE - 1) / STAGE;   // ring stages they pass through at start
   static constexpr int MERGE = (LAYOUT != kRowPair) ? NSETS * NRG * 2 * (NDB / 2 * 16 + 2) * 64 * 4 : 0;   // key-half exchange
@@ -349,7 +351,7 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
   static_assert(MODE != kPassInternal || LAYOUT == kRowPair, "internal pass: row-pair layout");
   // Row-pair layout: two tiles per barrier (tiles t, t+1 are computed while t+2, t+3 are in flight), measured 2 % faster
   // at the video shape than one tile per barrier; tile split and head_dim 64 the same; key split at 128: one tile per barrier, NS - 1 in flight.
-  constexpr bool kPairs = LAYOUT != kKeySplit || paired_halves(D, LAYOUT);
+  constexpr bool kPairs = !key_split(LAYOUT) || paired_halves(D, LAYOUT);
   constexpr bool kHalves = LAYOUT != kRowPair;       // two wavefronts per row group, each with half of the keys
   constexpr int AHEAD = kPairs ? C::NS - 2 : C::NS - 1;
   static_assert(!kPairs || C::NS % 2 == 0, "pairs of tiles: an even number of stages");
@@ -361,7 +363,7 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));     // wavefront-uniform (scalar)
   const int rg = (LAYOUT == kRowPair) ? wave : (wave % NRG);     // 32-row group
   const int half = kHalves ? (wave / NRG) : 0;                   // keys of this wavefront: half of every tile, or every other tile
-  const int kb0 = (LAYOUT == kKeySplit) ? half : 0;              // first 32-key block of a tile
+  const int kb0 = key_split(LAYOUT) ? half : 0;              // first 32-key block of a tile
 
   // ---- workgroup -> (row tile, batch, KV head, split).  Hardware deals consecutive workgroup ids round-robin
   // to the 8 XCDs; each XCD gets a contiguous range of units so that row tiles sharing K/V share an L2.
@@ -385,7 +387,7 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
     // run on even XCDs and odd-numbered ones on odd XCDs
     if (p.xcd_bias) w = (xcd >> 1) * (2 * q8) + 2 * j + (xcd & 1);
     if constexpr (MODE == kPassDenseHeads) {
-      if (p.div_rowtiles.d > 1) w = bid;     // whole heads drop out: deal a head's row tiles over the XCDs
+      if (LAYOUT == kRowPair || p.div_rowtiles.d > 1) w = bid;     // whole heads drop out: deal a head's row tiles over the XCDs
     }
     rest = fastdiv((uint32_t)w, p.div_rowtiles);
     rt = w - (int)(rest * p.div_rowtiles.d);
@@ -397,8 +399,45 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
     split = (int)(rest - r2 * p.div_nsplit.d);
     rest = r2;
   }
-  int b = (int)fastdiv(rest, p.div_hkv);
-  const int kvh = (int)(rest - (uint32_t)b * p.div_hkv.d);
+  int b, kvh;
+  constexpr bool kByRank = MODE == kPassDenseHeads && LAYOUT == kRowPair;
+  bool direct = p.direct != 0;                               // this workgroup writes the final partial
+  int rank = 0;
+  if constexpr (kByRank) {
+    // The first B * heads_cap * nsplit units belong to the flagged KV groups by rank (the workgroups that have work are then
+    // the first of the grid and spread evenly over the chip whatever the mask; dealt out by head, some masks left a
+    // shader engine with two rounds of workgroups: 569 or 1010 us for 6 of 12 heads); B * Hkv units at the end, one split
+    // each, are for groups beyond the hint.
+    const uint32_t ranked = (uint32_t)(p.B * p.heads_cap);
+    const uint32_t units = ranked * p.div_nsplit.d;
+    const bool extra = unit >= units;
+    const uint32_t bu = extra ? unit - units : rest;
+    const uint32_t per = extra ? (uint32_t)p.Hkv : (uint32_t)p.heads_cap;
+    b = (int)(bu / per);
+    const int want = (int)(bu - (uint32_t)b * per);          // rank, or KV group
+    int seen = 0, hit = -1;
+    for (int g0 = 0; g0 < p.Hkv && hit < 0; g0 += 64) {
+      unsigned long long mask = __ballot(g0 + lane < p.Hkv && group_flagged(p.head_on, b, p.Hq, p.G, g0 + lane));
+      if (extra) {
+        if (want < g0 + 64) {
+          const unsigned long long below = (1ull << (want - g0)) - 1;
+          if (((mask >> (want - g0)) & 1) && seen + __popcll(mask & below) >= p.heads_cap) hit = want;
+          break;
+        }
+      } else if (want < seen + __popcll(mask)) {
+        for (int k = want - seen; k > 0; --k) mask &= mask - 1;
+        hit = g0 + __ffsll(mask) - 1;
+      }
+      seen += __popcll(mask);
+    }
+    if (hit < 0) return;                                     // workgroup-uniform
+    kvh = __builtin_amdgcn_readfirstlane(hit);
+    rank = want;
+    if (extra) direct = true;
+  } else {
+    b = (int)fastdiv(rest, p.div_hkv);
+    kvh = (int)(rest - (uint32_t)b * p.div_hkv.d);
+  }
   if constexpr (MODE == kPassDensePaged) {
     if (p.seq_order != nullptr) {
       b = sload(p.seq_order, b);
@@ -437,31 +476,10 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
     head_active = row_ok && p.head_on[b * p.Hq + kvh * p.G + row / p.Bq] != 0;
     if (!__syncthreads_or(head_active ? 1 : 0)) return;
   }
-  bool direct = p.direct != 0;                               // this workgroup writes the final partial
-  int rank = kvh, ranks = p.Hkv;                             // where the KV group's split partials go
-  float* __restrict__ fin_o = p.ws_o;
-  float* __restrict__ fin_m = p.ws_m;
-  float* __restrict__ fin_l = p.ws_l;
-  if constexpr (MODE == kPassDenseHeads) {
-    if (p.heads_cap > 0) {
-      rank = 0;
-      for (int g0 = 0; g0 < kvh; g0 += C::THREADS) {
-        const int g = g0 + (int)threadIdx.x;
-        rank += __syncthreads_count(g < kvh && group_flagged(p.head_on, b, p.Hq, p.G, g));
-      }
-      rank = __builtin_amdgcn_readfirstlane(rank);
-      ranks = p.heads_cap;
-      if (rank >= ranks) {                                   // more flagged groups than the hint said
-        if (split != 0) return;
-        direct = true;
-      }
-      if (direct) {
-        fin_o = p.o_final;
-        fin_m = p.m_final;
-        fin_l = p.l_final;
-      }
-    }
-  }
+  const int slot = kByRank ? rank : kvh, slots = kByRank ? p.heads_cap : p.Hkv;      // where its split partials go
+  float* __restrict__ fin_o = kByRank ? p.o_final : p.ws_o;
+  float* __restrict__ fin_m = kByRank ? p.m_final : p.ws_m;
+  float* __restrict__ fin_l = kByRank ? p.l_final : p.ws_l;
 
   // contiguous cache: this KV head's [nkeys, D] slab; paged cache: the pool (tiles add their page offset)
   const unsigned char* __restrict__ Kg =
@@ -482,7 +500,6 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
   TileRange tr = (MODE == kPassInternal) ? TileRange{0, total}
                  : p.xcd_bias ? biased_range(total, p.nsplit, split) : split_range(total, p.div_nsplit, split);
   // per-head refresh, partials by rank: splits 2i and 2i + 1 take the even and the odd tiles of the same range
-  constexpr bool kByRank = MODE == kPassDenseHeads && LAYOUT == kRowPair;
   int stride = 1, first = 0;
   uint32_t rsrc = (p.div_rowtiles.d == 1) ? blockIdx.x : unit;
   if constexpr (kByRank) {
@@ -930,7 +947,7 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
       return;
     }
     if (!row_ok) return;
-    const size_t wrow = ((size_t)(split * p.B + b) * ranks + rank) * nrows + row;
+    const size_t wrow = ((size_t)(split * p.B + b) * slots + slot) * nrows + row;
 #pragma unroll
     for (int i = 0; i < NSETS; ++i) {
       float* __restrict__ w_o = i ? p.ws_o2 : p.ws_o;
@@ -967,6 +984,7 @@ hipError_t launch_stream(const PassParams& p, hipStream_t s) {
   const int ntile_rows = (nrows + C::ROWS - 1) / C::ROWS;
   long long nwg = (long long)p.B * p.Hkv * ntile_rows * p.nsplit;
   if (MODE == kPassDensePaged) nwg = (((long long)p.B * p.Hkv * p.nsplit + 7) / 8) * 8 * ntile_rows;
+  if (MODE == kPassDenseHeads && LAYOUT == kRowPair) nwg = (long long)p.B * (p.heads_cap * p.nsplit + p.Hkv) * ntile_rows;
   if (nwg >= (1ll << 31)) return hipErrorInvalidValue;
   PassParams q = p;
   if (MODE == kPassDensePaged) q.div_page = make_fastdiv((uint32_t)p.page_size);
@@ -974,7 +992,7 @@ hipError_t launch_stream(const PassParams& p, hipStream_t s) {
   {
     // long streams only: below 64 tiles per split a 1/64 bias rounds away
     const int tiles = (p.nkeys + kKeyTile - 1) / kKeyTile;
-    q.xcd_bias = (LAYOUT == kKeySplit && (MODE == kPassDense || MODE == kPassSparseRefresh) && ntile_rows == 1 && p.nsplit % 2 == 0 &&
+    q.xcd_bias = (key_split(LAYOUT) && (MODE == kPassDense || MODE == kPassSparseRefresh) && ntile_rows == 1 && p.nsplit % 2 == 0 &&
                   nwg % 8 == 0 && tiles >= 64 * p.nsplit) ? 1 : 0;
   }
   q.div_rowtiles = make_fastdiv((uint32_t)ntile_rows);
@@ -988,6 +1006,15 @@ hipError_t launch_stream(const PassParams& p, hipStream_t s) {
 template <int D, int MODE>
 hipError_t launch_key_split(const PassParams& p, hipStream_t s) {
   const int nrows = p.G * p.Bq;
+  if constexpr (D == 64 && (MODE == kPassSparseRefresh || MODE == kPassSparseReuse)) {
+    // sparse passes with short streams: waiting for pairs of tiles costs more than it saves (32 / 8 heads, 32 rows, a
+    // block at 32K keys, 16 tiles per split, 143.8 us single and 146.5 paired; at 48K, 24 tiles, 177.4 and 174.2)
+    if (p.nkeys < 24 * kKeyTile * p.nsplit) {
+      if (nrows <= 32) return launch_stream<D, MODE, kKeySplitSingle, 1>(p, s);
+      if (nrows <= 64) return launch_stream<D, MODE, kKeySplitSingle, 2>(p, s);
+      return launch_stream<D, MODE, kKeySplitSingle, 4>(p, s);
+    }
+  }
   if (nrows <= 32) return launch_stream<D, MODE, kKeySplit, 1>(p, s);
   if (nrows <= 64) return launch_stream<D, MODE, kKeySplit, 2>(p, s);
   return launch_stream<D, MODE, kKeySplit, 4>(p, s);
