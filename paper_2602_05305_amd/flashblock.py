@@ -108,19 +108,41 @@ def make_shape(batch, n_q_heads, n_kv_heads, head_dim, block_len, prefix_len, dt
                     int(code), float(scale))
 
 
+# A reuse step is one kernel of about 4 us, and a launch costs the host 3.4 us: marshalling has to stay well under
+# 1 us per call.  Device addresses are passed as integers (ctypes converts them by the argument types), and the current
+# stream's handle is asked for directly: torch.cuda.current_stream() builds a Stream object, 2.5 us.
 def _ptr(t):
-    return None if t is None else c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+def _nbytes(t):
+    return t.numel() * t.element_size()
+
+
+def _current_stream_handle():
+    """Handle of torch's current stream on the current device; the first call picks the function that gets it."""
+    global _current_stream_handle
+    import torch
+    get_device, get_stream = getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    handle = torch.cuda.current_stream().cuda_stream          # initialises the device where nothing has yet
+    if get_device is None or get_stream is None or get_stream(get_device()) != handle:
+        def current():
+            return torch.cuda.current_stream().cuda_stream
+    else:
+        def current():
+            return get_stream(get_device())
+    _current_stream_handle = current
+    return handle
 
 
 def _stream(stream):
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
-    return c_void_p(stream.cuda_stream) if hasattr(stream, "cuda_stream") else c_void_p(stream)
+        return _current_stream_handle()
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else stream
 
 
 def _check(status, where):
-    if status != FB_OK:
+    if status:
         lib = load_library()
         detail = lib.fb_status_string(status).decode()
         if status == FB_ERR_HIP:
@@ -151,14 +173,14 @@ def fb_workspace_bytes(shape: fb_shape, key_block: int = 0, topk: int = 0, n_spl
 def fb_external_partial(shape, q, k_prefix, v_prefix, o_part, m_part, lse_part, workspace, stream=None):
     st = load_library().fb_external_partial(ctypes.byref(shape), _ptr(q), _ptr(k_prefix), _ptr(v_prefix),
                                             _ptr(o_part), _ptr(m_part), _ptr(lse_part), _ptr(workspace),
-                                            workspace.numel() * workspace.element_size(), _stream(stream))
+                                            _nbytes(workspace), _stream(stream))
     _check(st, "fb_external_partial")
 
 
 def fb_external_partial_ex(shape, q, k_prefix, v_prefix, o_part, m_part, lse_part, n_splits, workspace, stream=None):
     st = load_library().fb_external_partial_ex(ctypes.byref(shape), _ptr(q), _ptr(k_prefix), _ptr(v_prefix),
                                                _ptr(o_part), _ptr(m_part), _ptr(lse_part), n_splits, _ptr(workspace),
-                                               workspace.numel() * workspace.element_size(), _stream(stream))
+                                               _nbytes(workspace), _stream(stream))
     _check(st, "fb_external_partial_ex")
 
 
@@ -167,7 +189,7 @@ def fb_external_partial_prof(shape, q, k_prefix, v_prefix, o_part, m_part, lse_p
     """ev_*: raw hipEvent_t handles (ints / c_void_p) or None."""
     st = load_library().fb_external_partial_prof(ctypes.byref(shape), _ptr(q), _ptr(k_prefix), _ptr(v_prefix),
                                                  _ptr(o_part), _ptr(m_part), _ptr(lse_part), n_splits, _ptr(workspace),
-                                                 workspace.numel() * workspace.element_size(), ev_begin, ev_attn_end,
+                                                 _nbytes(workspace), ev_begin, ev_attn_end,
                                                  ev_end, _stream(stream))
     _check(st, "fb_external_partial_prof")
 
@@ -191,7 +213,7 @@ def fb_external_partial_heads(shape, q, k_prefix, v_prefix, head_mask, o_part, m
     st = load_library().fb_external_partial_heads(ctypes.byref(shape), _ptr(q), _ptr(k_prefix), _ptr(v_prefix),
                                                   _ptr(head_mask), n_active_heads, _ptr(o_part), _ptr(m_part),
                                                   _ptr(lse_part),
-                                                  _ptr(workspace), workspace.numel() * workspace.element_size(),
+                                                  _ptr(workspace), _nbytes(workspace),
                                                   _stream(stream))
     _check(st, "fb_external_partial_heads")
 
@@ -210,7 +232,7 @@ def fb_paged_splits(shape) -> int:
 def fb_external_partial_paged(shape, q, kv, o_part, m_part, lse_part, workspace, n_splits=0, stream=None):
     st = load_library().fb_external_partial_paged(ctypes.byref(shape), _ptr(q), ctypes.byref(kv), _ptr(o_part),
                                                   _ptr(m_part), _ptr(lse_part), n_splits, _ptr(workspace),
-                                                  workspace.numel() * workspace.element_size(), _stream(stream))
+                                                  _nbytes(workspace), _stream(stream))
     _check(st, "fb_external_partial_paged")
 
 
@@ -219,7 +241,7 @@ def fb_refresh_step_paged(shape, q, kv, k_block, v_block, o_part, m_part, lse_pa
     st = load_library().fb_refresh_step_paged(ctypes.byref(shape), _ptr(q), ctypes.byref(kv), _ptr(k_block),
                                               _ptr(v_block), _ptr(o_part), _ptr(m_part), _ptr(lse_part), _ptr(out),
                                               _ptr(lse_out), n_splits, _ptr(workspace),
-                                              workspace.numel() * workspace.element_size(), _stream(stream))
+                                              _nbytes(workspace), _stream(stream))
     _check(st, "fb_refresh_step_paged")
 
 
@@ -238,7 +260,7 @@ def fb_refresh_step(shape, q, k_prefix, v_prefix, k_block, v_block, o_part, m_pa
                     workspace, stream=None):
     st = load_library().fb_refresh_step(ctypes.byref(shape), _ptr(q), _ptr(k_prefix), _ptr(v_prefix), _ptr(k_block),
                                         _ptr(v_block), _ptr(o_part), _ptr(m_part), _ptr(lse_part), _ptr(out),
-                                        _ptr(lse_out), _ptr(workspace), workspace.numel() * workspace.element_size(),
+                                        _ptr(lse_out), _ptr(workspace), _nbytes(workspace),
                                         _stream(stream))
     _check(st, "fb_refresh_step")
 
@@ -248,7 +270,7 @@ def fb_refresh_step_prof(shape, q, k_prefix, v_prefix, k_block, v_block, o_part,
     st = load_library().fb_refresh_step_prof(ctypes.byref(shape), _ptr(q), _ptr(k_prefix), _ptr(v_prefix),
                                              _ptr(k_block), _ptr(v_block), _ptr(o_part), _ptr(m_part),
                                              _ptr(lse_part), _ptr(out), _ptr(lse_out), _ptr(workspace),
-                                             workspace.numel() * workspace.element_size(),
+                                             _nbytes(workspace),
                                              ev_begin, ev_attn_end, ev_end, _stream(stream))
     _check(st, "fb_refresh_step_prof")
 
@@ -263,7 +285,7 @@ def fb_select_workspace_bytes(shape, key_block) -> int:
 
 
 def fb_select_topk(shape, q, k_pooled, key_block, topk, sel_idx, workspace=None, stream=None):
-    nbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    nbytes = 0 if workspace is None else _nbytes(workspace)
     st = load_library().fb_select_topk(ctypes.byref(shape), _ptr(q), _ptr(k_pooled), key_block, topk, _ptr(sel_idx),
                                        _ptr(workspace), nbytes, _stream(stream))
     _check(st, "fb_select_topk")
@@ -276,7 +298,7 @@ def fb_select_mass_workspace_bytes(shape, key_block) -> int:
 def fb_select_topk_mass(shape, q, k_prefix, lse_part, key_block, topk, sel_idx, mass_out, workspace, stream=None):
     st = load_library().fb_select_topk_mass(ctypes.byref(shape), _ptr(q), _ptr(k_prefix), _ptr(lse_part), key_block,
                                             topk, _ptr(sel_idx), _ptr(mass_out), _ptr(workspace),
-                                            workspace.numel() * workspace.element_size(), _stream(stream))
+                                            _nbytes(workspace), _stream(stream))
     _check(st, "fb_select_topk_mass")
 
 
@@ -285,5 +307,5 @@ def fb_sparse_external_residual(shape, mode, q, k_prefix, v_prefix, key_block, t
     st = load_library().fb_sparse_external_residual(
         ctypes.byref(shape), mode, _ptr(q), _ptr(k_prefix), _ptr(v_prefix), key_block, topk, _ptr(sel_idx),
         _ptr(res_o), _ptr(res_m), _ptr(res_lse), _ptr(o_part), _ptr(m_part), _ptr(lse_part), _ptr(workspace),
-        workspace.numel() * workspace.element_size(), _stream(stream))
+        _nbytes(workspace), _stream(stream))
     _check(st, "fb_sparse_external_residual")
