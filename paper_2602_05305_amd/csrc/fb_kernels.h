@@ -144,6 +144,7 @@ struct PassParams {
   int xcd_bias;
   FastDiv div_rowtiles, div_nsplit, div_hkv;   // bf16 pass: decomposition of the linear workgroup index
   FastDiv div_page;                            // bf16 paged pass: key index -> page slot
+  FastDiv div_bias;                            // streaming bf16 pass, xcd_bias: by 64 * nsplit
   FastDiv div_tpb;                             // streaming sparse passes: tile index -> key block (tiles per key block)
 };
 
@@ -294,12 +295,13 @@ __device__ __forceinline__ TileRange split_range(int total, int nsplit, int spli
 // clocks, with the head-to-XCD assignment rotated), and the pass ends with its slowest XCD.  A fixed, deterministic
 // cut, deliberately a little weaker than the measured asymmetry: 128K pass 99.4 -> 97.4 us, batch 4 neutral; on a
 // board without the asymmetry it would cost under 2 %.
-__device__ __forceinline__ TileRange biased_range(int total, int nsplit, int split) {
-  auto cum = [](int s) -> unsigned long long { return 64ull * (unsigned)s + (unsigned long long)(s & 1); };
-  const unsigned long long den = 64ull * (unsigned)nsplit;
+// by_weights: division by 64 * nsplit (a 64-bit division here is some 250 cold instructions in front of the first load:
+// a refresh and a reuse step at 128K keys 112.2 -> 110.3 us); the host keeps total * 64 * nsplit below 2^31.
+__device__ __forceinline__ TileRange biased_range(int total, const FastDiv& by_weights, int split) {
+  auto cum = [](int s) -> uint32_t { return 64u * (uint32_t)s + (uint32_t)(s & 1); };
   TileRange r;
-  r.begin = (int)(((unsigned long long)(unsigned)total * cum(split)) / den);
-  r.end = (split + 1 == nsplit) ? total : (int)(((unsigned long long)(unsigned)total * cum(split + 1)) / den);
+  r.begin = (int)fastdiv((uint32_t)total * cum(split), by_weights);
+  r.end = (64u * (uint32_t)(split + 1) == by_weights.d) ? total : (int)fastdiv((uint32_t)total * cum(split + 1), by_weights);
   return r;
 }
 

@@ -498,7 +498,7 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
     total = (nkeys + C::KT - 1) / C::KT;
   }
   TileRange tr = (MODE == kPassInternal) ? TileRange{0, total}
-                 : p.xcd_bias ? biased_range(total, p.nsplit, split) : split_range(total, p.div_nsplit, split);
+                 : p.xcd_bias ? biased_range(total, p.div_bias, split) : split_range(total, p.div_nsplit, split);
   // per-head refresh, partials by rank: splits 2i and 2i + 1 take the even and the odd tiles of the same range
   int stride = 1, first = 0;
   uint32_t rsrc = (p.div_rowtiles.d == 1) ? blockIdx.x : unit;
@@ -993,7 +993,8 @@ hipError_t launch_stream(const PassParams& p, hipStream_t s) {
     // long streams only: below 64 tiles per split a 1/64 bias rounds away
     const int tiles = (p.nkeys + kKeyTile - 1) / kKeyTile;
     q.xcd_bias = (key_split(LAYOUT) && (MODE == kPassDense || MODE == kPassSparseRefresh) && ntile_rows == 1 && p.nsplit % 2 == 0 &&
-                  nwg % 8 == 0 && tiles >= 64 * p.nsplit) ? 1 : 0;
+                  nwg % 8 == 0 && tiles >= 64 * p.nsplit && (long long)tiles * 64 * p.nsplit < (1ll << 31)) ? 1 : 0;
+    q.div_bias = make_fastdiv(64u * (uint32_t)p.nsplit);
   }
   q.div_rowtiles = make_fastdiv((uint32_t)ntile_rows);
   q.div_nsplit = make_fastdiv((uint32_t)p.nsplit);
