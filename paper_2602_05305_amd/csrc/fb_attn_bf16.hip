@@ -911,6 +911,141 @@ __global__ __launch_bounds__(256 * NG, (VAR & 4) ? 2 : (NG > 1 || (MODE == kPass
   }
 }
 
+// Internal pass over a block of at most 64 keys, few rows: every wavefront is a workgroup of its own and finishes 32 rows
+// x 32 output columns without LDS and without a barrier.  The pass is a chain of latencies (launch, arguments, one round of
+// loads, two short matrix products, store), so what counts is that everything is requested at once: K rows and Q
+// rows come in matrix operand order straight from global memory, V as single elements (the column of a lane, its 8 keys of
+// a 16-key step; neighbouring lanes read neighbouring elements), the cached partial with them.  Scores and softmax are
+// repeated by the D / 32 wavefronts of a row group.  (Against 4 wavefronts that share a K / V tile through LDS: 4.12 -> 3.32 us
+// for 128 rows of 8 KV heads, head_dim 128, back to back.)
+template <int D, int NKB>
+__global__ __launch_bounds__(64) void internal_wave_kernel(const PassParams p) {
+  constexpr int NKS = D / 16, NDB = D / 32;
+  typedef const __attribute__((address_space(1))) uint16_t* gptr_u16;
+  typedef const __attribute__((address_space(1))) f32x4* gptr_f4;
+  typedef const __attribute__((address_space(1))) float* gptr_f;
+  const int lane = threadIdx.x, l32 = lane & 31, h = lane >> 5;
+  // one KV head's workgroups on one XCD: they share K, V and Q rows
+  const int bid = blockIdx.x, q8 = gridDim.x / 8, r8 = gridDim.x % 8, xcd = bid % 8;
+  const uint32_t w = (uint32_t)((xcd < r8 ? xcd * (q8 + 1) : r8 * (q8 + 1) + (xcd - r8) * q8) + bid / 8);
+  const int db = (int)(w % NDB);
+  const uint32_t rg = w / NDB;
+  const uint32_t bk = fastdiv(rg, p.div_rowtiles);               // batch * Hkv + KV head
+  const int rt = (int)(rg - bk * p.div_rowtiles.d);
+  const int nrows = p.G * p.Bq, nkeys = p.nkeys;
+  const int row = rt * 32 + l32;
+  const bool row_ok = row < nrows;
+  const size_t grow = (size_t)bk * nrows + min(row, nrows - 1);   // rows past the end read the last row; never stored
+  const __bf16* __restrict__ Q = (const __bf16*)p.q + grow * D + 8 * h;
+  const __bf16* __restrict__ K = (const __bf16*)p.k + (size_t)bk * nkeys * D;
+  const __bf16* __restrict__ V = (const __bf16*)p.v + (size_t)bk * nkeys * D;
+
+  u32x4 kr[NKB][NKS], qr[NKS];
+#pragma unroll
+  for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) kr[kb][ks] = gload128(K + (size_t)min(32 * kb + l32, nkeys - 1) * D + ks * 16 + 8 * h);
+#pragma unroll
+  for (int ks = 0; ks < NKS; ++ks) qr[ks] = gload128(Q + ks * 16);
+  uint16_t vr[2 * NKB][8];                                        // element e of step t: key 16 t + 8 (e / 4) + 4 h + e % 4
+#pragma unroll
+  for (int t = 0; t < 2 * NKB; ++t)
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      vr[t][e] = *((gptr_u16)V + (size_t)min(16 * t + 8 * (e / 4) + 4 * h + e % 4, nkeys - 1) * D + 32 * db + l32);
+  const bool has_ext = p.ext_o != nullptr;                        // uniform
+  f32x4 eo[4];
+  float em = -INFINITY, el = -INFINITY;
+  if (has_ext) {
+    em = *((gptr_f)p.ext_m + grow);
+    el = *((gptr_f)p.ext_lse + grow);
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) eo[q4] = *(gptr_f4)(p.ext_o + grow * D + 32 * db + 8 * q4 + 4 * h);
+  } else {
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) eo[q4] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+
+  f32x16 s[NKB];
+#pragma unroll
+  for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
+#pragma unroll
+  for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb)
+      s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kr[kb][ks]), __builtin_bit_cast(bf16x8, qr[ks]),
+                                                      s[kb], 0, 0, 0);
+  float m = -INFINITY;
+#pragma unroll
+  for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      if (32 * kb + 8 * (r / 4) + 4 * h + r % 4 >= nkeys) s[kb][r] = -INFINITY;
+      m = fmaxf(m, s[kb][r]);
+    }
+  m *= p.scale_log2;
+  m = fmaxf(m, __shfl_xor(m, 32, 64));
+  const float m_use = (m == -INFINITY) ? 0.f : m;
+  float l = 0.f;
+  bf16x8 pb[2 * NKB];
+#pragma unroll
+  for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float pf = __builtin_amdgcn_exp2f(fmaf(s[kb][r], p.scale_log2, -m_use));
+      l += pf;
+      pb[2 * kb + r / 8][r % 8] = (__bf16)pf;
+    }
+  l += __shfl_xor(l, 32, 64);
+  f32x16 o;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) o[r] = 0.f;
+#pragma unroll
+  for (int t = 0; t < 2 * NKB; ++t) {
+    u32x4 v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = (uint32_t)vr[t][2 * i] | ((uint32_t)vr[t][2 * i + 1] << 16);
+    o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v), pb[t], o, 0, 0, 0);
+  }
+  // Eq. 8-9 with the cached pair expressed through (o, m, lse): A_out e^{L_out-M} = o e^{m-M}
+  float me2 = -INFINITY, le = 0.f;
+  if (el != -INFINITY) {
+    me2 = em * kLog2e;
+    le = exp2f((el - em) * kLog2e);
+  }
+  const float M2 = fmaxf(me2, m);
+  const float Mu = (M2 == -INFINITY) ? 0.f : M2;
+  const float we = exp2f(me2 - Mu), wi = exp2f(m - Mu);
+  const float den = le * we + l * wi;
+  const float inv = den > 0.f ? 1.f / den : 0.f;
+  if (!row_ok) return;
+  __bf16* out = (__bf16*)p.out + grow * D + 32 * db + 4 * h;
+#pragma unroll
+  for (int q4 = 0; q4 < 4; ++q4) {
+    float r[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = (o[4 * q4 + i] * wi + eo[q4][i] * we) * inv;
+    u32x2 pk;
+    pk.x = pack_bf16x2(r[0], r[1]);
+    pk.y = pack_bf16x2(r[2], r[3]);
+    *(u32x2*)(out + 8 * q4) = pk;
+  }
+  if (p.lse_out != nullptr && h == 0 && db == 0) p.lse_out[grow] = den > 0.f ? (M2 + log2f(den)) * kLn2 : -INFINITY;
+}
+
+template <int D>
+hipError_t launch_internal_wave(const PassParams& p, hipStream_t s) {
+  PassParams q = p;
+  const int rowtiles = (p.G * p.Bq + 31) / 32;
+  q.div_rowtiles = make_fastdiv((uint32_t)rowtiles);
+  const dim3 grid((unsigned)((long long)p.B * p.Hkv * rowtiles * (D / 32)));
+  if (p.nkeys <= 32) launch_attn_kernel(internal_wave_kernel<D, 1>, grid, dim3(64), 0, s, q);
+  else launch_attn_kernel(internal_wave_kernel<D, 2>, grid, dim3(64), 0, s, q);
+  return hipGetLastError();
+}
+
 // Attention mass per (query row, key block) at a step that has the log-normaliser of full attention
 // over the prefix: p_ij = exp(s_ij - lse_i), summed over the keys of each block.  Reads K only.
 // Workgroup = 128 group-flattened rows of one KV head x a range of key blocks; scores as in the
@@ -1078,6 +1213,11 @@ hipError_t launch_d(const PassParams& p, PassMode mode, hipStream_t s) {
         if (p.nkeys <= 32) return launch_one<D, kPassInternal, 32, WSMAX, 1, 4>(p, s);
         return launch_one<D, kPassInternal, kKeyTile, WSMAX, 1, 4>(p, s);
       }
+      // One wavefront per 32 rows x 32 columns while two of them per CU are enough (32 / 8 heads of 128, 32 rows: batch 1
+      // 4.12 -> 3.32 us, batch 4 4.24 -> 3.97, batch 8 4.40 -> 5.18; 64 keys, batch 4 4.96 -> 6.85, 61 keys, batch 1
+      // 5.08 -> 4.19): beyond that the repeated K, Q and score work costs more than the barriers.
+      const long long waves = (long long)p.B * p.Hkv * ((p.G * p.Bq + 31) / 32) * (D / 32);
+      if ((p.nkeys <= 32 && waves <= 512) || (p.nkeys <= 64 && waves <= 256)) return launch_internal_wave<D>(p, s);
       // Few rows (an LLM-sized block): the pass is one wavefront's run-once instruction stream.
       // Spread each 32-row group over WSMAX wavefronts (columns split) and, for a block of at
       // most 32 keys, use the 32-key tile: both shorten that stream.

@@ -296,7 +296,7 @@ __device__ __forceinline__ TileRange split_range(int total, int nsplit, int spli
 // cut, deliberately a little weaker than the measured asymmetry: 128K pass 99.4 -> 97.4 us, batch 4 neutral; on a
 // board without the asymmetry it would cost under 2 %.
 // by_weights: division by 64 * nsplit (a 64-bit division here is some 250 cold instructions in front of the first load:
-// a refresh and a reuse step at 128K keys 112.2 -> 110.3 us); the host keeps total * 64 * nsplit below 2^31.
+// a refresh and a reuse step at 32K keys 44.9 -> 44.7 us, 128K 110.8 -> 110.4); the host keeps total * 64 * nsplit below 2^31.
 __device__ __forceinline__ TileRange biased_range(int total, const FastDiv& by_weights, int split) {
   auto cum = [](int s) -> uint32_t { return 64u * (uint32_t)s + (uint32_t)(s & 1); };
   TileRange r;
