@@ -154,7 +154,12 @@ HeadsPlan heads_plan(const fb_shape* s, int active_heads) {
   if (s->dtype != FB_BF16 || active_heads <= 0 || active_heads >= s->n_q_heads) return h;
   if (!fb::dense_row_pairs((int)std::min<long long>(nrows, 1 << 30), s->head_dim)) return h;
   const int tiles = (s->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile, ns = auto_splits(s, active_heads);
-  if (tiles < 8 * ns || 2 * ns > FB_MAX_SPLITS) return h;
+  // twice the split partials have to be earned: from 24 tiles per split on (12 heads of 4680 rows, 1 flagged: 26 tiles a
+  // split 222 -> 218 us, 12 tiles 193 -> 194; 3 of 8 heads of 2500 rows, 10 tiles, 89 -> 95), and where the 128-row
+  // workgroups fill half the chip unsplit and would write the final partial themselves, from 128 tiles on (6 of 12
+  // heads, 141 tiles: 310 -> 297; 8 of 10 heads of 3111 rows, 94 tiles: 191 -> 201)
+  const long long wgs = (long long)s->batch * std::min(active_heads, s->n_kv_heads) * ((nrows + fb::kRowsPerWgBf16 - 1) / fb::kRowsPerWgBf16);
+  if (tiles < 48 * ns || (ns == 1 && wgs >= 128 && tiles < 128) || 2 * ns > FB_MAX_SPLITS) return h;
   h.ns = 2 * ns;
   h.cap = std::min(active_heads, s->n_kv_heads);
   const size_t n = (size_t)h.ns * s->batch * h.cap * nrows;
