@@ -51,9 +51,13 @@ typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
-// (kKeySplitSingle: the key split with one tile per barrier at head_dim 64 as well)
-enum StreamLayout : int { kKeySplit = 0, kTileSplit = 1, kRowPair = 2, kKeySplitSingle = 3 };
+// (kKeySplitSingle: the key split with one tile per barrier at head_dim 64 as well; kRowPairRotated: the internal pass of
+// the refresh step, whose row pairs walk the block's tiles in rotated order like the external pass.  A layout of its own,
+// not a run-time switch: with one, every many-row reuse step carried the division, the wrap and 81 instructions more,
+// 0.4 to 1.7 % of 145 us for 12 heads of 4680 rows)
+enum StreamLayout : int { kKeySplit = 0, kTileSplit = 1, kRowPair = 2, kKeySplitSingle = 3, kRowPairRotated = 4 };
 constexpr bool key_split(int layout) { return layout == kKeySplit || layout == kKeySplitSingle; }
+constexpr bool row_pair(int layout) { return layout == kRowPair || layout == kRowPairRotated; }
 
 // Key split at head_dim 64: two tiles per barrier, their scores and weights computed together, because a tile's fixed cost
 // (barrier, refill, the softmax's cross-lane step) is large against its 16 KB: batch 4, 64K keys, 32 rows
@@ -65,7 +69,7 @@ constexpr bool paired_halves(int D, int layout) { return D == 64 && layout == kK
 // wavefronts: the small blocks of 4- and 8-token diffusion steps, where more row groups would compute padding rows)
 template <int D, int LAYOUT, int NSETS = 1, int NRG = 4>
 struct SCfg {
-  static constexpr int NW = (LAYOUT == kRowPair) ? 8 : 2 * NRG;   // wavefronts per workgroup
+  static constexpr int NW = (row_pair(LAYOUT)) ? 8 : 2 * NRG;   // wavefronts per workgroup
   static constexpr int THREADS = 64 * NW;
   static constexpr int KT = 64;                       // keys per tile
   static constexpr int ROWB = D * 2;                  // bytes per key row
@@ -75,14 +79,14 @@ struct SCfg {
   static constexpr int NLOAD = OPB / (THREADS * 16);  // direct-to-LDS loads per lane, operand and tile
   static constexpr int LSTEP = NW * 1024;             // LDS bytes one load of every wavefront covers
   static constexpr int LPT = 2 * NLOAD;               // loads per lane and tile
-  static constexpr int NS = (D == 128) ? 4 : (LAYOUT == kRowPair || LAYOUT == kKeySplitSingle) ? 6 : 8;       // ring stages
+  static constexpr int NS = (D == 128) ? 4 : (row_pair(LAYOUT) || LAYOUT == kKeySplitSingle) ? 6 : 8;       // ring stages
   static constexpr int NKS = D / 16;                  // MFMA k-steps of the score product
   static constexpr int NDB = D / 32;                  // 32-wide output column blocks
-  static constexpr int ROWS = (LAYOUT == kRowPair) ? 256 : 32 * NRG;
+  static constexpr int ROWS = (row_pair(LAYOUT)) ? 256 : 32 * NRG;
   static constexpr int NKB = key_split(LAYOUT) ? 1 : 2;    // 32-key blocks of a tile one wavefront computes
   static constexpr int QPARTS = (ROWS + 63) / 64;             // the query rows are loaded 64 at a time, like a K operand
   static constexpr int QSTAGES = (QPARTS * OPB + STAGE - 1) / STAGE;   // ring stages they pass through at start
-  static constexpr int MERGE = (LAYOUT != kRowPair) ? NSETS * NRG * 2 * (NDB / 2 * 16 + 2) * 64 * 4 : 0;   // key-half exchange
+  static constexpr int MERGE = (!row_pair(LAYOUT)) ? NSETS * NRG * 2 * (NDB / 2 * 16 + 2) * 64 * 4 : 0;   // key-half exchange
   static constexpr int RING = NS * STAGE;
   static constexpr int FIFO = RING > MERGE ? RING : MERGE;
   static constexpr int LDS = FIFO;
@@ -342,17 +346,17 @@ struct TileDesc {
 };
 
 template <int D, int MODE, int LAYOUT, int NRG>
-__global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void attn_stream_kernel(const PassParams p) {
+__global__ __launch_bounds__(((row_pair(LAYOUT)) ? 8 : 2 * NRG) * 64, 1) void attn_stream_kernel(const PassParams p) {
   constexpr int NSETS = (MODE == kPassSparseRefresh) ? 2 : 1;
   using C = SCfg<D, LAYOUT, NSETS, NRG>;
   static_assert(MODE == kPassDense || MODE == kPassDenseHeads || MODE == kPassDensePaged || MODE == kPassSparseReuse ||
                     MODE == kPassSparseRefresh || MODE == kPassInternal, "modes of the streaming kernel");
-  static_assert(MODE != kPassSparseRefresh || LAYOUT != kRowPair, "two accumulator sets: key halves");
-  static_assert(MODE != kPassInternal || LAYOUT == kRowPair, "internal pass: row-pair layout");
+  static_assert(MODE != kPassSparseRefresh || !row_pair(LAYOUT), "two accumulator sets: key halves");
+  static_assert((MODE != kPassInternal || row_pair(LAYOUT)) && (LAYOUT != kRowPairRotated || MODE == kPassInternal), "internal pass: row-pair layout");
   // Row-pair layout: two tiles per barrier (tiles t, t+1 are computed while t+2, t+3 are in flight), measured 2 % faster
   // at the video shape than one tile per barrier; tile split and head_dim 64 the same; key split at 128: one tile per barrier, NS - 1 in flight.
   constexpr bool kPairs = !key_split(LAYOUT) || paired_halves(D, LAYOUT);
-  constexpr bool kHalves = LAYOUT != kRowPair;       // two wavefronts per row group, each with half of the keys
+  constexpr bool kHalves = !row_pair(LAYOUT);       // two wavefronts per row group, each with half of the keys
   constexpr int AHEAD = kPairs ? C::NS - 2 : C::NS - 1;
   static_assert(!kPairs || C::NS % 2 == 0, "pairs of tiles: an even number of stages");
   // passes whose tiles come from a table (paged, sparse): the lookups are made one iteration ahead of the tile's
@@ -361,7 +365,7 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
   extern __shared__ __align__(16) unsigned char ring[];
   const int lane = threadIdx.x & 63, l32 = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));     // wavefront-uniform (scalar)
-  const int rg = (LAYOUT == kRowPair) ? wave : (wave % NRG);     // 32-row group
+  const int rg = (row_pair(LAYOUT)) ? wave : (wave % NRG);     // 32-row group
   const int half = kHalves ? (wave / NRG) : 0;                   // keys of this wavefront: half of every tile, or every other tile
   const int kb0 = key_split(LAYOUT) ? half : 0;              // first 32-key block of a tile
 
@@ -387,7 +391,7 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
     // run on even XCDs and odd-numbered ones on odd XCDs
     if (p.xcd_bias) w = (xcd >> 1) * (2 * q8) + 2 * j + (xcd & 1);
     if constexpr (MODE == kPassDenseHeads) {
-      if (LAYOUT == kRowPair || p.div_rowtiles.d > 1) w = bid;     // whole heads drop out: deal a head's row tiles over the XCDs
+      if (row_pair(LAYOUT) || p.div_rowtiles.d > 1) w = bid;     // whole heads drop out: deal a head's row tiles over the XCDs
     }
     rest = fastdiv((uint32_t)w, p.div_rowtiles);
     rt = w - (int)(rest * p.div_rowtiles.d);
@@ -400,7 +404,7 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
     rest = r2;
   }
   int b, kvh;
-  constexpr bool kByRank = MODE == kPassDenseHeads && LAYOUT == kRowPair;
+  constexpr bool kByRank = MODE == kPassDenseHeads && row_pair(LAYOUT);
   bool direct = p.direct != 0;                               // this workgroup writes the final partial
   int rank = 0;
   if constexpr (kByRank) {
@@ -521,7 +525,7 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
   }
   const int range = tr.end - tr.begin;
   const int ntiles = kByRank ? (range - first + stride - 1) / stride : range;
-  const int rot = ((MODE == kPassInternal && !p.rotate) || range <= 0) ? 0 : (int)((rsrc * 13u + (rsrc >> 5) * 7u) % (unsigned)range);
+  const int rot = ((MODE == kPassInternal && LAYOUT != kRowPairRotated) || range <= 0) ? 0 : (int)((rsrc * 13u + (rsrc >> 5) * 7u) % (unsigned)range);
   const uint32_t* __restrict__ bmask = p.blk_mask ? p.blk_mask + (size_t)bk * p.nblk : nullptr;
   const int32_t* __restrict__ ulist = p.union_list ? p.union_list + (size_t)bk * p.nblk : nullptr;
   const uint32_t* __restrict__ umask = p.union_mask ? p.union_mask + (size_t)bk * p.nblk : nullptr;
@@ -657,13 +661,15 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
         qmask[i] = d.mask;
       }
   }
-  // table words of the next tile to be issued, fetched one iteration ahead (lookups off the critical path)
+  // table words of the next tile to be issued, fetched one iteration ahead (lookups off the critical path; row-pair passes
+  // have no table, and there computing the tile ahead only lengthens the loop)
+  constexpr bool kLookAhead = !row_pair(LAYOUT);
   constexpr int NNEXT = kPairs ? 2 : 1;
   TileRaw rnext[NNEXT];
 #pragma unroll
   for (int u = 0; u < NNEXT; ++u) {
     rnext[u].e = 0; rnext[u].word = 0; rnext[u].mask = 0u;
-    if (AHEAD + u < ntiles) rnext[u] = tile_raw(AHEAD + u);
+    if (kLookAhead && AHEAD + u < ntiles) rnext[u] = tile_raw(AHEAD + u);
   }
 
   // per-lane LDS read addresses inside a stage
@@ -699,11 +705,11 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
   // follows in this slot; the queue then holds tiles t .. t + AHEAD + u
   auto refill = [&](int t, int u) {
     if (t + AHEAD + u < ntiles) {
-      const TileDesc d = tile_desc(rnext[u]);
+      const TileDesc d = tile_desc(kLookAhead ? rnext[u] : tile_raw(t + AHEAD + u));
       issue_tile(t + AHEAD + u, d);
       qk0[AHEAD + u] = d.k0;
       qmask[AHEAD + u] = d.mask;
-      if (t + AHEAD + u + NNEXT < ntiles) rnext[u] = tile_raw(t + AHEAD + u + NNEXT);
+      if (kLookAhead && t + AHEAD + u + NNEXT < ntiles) rnext[u] = tile_raw(t + AHEAD + u + NNEXT);
     }
   };
   auto advance = [&]() {
@@ -772,7 +778,7 @@ __global__ __launch_bounds__(((LAYOUT == kRowPair) ? 8 : 2 * NRG) * 64, 1) void 
     }
   };
 
-  if constexpr (LAYOUT == kRowPair) {
+  if constexpr (row_pair(LAYOUT)) {
     // two tiles per barrier; the prologue put tiles 0 .. AHEAD-1 in flight, iteration t adds tiles t+AHEAD, t+AHEAD+1
     // into the stages of tiles t-2, t-1 (or the query stages), which every wavefront left before this barrier
     static_assert(!kListed, "row-pair layout: dense passes only");
@@ -984,7 +990,7 @@ hipError_t launch_stream(const PassParams& p, hipStream_t s) {
   const int ntile_rows = (nrows + C::ROWS - 1) / C::ROWS;
   long long nwg = (long long)p.B * p.Hkv * ntile_rows * p.nsplit;
   if (MODE == kPassDensePaged) nwg = (((long long)p.B * p.Hkv * p.nsplit + 7) / 8) * 8 * ntile_rows;
-  if (MODE == kPassDenseHeads && LAYOUT == kRowPair) nwg = (long long)p.B * (p.heads_cap * p.nsplit + p.Hkv) * ntile_rows;
+  if (MODE == kPassDenseHeads && row_pair(LAYOUT)) nwg = (long long)p.B * (p.heads_cap * p.nsplit + p.Hkv) * ntile_rows;
   if (nwg >= (1ll << 31)) return hipErrorInvalidValue;
   PassParams q = p;
   if (MODE == kPassDensePaged) q.div_page = make_fastdiv((uint32_t)p.page_size);
@@ -1041,7 +1047,9 @@ hipError_t launch_stream_d(const PassParams& p, PassMode mode, hipStream_t s) {
     case kPassDensePaged: return launch_key_split<D, kPassDensePaged>(p, s);
     case kPassSparseReuse: return launch_key_split<D, kPassSparseReuse>(p, s);
     case kPassSparseRefresh: return launch_key_split<D, kPassSparseRefresh>(p, s);
-    case kPassInternal: return launch_stream<D, kPassInternal, kRowPair>(p, s);
+    case kPassInternal:
+      if (p.rotate) return launch_stream<D, kPassInternal, kRowPairRotated>(p, s);
+      return launch_stream<D, kPassInternal, kRowPair>(p, s);
     default: return hipErrorInvalidValue;
   }
 }
