@@ -38,6 +38,8 @@
  *     remembered in an atomic word, safe to race from several host threads) and the text of the
  *     last HIP error per thread.  Calls are asynchronous; buffers must stay valid until the stream
  *     has passed the call.  Two calls that share a workspace must be ordered on one stream.
+ *   - Overlap: where an entry point takes both, out may be q itself (a row's queries are read before its
+ *     output is written).  No other output, nor the workspace, may overlap an input or another output.
  *   - Alignment: every tensor pointer must be 16-byte aligned (FB_ERR_ALIGN otherwise).
  *   - Errors: every entry point returns an fb_status; nothing throws or aborts.  Arguments are
  *     validated on the host before the first launch, so every error except FB_ERR_HIP leaves

@@ -737,7 +737,8 @@ __global__ __launch_bounds__(256 * NG, (VAR & 4) ? 2 : (NG > 1 || (MODE == kPass
     if (ntiles > 0) {
       if (common > 0 || extra) tile_store<D, KT, kShare>(regs, smem, tid, grp);
       __syncthreads();
-      // the query registers have arrived by now (their loads went out with the first tile's); saying so here
+      // the query registers have arrived by now (their loads went out with the first tile's, in front of the barrier:
+      // the internal pass may write its output in their place); saying so here
       // keeps waits for them out of the tile loop, where in-order load counters would turn them into waits
       // for the next tile's prefetch
 #pragma unroll
@@ -1149,6 +1150,17 @@ hipError_t launch_one(const PassParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Whether the internal pass writes over any of its inputs: rows' bytes of storage type and of fp32.
+inline bool internal_in_place(const PassParams& p, int D) {
+  const size_t rows = (size_t)p.B * p.Hq * p.Bq, kv = (size_t)p.B * p.Hkv * p.nkeys * D * 2;
+  const struct { const void* at; size_t n; } outs[] = {{p.out, rows * D * 2}, {p.lse_out, rows * 4}},
+      ins[] = {{p.q, rows * D * 2}, {p.k, kv}, {p.v, kv}, {p.ext_o, rows * D * 4}, {p.ext_m, rows * 4}, {p.ext_lse, rows * 4}};
+  for (const auto& o : outs)
+    for (const auto& i : ins)
+      if (o.at && i.at && (uintptr_t)o.at < (uintptr_t)i.at + i.n && (uintptr_t)i.at < (uintptr_t)o.at + o.n) return true;
+  return false;
+}
+
 // Internal and fused passes (never or rarely split): row-pair workgroups when the pass is compute-bound, i.e. many
 // rows per KV head and enough 256-row workgroups to give every CU one.  (The dense external pass uses them for
 // every KV group above 128 rows, see dense_row_pairs.)
@@ -1215,9 +1227,11 @@ hipError_t launch_d(const PassParams& p, PassMode mode, hipStream_t s) {
       }
       // One wavefront per 32 rows x 32 columns while two of them per CU are enough (32 / 8 heads of 128, 32 rows: batch 1
       // 4.12 -> 3.32 us, batch 4 4.24 -> 3.97, batch 8 4.40 -> 5.18; 64 keys, batch 4 4.96 -> 6.85, 61 keys, batch 1
-      // 5.08 -> 4.19): beyond that the repeated K, Q and score work costs more than the barriers.
+      // 5.08 -> 4.19): beyond that the repeated K, Q and score work costs more than the barriers.  Not in place: D / 32
+      // workgroups read a row's inputs, and none waits for the others before it stores.
       const long long waves = (long long)p.B * p.Hkv * ((p.G * p.Bq + 31) / 32) * (D / 32);
-      if ((p.nkeys <= 32 && waves <= 512) || (p.nkeys <= 64 && waves <= 256)) return launch_internal_wave<D>(p, s);
+      if (((p.nkeys <= 32 && waves <= 512) || (p.nkeys <= 64 && waves <= 256)) && !internal_in_place(p, D))
+        return launch_internal_wave<D>(p, s);
       // Few rows (an LLM-sized block): the pass is one wavefront's run-once instruction stream.
       // Spread each 32-row group over WSMAX wavefronts (columns split) and, for a block of at
       // most 32 keys, use the 32-key tile: both shorten that stream.
