@@ -170,7 +170,8 @@ fb_status fb_external_partial_builtin_ws(const fb_shape* shape, const void* q, c
  * (0 = unknown, sized as if all were flagged).  The mask lives in device memory, so this is the
  * only way the library can tell that few workgroups will do real work and cut the prefix into
  * more splits to keep the GPU full; a wrong hint costs speed, never correctness.
- * workspace: >= fb_workspace_bytes(shape, 0, 0, fb_external_heads_splits(shape, n_active_heads)).
+ * workspace: >= fb_workspace_bytes(shape, 0, 0, fb_external_heads_splits(shape, n_active_heads)).  (That count is for
+ * sizing the workspace; the pass may cut the flagged heads' prefix into more splits than that.)
  */
 int32_t fb_external_heads_splits(const fb_shape* shape, int32_t n_active_heads);
 fb_status fb_external_partial_heads(const fb_shape* shape, const void* q, const void* k_prefix,

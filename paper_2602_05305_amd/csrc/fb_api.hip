@@ -138,37 +138,6 @@ int heads_splits(const fb_shape* s, int active_heads) {
   return s->dtype == FB_BF16 ? auto_splits(s, active_heads) : f32_splits(s, true);
 }
 
-// Per-head refresh over KV groups of more than 128 rows (bf16) with a hint: 256-row workgroups, each split of
-// auto_splits as two, its even and its odd tiles, so that the flagged groups fill the CUs that 128-row workgroups with two
-// tile streams each would.  The split partials are stored densely by rank among the flagged KV groups (cap groups per batch
-// element; groups beyond it are streamed unsplit), which is what the workspace has room for.  ns = 0: the hint says nothing,
-// or the shape is another kernel's.
-struct HeadsPlan {
-  int ns, cap;
-  size_t o, m, l, total;      // workspace offsets
-};
-
-HeadsPlan heads_plan(const fb_shape* s, int active_heads) {
-  HeadsPlan h = {0, 0, 0, 0, 0, 0};
-  const long long nrows = (long long)(s->n_q_heads / s->n_kv_heads) * s->block_len;
-  if (s->dtype != FB_BF16 || active_heads <= 0 || active_heads >= s->n_q_heads) return h;
-  if (!fb::dense_row_pairs((int)std::min<long long>(nrows, 1 << 30), s->head_dim)) return h;
-  const int tiles = (s->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile, ns = auto_splits(s, active_heads);
-  // twice the split partials have to be earned: from 24 tiles per split on (12 heads of 4680 rows, 1 flagged: 26 tiles a
-  // split 222 -> 218 us, 12 tiles 193 -> 194; 3 of 8 heads of 2500 rows, 10 tiles, 89 -> 95), and where the 128-row
-  // workgroups fill half the chip unsplit and would write the final partial themselves, from 128 tiles on (6 of 12
-  // heads, 141 tiles: 310 -> 297; 8 of 10 heads of 3111 rows, 94 tiles: 191 -> 201)
-  const long long wgs = (long long)s->batch * std::min(active_heads, s->n_kv_heads) * ((nrows + fb::kRowsPerWgBf16 - 1) / fb::kRowsPerWgBf16);
-  if (tiles < 48 * ns || (ns == 1 && wgs >= 128 && tiles < 128) || 2 * ns > FB_MAX_SPLITS) return h;
-  h.ns = 2 * ns;
-  h.cap = std::min(active_heads, s->n_kv_heads);
-  const size_t n = (size_t)h.ns * s->batch * h.cap * nrows;
-  h.m = align256(n * s->head_dim * sizeof(float));
-  h.l = h.m + align256(n * sizeof(float));
-  h.total = h.l + align256(n * sizeof(float));
-  return h;
-}
-
 int sparse_splits(const fb_shape* s, bool refresh) {
   (void)refresh;
   if (s->dtype != FB_BF16) return f32_splits(s, true);
@@ -223,6 +192,47 @@ WsLayout ws_layout(const fb_shape* s, int nsplit, int nsets, int nblk, int nspli
   w.order = off; off = align256(off + (size_t)s->batch * sizeof(int32_t));   // paged pass: sequences by length
   w.total = off;
   return w;
+}
+
+// Per-head refresh over KV groups of more than 128 rows (bf16) with a hint: 256-row workgroups, each split of
+// auto_splits as two, its even and its odd tiles, so that the flagged groups fill the CUs that 128-row workgroups with two
+// tile streams each would.  The split partials are stored densely by rank among the flagged KV groups (cap groups per batch
+// element; groups beyond it are streamed unsplit).  ns = 0: the hint says nothing, or the shape is another kernel's.
+struct HeadsPlan {
+  int ns, cap;
+  size_t o, m, l, total;      // workspace offsets
+};
+
+HeadsPlan heads_plan(const fb_shape* s, int active_heads) {
+  HeadsPlan h = {0, 0, 0, 0, 0, 0};
+  const long long nrows = (long long)(s->n_q_heads / s->n_kv_heads) * s->block_len;
+  if (s->dtype != FB_BF16 || active_heads <= 0 || active_heads >= s->n_q_heads) return h;
+  if (!fb::dense_row_pairs((int)std::min<long long>(nrows, 1 << 30), s->head_dim)) return h;
+  const int tiles = (s->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile, ns = auto_splits(s, active_heads);
+  // twice the split partials have to be earned: from 24 tiles per split on (12 heads of 4680 rows, 1 flagged: 26 tiles a
+  // split 222 -> 218 us, 12 tiles 193 -> 194; 3 of 8 heads of 2500 rows, 10 tiles, 89 -> 95), and where the 128-row
+  // workgroups fill half the chip unsplit and would write the final partial themselves, from 128 tiles on (6 of 12
+  // heads, 141 tiles: 310 -> 297; 8 of 10 heads of 3111 rows, 94 tiles: 191 -> 201)
+  const long long wgs = (long long)s->batch * std::min(active_heads, s->n_kv_heads) * ((nrows + fb::kRowsPerWgBf16 - 1) / fb::kRowsPerWgBf16);
+  if (tiles < 48 * ns || (ns == 1 && wgs >= 128 && tiles < 128) || 2 * ns > FB_MAX_SPLITS) return h;
+  h.ns = 2 * ns;
+  h.cap = std::min(active_heads, s->n_kv_heads);
+  const size_t n = (size_t)h.ns * s->batch * h.cap * nrows;
+  h.m = align256(n * s->head_dim * sizeof(float));
+  h.l = h.m + align256(n * sizeof(float));
+  h.total = h.l + align256(n * sizeof(float));
+  return h;
+}
+
+// The split count that callers size the workspace of the per-head refresh with: that of the pass, or more where the plan's
+// 2 ns cap group partials would not fit the (ns + 1) Hkv of it (7 of 8 heads of 2080 rows against 37440 keys: 28 and 24,
+// 343 us by the register-staged kernel and 302 by the plan).  The route of a caller who follows the header depends on
+// shape and hint alone.
+int heads_ws_splits(const fb_shape* s, int active_heads) {
+  int n = heads_splits(s, active_heads);
+  const HeadsPlan h = heads_plan(s, active_heads);
+  while (h.ns > 0 && ws_layout(s, n, 2, 0, 1).total < h.total) ++n;
+  return n;
 }
 
 fb_status check_key_block(const fb_shape* s, int32_t key_block, int32_t topk, int* nblk) {
@@ -363,8 +373,8 @@ fb_status external_partial_impl(const fb_shape* shape, const void* q, const void
     return FB_ERR_ALIGN;
   if (n_active_heads < 0) return FB_ERR_SHAPE;
   int ns = n_splits > 0 ? n_splits
-                             : (paged ? paged_splits(shape)
-                                      : use_head_mask ? heads_splits(shape, n_active_heads) : dense_splits(shape));
+                        : (paged ? paged_splits(shape)
+                                 : use_head_mask ? heads_splits(shape, n_active_heads) : dense_splits(shape));
   const WsLayout w = ws_layout(shape, ns, 1, 0);
   if (!workspace || workspace_bytes < w.total) return FB_ERR_WORKSPACE;
 
@@ -376,7 +386,7 @@ fb_status external_partial_impl(const fb_shape* shape, const void* q, const void
   fb::PassMode mode = use_head_mask ? fb::kPassDenseHeads : fb::kPassDense;
   if (use_head_mask) {
     const HeadsPlan h = heads_plan(shape, n_active_heads);
-    if (h.ns > 0 && h.total <= workspace_bytes) {
+    if (h.ns > 0 && h.total <= workspace_bytes) {        // (always, unless the buffer is below fb_workspace_bytes of heads_ws_splits)
       ns = p.nsplit = h.ns;
       p.heads_cap = h.cap;
       p.ws_o = (float*)ws; p.ws_m = (float*)(ws + h.m); p.ws_l = (float*)(ws + h.l);
@@ -437,7 +447,7 @@ fb_status fb_external_partial_prof(const fb_shape* shape, const void* q, const v
 
 int32_t fb_external_heads_splits(const fb_shape* shape, int32_t n_active_heads) {
   if (check_shape(shape) != FB_OK || n_active_heads < 0) return 0;
-  return heads_splits(shape, n_active_heads);
+  return heads_ws_splits(shape, n_active_heads);
 }
 
 fb_status fb_external_partial_heads(const fb_shape* shape, const void* q, const void* k_prefix,

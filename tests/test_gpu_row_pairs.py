@@ -81,3 +81,35 @@ def test_head_wise_refresh(Hq, Hkv, d, P, Bq, mask, hint, step):
     on = np.array(mask, dtype=bool)
     T.check_partial({k: v[:, on] for k, v in got.items()}, {k: v[:, on] for k, v in want.items()}, "bf16", w.name)
     assert (got["o"][:, ~on] == 7).all() and (got["m"][:, ~on] == 8).all() and (got["lse"][:, ~on] == 9).all()
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,P,Bq,active,ns", [
+    (4, 2, 128, 6300, 3300, 2, 2),      # both KV groups flagged: 8 group partials by rank; 2 splits hold 6
+    (8, 8, 128, 9300, 2080, 7, 2),      # 28 and 24
+    (8, 8, 128, 9300, 2080, 5, 3),      # 30 and 32: they fit
+])
+def test_head_wise_refresh_does_not_depend_on_the_workspace(Hq, Hkv, d, P, Bq, active, ns):
+    """The documented workspace and a larger one: the same result bit for bit.  One for the pass's ns splits is taken too."""
+    w = _wl(1, Hq, Hkv, d, P, Bq)
+    Kp, Vp = wl.make_prefix(w, 405)
+    (Q, _, _), _ = wl.make_block_steps(w, 405)
+    shape = T.shape_of(w)
+    q, kp, vp = (T.to_dev(x, "bf16") for x in (Q, Kp, Vp))
+    hm = torch.tensor([[0] * (Hq - active) + [1] * active], dtype=torch.uint8, device=T.DEV)
+    documented = fb.fb_workspace_bytes(shape, 0, 0, fb.fb_external_heads_splits(shape, active))
+    by_rank = (2 * ns * min(active, Hkv)) * (Hq // Hkv) * Bq * (d + 2) * 4
+    assert documented >= by_rank and documented >= fb.fb_workspace_bytes(shape, 0, 0, ns)
+    got = []
+    for n in (documented, 4 * documented, fb.fb_workspace_bytes(shape, 0, 0, ns)):
+        part = T.Partial(w)
+        part.o.zero_(), part.m.zero_(), part.lse.zero_()
+        fb.fb_external_partial_heads(shape, q, kp, vp, hm, part.o, part.m, part.lse,
+                                     torch.empty(n, device=T.DEV, dtype=torch.uint8), active)
+        torch.cuda.synchronize()
+        got.append(part)
+    for a, b in zip((got[0].o, got[0].m, got[0].lse), (got[1].o, got[1].m, got[1].lse)):
+        assert torch.equal(a, b)
+    on, step = slice(Hq - active, Hq), 131
+    want = {k: v[:, on] for k, v in orc.partial(Q[:, :, ::step], Kp, Vp).items()}
+    for part in got:
+        T.check_partial({k: v[:, on, ::step] for k, v in part.numpy().items()}, want, "bf16", w.name)
