@@ -134,8 +134,19 @@ int dense_splits(const fb_shape* s) {
 }
 
 // Splits of the per-head refresh.  fp32: one query head per workgroup.
+// bf16 with a hint: auto_splits, whose two candidates around 256 / groups both drop out where the stream is too short for 8
+// tiles per split of them, which leaves 1.  There, splits of 8 tiles, up to 7 (from 8 on the combine takes a workgroup for
+// every row, flagged or not: 1 of 10 heads of 1500 rows, head_dim 64, 6000 keys, 34.4 us with 11 and 20.1 with 7), and no
+// fewer than without a hint.  One split left a handful of CUs with the whole stream (hinted with 1, unhinted, now: 1 of 8
+// heads of 1000 rows, 3000 keys, 54.1, 23.1, 21.9 us; 1 of 12, 16000 keys, 210, 93.8, 48.5; 2 of 32 / 8 heads of 64 rows, 8000
+// keys, 84.2, 17.1, 16.6).
 int heads_splits(const fb_shape* s, int active_heads) {
-  return s->dtype == FB_BF16 ? auto_splits(s, active_heads) : f32_splits(s, true);
+  if (s->dtype != FB_BF16) return f32_splits(s, true);
+  const int ns = auto_splits(s, active_heads), tiles = (s->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile;
+  const long long groups = (long long)s->batch * std::min(active_heads, s->n_kv_heads) *
+                           (((long long)(s->n_q_heads / s->n_kv_heads) * s->block_len + fb::kRowsPerWgBf16 - 1) / fb::kRowsPerWgBf16);
+  if (active_heads <= 0 || active_heads >= s->n_q_heads || tiles >= 8 * (256 / groups)) return ns;
+  return std::max({ns, auto_splits(s), std::min(tiles / 8, 7)});
 }
 
 int sparse_splits(const fb_shape* s, bool refresh) {
@@ -194,8 +205,8 @@ WsLayout ws_layout(const fb_shape* s, int nsplit, int nsets, int nblk, int nspli
   return w;
 }
 
-// Per-head refresh over KV groups of more than 128 rows (bf16) with a hint: 256-row workgroups, each split of
-// auto_splits as two, its even and its odd tiles, so that the flagged groups fill the CUs that 128-row workgroups with two
+// Per-head refresh over KV groups of more than 128 rows (bf16) with a hint: 256-row workgroups, each of the ns
+// splits as two, its even and its odd tiles, so that the flagged groups fill the CUs that 128-row workgroups with two
 // tile streams each would.  The split partials are stored densely by rank among the flagged KV groups (cap groups per batch
 // element; groups beyond it are streamed unsplit).  ns = 0: the hint says nothing, or the shape is another kernel's.
 struct HeadsPlan {
@@ -203,12 +214,12 @@ struct HeadsPlan {
   size_t o, m, l, total;      // workspace offsets
 };
 
-HeadsPlan heads_plan(const fb_shape* s, int active_heads) {
+HeadsPlan heads_plan(const fb_shape* s, int active_heads, int ns) {
   HeadsPlan h = {0, 0, 0, 0, 0, 0};
   const long long nrows = (long long)(s->n_q_heads / s->n_kv_heads) * s->block_len;
   if (s->dtype != FB_BF16 || active_heads <= 0 || active_heads >= s->n_q_heads) return h;
   if (!fb::dense_row_pairs((int)std::min<long long>(nrows, 1 << 30), s->head_dim)) return h;
-  const int tiles = (s->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile, ns = auto_splits(s, active_heads);
+  const int tiles = (s->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile;
   // twice the split partials have to be earned: from 24 tiles per split on (12 heads of 4680 rows, 1 flagged: 26 tiles a
   // split 222 -> 218 us, 12 tiles 193 -> 194; 3 of 8 heads of 2500 rows, 10 tiles, 89 -> 95), and where the 128-row
   // workgroups fill half the chip unsplit and would write the final partial themselves, from 128 tiles on (6 of 12
@@ -230,7 +241,7 @@ HeadsPlan heads_plan(const fb_shape* s, int active_heads) {
 // shape and hint alone.
 int heads_ws_splits(const fb_shape* s, int active_heads) {
   int n = heads_splits(s, active_heads);
-  const HeadsPlan h = heads_plan(s, active_heads);
+  const HeadsPlan h = heads_plan(s, active_heads, n);
   while (h.ns > 0 && ws_layout(s, n, 2, 0, 1).total < h.total) ++n;
   return n;
 }
@@ -375,6 +386,9 @@ fb_status external_partial_impl(const fb_shape* shape, const void* q, const void
   int ns = n_splits > 0 ? n_splits
                         : (paged ? paged_splits(shape)
                                  : use_head_mask ? heads_splits(shape, n_active_heads) : dense_splits(shape));
+  // per-head refresh, bf16: a buffer below the documented size that holds the splits of auto_splits is taken with those
+  if (use_head_mask && shape->dtype == FB_BF16 && workspace_bytes < ws_layout(shape, ns, 1, 0).total)
+    ns = auto_splits(shape, n_active_heads);
   const WsLayout w = ws_layout(shape, ns, 1, 0);
   if (!workspace || workspace_bytes < w.total) return FB_ERR_WORKSPACE;
 
@@ -385,7 +399,7 @@ fb_status external_partial_impl(const fb_shape* shape, const void* q, const void
   p.head_on = use_head_mask ? head_mask : nullptr;
   fb::PassMode mode = use_head_mask ? fb::kPassDenseHeads : fb::kPassDense;
   if (use_head_mask) {
-    const HeadsPlan h = heads_plan(shape, n_active_heads);
+    const HeadsPlan h = heads_plan(shape, n_active_heads, ns);
     if (h.ns > 0 && h.total <= workspace_bytes) {        // (always, unless the buffer is below fb_workspace_bytes of heads_ws_splits)
       ns = p.nsplit = h.ns;
       p.heads_cap = h.cap;
