@@ -503,8 +503,13 @@ hipError_t launch_f32_rows(const PassParams& p, hipStream_t s) {
   // the internal pass has no splits to fill the chip with: 16-row workgroups until 64-row ones do
   if (MODE == kPassInternal && (long long)p.B * p.Hkv * ((nrows + 63) / 64) < 256) tile = 16;
   if (tile == 16) return launch_f32<D, MODE, 1, 1>(p, s);
-  if (tile == 32) return launch_f32<D, MODE, 2, 1>(p, s);
-  return launch_f32<D, MODE, 2, 2>(p, s);
+  // two accumulator sets at head_dim 128: 64-row workgroups have half the registers a wavefront and spill in the tile loop
+  // (32 / 8 heads of 40 rows, 4111 keys, refresh 138 us with 64 rows and 82 with 32)
+  constexpr bool fits64 = !(D == 128 && MODE == kPassSparseRefresh);
+  if constexpr (fits64) {
+    if (tile > 32) return launch_f32<D, MODE, 2, 2>(p, s);
+  }
+  return launch_f32<D, MODE, 2, 1>(p, s);
 }
 
 template <int D>

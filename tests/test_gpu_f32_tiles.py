@@ -81,3 +81,42 @@ def test_unselected_key_blocks_are_never_touched(Bq):
         keys = slice(64 * blk, 64 * blk + 64)
         want = orc.partial(Q[:, h:h + 1], Kp[:, h // 2:h // 2 + 1, keys], Vp[:, h // 2:h // 2 + 1, keys])
         T.check_partial({k: v[:, h:h + 1] for k, v in got.items()}, want, "f32", f"head {h}")
+
+
+@pytest.mark.parametrize("d,P,Bq,key_block,topk", [
+    (128, 700, 20, 64, 4), (128, 1029, 40, 128, 3),       # 32-row workgroups, one and two to a head
+    (64, 700, 20, 64, 4), (64, 1029, 40, 128, 3),         # 32 and 64 rows
+    (128, 257, 65, 64, 5), (64, 257, 65, 64, 0),          # three row tiles (two), all and none of the key blocks selected
+])
+def test_sparse_refresh_and_reuse(d, P, Bq, key_block, topk):
+    w = _wl(2, 4, 2, d, P, Bq, key_block=key_block, topk=topk)
+    print(f"[case] {w.name} key_block={key_block} topk={topk}", flush=True)
+    Kp, Vp = wl.make_prefix(w, 307)
+    steps = wl.make_block_steps(w, 307)
+    ora = orc.run_block_sparse(Kp, Vp, steps, 2, key_block, topk)
+    idx = {0: ora[0]["idx"]} if topk else None
+    for g, o in zip(T.run_sparse_block_gpu(w, Kp, Vp, steps, idx_per_refresh=idx, R=2), ora):
+        T.assert_close(g["out"], o["out"], "f32", w.name + " out")
+        T.check_partial(g["ext"], o["ext"], "f32", w.name + " sel(+)res")
+        T.check_partial(g["residual"], o["residual"], "f32", w.name + " residual")
+
+
+@pytest.mark.parametrize("d,P,Bq,mask", [
+    (128, 700, 10, [0, 1, 1, 0]), (128, 700, 20, [1, 0, 0, 0]), (64, 1029, 40, [0, 1, 0, 1]), (128, 1029, 40, [1, 1, 0, 1]),
+    (64, 65, 65, [0, 0, 0, 1]),
+])
+def test_head_wise_refresh(d, P, Bq, mask):
+    w = _wl(2, 4, 2, d, P, Bq)
+    Kp, Vp = wl.make_prefix(w, 309)
+    (Q, _, _), _ = wl.make_block_steps(w, 309)
+    shape, part = T.shape_of(w), T.Partial(w)
+    part.o.fill_(7), part.m.fill_(8), part.lse.fill_(9)
+    on = np.array([mask, mask[::-1]], dtype=bool)                    # another choice per batch element
+    ns = fb.fb_external_heads_splits(shape, sum(mask))
+    fb.fb_external_partial_heads(shape, T.to_dev(Q, "f32"), T.to_dev(Kp, "f32"), T.to_dev(Vp, "f32"),
+                                 torch.from_numpy(on.astype(np.uint8)).to(T.DEV), part.o, part.m, part.lse,
+                                 T.workspace(shape, n_splits=ns), sum(mask))
+    torch.cuda.synchronize()
+    got, want = part.numpy(), orc.partial(Q, Kp, Vp)
+    T.check_partial({k: v[on] for k, v in got.items()}, {k: v[on] for k, v in want.items()}, "f32", w.name)
+    assert (got["o"][~on] == 7).all() and (got["m"][~on] == 8).all() and (got["lse"][~on] == 9).all()
