@@ -1,5 +1,6 @@
-"""Routes of the many-row (row-pair) streaming kernel: the one-call refresh step as passes and the per-head refresh, at
-ragged sizes, against the numpy float64 oracle.  Tolerances: those of bf16 storage (fb_testlib)."""
+"""Many rows per KV head: the one-call refresh step (unsplit as two passes of the row-pair kernel; with splits or short
+streams as one register-staged pass and a combine) and the per-head refresh (partials by rank, and by head), at ragged
+sizes, against the numpy float64 oracle.  Tolerances: those of bf16 storage (fb_testlib)."""
 import numpy as np
 import pytest
 import torch
@@ -18,13 +19,14 @@ def _wl(B, Hq, Hkv, d, P, Bq):
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,d,P,Bq,small_ws", [
-    (1, 2, 2, 128, 1025, 129, False),     # 129 rows: the smallest row-pair group, one key past the tile, two splits
-    (1, 4, 1, 128, 512, 65, False),       # 260 rows, 8 tiles: one split, the pass writes the partial itself
-    (2, 2, 1, 64, 2000, 513, False),      # head_dim 64 from 1024 rows on
+    (1, 2, 2, 128, 1025, 129, False),     # 129 rows: one row in the second row tile, one key in the last tile
+    (1, 4, 1, 128, 512, 65, False),       # 260 rows of 4 heads, 8 tiles
+    (2, 2, 1, 64, 2000, 513, False),      # head_dim 64, 1026 rows
     (1, 2, 2, 128, 511, 200, False),      # 8 tiles, the last one ragged
     (1, 2, 2, 128, 500, 200, True),       # the smallest workspace the call accepts
 ])
 def test_refresh_step_in_passes(B, Hq, Hkv, d, P, Bq, small_ws):
+    """With splits: one register-staged pass over prefix and block, and the combine."""
     w = _wl(B, Hq, Hkv, d, P, Bq)
     Kp, Vp = wl.make_prefix(w, 401)
     steps = wl.make_block_steps(w, 401)
@@ -55,13 +57,75 @@ def test_refresh_step_in_passes(B, Hq, Hkv, d, P, Bq, small_ws):
     T.check_partial(ext.numpy(), ora[0]["ext"], "bf16", w.name + " ext")
 
 
+@pytest.mark.parametrize("Hq,Hkv,d,P,Bq", [
+    (16, 16, 128, 512, 2049),             # 8 tiles; 9 row tiles a head, the last with one row; 33 tiles of the block, one key in the last
+    (32, 16, 128, 700, 1030),             # heads straddle row tiles and wavefronts
+    (16, 16, 64, 577, 2049),
+])
+def test_refresh_step_without_splits_is_two_row_pair_passes(Hq, Hkv, d, P, Bq):
+    """Many rows per KV head, unsplit: neither pass leaves anything in the workspace (the register-staged pass over prefix and
+    block does).  The internal pass of this route walks the block's tiles in rotated order.  Every 13th row is compared."""
+    w = _wl(1, Hq, Hkv, d, P, Bq)
+    Kp, Vp = wl.make_prefix(w, 411)
+    steps = wl.make_block_steps(w, 411)
+    shape, ext = T.shape_of(w), T.Partial(w)
+    assert fb.fb_external_heads_splits(shape, 0) == 1 and Hkv * -(-(Hq // Hkv) * Bq // 256) >= 128 and Bq > 448
+    ws = torch.full((fb.fb_workspace_bytes(shape, 0, 0, 1),), 0xA5, device=T.DEV, dtype=torch.uint8)
+    events = [torch.cuda.Event(enable_timing=True) for _ in range(3)]
+    for e in events:
+        e.record()                                        # creates the handle
+    want_ext = orc.partial(steps[0][0][:, :, ::13], Kp, Vp)
+    for t, (Q, Kb, Vb) in enumerate(steps):
+        q, kb, vb = (T.to_dev(x, "bf16") for x in (Q, Kb, Vb))
+        out, lse = torch.empty_like(q), torch.empty(q.shape[:3], device=T.DEV)
+        if t == 0:
+            fb.fb_refresh_step_prof(shape, q, T.to_dev(Kp, "bf16"), T.to_dev(Vp, "bf16"), kb, vb, ext.o, ext.m, ext.lse, out, lse,
+                                    ws, *(e.cuda_event for e in events))
+        else:
+            fb.fb_internal_merge(shape, q, kb, vb, ext.o, ext.m, ext.lse, out, lse)
+        torch.cuda.synchronize()
+        want_out, want_lse = orc.merge(want_ext, orc.partial(Q[:, :, ::13], Kb, Vb))
+        T.assert_close(out[:, :, ::13].double().cpu().numpy(), want_out, "bf16", f"{w.name} step {t} out")
+        T.assert_close(lse[:, :, ::13].double().cpu().numpy(), np.asarray(want_lse), "bf16", f"{w.name} step {t} lse", lse=True)
+    assert bool((ws == 0xA5).all())
+    assert 0 < events[0].elapsed_time(events[1]) < events[0].elapsed_time(events[2])
+    T.check_partial({k: v[:, :, ::13] for k, v in ext.numpy().items()}, want_ext, "bf16", w.name + " ext")
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,P,Bq,masks,hint", [
+    (4, 4, 128, 6200, 2900, [[0, 1, 0, 1], [0, 0, 1, 1]], 2),       # two batch elements, 4 splits, other groups in each
+    (4, 4, 128, 6200, 2900, [[0, 1, 1, 1], [0, 0, 0, 1]], 2),       # hint too low in one: its third group runs unsplit
+    (16, 4, 128, 6200, 700, [[0] * 4 + [0, 0, 1, 1] + [0] * 4 + [1, 0, 0, 1]], 4),      # wavefronts straddle flagged and other heads
+    (4, 4, 64, 9300, 2900, [[0, 1, 1, 1]], 3),                      # 6 splits, an odd tile count per range
+])
+def test_head_wise_refresh_by_rank(Hq, Hkv, d, P, Bq, masks, hint):
+    """Split partials by rank among the flagged KV groups: the first flagged group's are where group 0's would be by head, though
+    group 0 is not flagged.  Every 131st row is compared."""
+    B = len(masks)
+    w = _wl(B, Hq, Hkv, d, P, Bq)
+    Kp, Vp = wl.make_prefix(w, 413)
+    (Q, _, _), _ = wl.make_block_steps(w, 413)
+    shape, part, on = T.shape_of(w), T.Partial(w), np.array(masks, dtype=bool)
+    assert not on[0, :Hq // Hkv].any()
+    part.o.fill_(7), part.m.fill_(8), part.lse.fill_(9)
+    n = fb.fb_workspace_bytes(shape, 0, 0, fb.fb_external_heads_splits(shape, hint))
+    ws = torch.full((n,), 0xA5, device=T.DEV, dtype=torch.uint8)
+    fb.fb_external_partial_heads(shape, T.to_dev(Q, "bf16"), T.to_dev(Kp, "bf16"), T.to_dev(Vp, "bf16"),
+                                 torch.tensor(masks, dtype=torch.uint8, device=T.DEV), part.o, part.m, part.lse, ws, hint)
+    torch.cuda.synchronize()
+    assert not bool((ws[:Hq // Hkv * Bq * d * 4] == 0xA5).all())
+    got, want = {k: v[:, :, ::131] for k, v in part.numpy().items()}, orc.partial(Q[:, :, ::131], Kp, Vp)
+    T.check_partial({k: v[on] for k, v in got.items()}, {k: v[on] for k, v in want.items()}, "bf16", w.name)
+    assert (got["o"][~on] == 7).all() and (got["m"][~on] == 8).all() and (got["lse"][~on] == 9).all()
+
+
 @pytest.mark.parametrize("Hq,Hkv,d,P,Bq,mask,hint,step", [
     (8, 2, 128, 3300, 40, [0, 1, 0, 0, 0, 0, 1, 1], 3, 1),      # 160 rows of 4 heads: wavefronts straddle flagged and other heads
-    (4, 4, 128, 3300, 300, [0, 0, 1, 0], 1, 1),                 # one head, its even and its odd tiles
-    (4, 4, 128, 3300, 300, [1, 0, 1, 1], 1, 1),                 # hint too low: the groups beyond it run unsplit
-    (6, 3, 128, 5000, 90, [0, 0, 0, 1, 1, 0], 2, 1),            # partials of groups 1 and 2 in the slots of the first two
-    (8, 8, 128, 9300, 2080, [1, 0, 1, 1, 0, 0, 1, 1], 5, 41),   # 3 ranges, 6 splits, an odd tile count per range
-    (4, 4, 128, 2100, 300, [0, 0, 1, 0], 1, 1),                 # too few tiles: 128-row workgroups, as without a hint
+    (4, 4, 128, 3300, 300, [0, 0, 1, 0], 1, 1),                 # one head
+    (4, 4, 128, 3300, 300, [1, 0, 1, 1], 1, 1),                 # hint too low
+    (6, 3, 128, 5000, 90, [0, 0, 0, 1, 1, 0], 2, 1),            # groups 1 and 2 of 3
+    (8, 8, 128, 9300, 2080, [1, 0, 1, 1, 0, 0, 1, 1], 5, 41),   # by rank: 3 ranges, 6 splits
+    (4, 4, 128, 2100, 300, [0, 0, 1, 0], 1, 1),                 # 33 tiles
     (4, 4, 128, 530, 300, [1, 0, 1, 0], 0, 1),                  # no hint, one split
     (2, 2, 64, 3300, 1030, [0, 1], 1, 7),
 ])
