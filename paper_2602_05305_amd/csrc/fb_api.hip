@@ -37,7 +37,7 @@ fb_status check_shape(const fb_shape* s) {
   if (!(s->scale >= 0.f) || isinf(s->scale)) return FB_ERR_SHAPE;   // rejects NaN and negatives
   if (s->head_dim < 1) return FB_ERR_SHAPE;
   if (s->head_dim != 64 && s->head_dim != 128) return FB_ERR_UNSUPPORTED;
-  if ((long long)s->batch * s->n_q_heads > 65535) return FB_ERR_UNSUPPORTED;   // grid.y of the fp32 pass
+  if ((long long)s->batch * s->n_q_heads > 65535) return FB_ERR_UNSUPPORTED;   // grid.y of the fp32 mass kernel
   const long long rows = (long long)s->batch * s->n_q_heads * s->block_len;
   if (rows > (1ll << 28)) return FB_ERR_UNSUPPORTED;
   return FB_OK;
@@ -52,18 +52,15 @@ long long rows_of(const fb_shape* s) { return (long long)s->batch * s->n_q_heads
 constexpr size_t kBuiltinWsBytes = (size_t)20 * 1024 * 1024;
 
 // Splits of the fp32 passes: workgroups of f32_row_tile rows, one per CU (their K/V stages take most of the LDS), so as
-// many splits as keep the workgroup count within 256 (one round); a split is at least one tile.  The split partials are
-// kept within the built-in scratch array, so that more splits than a shape used to have never make it too large for
-// fb_external_partial_builtin_ws.  per_head: the passes whose workgroups belong to one query head.
+// many splits as keep the workgroup count within 256 (one round); a split is at least one tile.  256 partials of at most 64
+// rows are 8.5 MB: two or more splits and the block-internal set (as much as half of them) always fit the built-in scratch
+// array.  per_head: the passes whose workgroups belong to one query head.
 int f32_splits(const fb_shape* s, bool per_head) {
   const int tiles = (s->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile;
   const long long nrows = per_head ? s->block_len : (long long)(s->n_q_heads / s->n_kv_heads) * s->block_len;
   const long long rt = fb::f32_row_tile(nrows);
   const long long groups = (long long)s->batch * (per_head ? s->n_q_heads : s->n_kv_heads) * ((nrows + rt - 1) / rt);
   long long ns = 256 / groups;
-  const long long split_bytes = rows_of(s) * (s->head_dim + 2) * (long long)sizeof(float);
-  const long long fit = (long long)(kBuiltinWsBytes - 4096) / split_bytes - 1;    // + the block-internal set; alignment
-  if (ns > fit) ns = fit;
   if (ns > tiles) ns = tiles;
   if (ns > FB_MAX_SPLITS) ns = FB_MAX_SPLITS;
   if (ns < 1) ns = 1;
