@@ -266,11 +266,12 @@ fb_status fb_internal_merge(const fb_shape* shape, const void* q, const void* k_
 /*
  * A whole refresh step in two launches: the single-pass formulation of Section 4.4 (one attention
  * pass over [prefix || block] whose block-external statistics are kept at the block boundary), cut
- * into splits for a 256-CU part.  One streaming launch covers the prefix splits and, as one more
- * split, the block's own keys; the combine launch folds the prefix splits into the partial to
- * cache (o_part, m_part, lse_part: exactly what fb_external_partial returns, up to the order of
- * floating-point sums) and, in the same pass, merges it with the block-internal statistics by
- * Eq. 8-9 into out / lse_out (what fb_internal_merge would return for this step).
+ * into splits for a 256-CU part.  The first launch streams the prefix splits, where the shape makes that
+ * the faster form with the block's own keys as one more split; the second folds the splits into the
+ * partial to cache (o_part, m_part, lse_part: exactly what fb_external_partial returns, up to the order
+ * of floating-point sums), computes the block-internal attention if the first did not, and merges the
+ * two by Eq. 8-9 into out / lse_out (what fb_internal_merge would return for this step).  With a single
+ * split the first launch writes the partial itself.
  * Arguments as in fb_external_partial and fb_internal_merge; lse_out may be NULL.
  * workspace: >= fb_workspace_bytes(shape, 0, 0, 0).
  */

@@ -27,8 +27,8 @@ fb_status fb_external_partial_prof(const fb_shape* shape, const void* q, const v
                                    void* ev_end, void* hip_stream);
 
 /* fb_refresh_step that also records three caller-created HIP events, as
- * fb_external_partial_prof does (before the streaming kernel, between it and the combine, after
- * the combine).  Any of the three may be NULL.  Results are identical to fb_refresh_step. */
+ * fb_external_partial_prof does (before the pass over the prefix, between it and the launch that
+ * follows, after that launch: the combine, or the kernel that folds or merges in its place).  Any of the three may be NULL.  Results are identical to fb_refresh_step. */
 fb_status fb_refresh_step_prof(const fb_shape* shape, const void* q, const void* k_prefix,
                                const void* v_prefix, const void* k_block, const void* v_block,
                                float* o_part, float* m_part, float* lse_part, void* out,

@@ -500,7 +500,9 @@ template <int D, int MODE>
 hipError_t launch_f32_rows(const PassParams& p, hipStream_t s) {
   const int nrows = f32_per_head(MODE) ? p.Bq : p.G * p.Bq;
   int tile = f32_row_tile(nrows);
-  // the internal pass has no splits to fill the chip with: 16-row workgroups until 64-row ones do
+  // the internal pass has no splits to fill the chip with: 16-row workgroups until 64-row ones do (blocks of 32, 64-row
+  // workgroups: 16 of them 14.2 us, 7.2 with 16 rows; 128 14.8 and 13.2; 256 15.5 and 23.8; blocks of 1000, 192 of them, 85
+  // and 105)
   if (MODE == kPassInternal && (long long)p.B * p.Hkv * ((nrows + 63) / 64) < 256) tile = 16;
   if (tile == 16) return launch_f32<D, MODE, 1, 1>(p, s);
   // two accumulator sets at head_dim 128: 64-row workgroups have half the registers a wavefront and spill in the tile loop

@@ -62,7 +62,10 @@ constexpr bool row_pair(int layout) { return layout == kRowPair || layout == kRo
 // Key split at head_dim 64: two tiles per barrier, their scores and weights computed together, because a tile's fixed cost
 // (barrier, refill, the softmax's cross-lane step) is large against its 16 KB: batch 4, 64K keys, 32 rows
 // per KV head 118 -> 101 us a refresh and a reuse step, 128K keys 64.6 -> 60.7, a sparse block at 64K 209 -> 201.  Not at
-// head_dim 128, where pairs of tiles leave 64 KB in flight instead of 96 (128K keys: 1 % slower).
+// head_dim 128, where pairs of tiles leave 64 KB in flight instead of 96 (128K keys: 1 % slower).  Dense and paged passes: at every
+// length the kernel takes (one tile -> two; 8, 16, 40 tiles per split: 128 rows of 8 KV heads 19.05 -> 18.95, 26.0 -> 25.3,
+// 46.8 -> 45.1 us; 64 rows 17.4 -> 17.7, 23.9 -> 23.4, 42.8 -> 40.0; 64 paged sequences of 16 rows 13.8 -> 12.6, 21.6 ->
+// 20.2, 42.9 -> 37.5).
 constexpr bool paired_halves(int D, int layout) { return D == 64 && layout == kKeySplit; }
 
 // NRG: 32-row groups of a key-split workgroup (4: 128 rows, 8 wavefronts; 2: 64 rows, 4 wavefronts; 1: 32 rows, 2
@@ -533,7 +536,8 @@ __global__ __launch_bounds__(((row_pair(LAYOUT)) ? 8 : 2 * NRG) * 64, 1) void at
     }
   }
   if constexpr (LAYOUT == kTileSplit) {
-    // as the register-staged refresh pass cuts them: the last split is blk_cost tiles shorter
+    // as the register-staged refresh pass cuts them, so that the running references start from the same tiles and results
+    // stay the same up to fp32 sums: the last split is blk_cost tiles (at most half a split, 3 for a block of one tile) shorter
     tr = split_range(total + p.blk_cost, p.div_nsplit, split);
     tr.begin = min(tr.begin, total);
     tr.end = min(tr.end, total);

@@ -177,7 +177,9 @@ def test_paged_deployment_shape_batch128_small_blocks(block_len):
     ("bf16", 4, 8, 2, 128, 2048, 32, 128, [1617, 64, 0, 1000], 0),     # library split count
     ("bf16", 3, 8, 2, 128, 4096, 8, 256, [4096, 300, 2222], 4),        # several splits, small block: fold kernel
     ("bf16", 2, 8, 2, 64, 1024, 16, 64, [1024, 65], 1),                # one split: paged pass writes the partial
-    ("bf16", 2, 4, 4, 128, 1024, 70, 128, [1000, 512], 3),             # block above 64 rows: combine + internal pass
+    ("bf16", 2, 4, 4, 128, 1024, 70, 128, [1000, 512], 3),             # block above 64 rows: the internal pass folds the splits
+    ("bf16", 6, 32, 8, 128, 1100, 32, 64, [1100, 64, 0, 700, 1, 513], 2),   # more than 4096 rows: the same
+    ("bf16", 2, 4, 4, 128, 1024, 70, 128, [1000, 512], 8),             # 8 splits: combine + internal pass
     ("f32", 3, 4, 2, 64, 576, 8, 64, [200, 0, 513], 2),
     ("f32", 2, 4, 4, 64, 640, 5, 128, [640, 129], 2),                  # block not a multiple of 4
 ])
