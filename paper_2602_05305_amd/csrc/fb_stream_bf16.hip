@@ -251,8 +251,7 @@ __device__ __forceinline__ void tile_softmax_pv(WaveAcc<D / 32>& st, f32x16 (&s)
   tile_pv<D, NKB>(st, pb, stage, vaddr, kb0);
 }
 
-// One tile of a wavefront for every accumulator set that any of its rows feeds (on).  A function, not a part of the kernel's
-// lambdas: written out in one of those, the sparse refresh pass at head_dim 128 (two sets, 256 registers) spilled four.
+// One tile of a wavefront for every accumulator set that any of its rows feeds (on).
 template <int D, int NSETS, int NKB>
 __device__ __forceinline__ void sets_tile(WaveAcc<D / 32> (&accs)[NSETS], const bool (&on)[NSETS], const bf16x8 (&qreg)[D / 16],
                                           const unsigned char* __restrict__ stage, const uint32_t (&kaddr)[D / 16],
@@ -752,7 +751,20 @@ __global__ __launch_bounds__(((row_pair(LAYOUT)) ? 8 : 2 * NRG) * 64, 1) void at
       any_on = any_on || on[i];
     }
     if (kMasked && !__any(any_on)) return;
-    sets_tile<D, NSETS, C::NKB>(accs, on, qreg, stage, kaddr, vaddr, kb0, p.scale_log2, nvalid, h);
+    if constexpr (D == 128 && NSETS > 1 && NRG == 4) {
+      // the one form with 256 registers and two accumulator sets: written out here, four of them spill.  With fewer row
+      // groups, which have registers to spare, the call is 4 to 7 % slower (16 rows per KV head, batch 4, 16752 keys, refresh
+      // 76 against 79 us)
+      sets_tile<D, NSETS, C::NKB>(accs, on, qreg, stage, kaddr, vaddr, kb0, p.scale_log2, nvalid, h);
+    } else {
+      f32x16 s[C::NKB];
+      tile_scores<D, C::NKB>(s, qreg, stage, kaddr, kb0);
+#pragma unroll
+      for (int i = 0; i < NSETS; ++i) {
+        if (NSETS > 1 && !__any(on[i])) continue;
+        tile_softmax_pv<D, C::NKB>(accs[i], s, stage, vaddr, kb0, p.scale_log2, on[i], nvalid, h);
+      }
+    }
   };
 
   // two tiles whose key halves this wavefront owns: as half_tile for one and then the other, with the same results bit for
