@@ -161,6 +161,18 @@ __device__ __forceinline__ void tile_scores(f32x16 (&s)[NKB], const bf16x8 (&qre
       for (int kb = 0; kb < NKB; ++kb)
         s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[u][kb], qreg[ks0 + u], s[kb], 0, 0, 0);
   }
+  if constexpr (D == 128 && NKB == 1) {
+    // one accumulator chain: every operand is requested one MFMA ahead.  Left to itself the compiler does so in some
+    // instantiations and waits for each read in front of its MFMA in others (per-head refresh, up to 32 rows per KV head: 190
+    // cycles a tile; 4 x 8 KV groups, 16752 keys, 59.5 -> 56.8 us; a sparse block at 64K keys 261.3 -> 258.7)
+    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);         // LDS reads
+#pragma unroll
+    for (int ks = 2; ks < NKS; ++ks) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);       // MFMA
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+  }
 }
 
 // Online softmax update with the tile's scores: moves the running reference if needed (rescaling the accumulators),
