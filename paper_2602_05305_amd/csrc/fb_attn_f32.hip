@@ -500,10 +500,18 @@ template <int D, int MODE>
 hipError_t launch_f32_rows(const PassParams& p, hipStream_t s) {
   const int nrows = f32_per_head(MODE) ? p.Bq : p.G * p.Bq;
   int tile = f32_row_tile(nrows);
-  // the internal pass has no splits to fill the chip with: 16-row workgroups until 64-row ones do (blocks of 32, 64-row
-  // workgroups: 16 of them 14.2 us, 7.2 with 16 rows; 128 14.8 and 13.2; 256 15.5 and 23.8; blocks of 1000, 192 of them, 85
-  // and 105)
-  if (MODE == kPassInternal && (long long)p.B * p.Hkv * ((nrows + 63) / 64) < 256) tile = 16;
+  if (MODE == kPassInternal) {
+    // the internal pass has no splits to fill the chip with: 16-row workgroups until 64-row ones do (blocks of 32, 64-row
+    // workgroups: 16 of them 14.2 us, 7.2 with 16 rows; 128 14.8 and 13.2; 256 15.5 and 23.8; blocks of 1000, 192 of them, 85
+    // and 105)
+    if ((long long)p.B * p.Hkv * ((nrows + 63) / 64) < 256) tile = 16;
+  } else {
+    // too few tiles for the splits that would fill the chip: smaller workgroups as long as they are one round (128 rows of 8
+    // KV heads, head_dim 128, 8 / 64 / 192 keys: 64-row workgroups 12.9 / 12.6 / 15.2 us, 16-row ones 6.4 / 6.6 / 9.4)
+    const long long units = (long long)p.B * (f32_per_head(MODE) ? p.Hq : p.Hkv) * (p.nsplit + (MODE == kPassRefreshFused ? 1 : 0));
+    if (units * ((nrows + 15) / 16) <= 256) tile = 16;
+    else if (tile > 32 && units * ((nrows + 31) / 32) <= 256) tile = 32;
+  }
   if (tile == 16) return launch_f32<D, MODE, 1, 1>(p, s);
   // two accumulator sets at head_dim 128: 64-row workgroups have half the registers a wavefront and spill in the tile loop
   // (32 / 8 heads of 40 rows, 4111 keys, refresh 138 us with 64 rows and 82 with 32)
