@@ -417,7 +417,7 @@ __global__ __launch_bounds__(256 * WR, 1) void attn_f32_kernel(const PassParams 
 }
 
 // Attention mass per (query row, key block): sum over the block's keys of exp(s - lse), fp32 storage.
-// Same work decomposition as the attention pass (one wavefront per query row, lane j scores key j).
+// One wavefront per query row, 4 rows of one query head per workgroup, lane j scores key j of a tile staged in LDS.
 template <int D>
 __global__ __launch_bounds__(256) void block_mass_f32_kernel(const MassParams p) {
   constexpr int KSTR = D + 4;
@@ -473,6 +473,112 @@ __global__ __launch_bounds__(256) void block_mass_f32_kernel(const MassParams p)
   }
 }
 
+// At most 16 keys (the small blocks' internal pass, a prefix that short): one wavefront per query row, no LDS, no barrier.  A
+// tile of 64 keys costs the same loads and matrix products however few of its keys exist; here everything is requested at once
+// (lane = key x quarter of the score product; 64 lanes across the columns of V and of the cached partial).
+// What bounds it is launch and one memory round trip.  (128 rows of 8 KV heads, head_dim 128, blocks of 4: 6.9 us with 16-row
+// workgroups, 5.2 with the earlier form that staged K in LDS, 3.7 so.)
+constexpr int kFewKeys = 16;
+
+template <int D, int MODE>
+__global__ __launch_bounds__(256) void attn_f32_few_kernel(const PassParams p) {
+  static_assert(MODE == kPassInternal || MODE == kPassDense, "unsplit passes");
+  constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
+  constexpr int NC = D / 64, NQ4 = D / 16;
+  typedef float colv __attribute__((ext_vector_type(NC)));
+  const int lane = threadIdx.x & 63, key = lane >> 2, part = lane & 3;
+  const uint32_t row = blockIdx.x * 4 + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // batch, head, block row
+  if (row >= (uint32_t)(p.B * p.Hq * p.Bq)) return;           // wavefront-uniform
+  const int nkeys = p.nkeys;
+  const size_t bk = fastdiv(row, p.div_rowtiles);             // divisor: rows of a KV group
+  const float* __restrict__ Q = (const float*)p.q + (size_t)row * D;
+  const float* __restrict__ K = (const float*)p.k + bk * nkeys * D;
+  const float* __restrict__ V = (const float*)p.v + bk * nkeys * D + lane * NC;
+  f32x4 k4[NQ4], q4[NQ4];
+#pragma unroll
+  for (int i = 0; i < NQ4; ++i) {
+    k4[i] = *(const f32x4*)(K + (size_t)min(key, nkeys - 1) * D + (part + 4 * i) * 4);
+    q4[i] = *(const f32x4*)(Q + (part + 4 * i) * 4);
+  }
+  colv v[kFewKeys];
+#pragma unroll
+  for (int j = 0; j < kFewKeys; ++j) v[j] = *(const colv*)(V + (size_t)min(j, nkeys - 1) * D);
+  const bool has_ext = MODE == kPassInternal && p.ext_o != nullptr;      // uniform
+  float em = -INFINITY, el = -INFINITY;
+  colv eo = 0.f;
+  if (has_ext) {
+    em = p.ext_m[row];
+    el = p.ext_lse[row];
+    eo = *(const colv*)(p.ext_o + (size_t)row * D + lane * NC);
+  }
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < NQ4; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s = fmaf(k4[i][r], q4[i][r], s);
+  s += __shfl_xor(s, 1, 64);
+  s += __shfl_xor(s, 2, 64);
+  if (key >= nkeys) s = -INFINITY;
+  float m = s * p.scale_log2;
+#pragma unroll
+  for (int x = 4; x < 64; x <<= 1) m = fmaxf(m, __shfl_xor(m, x, 64));
+  const float m_use = (m == -INFINITY) ? 0.f : m;
+  const float w = __builtin_amdgcn_exp2f(fmaf(s, p.scale_log2, -m_use));
+  float l = w;
+#pragma unroll
+  for (int x = 4; x < 64; x <<= 1) l += __shfl_xor(l, x, 64);
+  colv o = 0.f;
+#pragma unroll
+  for (int j = 0; j < kFewKeys; ++j)
+    if (j < nkeys) {                                          // uniform: a weight of 0 must not meet the duplicated last key
+      const float wj = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(w), 4 * j));
+#pragma unroll
+      for (int c = 0; c < NC; ++c) o[c] = fmaf(wj, v[j][c], o[c]);
+    }
+  if constexpr (MODE == kPassInternal) {
+    // Eq. 8-9 with the cached pair expressed through (o, m, lse): A_out e^{L_out-M} = o e^{m-M}.
+    float me2 = -INFINITY, le = 0.f;
+    if (el != -INFINITY) {
+      me2 = em * kLog2e;
+      le = exp2f((el - em) * kLog2e);
+    }
+    const float M2 = fmaxf(me2, m);
+    const float M2u = (M2 == -INFINITY) ? 0.f : M2;
+    const float we = exp2f(me2 - M2u), wi = exp2f(m - M2u);
+    const float den = le * we + l * wi;
+    const float inv = den > 0.f ? 1.f / den : 0.f;
+    colv num = o * wi;
+    if (le > 0.f) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) num[c] = fmaf(eo[c], we, num[c]);
+    }
+    *(colv*)((float*)p.out + (size_t)row * D + lane * NC) = num * inv;
+    if (p.lse_out != nullptr && lane == 0) p.lse_out[row] = den > 0.f ? (M2 + log2f(den)) * kLn2 : -INFINITY;
+  } else {
+    // the final partial; same unit conversion as the split combine
+    float m_nat = -INFINITY, L = -INFINITY, adj = 0.f;
+    if (l > 0.f) {
+      m_nat = m * kLn2;
+      adj = exp2f(m - m_nat * kLog2e);
+      L = (m + log2f(l)) * kLn2;
+    }
+    *(colv*)(p.ws_o + (size_t)row * D + lane * NC) = o * adj;
+    if (lane == 0) {
+      p.ws_m[row] = m_nat;
+      p.ws_l[row] = L;
+    }
+  }
+}
+
+template <int D, int MODE>
+hipError_t launch_f32_few(const PassParams& p, hipStream_t s) {
+  PassParams q = p;
+  q.div_rowtiles = make_fastdiv((uint32_t)(p.G * p.Bq));
+  const long long rows = (long long)p.B * p.Hq * p.Bq;
+  hipLaunchKernelGGL((attn_f32_few_kernel<D, MODE>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, q);
+  return hipGetLastError();
+}
+
 template <int D, int MODE, int RB, int WR>
 hipError_t launch_f32(const PassParams& p, hipStream_t s) {
   using C = FCfg<D, RB, WR>;
@@ -498,6 +604,14 @@ hipError_t launch_f32(const PassParams& p, hipStream_t s) {
 
 template <int D, int MODE>
 hipError_t launch_f32_rows(const PassParams& p, hipStream_t s) {
+  if constexpr (MODE == kPassInternal || MODE == kPassDense) {
+    // up to 4096 rows, or 32 to a KV head, which a 16-row workgroup pads or a 64-row one does (head_dim 128, 4 / 16 keys: 128
+    // rows 6.9 -> 3.7 / 6.9 -> 3.8 us, 4096 rows 7.2 -> 6.8 / 7.2 -> 6.9; 16 rows of 1024 KV heads 23.9 -> 18.8; but 128 rows
+    // of 128 KV heads, 16 keys, 15.1 -> 18.8)
+    const long long rows = (long long)p.B * p.Hq * p.Bq;
+    if (p.nkeys >= 1 && p.nkeys <= kFewKeys && (MODE == kPassInternal || p.direct) && (rows <= 4096 || p.G * p.Bq <= 32))
+      return launch_f32_few<D, MODE>(p, s);
+  }
   const int nrows = f32_per_head(MODE) ? p.Bq : p.G * p.Bq;
   int tile = f32_row_tile(nrows);
   if (MODE == kPassInternal) {

@@ -63,6 +63,58 @@ def test_internal_pass_with_64_row_workgroups():
     T.assert_close(lse.double().cpu().numpy(), part["lse"], "f32", "internal lse", lse=True)
 
 
+@pytest.mark.parametrize("ext", ["none", "empty", "partial"])
+@pytest.mark.parametrize("B,Hq,Hkv,d,Bq", [
+    (1, 1, 1, 64, 1), (1, 3, 1, 128, 1), (2, 6, 2, 64, 4), (1, 8, 2, 128, 8), (1, 4, 4, 128, 15), (1, 4, 2, 64, 16), (1, 3, 3, 128, 16),
+    (1, 4, 2, 128, 17),                                              # one key too many for a wavefront per row
+    (16, 32, 1, 64, 8), (17, 32, 1, 64, 8), (40, 32, 8, 64, 8),      # 4096 rows; 4352 of one KV head, and of 8 with 32 each
+])
+def test_internal_pass_over_few_keys(B, Hq, Hkv, d, Bq, ext):
+    P = 0 if ext == "empty" else 70
+    w = _wl(B, Hq, Hkv, d, P, Bq, S=1)
+    Kp, Vp = wl.make_prefix(w, 311)
+    (Q, Kb, Vb), = wl.make_block_steps(w, 311)
+    shape, part = T.shape_of(w), T.Partial(w)
+    q, parts = T.to_dev(Q, "f32"), (None, None, None)
+    inn = orc.partial(Q, Kb, Vb)
+    want_out, want_lse = orc.normalized(inn), inn["lse"]
+    if ext != "none":
+        kp, vp = (T.to_dev(Kp, "f32"), T.to_dev(Vp, "f32")) if P else (None, None)
+        fb.fb_external_partial(shape, q, kp, vp, part.o, part.m, part.lse, T.workspace(shape))
+        parts = (part.o, part.m, part.lse)
+        want_out, want_lse = orc.merge(orc.partial(Q, Kp, Vp), inn)
+    out, lse = torch.empty_like(q), torch.empty(q.shape[:3], device=T.DEV)
+    fb.fb_internal_merge(shape, q, T.to_dev(Kb, "f32"), T.to_dev(Vb, "f32"), *parts, out, lse)
+    torch.cuda.synchronize()
+    T.assert_close(out.double().cpu().numpy(), want_out, "f32", w.name + " out")
+    T.assert_close(lse.double().cpu().numpy(), np.asarray(want_lse), "f32", w.name + " lse", lse=True)
+
+
+@pytest.mark.parametrize("P", [1, 3, 15, 16, 17])
+@pytest.mark.parametrize("Hq,Hkv,d,Bq", [(1, 1, 64, 1), (6, 2, 128, 13), (4, 4, 64, 70)])
+def test_prefix_of_few_keys(Hq, Hkv, d, Bq, P):
+    w = _wl(2, Hq, Hkv, d, P, Bq, S=1, R=1)
+    Kp, Vp = wl.make_prefix(w, 313)
+    (Q, _, _), = wl.make_block_steps(w, 313)
+    shape, part = T.shape_of(w), T.Partial(w)
+    fb.fb_external_partial(shape, T.to_dev(Q, "f32"), T.to_dev(Kp, "f32"), T.to_dev(Vp, "f32"), part.o, part.m, part.lse,
+                           T.workspace(shape))
+    torch.cuda.synchronize()
+    T.check_partial(part.numpy(), orc.partial(Q, Kp, Vp), "f32", w.name)
+
+
+def test_few_keys_with_an_infinite_last_value():
+    """The last key's value row is infinite and its weight is not 0: infinities, and no NaN, where the row is added."""
+    w = _wl(1, 2, 1, 64, 0, 5, S=1)
+    (Q, Kb, Vb), = wl.make_block_steps(w, 315)
+    Vb[..., -1, :] = np.inf
+    q = T.to_dev(Q, "f32")
+    out = torch.empty_like(q)
+    fb.fb_internal_merge(T.shape_of(w), q, T.to_dev(Kb, "f32"), T.to_dev(Vb, "f32"), None, None, None, out, None)
+    torch.cuda.synchronize()
+    assert bool(torch.isposinf(out).all())
+
+
 @pytest.mark.parametrize("Bq", [7, 20, 40])
 def test_unselected_key_blocks_are_never_touched(Bq):
     """Sparse reuse: an infinity in a key block that another head of the group selected leaves this head's rows alone."""
