@@ -228,8 +228,8 @@ fb_status fb_external_partial_paged(const fb_shape* shape, const void* q, const 
  * attention and Eq. 8-9 merge (what fb_internal_merge would return), in two launches where the shape allows it:
  * with one split the paged pass writes the partial itself and the internal pass follows; with several
  * splits and a block of at most 64 rows (a multiple of 4) one kernel folds the splits, computes the rows'
- * block-internal attention and merges; with fewer than 8 splits otherwise (bf16) the internal pass folds them;
- * else split combine + internal pass (three launches).
+ * block-internal attention and merges; with fewer than 8 splits and few rows per KV head otherwise (bf16) the
+ * internal pass folds them; else split combine + internal pass (three launches).
  * Arguments as in fb_external_partial_paged and fb_internal_merge; lse_out may be NULL.  Workspace as for
  * fb_external_partial_paged.  (Batches above 128 sequences add the sequence-ordering launch.)
  */

@@ -627,13 +627,16 @@ fb_status fb_refresh_step_prof(const fb_shape* shape, const void* q, const void*
   }
   // Few splits, up to 128 rows per KV head and a block of one tile: the streaming kernel over the prefix, then the internal
   // pass folds the splits, against the register-staged pass over both and the combine (a refresh and a reuse step, head_dim
-  // 128: batch 6, 31 rows, 9000 keys 90.8 -> 83.3 us; batch 8, 32 rows, 20000 keys 146 -> 138; head_dim 64: batch 16, 24
-  // rows, 30000 keys 118 -> 107, but 5003 keys, 20 tiles per split, 30.9 -> 32.1: from 32 tiles per split on)
+  // 128: batch 6, 31 rows, 9000 keys 90.8 -> 83.3 us; batch 8, 32 rows, 20000 keys 146 -> 138).  head_dim 64 by tiles per split
+  // (a refresh step): more than one round of workgroups from 32 on (36 tiles, 288 workgroups, blocks of 9 62.5 -> 58.5); one
+  // round from 44 on (64 KV heads, blocks of 24, 36 tiles 36.4 -> 37.4, 48 44.2 -> 44.2, 64 57.2 -> 53.7), blocks of more than
+  // one 32-key tile from 64 on (blocks of 61, 36 tiles 39.5 -> 41.7, 56 54.1 -> 54.6, 64 63.7 -> 60.6)
+  const int d64_tiles = (long long)p.B * p.Hkv * ns > 256 ? 32 : p.Bq <= 32 ? 44 : 64;
   fb::PassParams in = base_pass(shape, q, k_block, v_block, shape->block_len, 1);
   in.fold_ns = ns;
   const bool fold_internal = shape->dtype == FB_BF16 && !small_block && ns > 1 && p.G * p.Bq <= 128 &&
                              p.Bq <= fb::kKeyTile && fb::stream_bf16_covers(p, shape->head_dim, fb::kPassDense) &&
-                             (shape->head_dim == 128 || shape->prefix_len >= 32 * fb::kKeyTile * ns) &&
+                             (shape->head_dim == 128 || shape->prefix_len >= (long long)d64_tiles * fb::kKeyTile * ns) &&
                              fb::internal_fold_covers(in, shape->head_dim);
   p.whole_tiles = fold_internal ? 1 : 0;
   p.ws_o = (float*)(ws + w.o[0]); p.ws_m = (float*)(ws + w.m[0]); p.ws_l = (float*)(ws + w.l[0]);
@@ -680,13 +683,17 @@ fb_status fb_refresh_step_paged(const fb_shape* shape, const void* q, const fb_p
   // few rows: one kernel of 4 rows per workgroup folds, computes the rows' block-internal attention and merges (as in
   // fb_refresh_step; beyond a few thousand rows that latency chain loses: 219 vs ~165 us per step at batch 32, block 32).
   // Few splits otherwise (bf16): the internal pass folds them (batch 8,
-  // 32 rows, up to 8000 keys 61.2 -> 58.5 us a refresh and a reuse step; batch 32 162.2 -> 159.7).  Else combine + internal pass.
+  // 32 rows, up to 8000 keys 61.2 -> 58.5 us a refresh and a reuse step; batch 32 162.2 -> 159.7); at head_dim 128 blocks of more
+  // than one 32-key tile only in one round of its 32-row workgroups (blocks of 64, 256 of them, 45.4 -> 43.9 a refresh step;
+  // blocks of 40, 640 of them, 96.7 -> 102).  Else combine + internal pass.
   fb::PassParams in = base_pass(shape, q, k_block, v_block, shape->block_len, 1);
   in.out = out; in.lse_out = lse_out;
   in.fold_ns = n_splits > 0 ? n_splits : paged_splits(shape);
   const bool fold_kernel = shape->block_len <= fb::kMaxInlineBlock && shape->block_len % fb::kFoldRows == 0 &&
                            rows_of(shape) <= kFoldKernelMaxRows;
+  const bool one_round = (long long)in.B * in.Hkv * ((in.G * in.Bq + 31) / 32) <= 256;
   const bool fold_internal = !fold_kernel && shape->dtype == FB_BF16 && in.fold_ns > 1 &&
+                             (shape->head_dim == 64 || in.Bq <= 32 || one_round) &&
                              fb::internal_fold_covers(in, shape->head_dim);
   fb::CombineParams c;
   st = external_partial_impl(shape, q, nullptr, nullptr, kv, nullptr, false, 0, o_part, m_part, lse_part, n_splits,

@@ -1287,8 +1287,11 @@ hipError_t launch_block_mass_bf16(const MassParams& p, int D, hipStream_t s) {
   return hipGetLastError();
 }
 
+// The folding pass runs 32-row workgroups (64 at head_dim 64) that each load the block's keys again: up to 128 rows per KV head,
+// 512 at head_dim 64 (paged refresh step with combine and internal pass -> folding: head_dim 128, 128 rows, batch 16 93.4 -> 91.0
+// us, 300 rows 126 -> 132, 771 rows 126 -> 150; head_dim 64, 128 rows 62.2 -> 56.6, 456 rows 31.5 -> 30.1, 600 rows 123 -> 125).
 bool internal_fold_covers(const PassParams& p, int D) {
-  return p.fold_ns > 0 && p.fold_ns < 8 && !use_row_pairs(p) && !stream_bf16_covers(p, D, kPassInternal);
+  return p.fold_ns > 0 && p.fold_ns < 8 && p.G * p.Bq <= (D == 128 ? 128 : 512) && !stream_bf16_covers(p, D, kPassInternal);
 }
 
 int attn_bf16_dense_name(const PassParams& p, int D, char* buf, size_t n) {

@@ -64,8 +64,10 @@ def test_sparse_streams(P, key_block, topk, G, Bq):
     (6, 16, 8, 128, 4000, 31),       # 62 rows per KV head, 6 splits folded by the internal pass
     (16, 8, 4, 128, 3000, 9),        # 18 rows
     (10, 8, 4, 128, 4100, 64),       # 128 rows, a block of one whole tile
-    (16, 8, 4, 64, 9000, 24),        # head_dim 64, more than 32 tiles per split
-    (16, 8, 4, 64, 8100, 24),        # fewer than 32
+    (16, 8, 4, 64, 9000, 24),        # head_dim 64, one round of workgroups, fewer than 44 tiles per split
+    (16, 8, 4, 64, 12000, 24),       # more
+    (16, 8, 4, 64, 12100, 33),       # a block of two 32-key tiles
+    (20, 8, 4, 64, 9100, 33),        # more than one round, more than 32 tiles
     (40, 8, 4, 128, 700, 40),        # too short for the streaming kernel
 ])
 def test_refresh_step_with_few_splits(B, Hq, Hkv, d, P, Bq):
@@ -89,5 +91,5 @@ def test_refresh_step_with_few_splits(B, Hq, Hkv, d, P, Bq):
         T.assert_close(lse.double().cpu().numpy(), ora[t]["lse"], "bf16", f"{w.name} step {t} lse", lse=True)
     rows, ns = B * Hq * Bq, fb.fb_external_heads_splits(shape, 0)
     behind = ns * rows * d * 4 + 2 * 256 * -(-ns * rows * 4 // 256)
-    assert bool((ws[behind:behind + rows * d * 4] == 0xA5).all()) == (P not in (2700, 8100, 700))
+    assert bool((ws[behind:behind + rows * d * 4] == 0xA5).all()) == (P not in (2700, 9000, 12100, 700))
     T.check_partial(ext.numpy(), ora[0]["ext"], "bf16", w.name + " ext")
