@@ -134,7 +134,8 @@ int dense_splits(const fb_shape* s) {
 // bf16 with a hint: auto_splits, whose two candidates around 256 / groups both drop out where the stream is too short for 8
 // tiles per split of them, which leaves 1.  There, splits of 8 tiles, up to 7 (from 8 on the combine takes a workgroup for
 // every row, flagged or not: 1 of 10 heads of 1500 rows, head_dim 64, 6000 keys, 34.4 us with 11 and 20.1 with 7), and no
-// fewer than without a hint.  One split left a handful of CUs with the whole stream (hinted with 1, unhinted, now: 1 of 8
+// fewer than without a hint; from 16 tiles on, below which the combine costs what the splits save (15 of 16 heads of 319
+// rows, batch 2, 9 tiles, 18.5 us with 1 and 19.9 with 2).  One split left a handful of CUs with the whole stream (hinted with 1, unhinted, now: 1 of 8
 // heads of 1000 rows, 3000 keys, 54.1, 23.1, 21.9 us; 1 of 12, 16000 keys, 210, 93.8, 48.5; 2 of 32 / 8 heads of 64 rows, 8000
 // keys, 84.2, 17.1, 16.6).
 int heads_splits(const fb_shape* s, int active_heads) {
@@ -142,7 +143,7 @@ int heads_splits(const fb_shape* s, int active_heads) {
   const int ns = auto_splits(s, active_heads), tiles = (s->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile;
   const long long groups = (long long)s->batch * std::min(active_heads, s->n_kv_heads) *
                            (((long long)(s->n_q_heads / s->n_kv_heads) * s->block_len + fb::kRowsPerWgBf16 - 1) / fb::kRowsPerWgBf16);
-  if (active_heads <= 0 || active_heads >= s->n_q_heads || tiles >= 8 * (256 / groups)) return ns;
+  if (active_heads <= 0 || active_heads >= s->n_q_heads || tiles < 16 || tiles >= 8 * (256 / groups)) return ns;
   return std::max({ns, auto_splits(s), std::min(tiles / 8, 7)});
 }
 

@@ -131,15 +131,15 @@ def test_external_partial_heads_error_paths():
 @pytest.mark.parametrize("heads,kv,rows,prefix", [(8, 8, 1000, 3000), (12, 12, 1000, 16000), (32, 8, 64, 8000), (4, 4, 40, 100),
                                                   (12, 12, 4680, 37440), (10, 5, 300, 0), (32, 1, 9, 700)])
 def test_a_hint_on_a_short_stream_never_means_fewer_splits(heads, kv, rows, prefix):
-    """Where a split of the flagged groups that fill 256 workgroups would have fewer than 8 tiles."""
+    """Where a split of the flagged groups that fill 256 workgroups would have fewer than 8 tiles, from 16 tiles on."""
     s = _ok_shape(dtype="bf16", head_dim=128, n_q_heads=heads, n_kv_heads=kv, block_len=rows, prefix_len=prefix)
     tiles, plain, short = -(-prefix // 64), fb.fb_external_heads_splits(s, 0), 0
     for active in range(1, heads):
         groups = min(active, kv) * -(-heads // kv * rows // 128)
-        if tiles < 8 * (256 // groups):
+        if 16 <= tiles < 8 * (256 // groups):
             short += 1
             assert fb.fb_external_heads_splits(s, active) >= max(plain, min(tiles // 8, 7), 1), active
-    assert short > 0 or (heads, prefix) == (12, 37440)
+    assert short > 0 or prefix in (37440, 0, 100, 700)
 
 
 def _paged(**kw):
