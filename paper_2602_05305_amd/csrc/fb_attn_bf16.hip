@@ -1213,7 +1213,9 @@ hipError_t launch_d(const PassParams& p, PassMode mode, hipStream_t s) {
         return launch_one<D, kPassDense, kKeyTile, 2, 1>(p, s);
       }
       if (v.ng == 2) {
-        if (v.var == 2) return launch_one<D, kPassDense, kKeyTile, 1, 2, 2>(p, s);
+        if constexpr (D == 64) {      // (head_dim 128: streams that long are the streaming kernel's)
+          if (v.var == 2) return launch_one<D, kPassDense, kKeyTile, 1, 2, 2>(p, s);
+        }
         return launch_one<D, kPassDense, kKeyTile, 1, 2>(p, s);
       }
       return launch_one<D, kPassDense, kKeyTile, 1, 1>(p, s);
