@@ -322,7 +322,9 @@ const char* fb_external_kernel_name(const fb_shape* shape) {
   name[0] = 0;
   if (check_shape(shape) != FB_OK) return name;
   if (shape->dtype != FB_BF16) {
-    snprintf(name, sizeof(name), "attn_f32_kernel<%d, %d>", shape->head_dim, (int)fb::kPassDense);
+    const bool few = dense_splits(shape) == 1 &&
+                     fb::f32_few_keys(rows_of(shape), (long long)(shape->n_q_heads / shape->n_kv_heads) * shape->block_len, shape->prefix_len);
+    snprintf(name, sizeof(name), "attn_f32_%skernel<%d, %d>", few ? "few_" : "", shape->head_dim, (int)fb::kPassDense);
     return name;
   }
   const fb::PassParams p = base_pass(shape, nullptr, nullptr, nullptr, shape->prefix_len, dense_splits(shape));

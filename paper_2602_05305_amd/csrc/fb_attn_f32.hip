@@ -478,8 +478,6 @@ __global__ __launch_bounds__(256) void block_mass_f32_kernel(const MassParams p)
 // (lane = key x quarter of the score product; 64 lanes across the columns of V and of the cached partial).
 // What bounds it is launch and one memory round trip.  (128 rows of 8 KV heads, head_dim 128, blocks of 4: 6.9 us with 16-row
 // workgroups, 5.2 with the earlier form that staged K in LDS, 3.7 so.)
-constexpr int kFewKeys = 16;
-
 template <int D, int MODE>
 __global__ __launch_bounds__(256) void attn_f32_few_kernel(const PassParams p) {
   static_assert(MODE == kPassInternal || MODE == kPassDense, "unsplit passes");
@@ -500,9 +498,9 @@ __global__ __launch_bounds__(256) void attn_f32_few_kernel(const PassParams p) {
     k4[i] = *(const f32x4*)(K + (size_t)min(key, nkeys - 1) * D + (part + 4 * i) * 4);
     q4[i] = *(const f32x4*)(Q + (part + 4 * i) * 4);
   }
-  colv v[kFewKeys];
+  colv v[kFewKeysF32];
 #pragma unroll
-  for (int j = 0; j < kFewKeys; ++j) v[j] = *(const colv*)(V + (size_t)min(j, nkeys - 1) * D);
+  for (int j = 0; j < kFewKeysF32; ++j) v[j] = *(const colv*)(V + (size_t)min(j, nkeys - 1) * D);
   const bool has_ext = MODE == kPassInternal && p.ext_o != nullptr;      // uniform
   float em = -INFINITY, el = -INFINITY;
   colv eo = 0.f;
@@ -529,7 +527,7 @@ __global__ __launch_bounds__(256) void attn_f32_few_kernel(const PassParams p) {
   for (int x = 4; x < 64; x <<= 1) l += __shfl_xor(l, x, 64);
   colv o = 0.f;
 #pragma unroll
-  for (int j = 0; j < kFewKeys; ++j)
+  for (int j = 0; j < kFewKeysF32; ++j)
     if (j < nkeys) {                                          // uniform: a weight of 0 must not meet the duplicated last key
       const float wj = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(w), 4 * j));
 #pragma unroll
@@ -605,11 +603,7 @@ hipError_t launch_f32(const PassParams& p, hipStream_t s) {
 template <int D, int MODE>
 hipError_t launch_f32_rows(const PassParams& p, hipStream_t s) {
   if constexpr (MODE == kPassInternal || MODE == kPassDense) {
-    // up to 4096 rows, or 32 to a KV head, which a 16-row workgroup pads or a 64-row one does (head_dim 128, 4 / 16 keys: 128
-    // rows 6.9 -> 3.7 / 6.9 -> 3.8 us, 4096 rows 7.2 -> 6.8 / 7.2 -> 6.9; 16 rows of 1024 KV heads 23.9 -> 18.8; but 128 rows
-    // of 128 KV heads, 16 keys, 15.1 -> 18.8)
-    const long long rows = (long long)p.B * p.Hq * p.Bq;
-    if (p.nkeys >= 1 && p.nkeys <= kFewKeys && (MODE == kPassInternal || p.direct) && (rows <= 4096 || p.G * p.Bq <= 32))
+    if ((MODE == kPassInternal || p.direct) && f32_few_keys((long long)p.B * p.Hq * p.Bq, p.G * p.Bq, p.nkeys))
       return launch_f32_few<D, MODE>(p, s);
   }
   const int nrows = f32_per_head(MODE) ? p.Bq : p.G * p.Bq;

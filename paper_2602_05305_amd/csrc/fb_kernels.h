@@ -228,6 +228,14 @@ constexpr int kRowsPerWgF32 = 4;     // fp32 mass kernel: 4 waves x 1 row
 // batch 4 115 -> 93, 12 heads of 1000 rows 399 -> 297.  17 to 32 rows in one workgroup, which reads K and V once, though two
 // of 16 rows take less at 24 rows of 8 heads (4111 keys 20.6 and 18.1 us).
 inline int f32_row_tile(long long nrows) { return nrows <= 16 ? 16 : nrows <= 32 ? 32 : 64; }
+// fp32 internal and unsplit dense passes over at most 16 keys: one wavefront per row (attn_f32_few_kernel).  Up to 4096 rows, or
+// 32 to a KV head, which a 16-row workgroup pads or a 64-row one does (head_dim 128, 4 / 16 keys: 128 rows 6.9 -> 3.7 / 6.9 -> 3.8
+// us, 4096 rows 7.2 -> 6.8 / 7.2 -> 6.9; 16 rows of 1024 KV heads 23.9 -> 18.8; but 128 rows of 128 KV heads, 16 keys, 15.1 ->
+// 18.8).
+constexpr int kFewKeysF32 = 16;
+inline bool f32_few_keys(long long rows, long long group_rows, int nkeys) {
+  return nkeys >= 1 && nkeys <= kFewKeysF32 && (rows <= 4096 || group_rows <= 32);
+}
 // bf16 dense external pass: KV groups of more than 128 rows run row-pair workgroups (8 wavefronts, 256 rows, one
 // shared tile stream), so every K/V tile is staged once per 256 rows.  At head_dim 64 that measures the same as
 // 128-row workgroups (32.6 vs 33.8 us at 256 rows, 32K keys) but leaves twice the splits to fold, so there only

@@ -328,6 +328,13 @@ def test_builtin_workspace_entry_rejects_on_the_host():
     assert lib.fb_external_partial_builtin_ws(ctypes.byref(bad), one, one, one, one, one, one, None) == fb.FB_ERR_SHAPE
 
 
+def test_external_kernel_name_over_few_fp32_keys():
+    name = lambda *a: fb.fb_external_kernel_name(fb.make_shape(*a))
+    assert name(1, 4, 4, 64, 16, 16, "f32") == "attn_f32_few_kernel<64, 0>"
+    assert name(1, 4, 4, 64, 16, 17, "f32") == name(16, 32, 4, 64, 16, 16, "f32") == name(1, 4, 4, 64, 16, 0, "f32") == "attn_f32_kernel<64, 0>"
+    assert name(64, 32, 32, 128, 32, 3, "f32") == "attn_f32_few_kernel<128, 0>"      # many rows, 32 to a KV head
+
+
 def test_external_kernel_name_follows_the_launch_rules():
     """Host-only query the benchmark labels its roofline with: streaming kernel (with 1, 2 or 4 row groups per workgroup) for up
     to 128 rows per KV group and at least 8 tiles per split, register-staged kernel for short prefixes, fp32 kernel for fp32."""
