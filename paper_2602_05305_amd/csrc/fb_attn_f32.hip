@@ -615,7 +615,7 @@ hipError_t launch_f32_rows(const PassParams& p, hipStream_t s) {
     if ((long long)p.B * p.Hkv * ((nrows + 63) / 64) < 256) tile = 16;
   } else {
     // too few tiles for the splits that would fill the chip: smaller workgroups as long as they are one round (128 rows of 8
-    // KV heads, head_dim 128, 8 / 64 / 192 keys: 64-row workgroups 12.9 / 12.6 / 15.2 us, 16-row ones 6.4 / 6.6 / 9.4)
+    // KV heads, head_dim 128, 32 / 64 / 192 keys: 64-row workgroups 12.9 / 12.7 / 15.5 us, 16-row ones 6.4 / 6.2 / 9.2)
     const long long units = (long long)p.B * (f32_per_head(MODE) ? p.Hq : p.Hkv) * (p.nsplit + (MODE == kPassRefreshFused ? 1 : 0));
     if (units * ((nrows + 15) / 16) <= 256) tile = 16;
     else if (tile > 32 && units * ((nrows + 31) / 32) <= 256) tile = 32;
