@@ -125,7 +125,7 @@ struct PassParams {
   // folds, writes to o_final / m_final / l_final (natural-log units) and merges
   int fold_ns;
   // streaming kernel, refresh step: whole tiles for the two wavefronts of a row group, splits cut with blk_cost; and the
-  // instantiation of the many-row internal pass that visits its tiles in rotated order
+  // many-row internal pass visits its tiles in rotated order
   int whole_tiles, rotate;
   // paged pass: k/v point at the pools [num_pages, Hkv, page_size, D]
   const int32_t* block_table; // [B, max_pages] page ids

@@ -18,9 +18,7 @@
 //              the tile's key block to, so the eight wavefronts stay evenly loaded whatever the selection.
 //              At head_dim 64 two tiles per barrier.
 //   kTileSplit the same with whole tiles: half h takes every other tile, two tiles per barrier.
-//   kRowPair   256 rows, wavefront w owns rows [32 w, +32) and whole tiles (many rows per KV head: a staged
-//              tile serves twice the rows).  Two tiles per barrier: inside an iteration the two wavefronts of a SIMD
-//              are free to drift apart by a tile, so that one's softmax can run under the other's MFMAs.
+//   kRowPair   256 rows, 4 wavefronts of 64 rows and whole tiles (many rows per KV head): fb_rows_bf16.h.
 //   Per tile and wavefront: S^T = K Q^T on v_mfma_f32_32x32x16_bf16 (A = K rows from LDS, B = Q^T in
 //   registers), in-lane online softmax with a lazily moved reference, O^T += V^T P^T with the lane's own
 //   probabilities as the B operand (register layout reasoning: fb_attn_bf16.hip, which is the same).
@@ -36,28 +34,14 @@
 #include <stdio.h>
 
 #include "fb_kernels.h"
+#include "fb_rows_bf16.h"
 
 namespace fb {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
-
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
-
-// (kKeySplitSingle: the key split with one tile per barrier at head_dim 64 as well; kRowPairRotated: the internal pass of
-// the refresh step, whose row pairs walk the block's tiles in rotated order like the external pass.  A layout of its own,
-// not a run-time switch: with one, every many-row reuse step carried the division, the wrap and 81 instructions more,
-// 0.4 to 1.7 % of 145 us for 12 heads of 4680 rows)
-enum StreamLayout : int { kKeySplit = 0, kTileSplit = 1, kRowPair = 2, kKeySplitSingle = 3, kRowPairRotated = 4 };
+// (kKeySplitSingle: the key split with one tile per barrier at head_dim 64 as well)
+enum StreamLayout : int { kKeySplit = 0, kTileSplit = 1, kRowPair = 2, kKeySplitSingle = 3 };
 constexpr bool key_split(int layout) { return layout == kKeySplit || layout == kKeySplitSingle; }
-constexpr bool row_pair(int layout) { return layout == kRowPair || layout == kRowPairRotated; }
 
 // Key split at head_dim 64: two tiles per barrier, their scores and weights computed together, because a tile's fixed cost
 // (barrier, refill, the softmax's cross-lane step) is large against its 16 KB: batch 4, 64K keys, 32 rows
@@ -72,7 +56,7 @@ constexpr bool paired_halves(int D, int layout) { return D == 64 && layout == kK
 // wavefronts: the small blocks of 4- and 8-token diffusion steps, where more row groups would compute padding rows)
 template <int D, int LAYOUT, int NSETS = 1, int NRG = 4>
 struct SCfg {
-  static constexpr int NW = (row_pair(LAYOUT)) ? 8 : 2 * NRG;   // wavefronts per workgroup
+  static constexpr int NW = 2 * NRG;                  // wavefronts per workgroup
   static constexpr int THREADS = 64 * NW;
   static constexpr int KT = 64;                       // keys per tile
   static constexpr int ROWB = D * 2;                  // bytes per key row
@@ -82,14 +66,14 @@ struct SCfg {
   static constexpr int NLOAD = OPB / (THREADS * 16);  // direct-to-LDS loads per lane, operand and tile
   static constexpr int LSTEP = NW * 1024;             // LDS bytes one load of every wavefront covers
   static constexpr int LPT = 2 * NLOAD;               // loads per lane and tile
-  static constexpr int NS = (D == 128) ? 4 : (row_pair(LAYOUT) || LAYOUT == kKeySplitSingle) ? 6 : 8;       // ring stages
+  static constexpr int NS = (D == 128) ? 4 : LAYOUT == kKeySplitSingle ? 6 : 8;       // ring stages
   static constexpr int NKS = D / 16;                  // MFMA k-steps of the score product
   static constexpr int NDB = D / 32;                  // 32-wide output column blocks
-  static constexpr int ROWS = (row_pair(LAYOUT)) ? 256 : 32 * NRG;
+  static constexpr int ROWS = 32 * NRG;
   static constexpr int NKB = key_split(LAYOUT) ? 1 : 2;    // 32-key blocks of a tile one wavefront computes
   static constexpr int QPARTS = (ROWS + 63) / 64;             // the query rows are loaded 64 at a time, like a K operand
   static constexpr int QSTAGES = (QPARTS * OPB + STAGE - 1) / STAGE;   // ring stages they pass through at start
-  static constexpr int MERGE = (!row_pair(LAYOUT)) ? NSETS * NRG * 2 * (NDB / 2 * 16 + 2) * 64 * 4 : 0;   // key-half exchange
+  static constexpr int MERGE = NSETS * NRG * 2 * (NDB / 2 * 16 + 2) * 64 * 4;   // key-half exchange
   static constexpr int RING = NS * STAGE;
   static constexpr int FIFO = RING > MERGE ? RING : MERGE;
   static constexpr int LDS = FIFO;
@@ -111,14 +95,6 @@ __device__ __forceinline__ void wait_tiles(int tiles) {
   else if (kMax >= 2 && tiles >= 2) wait_vm<(kMax >= 2 ? 2 : 0) * LPT>();
   else if (kMax >= 1 && tiles >= 1) wait_vm<(kMax >= 1 ? 1 : 0) * LPT>();
   else wait_vm<0>();
-}
-
-__device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  bf16x2 v;
-  v[0] = (__bf16)a;
-  v[1] = (__bf16)b;
-  return __builtin_bit_cast(uint32_t, v);
 }
 
 // Running softmax state of the 32 rows a wavefront owns (one row per lane pair l, l^32).
@@ -374,28 +350,22 @@ struct TileDesc {
   const unsigned char* vt;
 };
 
+// Two wavefronts per row group (every layout but kRowPair).
 template <int D, int MODE, int LAYOUT, int NRG>
-__global__ __launch_bounds__(((row_pair(LAYOUT)) ? 8 : 2 * NRG) * 64, 1) void attn_stream_kernel(const PassParams p) {
+__device__ __forceinline__ void halves_pass(const PassParams& p, unsigned char* ring) {
   constexpr int NSETS = (MODE == kPassSparseRefresh) ? 2 : 1;
   using C = SCfg<D, LAYOUT, NSETS, NRG>;
   static_assert(MODE == kPassDense || MODE == kPassDenseHeads || MODE == kPassDensePaged || MODE == kPassSparseReuse ||
-                    MODE == kPassSparseRefresh || MODE == kPassInternal, "modes of the streaming kernel");
-  static_assert(MODE != kPassSparseRefresh || !row_pair(LAYOUT), "two accumulator sets: key halves");
-  static_assert((MODE != kPassInternal || row_pair(LAYOUT)) && (LAYOUT != kRowPairRotated || MODE == kPassInternal), "internal pass: row-pair layout");
-  // Row-pair layout: two tiles per barrier (tiles t, t+1 are computed while t+2, t+3 are in flight), measured 2 % faster
-  // at the video shape than one tile per barrier; tile split and head_dim 64 the same; key split at 128: one tile per barrier, NS - 1 in flight.
+                    MODE == kPassSparseRefresh, "modes of this form");
+  // Tile split and head_dim 64: two tiles per barrier (tiles t, t+1 are computed while t+2, t+3 are in flight); key split at 128:
+  // one tile per barrier, NS - 1 in flight.
   constexpr bool kPairs = !key_split(LAYOUT) || paired_halves(D, LAYOUT);
-  constexpr bool kHalves = !row_pair(LAYOUT);       // two wavefronts per row group, each with half of the keys
   constexpr int AHEAD = kPairs ? C::NS - 2 : C::NS - 1;
   static_assert(!kPairs || C::NS % 2 == 0, "pairs of tiles: an even number of stages");
-  // passes whose tiles come from a table (paged, sparse): the lookups are made one iteration ahead of the tile's
-  // issue, and (first key, mask) travel to the tile's compute in a register queue
-  constexpr bool kListed = (MODE == kPassDensePaged || MODE == kPassSparseReuse || MODE == kPassSparseRefresh);
-  extern __shared__ __align__(16) unsigned char ring[];
   const int lane = threadIdx.x & 63, l32 = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));     // wavefront-uniform (scalar)
-  const int rg = (row_pair(LAYOUT)) ? wave : (wave % NRG);     // 32-row group
-  const int half = kHalves ? (wave / NRG) : 0;                   // keys of this wavefront: half of every tile, or every other tile
+  const int rg = wave % NRG;                                   // 32-row group
+  const int half = wave / NRG;                                 // keys of this wavefront: half of every tile, or every other tile
   const int kb0 = key_split(LAYOUT) ? half : 0;              // first 32-key block of a tile
 
   // ---- workgroup -> (row tile, batch, KV head, split).  Hardware deals consecutive workgroup ids round-robin
@@ -420,57 +390,17 @@ __global__ __launch_bounds__(((row_pair(LAYOUT)) ? 8 : 2 * NRG) * 64, 1) void at
     // run on even XCDs and odd-numbered ones on odd XCDs
     if (p.xcd_bias) w = (xcd >> 1) * (2 * q8) + 2 * j + (xcd & 1);
     if constexpr (MODE == kPassDenseHeads) {
-      if (row_pair(LAYOUT) || p.div_rowtiles.d > 1) w = bid;     // whole heads drop out: deal a head's row tiles over the XCDs
+      if (p.div_rowtiles.d > 1) w = bid;     // whole heads drop out: deal a head's row tiles over the XCDs
     }
     rest = fastdiv((uint32_t)w, p.div_rowtiles);
     rt = w - (int)(rest * p.div_rowtiles.d);
   }
   const uint32_t unit = rest;
-  int split = 0;
-  if constexpr (MODE != kPassInternal) {
-    const uint32_t r2 = fastdiv(rest, p.div_nsplit);
-    split = (int)(rest - r2 * p.div_nsplit.d);
-    rest = r2;
-  }
-  int b, kvh;
-  constexpr bool kByRank = MODE == kPassDenseHeads && row_pair(LAYOUT);
-  bool direct = p.direct != 0;                               // this workgroup writes the final partial
-  int rank = 0;
-  if constexpr (kByRank) {
-    // The first B * heads_cap * nsplit units belong to the flagged KV groups by rank (the workgroups that have work are then
-    // the first of the grid and spread evenly over the chip whatever the mask; dealt out by head, some masks left a
-    // shader engine with two rounds of workgroups: 569 or 1010 us for 6 of 12 heads); B * Hkv units at the end, one split
-    // each, are for groups beyond the hint.
-    const uint32_t ranked = (uint32_t)(p.B * p.heads_cap);
-    const uint32_t units = ranked * p.div_nsplit.d;
-    const bool extra = unit >= units;
-    const uint32_t bu = extra ? unit - units : rest;
-    const uint32_t per = extra ? (uint32_t)p.Hkv : (uint32_t)p.heads_cap;
-    b = (int)(bu / per);
-    const int want = (int)(bu - (uint32_t)b * per);          // rank, or KV group
-    int seen = 0, hit = -1;
-    for (int g0 = 0; g0 < p.Hkv && hit < 0; g0 += 64) {
-      unsigned long long mask = __ballot(g0 + lane < p.Hkv && group_flagged(p.head_on, b, p.Hq, p.G, g0 + lane));
-      if (extra) {
-        if (want < g0 + 64) {
-          const unsigned long long below = (1ull << (want - g0)) - 1;
-          if (((mask >> (want - g0)) & 1) && seen + __popcll(mask & below) >= p.heads_cap) hit = want;
-          break;
-        }
-      } else if (want < seen + __popcll(mask)) {
-        for (int k = want - seen; k > 0; --k) mask &= mask - 1;
-        hit = g0 + __ffsll(mask) - 1;
-      }
-      seen += __popcll(mask);
-    }
-    if (hit < 0) return;                                     // workgroup-uniform
-    kvh = __builtin_amdgcn_readfirstlane(hit);
-    rank = want;
-    if (extra) direct = true;
-  } else {
-    b = (int)fastdiv(rest, p.div_hkv);
-    kvh = (int)(rest - (uint32_t)b * p.div_hkv.d);
-  }
+  const uint32_t r2 = fastdiv(rest, p.div_nsplit);
+  const int split = (int)(rest - r2 * p.div_nsplit.d);
+  rest = r2;
+  int b = (int)fastdiv(rest, p.div_hkv);
+  const int kvh = (int)(rest - (uint32_t)b * p.div_hkv.d);
   if constexpr (MODE == kPassDensePaged) {
     if (p.seq_order != nullptr) {
       b = sload(p.seq_order, b);
@@ -509,11 +439,6 @@ __global__ __launch_bounds__(((row_pair(LAYOUT)) ? 8 : 2 * NRG) * 64, 1) void at
     head_active = row_ok && p.head_on[b * p.Hq + kvh * p.G + row / p.Bq] != 0;
     if (!__syncthreads_or(head_active ? 1 : 0)) return;
   }
-  const int slot = kByRank ? rank : kvh, slots = kByRank ? p.heads_cap : p.Hkv;      // where its split partials go
-  float* __restrict__ fin_o = kByRank ? p.o_final : p.ws_o;
-  float* __restrict__ fin_m = kByRank ? p.m_final : p.ws_m;
-  float* __restrict__ fin_l = kByRank ? p.l_final : p.ws_l;
-
   // contiguous cache: this KV head's [nkeys, D] slab; paged cache: the pool (tiles add their page offset)
   const unsigned char* __restrict__ Kg =
       (const unsigned char*)p.k + ((MODE == kPassDensePaged) ? (size_t)0 : (size_t)bk * nkeys * C::ROWB);
@@ -530,22 +455,8 @@ __global__ __launch_bounds__(((row_pair(LAYOUT)) ? 8 : 2 * NRG) * 64, 1) void at
   } else {
     total = (nkeys + C::KT - 1) / C::KT;
   }
-  TileRange tr = (MODE == kPassInternal) ? TileRange{0, total}
-                 : p.xcd_bias ? biased_range(total, p.div_bias, split) : split_range(total, p.div_nsplit, split);
-  // per-head refresh, partials by rank: splits 2i and 2i + 1 take the even and the odd tiles of the same range
-  int stride = 1, first = 0;
-  uint32_t rsrc = (p.div_rowtiles.d == 1) ? blockIdx.x : unit;
-  if constexpr (kByRank) {
-    if (direct) {
-      tr = TileRange{0, total};
-    } else {
-      const int pairs = p.nsplit / 2;
-      tr = split_range(total, pairs, split >> 1);
-      stride = 2;
-      first = split & 1;
-      rsrc = (uint32_t)((b * p.Hkv + kvh) * pairs + (split >> 1));
-    }
-  }
+  TileRange tr = p.xcd_bias ? biased_range(total, p.div_bias, split) : split_range(total, p.div_nsplit, split);
+  const uint32_t rsrc = (p.div_rowtiles.d == 1) ? blockIdx.x : unit;
   if constexpr (LAYOUT == kTileSplit) {
     // as the register-staged refresh pass cuts them, so that the running references start from the same tiles and results
     // stay the same up to fp32 sums: the last split is blk_cost tiles (at most half a split, 3 for a block of one tile) shorter
@@ -553,15 +464,14 @@ __global__ __launch_bounds__(((row_pair(LAYOUT)) ? 8 : 2 * NRG) * 64, 1) void at
     tr.begin = min(tr.begin, total);
     tr.end = min(tr.end, total);
   }
-  const int range = tr.end - tr.begin;
-  const int ntiles = kByRank ? (range - first + stride - 1) / stride : range;
-  const int rot = ((MODE == kPassInternal && LAYOUT != kRowPairRotated) || range <= 0) ? 0 : (int)((rsrc * 13u + (rsrc >> 5) * 7u) % (unsigned)range);
+  const int ntiles = tr.end - tr.begin;
+  const int rot = ntiles <= 0 ? 0 : (int)((rsrc * 13u + (rsrc >> 5) * 7u) % (unsigned)ntiles);
   const uint32_t* __restrict__ bmask = p.blk_mask ? p.blk_mask + (size_t)bk * p.nblk : nullptr;
   const int32_t* __restrict__ ulist = p.union_list ? p.union_list + (size_t)bk * p.nblk : nullptr;
   const uint32_t* __restrict__ umask = p.union_mask ? p.union_mask + (size_t)bk * p.nblk : nullptr;
   auto tile_raw = [&](int i) -> TileRaw {        // i-th tile of this workgroup: table lookups only
-    int j = (kByRank ? stride * i + first : i) + rot;
-    if (j >= range) j -= range;
+    int j = i + rot;
+    if (j >= ntiles) j -= ntiles;
     TileRaw r;
     r.e = tr.begin + j;
     r.word = 0;
@@ -691,15 +601,13 @@ __global__ __launch_bounds__(((row_pair(LAYOUT)) ? 8 : 2 * NRG) * 64, 1) void at
         qmask[i] = d.mask;
       }
   }
-  // table words of the next tile to be issued, fetched one iteration ahead (lookups off the critical path; row-pair passes
-  // have no table, and there computing the tile ahead only lengthens the loop)
-  constexpr bool kLookAhead = !row_pair(LAYOUT);
+  // table words of the next tile to be issued, fetched one iteration ahead (lookups off the critical path)
   constexpr int NNEXT = kPairs ? 2 : 1;
   TileRaw rnext[NNEXT];
 #pragma unroll
   for (int u = 0; u < NNEXT; ++u) {
     rnext[u].e = 0; rnext[u].word = 0; rnext[u].mask = 0u;
-    if (kLookAhead && AHEAD + u < ntiles) rnext[u] = tile_raw(AHEAD + u);
+    if (AHEAD + u < ntiles) rnext[u] = tile_raw(AHEAD + u);
   }
 
   // per-lane LDS read addresses inside a stage
@@ -735,11 +643,11 @@ __global__ __launch_bounds__(((row_pair(LAYOUT)) ? 8 : 2 * NRG) * 64, 1) void at
   // follows in this slot; the queue then holds tiles t .. t + AHEAD + u
   auto refill = [&](int t, int u) {
     if (t + AHEAD + u < ntiles) {
-      const TileDesc d = tile_desc(kLookAhead ? rnext[u] : tile_raw(t + AHEAD + u));
+      const TileDesc d = tile_desc(rnext[u]);
       issue_tile(t + AHEAD + u, d);
       qk0[AHEAD + u] = d.k0;
       qmask[AHEAD + u] = d.mask;
-      if (kLookAhead && t + AHEAD + u + NNEXT < ntiles) rnext[u] = tile_raw(t + AHEAD + u + NNEXT);
+      if (t + AHEAD + u + NNEXT < ntiles) rnext[u] = tile_raw(t + AHEAD + u + NNEXT);
     }
   };
   auto advance = [&]() {
@@ -815,31 +723,7 @@ __global__ __launch_bounds__(((row_pair(LAYOUT)) ? 8 : 2 * NRG) * 64, 1) void at
     }
   };
 
-  if constexpr (row_pair(LAYOUT)) {
-    // two tiles per barrier; the prologue put tiles 0 .. AHEAD-1 in flight, iteration t adds tiles t+AHEAD, t+AHEAD+1
-    // into the stages of tiles t-2, t-1 (or the query stages), which every wavefront left before this barrier
-    static_assert(!kListed, "row-pair layout: dense passes only");
-    // per-head refresh: a wavefront computes its rows if any of them is of a flagged head (rows of the others are
-    // computed along and not stored)
-    const bool wave_on = (MODE != kPassDenseHeads) || __any(head_active);
-    for (int t = 0; t < ntiles; t += 2) {
-      wait_tiles<C::LPT>(min(AHEAD - 2, max(ntiles - 2 - t, 0)));   // tiles issued after tile t+1 so far
-      __syncthreads();
-#pragma unroll
-      for (int u = 0; u < 2; ++u) refill(t, u);
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-        if (t + u < ntiles) {
-          const unsigned char* stage = ring + ((t + u) % C::NS) * C::STAGE;
-          const int nvalid = min(C::KT, nkeys - qk0[u]);
-          if (!wave_on) continue;
-          f32x16 s[C::NKB];
-          tile_scores<D, C::NKB>(s, qreg, stage, kaddr, kb0);
-          tile_softmax_pv<D, C::NKB>(acc, s, stage, vaddr, kb0, p.scale_log2, true, nvalid, h);
-        }
-      advance();
-    }
-  } else if constexpr (LAYOUT == kTileSplit) {
+  if constexpr (LAYOUT == kTileSplit) {
     for (int t = 0; t < ntiles; t += 2) {
       wait_tiles<C::LPT>(min(AHEAD - 2, max(ntiles - 2 - t, 0)));   // tiles issued after tile t+1 so far
       __syncthreads();
@@ -876,12 +760,12 @@ __global__ __launch_bounds__(((row_pair(LAYOUT)) ? 8 : 2 * NRG) * 64, 1) void at
     }
   }
 
-  // Output column blocks this wavefront finishes and stores.  Row-pair layout: all of them.  Key-split layout: the two
-  // wavefronts of a row group exchange halves, so that both take part in the merge and in the stores (the wavefront of
-  // key half 0 keeps the lower column blocks, the other one the upper ones).
-  constexpr int NDBK = (kHalves) ? C::NDB / 2 : C::NDB;
-  const int db_keep = (kHalves) ? half * NDBK : 0;
-  if constexpr (kHalves) {
+  // Output column blocks this wavefront finishes and stores: the two wavefronts of a row group exchange halves, so that both
+  // take part in the merge and in the stores (the wavefront of key half 0 keeps the lower column blocks, the other one the
+  // upper ones).
+  constexpr int NDBK = C::NDB / 2;
+  const int db_keep = half * NDBK;
+  {
     // ---- merge the two key halves through LDS.  Record per (set, row group, key half): the NDBK column blocks the
     // wavefront gives away, then its m and l; [register][lane] so that neighbouring lanes hit neighbouring banks.
     constexpr int REC = NDBK * 16 + 2;
@@ -928,43 +812,8 @@ __global__ __launch_bounds__(((row_pair(LAYOUT)) ? 8 : 2 * NRG) * 64, 1) void at
 
   // ---- epilogue
   const float l_row = acc.l + __shfl_xor(acc.l, 32, 64);
-  if constexpr (MODE == kPassInternal) {
-    if (!row_ok) return;
-    // Eq. 8-9 with the cached pair expressed through (o, m, lse): A_out e^{L_out-M} = o e^{m-M}
-    const bool has_ext = p.ext_o != nullptr;             // workgroup-uniform
-    float me2 = -INFINITY, le = 0.f;
-    if (has_ext) {
-      const float em = p.ext_m[grow], el = p.ext_lse[grow];
-      if (el != -INFINITY) {
-        me2 = em * kLog2e;
-        le = exp2f((el - em) * kLog2e);
-      }
-    }
-    const float M2 = fmaxf(me2, acc.m);
-    const float Mu = (M2 == -INFINITY) ? 0.f : M2;
-    const float we = exp2f(me2 - Mu), wi = exp2f(acc.m - Mu);
-    const float den = le * we + l_row * wi;
-    const float inv = den > 0.f ? 1.f / den : 0.f;
-    __bf16* out = (__bf16*)p.out + grow * D;
-#pragma unroll
-    for (int db = 0; db < NDBK; ++db)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int d0 = 32 * (db_keep + db) + 8 * q4 + 4 * h;
-        f32x4 e = {0.f, 0.f, 0.f, 0.f};
-        if (has_ext) e = *(const f32x4*)(p.ext_o + grow * D + d0);
-        float r[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) r[i] = (acc.o[db][4 * q4 + i] * wi + e[i] * we) * inv;
-        u32x2 pk;
-        pk.x = pack_bf16x2(r[0], r[1]);
-        pk.y = pack_bf16x2(r[2], r[3]);
-        *(u32x2*)(out + d0) = pk;
-      }
-    if (p.lse_out != nullptr && h == 0) p.lse_out[grow] = den > 0.f ? (M2 + log2f(den)) * kLn2 : -INFINITY;
-    return;
-  } else {
-    if (direct) {
+  {
+    if (p.direct) {
       // single split: this is the final partial.  Same conversion as the split combine: m is rounded when
       // converted to natural-log units, o is rescaled to the reference consumers recover from it.
       if (!(row_ok && head_active)) return;
@@ -981,16 +830,16 @@ __global__ __launch_bounds__(((row_pair(LAYOUT)) ? 8 : 2 * NRG) * 64, 1) void at
           const int d0 = 32 * (db_keep + db) + 8 * q4 + 4 * h;
           f32x4 o4 = {acc.o[db][4 * q4] * adj, acc.o[db][4 * q4 + 1] * adj, acc.o[db][4 * q4 + 2] * adj,
                       acc.o[db][4 * q4 + 3] * adj};
-          *(f32x4*)(fin_o + grow * D + d0) = o4;
+          *(f32x4*)(p.ws_o + grow * D + d0) = o4;
         }
       if (h == 0 && half == 0) {
-        fin_m[grow] = m_nat;
-        fin_l[grow] = L;
+        p.ws_m[grow] = m_nat;
+        p.ws_l[grow] = L;
       }
       return;
     }
     if (!row_ok) return;
-    const size_t wrow = ((size_t)(split * p.B + b) * slots + slot) * nrows + row;
+    const size_t wrow = ((size_t)(split * p.B + b) * p.Hkv + kvh) * nrows + row;
 #pragma unroll
     for (int i = 0; i < NSETS; ++i) {
       float* __restrict__ w_o = i ? p.ws_o2 : p.ws_o;
@@ -1016,9 +865,16 @@ __global__ __launch_bounds__(((row_pair(LAYOUT)) ? 8 : 2 * NRG) * 64, 1) void at
   }
 }
 
+template <int D, int MODE, int LAYOUT, int NRG>
+__global__ __launch_bounds__(LAYOUT == kRowPair ? RCfg<D>::THREADS : 2 * NRG * 64, 1) void attn_stream_kernel(const PassParams p) {
+  extern __shared__ __align__(16) unsigned char ring[];
+  if constexpr (LAYOUT == kRowPair) rows_pass<D, MODE>(p, ring);
+  else halves_pass<D, MODE, LAYOUT, NRG>(p, ring);
+}
+
 template <int D, int MODE, int LAYOUT, int NRG = 4>
 hipError_t launch_stream(const PassParams& p, hipStream_t s) {
-  using C = SCfg<D, LAYOUT, (MODE == kPassSparseRefresh) ? 2 : 1, NRG>;
+  using C = std::conditional_t<LAYOUT == kRowPair, RCfg<D>, SCfg<D, LAYOUT, (MODE == kPassSparseRefresh) ? 2 : 1, NRG>>;
   auto kern = attn_stream_kernel<D, MODE, LAYOUT, NRG>;
   static LdsLimit lim;
   hipError_t e = raise_lds_limit(kern, C::LDS, lim, C::LDS);
@@ -1027,7 +883,7 @@ hipError_t launch_stream(const PassParams& p, hipStream_t s) {
   const int ntile_rows = (nrows + C::ROWS - 1) / C::ROWS;
   long long nwg = (long long)p.B * p.Hkv * ntile_rows * p.nsplit;
   if (MODE == kPassDensePaged) nwg = (((long long)p.B * p.Hkv * p.nsplit + 7) / 8) * 8 * ntile_rows;
-  if (MODE == kPassDenseHeads && row_pair(LAYOUT)) nwg = (long long)p.B * (p.heads_cap * p.nsplit + p.Hkv) * ntile_rows;
+  if (MODE == kPassDenseHeads && LAYOUT == kRowPair) nwg = (long long)p.B * (p.heads_cap * p.nsplit + p.Hkv) * ntile_rows;
   if (nwg >= (1ll << 31)) return hipErrorInvalidValue;
   PassParams q = p;
   if (MODE == kPassDensePaged) q.div_page = make_fastdiv((uint32_t)p.page_size);
@@ -1085,7 +941,6 @@ hipError_t launch_stream_d(const PassParams& p, PassMode mode, hipStream_t s) {
     case kPassSparseReuse: return launch_key_split<D, kPassSparseReuse>(p, s);
     case kPassSparseRefresh: return launch_key_split<D, kPassSparseRefresh>(p, s);
     case kPassInternal:
-      if (p.rotate) return launch_stream<D, kPassInternal, kRowPairRotated>(p, s);
       return launch_stream<D, kPassInternal, kRowPair>(p, s);
     default: return hipErrorInvalidValue;
   }
