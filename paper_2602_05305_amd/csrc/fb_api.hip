@@ -622,6 +622,15 @@ fb_status fb_refresh_step_prof(const fb_shape* shape, const void* q, const void*
   char* ws = (char*)workspace;
   fb::PassParams p = base_pass(shape, q, k_prefix, v_prefix, shape->prefix_len, ns);
   p.k2 = k_block; p.v2 = v_block;
+  if (shape->dtype == FB_F32 && fb::f32_refresh_one((long long)p.B * p.Hkv * ((p.G * p.Bq + 15) / 16), shape->head_dim, shape->prefix_len, p.Bq)) {
+    // one launch, no split partials (the workspace stays unused)
+    p.nsplit = 1;
+    p.ws_o = o_part; p.ws_m = m_part; p.ws_l = lse_part;
+    p.out = out; p.lse_out = lse_out;
+    hipError_t e = timed_attn(shape, p, fb::kPassRefreshOne, stream, ev_begin, ev_attn_end);
+    if (e == hipSuccess && ev_end) e = hipEventRecord((hipEvent_t)ev_end, stream);
+    return e == hipSuccess ? FB_OK : hip_fail(e);
+  }
   {
     // prefix tiles the block phase is worth (its cold load, LDS hand-over and epilogue), capped at half a split
     const int tiles = (shape->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile;

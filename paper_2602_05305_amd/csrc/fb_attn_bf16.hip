@@ -1150,17 +1150,6 @@ hipError_t launch_one(const PassParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Whether the internal pass writes over any of its inputs: rows' bytes of storage type and of fp32.
-inline bool internal_in_place(const PassParams& p, int D) {
-  const size_t rows = (size_t)p.B * p.Hq * p.Bq, kv = (size_t)p.B * p.Hkv * p.nkeys * D * 2;
-  const struct { const void* at; size_t n; } outs[] = {{p.out, rows * D * 2}, {p.lse_out, rows * 4}},
-      ins[] = {{p.q, rows * D * 2}, {p.k, kv}, {p.v, kv}, {p.ext_o, rows * D * 4}, {p.ext_m, rows * 4}, {p.ext_lse, rows * 4}};
-  for (const auto& o : outs)
-    for (const auto& i : ins)
-      if (o.at && i.at && (uintptr_t)o.at < (uintptr_t)i.at + i.n && (uintptr_t)i.at < (uintptr_t)o.at + o.n) return true;
-  return false;
-}
-
 // Internal and fused passes (never or rarely split): row-pair workgroups when the pass is compute-bound, i.e. many
 // rows per KV head and enough 256-row workgroups to give every CU one.  (The dense external pass uses them for
 // every KV group above 128 rows, see dense_row_pairs.)
@@ -1232,7 +1221,7 @@ hipError_t launch_d(const PassParams& p, PassMode mode, hipStream_t s) {
       // 5.08 -> 4.19): beyond that the repeated K, Q and score work costs more than the barriers.  Not in place: D / 32
       // workgroups read a row's inputs, and none waits for the others before it stores.
       const long long waves = (long long)p.B * p.Hkv * ((p.G * p.Bq + 31) / 32) * (D / 32);
-      if (((p.nkeys <= 32 && waves <= 512) || (p.nkeys <= 64 && waves <= 256)) && !internal_in_place(p, D))
+      if (((p.nkeys <= 32 && waves <= 512) || (p.nkeys <= 64 && waves <= 256)) && !internal_in_place(p, D, 2))
         return launch_internal_wave<D>(p, s);
       // Few rows (an LLM-sized block): the pass is one wavefront's run-once instruction stream.
       // Spread each 32-row group over WSMAX wavefronts (columns split) and, for a block of at
@@ -1275,6 +1264,7 @@ hipError_t launch_d(const PassParams& p, PassMode mode, hipStream_t s) {
     case kPassSparseReuse:
       if (p.nsplit > 1) return launch_one<D, kPassSparseReuse, kKeyTile, 1, 2>(p, s);
       return launch_one<D, kPassSparseReuse, kKeyTile, 1, 1>(p, s);
+    case kPassRefreshOne: break;                 // fp32 only
   }
   return hipErrorInvalidValue;
 }

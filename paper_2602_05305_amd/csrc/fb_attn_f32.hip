@@ -35,20 +35,30 @@ __device__ __forceinline__ float wave_sum(float x) {
   return x;
 }
 
+// Maximum over the lanes l, l ^ 16, l ^ 32, l ^ 48, by exchanging rows of lanes in registers (a shuffle goes through the LDS).
+__device__ __forceinline__ float max_quarters(float x) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
 constexpr bool f32_per_head(int mode) {
   return mode == kPassDenseHeads || mode == kPassSparseRefresh || mode == kPassSparseReuse;
 }
 
-template <int D, int RB, int WR>
+// TG > 1: tiles side by side, one per group of 4 WR wavefronts, and a stage for every tile of the stream, kOneTiles at most
+// (one-launch refresh step at head_dim 64)
+template <int D, int RB, int WR, int TG = 1>
 struct FCfg {
-  static constexpr int NW = 4 * WR, THREADS = 64 * NW;
+  static constexpr int GW = 4 * WR, NW = GW * TG, THREADS = 64 * NW;   // wavefronts of a group, of the workgroup
   static constexpr int ROWS = 16 * RB * WR;             // query rows of a workgroup
   static constexpr int ROWB = D * 4, CPR = ROWB / 16;   // bytes and 16-byte chunks of a key row
   static constexpr int OPB = kKeyTile * ROWB, STAGE = 2 * OPB;
-  static constexpr int NLOAD = OPB / (THREADS * 16);    // direct-to-LDS loads per lane, operand and tile
+  static constexpr int NLOAD = OPB / (GW * 1024);       // direct-to-LDS loads per lane, operand and tile
   static constexpr int NQ = D / 16;                     // float4 query registers per row block
   static constexpr int NDB = D / 16, NDBK = NDB / 4;    // 16-wide output column blocks; per finishing wavefront
-  static constexpr int RING = 2 * STAGE;
+  static constexpr int RING = (TG > 1 ? kOneTiles : 2) * STAGE;
   static constexpr int MERGE = NW * RB * (NDB * 1024 + 512);
   static constexpr int LDS = RING > MERGE ? RING : MERGE;
   static_assert(LDS <= 160 * 1024 && 2 * NLOAD <= 63, "LDS size and load counter");
@@ -78,17 +88,24 @@ __device__ __forceinline__ void f32_tile(FState<RB, D / 16>& st, const f32x4 (&q
                                          const unsigned char* __restrict__ stage, const uint32_t (&kaddr)[D / 16],
                                          const uint32_t (&vaddr)[D / 16], float scale_log2, int key0, int nvalid) {
   using C = FCfg<D, RB, WR>;
-  f32x4 s[RB];
+  // two accumulator chains at least: a chain's product waits for the one before it
+  constexpr int NC = RB == 1 ? 2 : 1;
+  f32x4 s[RB], part[NC][RB];
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) s[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) part[c][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int j = 0; j < C::NQ; ++j) {
     const f32x4 a = *(const f32x4*)(stage + kaddr[j]);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb) s[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], q[rb][j][i], s[rb], 0, 0, 0);
+      for (int rb = 0; rb < RB; ++rb)
+        part[i % NC][rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], q[rb][j][i], part[i % NC][rb], 0, 0, 0);
   }
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) s[rb] = NC == 1 ? part[0][rb] : part[0][rb] + part[NC - 1][rb];
   // s[rb][r] = raw dot product of row lane%16 with key key0 + r of the tile (key0 includes the lane's 4 (lane/16))
   if (nvalid < kKeyTile) {
 #pragma unroll
@@ -100,8 +117,7 @@ __device__ __forceinline__ void f32_tile(FState<RB, D / 16>& st, const f32x4 (&q
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     float tmax = fmaxf(fmaxf(s[rb][0], s[rb][1]), fmaxf(s[rb][2], s[rb][3])) * scale_log2;
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+    tmax = max_quarters(tmax);
     const float m_new = fmaxf(st.m[rb], tmax);
     const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
     const float alpha = __builtin_amdgcn_exp2f(st.m[rb] - m_use);
@@ -131,16 +147,20 @@ __device__ __forceinline__ void f32_tile(FState<RB, D / 16>& st, const f32x4 (&q
     }
 }
 
-template <int D, int MODE, int RB, int WR>
-__global__ __launch_bounds__(256 * WR, 1) void attn_f32_kernel(const PassParams p) {
-  using C = FCfg<D, RB, WR>;
+template <int D, int MODE, int RB, int WR, int TG = 1>
+__global__ __launch_bounds__(256 * WR * TG, 1) void attn_f32_kernel(const PassParams p) {
+  using C = FCfg<D, RB, WR, TG>;
   constexpr bool kPerHead = f32_per_head(MODE);
-  constexpr int NSETS = (MODE == kPassSparseRefresh) ? 2 : 1;
+  // kPassRefreshOne, a whole refresh step in one launch: the prefix's tiles and then the block's own are one stream with two sets
+  // of statistics; the first one is written as the final partial, then the second is merged in (Eq. 8-9)
+  constexpr bool kOne = (MODE == kPassRefreshOne);
+  constexpr int NSETS = (MODE == kPassSparseRefresh || kOne) ? 2 : 1;
   constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
   extern __shared__ __align__(16) unsigned char ring[];
   const int lane = threadIdx.x & 63, l16 = lane & 15, g4 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int wk = wave & 3, wr = wave >> 2;
+  const int wk = wave & 3, wr = (wave >> 2) % WR, tg = TG == 1 ? 0 : wave / C::GW, gwave = TG == 1 ? wave : wave % C::GW;
+  static_assert(TG == 1 || MODE == kPassRefreshOne, "tile groups");
 
   // ---- workgroup -> (row tile, split, head, batch); each XCD gets a contiguous range so that row tiles and heads that
   // share K/V share an L2 (ragged paged sequences are dealt round-robin instead)
@@ -189,16 +209,18 @@ __global__ __launch_bounds__(256 * WR, 1) void attn_f32_kernel(const PassParams 
   } else {
     total = (nkeys + kKeyTile - 1) / kKeyTile;
   }
+  const int prefix_tiles = total;
+  if constexpr (kOne) total += (p.Bq + kKeyTile - 1) / kKeyTile;
   TileRange tr = {0, total};
-  if (MODE != kPassInternal && !own_block) tr = split_range(total, p.nsplit, split);
+  if (MODE != kPassInternal && !kOne && !own_block) tr = split_range(total, p.nsplit, split);
   struct Tile {
     int k0;
     bool is_sel;
     size_t off;      // bytes from Kg / Vg
   };
-  int e_next = tr.begin;
+  int e_next = tr.begin + tg;
   auto next_tile = [&](Tile& t) -> bool {
-    for (; e_next < tr.end; ++e_next) {
+    for (; e_next < tr.end; e_next += TG) {
       t.is_sel = true;
       if constexpr (MODE == kPassSparseReuse) {
         const int blk = sload(p.union_list + (size_t)bk * p.nblk, e_next / tpb);
@@ -207,6 +229,10 @@ __global__ __launch_bounds__(256 * WR, 1) void attn_f32_kernel(const PassParams 
         if (!((mask >> (unit_h - kvh * p.G)) & 1u) || t.k0 >= nkeys) continue;
       } else {
         t.k0 = e_next * kKeyTile;
+        if constexpr (kOne) {
+          t.is_sel = e_next < prefix_tiles;
+          if (!t.is_sel) t.k0 -= prefix_tiles * kKeyTile;
+        }
         if constexpr (MODE == kPassSparseRefresh) {
           const uint32_t mask = (uint32_t)sload(p.blk_mask + (size_t)bk * p.nblk, t.k0 / p.key_block);
           t.is_sel = ((mask >> (unit_h - kvh * p.G)) & 1u) != 0u;
@@ -219,34 +245,44 @@ __global__ __launch_bounds__(256 * WR, 1) void attn_f32_kernel(const PassParams 
       } else {
         t.off = (size_t)t.k0 * C::ROWB;
       }
-      ++e_next;
+      e_next += TG;
       return true;
     }
     return false;
   };
 
+  auto keys_of = [&](const Tile& t) -> int { return kOne && !t.is_sel ? p.Bq : nkeys; };
+
   // ---- direct-to-LDS load slots: operand chunk (j*NW + wave)*64 + lane lives at LDS row chunk / CPR, position chunk % CPR
   const uint32_t ring_base = (uint32_t)(uintptr_t)ring;
   auto issue = [&](const Tile& t, int stage_i) {
-    const uint32_t base = ring_base + (uint32_t)stage_i * C::STAGE + wave * 1024;
-    const int last = min(kKeyTile, nkeys - t.k0) - 1;         // rows past the end read the last key (masked below)
-#pragma unroll
-    for (int j = 0; j < C::NLOAD; ++j) {
-      const int chunk = (j * C::NW + wave) * 64 + lane, r = chunk / C::CPR, pc = chunk % C::CPR;
-      dma16(Kg + t.off, (uint32_t)(min(r, last) * C::ROWB + ((pc - C::rot_k(r)) & (C::CPR - 1)) * 16),
-            base + j * C::NW * 1024);
+    const uint32_t base = ring_base + (uint32_t)stage_i * C::STAGE + gwave * 1024;
+    const int last = min(kKeyTile, keys_of(t) - t.k0) - 1;    // rows past the end read the last key (masked below)
+    const unsigned char* kt = Kg + t.off;
+    const unsigned char* vt = Vg + t.off;
+    if constexpr (kOne) {
+      if (!t.is_sel) {
+        kt = (const unsigned char*)p.k2 + (size_t)bk * p.Bq * C::ROWB + t.off;
+        vt = (const unsigned char*)p.v2 + (size_t)bk * p.Bq * C::ROWB + t.off;
+      }
     }
 #pragma unroll
     for (int j = 0; j < C::NLOAD; ++j) {
-      const int chunk = (j * C::NW + wave) * 64 + lane, r = chunk / C::CPR, pc = chunk % C::CPR;
-      dma16(Vg + t.off, (uint32_t)(min(r, last) * C::ROWB + ((pc - C::rot_v(r)) & (C::CPR - 1)) * 16),
-            base + C::OPB + j * C::NW * 1024);
+      const int chunk = (j * C::GW + gwave) * 64 + lane, r = chunk / C::CPR, pc = chunk % C::CPR;
+      dma16(kt, (uint32_t)(min(r, last) * C::ROWB + ((pc - C::rot_k(r)) & (C::CPR - 1)) * 16),
+            base + j * C::GW * 1024);
+    }
+#pragma unroll
+    for (int j = 0; j < C::NLOAD; ++j) {
+      const int chunk = (j * C::GW + gwave) * 64 + lane, r = chunk / C::CPR, pc = chunk % C::CPR;
+      dma16(vt, (uint32_t)(min(r, last) * C::ROWB + ((pc - C::rot_v(r)) & (C::CPR - 1)) * 16),
+            base + C::OPB + j * C::GW * 1024);
     }
   };
 
   Tile t0 = {0, true, 0}, t1 = {0, true, 0}, t2 = {0, true, 0};
   bool have0 = next_tile(t0);
-  if (have0) issue(t0, 0);
+  if (have0) issue(t0, tg);
   // queries: rows past the end read the group's last row; what they compute is never stored
   const int row0 = rt * C::ROWS + wr * 16 * RB;
   f32x4 q[RB][C::NQ];
@@ -262,7 +298,7 @@ __global__ __launch_bounds__(256 * WR, 1) void attn_f32_kernel(const PassParams 
 #pragma unroll
     for (int j = 0; j < C::NQ; ++j) asm volatile("" ::"v"(q[rb][j]));
   bool have1 = have0 && next_tile(t1);
-  if (have1) issue(t1, 1);
+  if (have1) issue(t1, tg + TG);
 
   // per-lane LDS read addresses inside a stage
   uint32_t kaddr[C::NQ], vaddr[C::NDB];
@@ -279,25 +315,39 @@ __global__ __launch_bounds__(256 * WR, 1) void attn_f32_kernel(const PassParams 
 #pragma unroll
   for (int i = 0; i < NSETS; ++i) sets[i].init();
 
-  for (int t = 0; have0; ++t) {
-    if (have1) wait_vm<2 * C::NLOAD>();
-    else wait_vm<0>();
+  bool have3 = false;
+  Tile t3 = {0, true, 0};
+  if constexpr (TG > 1) {                                       // everything is requested here; no stage is used twice
+    static_assert(3 * TG >= kOneTiles, "three tiles a group");
+    have3 = have1 && next_tile(t3);
+    if (have3) issue(t3, tg + 2 * TG);
+    wait_vm<0>();
     __syncthreads();
-    unsigned char* stage = ring + (t & 1) * C::STAGE;
-    const int nvalid = min(kKeyTile, nkeys - t0.k0);
-    if (nvalid < kKeyTile) {
-      // value rows past the end: a weight of 0 must not meet an infinity or NaN of the duplicated last key
-      for (int c = nvalid * C::CPR + (int)threadIdx.x; c < kKeyTile * C::CPR; c += C::THREADS)
-        *(f32x4*)(stage + C::OPB + c * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  for (int t = 0; have0; ++t) {
+    if constexpr (TG == 1) {
+      if (have1) wait_vm<2 * C::NLOAD>();
+      else wait_vm<0>();
       __syncthreads();
+    }
+    unsigned char* stage = ring + (TG > 1 ? tg + t * TG : t & 1) * C::STAGE;
+    const int nvalid = min(kKeyTile, keys_of(t0) - t0.k0);
+    if (nvalid < kKeyTile) {
+      // value rows past the end: a weight of 0 must not meet an infinity or NaN of the duplicated last key.  A wavefront reads
+      // the rows of its own 16 keys and clears them itself.
+      for (int c = max(nvalid, 16 * wk) * C::CPR + lane; c < (16 * wk + 16) * C::CPR; c += 64)
+        *(f32x4*)(stage + C::OPB + c * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     const int key0 = 16 * wk + 4 * g4;
     if (NSETS > 1 && !t0.is_sel)
       f32_tile<D, RB, WR>(sets[NSETS - 1], q, stage, kaddr, vaddr, p.scale_log2, key0, nvalid);
     else
       f32_tile<D, RB, WR>(sets[0], q, stage, kaddr, vaddr, p.scale_log2, key0, nvalid);
-    const bool have2 = have1 && next_tile(t2);                // workgroup-uniform
-    if (have2) {
+    const bool have2 = TG > 1 ? have3 : have1 && next_tile(t2);      // workgroup-uniform (several groups: group-uniform)
+    if constexpr (TG > 1) {
+      t2 = t3;
+      have3 = false;
+    } else if (have2) {
       __syncthreads();                                        // every wavefront has left this stage
       issue(t2, t & 1);
     }
@@ -309,6 +359,8 @@ __global__ __launch_bounds__(256 * WR, 1) void attn_f32_kernel(const PassParams 
 
   // ---- the four key quarters of a row block meet in LDS: records [wavefront][row block][column block][lane], then
   // (m, l) per lane; wavefront wk finishes column blocks [wk*NDBK, +NDBK), folding the quarters in order
+  float pm[kOne ? RB : 1], pl[kOne ? RB : 1];                   // kPassRefreshOne: the prefix's statistics
+  f32x4 po[kOne ? RB : 1][C::NDBK];
 #pragma unroll
   for (int i = 0; i < NSETS; ++i) {
     __syncthreads();
@@ -324,15 +376,17 @@ __global__ __launch_bounds__(256 * WR, 1) void attn_f32_kernel(const PassParams 
       rec_ml[(wave * RB + rb) * 64 + lane] = make_float2(sets[i].m[rb], l);
     }
     __syncthreads();
+    if (TG > 1 && tg != 0) continue;                          // the first group finishes
+    constexpr int NR = 4 * TG;                                // records of a row block: key quarter by quarter, group by group
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       const int row = row0 + 16 * rb + l16;
       const bool row_ok = row < nrows;
       const size_t grow = grow_base + row;
-      float mq[4], lq[4], M = -INFINITY;
+      float mq[NR], lq[NR], M = -INFINITY;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const float2 ml = rec_ml[((wr * 4 + w) * RB + rb) * 64 + lane];
+      for (int w = 0; w < NR; ++w) {
+        const float2 ml = rec_ml[(((w / 4 * WR + wr) * 4 + w % 4) * RB + rb) * 64 + lane];
         mq[w] = ml.x;
         lq[w] = ml.y;
         M = fmaxf(M, ml.x);
@@ -343,12 +397,12 @@ __global__ __launch_bounds__(256 * WR, 1) void attn_f32_kernel(const PassParams 
 #pragma unroll
       for (int d = 0; d < C::NDBK; ++d) o[d] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
+      for (int w = 0; w < NR; ++w) {
         const float wgt = __builtin_amdgcn_exp2f(mq[w] - Mu);
         l = fmaf(lq[w], wgt, l);
 #pragma unroll
         for (int d = 0; d < C::NDBK; ++d) {
-          const f32x4 x = rec_o[(((wr * 4 + w) * RB + rb) * C::NDB + wk * C::NDBK + d) * 64 + lane];
+          const f32x4 x = rec_o[((((w / 4 * WR + wr) * 4 + w % 4) * RB + rb) * C::NDB + wk * C::NDBK + d) * 64 + lane];
 #pragma unroll
           for (int r = 0; r < 4; ++r) o[d][r] = fmaf(x[r], wgt, o[d][r]);
         }
@@ -356,10 +410,21 @@ __global__ __launch_bounds__(256 * WR, 1) void attn_f32_kernel(const PassParams 
       if (!row_ok) continue;
       const int d0 = wk * C::NDBK * 16 + 4 * g4;              // first column of o[0]; o[d] is 16 d further
       const bool writes_ml = (wk == 0 && g4 == 0);
-      if constexpr (MODE == kPassInternal) {
+      if constexpr (kOne) {
+        if (i == 0) {
+          pm[rb] = M;
+          pl[rb] = l;
+#pragma unroll
+          for (int d = 0; d < C::NDBK; ++d) po[rb][d] = o[d];
+        }
+      }
+      if (MODE == kPassInternal || (kOne && i == 1)) {
         // Eq. 8-9 with the cached pair expressed through (o, m, lse): A_out e^{L_out-M} = o e^{m-M}.
         float me2 = -INFINITY, le = 0.f;
-        if (p.ext_o != nullptr) {
+        if constexpr (kOne) {
+          me2 = pm[rb];
+          le = pl[rb];
+        } else if (p.ext_o != nullptr) {
           const float me = p.ext_m[grow], lse = p.ext_lse[grow];
           if (lse != -INFINITY) {
             me2 = me * kLog2e;
@@ -375,7 +440,7 @@ __global__ __launch_bounds__(256 * WR, 1) void attn_f32_kernel(const PassParams 
         for (int d = 0; d < C::NDBK; ++d) {
           f32x4 num = o[d] * wi;
           if (le > 0.f) {
-            const f32x4 x = *(const f32x4*)(p.ext_o + grow * D + d0 + 16 * d);
+            const f32x4 x = kOne ? po[kOne ? rb : 0][d] : *(const f32x4*)(p.ext_o + grow * D + d0 + 16 * d);
 #pragma unroll
             for (int r = 0; r < 4; ++r) num[r] = fmaf(x[r], we, num[r]);
           }
@@ -383,7 +448,7 @@ __global__ __launch_bounds__(256 * WR, 1) void attn_f32_kernel(const PassParams 
         }
         if (p.lse_out != nullptr && writes_ml) p.lse_out[grow] = den > 0.f ? (M2 + log2f(den)) * kLn2 : -INFINITY;
       } else {
-        if (p.direct) {
+        if (kOne || p.direct) {
           // single split: this is the final partial; same unit conversion as the split combine
           float m_nat = -INFINITY, L = -INFINITY, adj = 0.f;
           if (l > 0.f) {
@@ -568,6 +633,128 @@ __global__ __launch_bounds__(256) void attn_f32_few_kernel(const PassParams p) {
   }
 }
 
+// Internal pass over 17 to 64 keys, few rows: every wavefront is a workgroup of its own and finishes 16 rows x 32 output
+// columns without LDS and without a barrier (the fp32 form of internal_wave_kernel in fb_attn_bf16.hip).  What bounds it is
+// launch, one memory round trip and one wavefront's products: K and Q rows in matrix operand order and V's single elements are
+// requested at once, with the cached partial; the D / 32 wavefronts of a row block repeat its scores.  (Against 16-row workgroups of
+// 4 wavefronts that stage a tile of 64 keys in LDS: 128 rows of 8 KV heads, blocks of 32, 6.7 -> 4.8 us.)
+template <int D, int NKQ>
+__global__ __launch_bounds__(64) void internal_f32_wave_kernel(const PassParams p) {
+  constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
+  constexpr int NQ = D / 16, NW = D / 32;
+  const int lane = threadIdx.x, l16 = lane & 15, g4 = lane >> 4;
+  // one KV head's workgroups on one XCD: they share K, V and Q rows
+  const int bid = blockIdx.x, q8 = gridDim.x / 8, r8 = gridDim.x % 8, xcd = bid % 8;
+  const uint32_t w = (uint32_t)((xcd < r8 ? xcd * (q8 + 1) : r8 * (q8 + 1) + (xcd - r8) * q8) + bid / 8);
+  const int cw = (int)(w % NW);                                  // 32-column group
+  const uint32_t rg = w / NW;
+  const uint32_t bk = fastdiv(rg, p.div_rowtiles);               // batch * Hkv + KV head
+  const int rt = (int)(rg - bk * p.div_rowtiles.d);
+  const int nrows = p.G * p.Bq, nkeys = p.nkeys;
+  const int row = rt * 16 + l16;
+  const bool row_ok = row < nrows;
+  const size_t grow = (size_t)bk * nrows + min(row, nrows - 1);   // rows past the end read the last row; never stored
+  const float* __restrict__ Q = (const float*)p.q + grow * D + 4 * g4;
+  const float* __restrict__ K = (const float*)p.k + (size_t)bk * nkeys * D;
+  const float* __restrict__ V = (const float*)p.v + (size_t)bk * nkeys * D + 32 * cw;
+  f32x4 kr[NKQ][NQ], qr[NQ];
+#pragma unroll
+  for (int j = 0; j < NQ; ++j) qr[j] = *(const f32x4*)(Q + 16 * j);
+#pragma unroll
+  for (int u = 0; u < NKQ; ++u)
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) kr[u][j] = *(const f32x4*)(K + (size_t)min(16 * u + l16, nkeys - 1) * D + 16 * j + 4 * g4);
+  float vr[NKQ][4][2];                                            // key 16 u + 4 g4 + r, column 16 db + l16
+#pragma unroll
+  for (int u = 0; u < NKQ; ++u)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int db = 0; db < 2; ++db) vr[u][r][db] = V[(size_t)min(16 * u + 4 * g4 + r, nkeys - 1) * D + 16 * db + l16];
+  const bool has_ext = p.ext_o != nullptr;                        // uniform
+  f32x4 eo[2];
+  float em = -INFINITY, el = -INFINITY;
+  if (has_ext) {
+    em = p.ext_m[grow];
+    el = p.ext_lse[grow];
+#pragma unroll
+    for (int db = 0; db < 2; ++db) eo[db] = *(const f32x4*)(p.ext_o + grow * D + 32 * cw + 16 * db + 4 * g4);
+  }
+  f32x4 s[NKQ];
+#pragma unroll
+  for (int u = 0; u < NKQ; ++u) s[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < NQ; ++j)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int u = 0; u < NKQ; ++u) s[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[u][j][i], qr[j][i], s[u], 0, 0, 0);
+  float m = -INFINITY;
+#pragma unroll
+  for (int u = 0; u < NKQ; ++u)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if (16 * u + 4 * g4 + r >= nkeys) s[u][r] = -INFINITY;
+      m = fmaxf(m, s[u][r]);
+    }
+  m *= p.scale_log2;
+  m = max_quarters(m);
+  const float m_use = (m == -INFINITY) ? 0.f : m;
+  float l = 0.f;
+#pragma unroll
+  for (int u = 0; u < NKQ; ++u)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      s[u][r] = __builtin_amdgcn_exp2f(fmaf(s[u][r], p.scale_log2, -m_use));
+      l += s[u][r];
+    }
+  l += __shfl_xor(l, 16, 64);
+  l += __shfl_xor(l, 32, 64);
+  f32x4 o[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+  for (int u = 0; u < NKQ; ++u)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const bool there = 16 * u + 4 * g4 + r < nkeys;             // a weight of 0 must not meet the duplicated last key
+#pragma unroll
+      for (int db = 0; db < 2; ++db) o[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(there ? vr[u][r][db] : 0.f, s[u][r], o[db], 0, 0, 0);
+    }
+  // Eq. 8-9 with the cached pair expressed through (o, m, lse): A_out e^{L_out-M} = o e^{m-M}.
+  float me2 = -INFINITY, le = 0.f;
+  if (el != -INFINITY) {
+    me2 = em * kLog2e;
+    le = exp2f((el - em) * kLog2e);
+  }
+  const float M2 = fmaxf(me2, m);
+  const float M2u = (M2 == -INFINITY) ? 0.f : M2;
+  const float we = exp2f(me2 - M2u), wi = exp2f(m - M2u);
+  const float den = le * we + l * wi;
+  const float inv = den > 0.f ? 1.f / den : 0.f;
+  if (!row_ok) return;
+#pragma unroll
+  for (int db = 0; db < 2; ++db) {
+    f32x4 num = o[db] * wi;
+    if (le > 0.f) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) num[r] = fmaf(eo[db][r], we, num[r]);
+    }
+    *(f32x4*)((float*)p.out + grow * D + 32 * cw + 16 * db + 4 * g4) = num * inv;
+  }
+  if (p.lse_out != nullptr && g4 == 0 && cw == 0) p.lse_out[grow] = den > 0.f ? (M2 + log2f(den)) * kLn2 : -INFINITY;
+}
+
+template <int D>
+hipError_t launch_internal_f32_wave(const PassParams& p, hipStream_t s) {
+  PassParams q = p;
+  const int rowtiles = (p.G * p.Bq + 15) / 16;
+  q.div_rowtiles = make_fastdiv((uint32_t)rowtiles);
+  const dim3 grid((unsigned)((long long)p.B * p.Hkv * rowtiles * (D / 32)));
+  if (p.nkeys <= 32) hipLaunchKernelGGL((internal_f32_wave_kernel<D, 2>), grid, dim3(64), 0, s, q);
+  else if (p.nkeys <= 48) hipLaunchKernelGGL((internal_f32_wave_kernel<D, 3>), grid, dim3(64), 0, s, q);
+  else hipLaunchKernelGGL((internal_f32_wave_kernel<D, 4>), grid, dim3(64), 0, s, q);
+  return hipGetLastError();
+}
+
 template <int D, int MODE>
 hipError_t launch_f32_few(const PassParams& p, hipStream_t s) {
   PassParams q = p;
@@ -577,10 +764,10 @@ hipError_t launch_f32_few(const PassParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int D, int MODE, int RB, int WR>
+template <int D, int MODE, int RB, int WR, int TG = 1>
 hipError_t launch_f32(const PassParams& p, hipStream_t s) {
-  using C = FCfg<D, RB, WR>;
-  auto kern = attn_f32_kernel<D, MODE, RB, WR>;
+  using C = FCfg<D, RB, WR, TG>;
+  auto kern = attn_f32_kernel<D, MODE, RB, WR, TG>;
   static LdsLimit lim;
   hipError_t e = raise_lds_limit(kern, C::LDS, lim, C::LDS);
   if (e != hipSuccess) return e;
@@ -607,6 +794,15 @@ hipError_t launch_f32_rows(const PassParams& p, hipStream_t s) {
       return launch_f32_few<D, MODE>(p, s);
   }
   const int nrows = f32_per_head(MODE) ? p.Bq : p.G * p.Bq;
+  if constexpr (MODE == kPassInternal) {
+    // One wavefront per 16 rows x 32 columns while repeating the scores per column group costs less than a staged tile of 64
+    // keys.  Before -> so, us (32 / 8 heads, head_dim 128 unless noted): 32 keys, 256 wavefronts 6.7 -> 4.8, 2048 13.5 -> 10.2
+    // (head_dim 64, 2048 10.1 -> 7.0); 48 keys, 384 6.7 -> 6.0, 640 level (head_dim 64, 1536 9.2 -> 7.2); 64 keys, 256 6.5 -> 5.8,
+    // 512 6.5 -> 7.0 (head_dim 64, 512 5.2 -> 5.3).  Not in place: several workgroups read a row's queries.
+    const long long waves = (long long)p.B * p.Hkv * ((nrows + 15) / 16) * (D / 32);
+    const long long most = p.nkeys <= 32 ? 2048 : p.nkeys <= 48 ? (D == 64 ? 1536 : 512) : 256;
+    if (p.nkeys > kFewKeysF32 && p.nkeys <= 64 && waves <= most && !internal_in_place(p, D, 4)) return launch_internal_f32_wave<D>(p, s);
+  }
   int tile = f32_row_tile(nrows);
   if (MODE == kPassInternal) {
     // the internal pass has no splits to fill the chip with: 16-row workgroups until 64-row ones do (blocks of 32, 64-row
@@ -640,6 +836,7 @@ hipError_t launch_d(const PassParams& p, PassMode mode, hipStream_t s) {
     case kPassDenseHeads: return launch_f32_rows<D, kPassDenseHeads>(p, s);
     case kPassDensePaged: return launch_f32_rows<D, kPassDensePaged>(p, s);
     case kPassRefreshFused: return launch_f32_rows<D, kPassRefreshFused>(p, s);
+    case kPassRefreshOne: return launch_f32<D, kPassRefreshOne, 1, 1, D == 64 ? 2 : 1>(p, s);      // (the caller has checked f32_refresh_one)
   }
   return hipErrorInvalidValue;
 }

@@ -90,7 +90,8 @@ enum PassMode : int {
   kPassSparseReuse = 3,    // only key blocks of the per-KV-group union list; selected set only
   kPassDenseHeads = 4,     // dense, but only query heads flagged in head_on take part (others keep their cache)
   kPassDensePaged = 5,     // dense over a paged KV pool with a block table and per-sequence prefix lengths
-  kPassRefreshFused = 6    // dense over the prefix plus one extra split over the block's own keys (partial set 1)
+  kPassRefreshFused = 6,   // dense over the prefix plus one extra split over the block's own keys (partial set 1)
+  kPassRefreshOne = 7      // fp32: a whole refresh step in one kernel (prefix unsplit, final partial, then the block and the merge)
 };
 
 // One attention pass.  Rows of one KV group are addressed "group-flattened": query head
@@ -236,6 +237,29 @@ constexpr int kFewKeysF32 = 16;
 inline bool f32_few_keys(long long rows, long long group_rows, int nkeys) {
   return nkeys >= 1 && nkeys <= kFewKeysF32 && (rows <= 4096 || group_rows <= 32);
 }
+// fp32 refresh step in one launch (kPassRefreshOne): 16-row workgroups, one round of them, that run prefix and block tiles
+// themselves (head_dim 64: two tiles side by side, every tile with a stage of its own; 128: one after the other, 1.8 us each),
+// against splits, a combine and its launch.  A refresh step, us, before -> so: head_dim 64, 4 heads of 16 rows, 64 / 256 keys 7.1 ->
+// 6.1 / 8.2 -> 8.6 (9.0 where the host's two launches take longer; a block of 4 steps 23.4 -> 19.1), batch 2, 8 x 120 rows, 256 keys
+// 11.5 -> 9.0; a refresh and a reuse step, head_dim 128, 32 / 8 heads of 32 rows, 100 keys 18.6 -> 15.2, 8 x 384 rows, 128 keys
+// 18.6 -> 16.9.  One tile more: head_dim 64, 512 keys, tiles one after the other, 8.8 -> 13.8; 128, 256 keys 11.7 -> 15.
+constexpr int kOneTiles = 5;         // at head_dim 64: one LDS stage each
+inline bool f32_refresh_one(long long wgs16, int head_dim, int prefix_len, int block_len) {
+  const int tiles = (prefix_len + kKeyTile - 1) / kKeyTile + (block_len + kKeyTile - 1) / kKeyTile;
+  return head_dim == 64 ? tiles <= kOneTiles && wgs16 <= 256 : tiles <= 3 && wgs16 <= 256;
+}
+
+// Whether the internal pass writes over any of its inputs: rows' bytes of storage type and of fp32.
+inline bool internal_in_place(const PassParams& p, int D, size_t esize) {
+  const size_t rows = (size_t)p.B * p.Hq * p.Bq, kv = (size_t)p.B * p.Hkv * p.nkeys * D * esize;
+  const struct { const void* at; size_t n; } outs[] = {{p.out, rows * D * esize}, {p.lse_out, rows * 4}},
+      ins[] = {{p.q, rows * D * esize}, {p.k, kv}, {p.v, kv}, {p.ext_o, rows * D * 4}, {p.ext_m, rows * 4}, {p.ext_lse, rows * 4}};
+  for (const auto& o : outs)
+    for (const auto& i : ins)
+      if (o.at && i.at && (uintptr_t)o.at < (uintptr_t)i.at + i.n && (uintptr_t)i.at < (uintptr_t)o.at + o.n) return true;
+  return false;
+}
+
 // bf16 dense external pass: KV groups of more than 128 rows run row-pair workgroups (8 wavefronts, 256 rows, one
 // shared tile stream), so every K/V tile is staged once per 256 rows.  At head_dim 64 that measures the same as
 // 128-row workgroups (32.6 vs 33.8 us at 256 rows, 32K keys) but leaves twice the splits to fold, so there only
