@@ -252,7 +252,7 @@ __device__ __forceinline__ void tile_compute(WaveState<Cfg<D, KT>::NDB / WS>& st
 #pragma unroll
     for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, s[kb][r]);
   tmax = lane_on ? tmax * scale_log2 : -INFINITY;
-  tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+  tmax = max_halves(tmax);
   // Lazy reference update: the running reference m only moves when the tile maximum exceeds it
   // by more than kLazy (log2 units).  Weights then stay below 2^kLazy, which fp32 sums and the
   // relative precision of bf16 weights absorb, and (o, l, m) remain exactly paired; in return
@@ -795,7 +795,7 @@ __global__ __launch_bounds__(256 * NG, (VAR & 4) ? 2 : (NG > 1 || (MODE == kPass
       sel.m = M;
     }
     // ---------------------------------------------------------------- epilogue
-    const float l_sel = sel.l + __shfl_xor(sel.l, 32, 64);
+    const float l_sel = sum_halves(sel.l);
     if constexpr (MODE == kPassInternal) {
       if constexpr (!kExtEarly || kFold) load_ext();
       if (!row_ok) return;
@@ -885,7 +885,7 @@ __global__ __launch_bounds__(256 * NG, (VAR & 4) ? 2 : (NG > 1 || (MODE == kPass
         }
       }
       if constexpr (MODE == kPassSparseRefresh && !kSetSplit) {
-        const float l_res = res.l + __shfl_xor(res.l, 32, 64);
+        const float l_res = sum_halves(res.l);
         if (row_ok) {
 #pragma unroll
           for (int db = 0; db < NDBL; ++db)
@@ -987,7 +987,7 @@ __global__ __launch_bounds__(64) void internal_wave_kernel(const PassParams p) {
       m = fmaxf(m, s[kb][r]);
     }
   m *= p.scale_log2;
-  m = fmaxf(m, __shfl_xor(m, 32, 64));
+  m = max_halves(m);
   const float m_use = (m == -INFINITY) ? 0.f : m;
   float l = 0.f;
   bf16x8 pb[2 * NKB];
@@ -999,7 +999,7 @@ __global__ __launch_bounds__(64) void internal_wave_kernel(const PassParams p) {
       l += pf;
       pb[2 * kb + r / 8][r % 8] = (__bf16)pf;
     }
-  l += __shfl_xor(l, 32, 64);
+  l = sum_halves(l);
   f32x16 o;
 #pragma unroll
   for (int r = 0; r < 16; ++r) o[r] = 0.f;
@@ -1116,7 +1116,7 @@ __global__ __launch_bounds__(256) void block_mass_bf16_kernel(const MassParams p
     if (more) store_k<D, kKeyTile>(kr, stages + (cur ^ 1) * C::KBYTES, tid);
     __syncthreads();
     if ((t + 1) % tpb == 0 || !more) {                                  // the key block is complete
-      const float tot = acc + __shfl_xor(acc, 32, 64);
+      const float tot = sum_halves(acc);
       if (h == 0 && row_ok)
         p.rowmass[((size_t)b * p.nblk + t / tpb) * ((size_t)p.Hq * p.Bq) + hrow] = live ? tot : 0.f;
       acc = 0.f;

@@ -286,6 +286,17 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t off, uint32_t l
                : "memory", "m0");
 }
 
+// Maximum / sum of lanes l and l ^ 32, by exchanging the halves of the wavefront in registers (a shuffle goes through the LDS:
+// some 130 cycles in a tile's chain from scores to weights).
+__device__ __forceinline__ float max_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float sum_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // Per-head refresh: whether any query head of KV group `kvh` of batch element b is flagged.
 __device__ __forceinline__ bool group_flagged(const uint8_t* head_on, int b, int Hq, int G, int kvh) {
   uint32_t any = 0;

@@ -112,11 +112,6 @@ __device__ __forceinline__ void dma16_at(const void* base, uint32_t off, uint32_
                : "memory", "m0", "scc");
 }
 
-__device__ __forceinline__ float max_halves(float x) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
 template <int D, int MODE>
 __device__ __forceinline__ void rows_pass(const PassParams& p, unsigned char* ring) {
   using C = RCfg<D>;
@@ -548,7 +543,7 @@ __device__ __forceinline__ void rows_pass(const PassParams& p, unsigned char* ri
     const int row = row_of(g);
     const bool row_ok = row < nrows;
     const size_t grow = grow_base + row;
-    const float l_row = l[g] + __shfl_xor(l[g], 32, 64);
+    const float l_row = sum_halves(l[g]);
     if constexpr (MODE == kPassInternal) {
       if (row_ok) {
         const bool has_ext = p.ext_o != nullptr;

@@ -175,7 +175,7 @@ __device__ __forceinline__ void tile_softmax(WaveAcc<D / 32>& st, f32x16 (&s)[NK
 #pragma unroll
     for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, s[kb][r]);
   tmax = lane_on ? tmax * scale_log2 : -INFINITY;
-  tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+  tmax = max_halves(tmax);
   // Lazy reference: m moves only when the tile maximum exceeds it by more than kLazy (log2 units); weights
   // stay below 2^kLazy, (o, l, m) remain exactly paired, and the accumulators are rescaled on few tiles only.
   constexpr float kLazy = 8.f;
@@ -299,7 +299,7 @@ __device__ __forceinline__ void two_softmax_pv(WaveAcc<D / 32>& st, f32x16 (&s)[
     tmax[i] = on[i] ? tmax[i] * scale_log2 : -INFINITY;
   }
 #pragma unroll
-  for (int i = 0; i < 2; ++i) tmax[i] = fmaxf(tmax[i], __shfl_xor(tmax[i], 32, 64));
+  for (int i = 0; i < 2; ++i) tmax[i] = max_halves(tmax[i]);
   const float m_a = (tmax[0] > st.m + kLazy) ? tmax[0] : st.m;
   const float m_b = (tmax[1] > m_a + kLazy) ? tmax[1] : m_a;
   if (__any(m_b != m_a)) {
@@ -811,7 +811,7 @@ __device__ __forceinline__ void halves_pass(const PassParams& p, unsigned char* 
   }
 
   // ---- epilogue
-  const float l_row = acc.l + __shfl_xor(acc.l, 32, 64);
+  const float l_row = sum_halves(acc.l);
   {
     if (p.direct) {
       // single split: this is the final partial.  Same conversion as the split combine: m is rounded when
@@ -846,7 +846,7 @@ __device__ __forceinline__ void halves_pass(const PassParams& p, unsigned char* 
       float* __restrict__ w_m = i ? p.ws_m2 : p.ws_m;
       float* __restrict__ w_l = i ? p.ws_l2 : p.ws_l;
       const WaveAcc<C::NDB>& a = accs[i];
-      const float l_i = (i == 0) ? l_row : a.l + __shfl_xor(a.l, 32, 64);
+      const float l_i = (i == 0) ? l_row : sum_halves(a.l);
 #pragma unroll
       for (int db = 0; db < NDBK; ++db)
 #pragma unroll
