@@ -29,19 +29,9 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
-}
-
-// Maximum over the lanes l, l ^ 16, l ^ 32, l ^ 48, by exchanging rows of lanes in registers (a shuffle goes through the LDS).
-__device__ __forceinline__ float max_quarters(float x) {
-  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
+// Over the lanes l, l ^ 16, l ^ 32, l ^ 48.
+__device__ __forceinline__ float max_quarters(float x) { return max_halves(max_rows(x)); }
+__device__ __forceinline__ float sum_quarters(float x) { return sum_halves(sum_rows(x)); }
 
 constexpr bool f32_per_head(int mode) {
   return mode == kPassDenseHeads || mode == kPassSparseRefresh || mode == kPassSparseReuse;
@@ -369,8 +359,7 @@ __global__ __launch_bounds__(256 * WR * TG, 1) void attn_f32_kernel(const PassPa
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       float l = sets[i].l[rb];
-      l += __shfl_xor(l, 16, 64);
-      l += __shfl_xor(l, 32, 64);
+      l = sum_quarters(l);
 #pragma unroll
       for (int db = 0; db < C::NDB; ++db) rec_o[((wave * RB + rb) * C::NDB + db) * 64 + lane] = sets[i].o[rb][db];
       rec_ml[(wave * RB + rb) * 64 + lane] = make_float2(sets[i].m[rb], l);
@@ -579,17 +568,18 @@ __global__ __launch_bounds__(256) void attn_f32_few_kernel(const PassParams p) {
   for (int i = 0; i < NQ4; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) s = fmaf(k4[i][r], q4[i][r], s);
-  s += __shfl_xor(s, 1, 64);
-  s += __shfl_xor(s, 2, 64);
+  // the four lanes of a key (DPP quad_perm: l ^ 1, l ^ 2)
+  s += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0xb1, 0xf, 0xf, false));
+  s += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0x4e, 0xf, 0xf, false));
   if (key >= nkeys) s = -INFINITY;
   float m = s * p.scale_log2;
-#pragma unroll
-  for (int x = 4; x < 64; x <<= 1) m = fmaxf(m, __shfl_xor(m, x, 64));
+  m = fmaxf(m, turn16<4>(m));
+  m = max_quarters(fmaxf(m, turn16<8>(m)));
   const float m_use = (m == -INFINITY) ? 0.f : m;
   const float w = __builtin_amdgcn_exp2f(fmaf(s, p.scale_log2, -m_use));
   float l = w;
-#pragma unroll
-  for (int x = 4; x < 64; x <<= 1) l += __shfl_xor(l, x, 64);
+  l += turn16<4>(l);
+  l = sum_quarters(l + turn16<8>(l));
   colv o = 0.f;
 #pragma unroll
   for (int j = 0; j < kFewKeysF32; ++j)
@@ -708,8 +698,7 @@ __global__ __launch_bounds__(64) void internal_f32_wave_kernel(const PassParams 
       s[u][r] = __builtin_amdgcn_exp2f(fmaf(s[u][r], p.scale_log2, -m_use));
       l += s[u][r];
     }
-  l += __shfl_xor(l, 16, 64);
-  l += __shfl_xor(l, 32, 64);
+  l = sum_quarters(l);
   f32x4 o[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
   for (int u = 0; u < NKQ; ++u)

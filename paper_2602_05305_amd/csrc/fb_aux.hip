@@ -236,17 +236,6 @@ __device__ __forceinline__ float4 load4(const void* base, size_t i, int is_bf16)
   }
   return *(const float4*)((const float*)base + i);
 }
-__device__ __forceinline__ float wave_max_f(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
-  return x;
-}
-__device__ __forceinline__ float wave_sum_f(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
-}
-
 template <int D>
 __global__ __launch_bounds__(256) void refresh_fold_kernel(const CombineParams p) {
   constexpr int RW = kFoldRows;
@@ -394,9 +383,9 @@ __global__ __launch_bounds__(256) void refresh_fold_kernel(const CombineParams p
     }
     s2 = d * p.scale_log2;
   }
-  const float mi = wave_max_f(s2);
+  const float mi = wave_max(s2);
   const float w = (lane < p.Bq) ? fast_exp2(s2 - mi) : 0.f;
-  const float li = wave_sum_f(w);
+  const float li = wave_sum(w);
   __syncthreads();                                 // the row's folded external statistics are in LDS
   if (!has_row) return;
 
@@ -605,9 +594,8 @@ __global__ __launch_bounds__(256) void block_scores_kernel(const SelectParams p)
     float part[kScoreU];
 #pragma unroll
     for (int u = 0; u < kScoreU; ++u) part[u] = chunk_dot(a[u], q4);
-    for (int o = cpr / 2; o > 0; o >>= 1)
 #pragma unroll
-      for (int u = 0; u < kScoreU; ++u) part[u] += __shfl_xor(part[u], o, 64);
+    for (int u = 0; u < kScoreU; ++u) part[u] = sum16(cpr == 32 ? sum_rows(part[u]) : part[u]);
     float* dst = p.scores_ws + (size_t)(b * p.Hq + kvh * p.G + g) * nblk;
 #pragma unroll
     for (int u = 0; u < kScoreU; ++u) {
@@ -681,9 +669,8 @@ __global__ __launch_bounds__(256) void qbar_scores_kernel(const SelectParams p) 
     float part[kScoreU];
 #pragma unroll
     for (int u = 0; u < kScoreU; ++u) part[u] = chunk_dot(a[u], q4);
-    for (int o = cpr / 2; o > 0; o >>= 1)
 #pragma unroll
-      for (int u = 0; u < kScoreU; ++u) part[u] += __shfl_xor(part[u], o, 64);
+    for (int u = 0; u < kScoreU; ++u) part[u] = sum16(cpr == 32 ? sum_rows(part[u]) : part[u]);
     float* dst = p.scores_ws + (size_t)(b * p.Hq + kvh * G + g) * nblk;
 #pragma unroll
     for (int u = 0; u < kScoreU; ++u) {
@@ -762,9 +749,8 @@ __global__ __launch_bounds__(256) void select_topk_kernel(const SelectParams p) 
         const float4 a = *(const float4*)(kp + (size_t)r * D + 4 * c);
         part[u] = chunk_dot(a, q4);
       }
-      for (int o = cpr / 2; o > 0; o >>= 1)
 #pragma unroll
-        for (int u = 0; u < U; ++u) part[u] += __shfl_xor(part[u], o, 64);
+      for (int u = 0; u < U; ++u) part[u] = sum16(cpr == 32 ? sum_rows(part[u]) : part[u]);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int r = r0 + u * 4 * rpw + rsub;

@@ -297,6 +297,37 @@ __device__ __forceinline__ float sum_halves(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// Lane l's value combined with lane l ^ 16's.
+__device__ __forceinline__ float max_rows(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float sum_rows(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// The value of the lane N below, around the 16 lanes of a row (DPP row_ror).  Where a value repeats every 2 N lanes, that is
+// lane l ^ N's.
+template <int N>
+__device__ __forceinline__ float turn16(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + N, 0xf, 0xf, false));
+}
+// Sum / maximum over the 16 lanes of a row, over the wavefront: the order of the butterfly over lanes 32, 16, 8, 4, 2, 1.
+__device__ __forceinline__ float sum16(float x) {
+  x += turn16<8>(x);
+  x += turn16<4>(x);
+  x += turn16<2>(x);
+  return x + turn16<1>(x);
+}
+__device__ __forceinline__ float max16(float x) {
+  x = fmaxf(x, turn16<8>(x));
+  x = fmaxf(x, turn16<4>(x));
+  x = fmaxf(x, turn16<2>(x));
+  return fmaxf(x, turn16<1>(x));
+}
+__device__ __forceinline__ float wave_sum(float x) { return sum16(sum_rows(sum_halves(x))); }
+__device__ __forceinline__ float wave_max(float x) { return max16(max_rows(max_halves(x))); }
+
 // Per-head refresh: whether any query head of KV group `kvh` of batch element b is flagged.
 __device__ __forceinline__ bool group_flagged(const uint8_t* head_on, int b, int Hq, int G, int kvh) {
   uint32_t any = 0;
