@@ -36,7 +36,7 @@ __global__ __launch_bounds__(256) void read_vgpr_kernel(const u32x4* __restrict_
 
 // One 16-byte direct-to-LDS load per lane: the wavefront's 64 chunks land contiguously at lds_base.
 __device__ __forceinline__ void lds_load16(const void* gaddr, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off"
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
                :
                : "v"(gaddr), "s"(lds_base)
                : "memory", "m0");

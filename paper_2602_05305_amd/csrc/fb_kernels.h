@@ -270,7 +270,8 @@ inline bool dense_row_pairs(int nrows, int head_dim) {
 
 // ---- device helpers shared by the attention kernels -------------------------------------
 // One 16-byte direct-to-LDS load per lane: lane l's chunk lands at LDS byte lds_base + 16 l.  Global address =
-// base (wavefront-uniform) + off (per lane, unsigned 32-bit).
+// base (wavefront-uniform) + off (per lane, unsigned 32-bit).  A direct-to-LDS load needs one wait state after a scalar write of
+// M0, which nothing puts between two instructions of one asm block: hence the s_nop, here and wherever M0 is written by hand.
 __device__ __forceinline__ void dma16(const void* base, uint32_t off, uint32_t lds_base) {
   // base and lds_base are wavefront-uniform by construction; readfirstlane says so to the compiler, which
   // otherwise may hand the "s" operands over in vector registers (not encodable here)
@@ -280,7 +281,7 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t off, uint32_t l
   const uint32_t b_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
   const uint64_t bu = ((uint64_t)b_hi << 32) | (uint64_t)b_lo;
   const uint32_t lu = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_base);
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                :
                : "v"(off), "s"(bu), "s"(lu)
                : "memory", "m0");

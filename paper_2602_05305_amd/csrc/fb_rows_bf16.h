@@ -106,7 +106,7 @@ __device__ __forceinline__ void dma16_at(const void* base, uint32_t off, uint32_
   const uint32_t b_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
   const uint64_t bu = ((uint64_t)b_hi << 32) | (uint64_t)b_lo;
   const uint32_t lu = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_base);
-  asm volatile("s_add_u32 m0, %2, %3\n\tglobal_load_lds_dwordx4 %0, %1"
+  asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                :
                : "v"(off), "s"(bu), "s"(lu), "i"(AT)
                : "memory", "m0", "scc");
