@@ -573,12 +573,12 @@ __global__ __launch_bounds__(256) void attn_f32_few_kernel(const PassParams p) {
   s += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0x4e, 0xf, 0xf, false));
   if (key >= nkeys) s = -INFINITY;
   float m = s * p.scale_log2;
-  m = fmaxf(m, turn16<4>(m));
+  m = fmaxf(m, swap_quads(m));
   m = max_quarters(fmaxf(m, turn16<8>(m)));
   const float m_use = (m == -INFINITY) ? 0.f : m;
   const float w = __builtin_amdgcn_exp2f(fmaf(s, p.scale_log2, -m_use));
-  float l = w;
-  l += turn16<4>(l);
+  // in the same order on every lane: all columns of a row are divided by the same denominator
+  float l = w + swap_quads(w);
   l = sum_quarters(l + turn16<8>(l));
   colv o = 0.f;
 #pragma unroll

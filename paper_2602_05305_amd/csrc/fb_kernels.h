@@ -313,6 +313,11 @@ template <int N>
 __device__ __forceinline__ float turn16(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + N, 0xf, 0xf, false));
 }
+// Lane l ^ 4's value where the four lanes of every quad hold the same one (DPP row_half_mirror: lane 7 - l within eight lanes).  A
+// turn by 4 would not do before a turn by 8: lanes of even and of odd quads would add up in different orders.
+__device__ __forceinline__ float swap_quads(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x141, 0xf, 0xf, false));
+}
 // Sum / maximum over the 16 lanes of a row, over the wavefront: the order of the butterfly over lanes 32, 16, 8, 4, 2, 1.
 __device__ __forceinline__ float sum16(float x) {
   x += turn16<8>(x);

@@ -73,3 +73,24 @@ def test_internal_pass_without_partial_and_with_infinite_values(Bq):
     p /= p.sum(-1, keepdims=True)
     want = np.einsum("hqk,hkd->hqd", p, np.where(np.isinf(Vb[0]), 0.0, Vb[0]).astype(np.float64))
     assert np.abs(got[0, 1] - want[1]).max() <= 1e-5 and np.abs(got[0, 0, :, 64:] - want[0, :, 64:]).max() <= 1e-5
+
+
+@pytest.mark.parametrize("n,d", [(3, 64), (4, 128), (7, 64), (13, 128), (16, 64), (16, 128)])
+def test_one_denominator_per_row(n, d):
+    """At most 16 keys (one wavefront per row): every key's value row is one number repeated, so all columns of an output row are the
+    same sum over the same denominator and have to be equal bit for bit, with and without a cached partial, which is constant
+    over the columns as well."""
+    B, H, Bq = 4, 8, n
+    g = torch.Generator(device=T.DEV)
+    g.manual_seed(613 + n + d)
+    normal = lambda *s: torch.randn(s, generator=g, device=T.DEV)
+    q, k = normal(B, H, Bq, d), normal(B, H, Bq, d)
+    v, eo = (normal(B, H, Bq, 1).expand(B, H, Bq, d).contiguous() for _ in range(2))
+    em = normal(B, H, Bq)
+    shape = fb.make_shape(B, H, H, d, Bq, 64, "f32")
+    for ext in ((None, None, None), (eo, em, em + 1)):
+        out = torch.empty_like(q)
+        fb.fb_internal_merge(shape, q, k, v, *ext, out, None)
+        torch.cuda.synchronize()
+        uneven = (out != out[..., :1]).any(-1).sum().item()
+        assert uneven == 0, f"{uneven} of {B * H * Bq} rows"
