@@ -578,34 +578,42 @@ __device__ __forceinline__ void rows_pass(const PassParams& p, unsigned char* ri
           }
         if (p.lse_out != nullptr && h == 0) p.lse_out[grow] = den > 0.f ? (M2 + log2f(den)) * kLn2 : -INFINITY;
       }
-    } else {
-      if (direct ? row_active(g) : row_ok) {
-        float mo = mold[g], lo = l_row, adj = 1.f;
-        if (direct) {
-          mo = -INFINITY; lo = -INFINITY; adj = 0.f;
-          if (l_row > 0.f) {
-            mo = mold[g] * kLn2;
-            adj = exp2f(mold[g] - mo * kLog2e);
-            lo = (mold[g] + log2f(l_row)) * kLn2;
-          }
+    } else if (direct) {
+      // the final partial: natural-log units, o rescaled to the reference that consumers recover from the rounded m
+      if (row_active(g)) {
+        float mo = -INFINITY, lo = -INFINITY, adj = 0.f;
+        if (l_row > 0.f) {
+          mo = mold[g] * kLn2;
+          adj = exp2f(mold[g] - mo * kLog2e);
+          lo = (mold[g] + log2f(l_row)) * kLn2;
         }
-        const size_t wrow = direct ? grow : ((size_t)(split * p.B + b) * (kHeads ? p.heads_cap : p.Hkv) + (kHeads ? rank : kvh)) * nrows + row;
-        float* __restrict__ w_o = kHeads && direct ? p.o_final : p.ws_o;
-        float* __restrict__ w_m = kHeads && direct ? p.m_final : p.ws_m;
-        float* __restrict__ w_l = kHeads && direct ? p.l_final : p.ws_l;
+        float* __restrict__ fin_o = kHeads ? p.o_final : p.ws_o;
 #pragma unroll
         for (int db = 0; db < C::NDB; ++db)
 #pragma unroll
           for (int q4 = 0; q4 < 4; ++q4) {
-            const int d0 = 32 * db + 8 * q4 + 4 * h;
-            f32x4 o4 = {o[g][db][4 * q4] * adj, o[g][db][4 * q4 + 1] * adj, o[g][db][4 * q4 + 2] * adj, o[g][db][4 * q4 + 3] * adj};
-            if (direct) *(f32x4*)(w_o + wrow * D + d0) = o4;
-            else __builtin_nontemporal_store(o4, (f32x4*)(w_o + wrow * D + d0));
+            const f32x4 o4 = {o[g][db][4 * q4] * adj, o[g][db][4 * q4 + 1] * adj, o[g][db][4 * q4 + 2] * adj, o[g][db][4 * q4 + 3] * adj};
+            *(f32x4*)(fin_o + grow * D + 32 * db + 8 * q4 + 4 * h) = o4;
           }
         if (h == 0) {
-          w_m[wrow] = mo;
-          w_l[wrow] = lo;
+          (kHeads ? p.m_final : p.ws_m)[grow] = mo;
+          (kHeads ? p.l_final : p.ws_l)[grow] = lo;
         }
+      }
+    } else if (row_ok) {
+      // (a branch of its own down to the stores: sharing them with the final partial's costs them their non-temporal hint, and these
+      // partials, read once by the combine, then displace K and V in L2)
+      const size_t wrow = ((size_t)(split * p.B + b) * (kHeads ? p.heads_cap : p.Hkv) + (kHeads ? rank : kvh)) * nrows + row;
+#pragma unroll
+      for (int db = 0; db < C::NDB; ++db)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const f32x4 o4 = {o[g][db][4 * q4], o[g][db][4 * q4 + 1], o[g][db][4 * q4 + 2], o[g][db][4 * q4 + 3]};
+          __builtin_nontemporal_store(o4, (f32x4*)(p.ws_o + wrow * D + 32 * db + 8 * q4 + 4 * h));
+        }
+      if (h == 0) {
+        p.ws_m[wrow] = mold[g];
+        p.ws_l[wrow] = l_row;
       }
     }
   }

@@ -1,6 +1,10 @@
-"""Wait states that the compiler cannot put inside an inline-assembly block, checked in the built gfx950 code of both libraries: a
-direct-to-LDS load takes its LDS address from M0 and must not directly follow the scalar instruction that writes M0 (one wait
-state; without it the load may land at the previous load's address)."""
+"""Properties of the built gfx950 code that the sources ask for and the compiler can lose.
+
+A direct-to-LDS load takes its LDS address from M0 and must not directly follow the scalar instruction that writes M0 (one wait state,
+which the compiler cannot put inside an inline-assembly block; without it the load may land at the previous load's address).
+
+The dense streaming passes store split partials non-temporally and the final partial of an unsplit pass normally; where the two
+stores share code, they are merged and the hint is gone."""
 import os
 import re
 import shutil
@@ -47,3 +51,18 @@ def test_direct_to_lds_load_waits_for_m0(lib, tmp_path):
                 early.append(f"{func}: {before}; {text}")
     assert loads > 0
     assert not early, f"{len(early)} of {loads} loads, first: {early[0]}"
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler in this installation")
+def test_split_partials_are_stored_non_temporally(tmp_path):
+    if not os.path.exists(fb_build.LIB):
+        fb_build.build(force=True)
+    stores = {}
+    for func, text in _instructions(fb_build.LIB, tmp_path):
+        kernel = re.search(r"attn_stream_kernelILi(64|128)ELi([04])ELi\dELi\dE", func)      # modes: dense, per-head refresh
+        if kernel and text.startswith("global_store_dwordx4"):
+            n = stores.setdefault(func, [0, 0])
+            n[text.endswith(" nt")] += 1
+    assert len(stores) >= 20
+    for func, (plain, hinted) in stores.items():
+        assert plain == hinted, f"{func}: {hinted} of {plain + hinted} row stores are non-temporal"
