@@ -517,6 +517,7 @@ __device__ __forceinline__ void rows_pass(const PassParams& p, unsigned char* ri
 #pragma unroll
         for (int r = 0; r < 16; ++r) mx[g] = fmaxf(mx[g], sa[g][kb][r]);
     static_for<0, 5>(ref_step);
+    alpha[0] = alpha[1] = 1.f;         // the first reference: nothing to rescale (the branch of a moved one costs 3600 cycles)
     // the queries and K(0) have been read by everyone; K(1) and V(0) have landed
     wait_vm<3 * C::NLOAD>();
     __syncthreads();
