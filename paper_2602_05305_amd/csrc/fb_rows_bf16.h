@@ -49,6 +49,10 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
+// Shortest range of tiles.  Loads run ahead, five tiles of them before the loop, which looks out for the ragged tile from its own first
+// requests on: a range that ends with one must not come round to it before.
+constexpr int kRowsTiles = 5;
+
 template <int D>
 struct RCfg {
   static constexpr int THREADS = 256, ROWS = 256, KT = 64;
@@ -176,7 +180,7 @@ __device__ __forceinline__ void rows_pass(const PassParams& p, unsigned char* ri
     kvh = (int)(rest - (uint32_t)b * p.div_hkv.d);
   }
   const int bk = b * p.Hkv + kvh;
-  const int nkeys = p.nkeys;                                 // at least one whole tile
+  const int nkeys = p.nkeys;                                 // at least kRowsTiles tiles to a range (launch_stream sees to it)
   const int row0 = rt * C::ROWS;
   const size_t grow_base = (size_t)(b * p.Hq + kvh * p.G) * p.Bq;
   auto row_of = [&](int g) { return row0 + wave * 64 + g * 32 + l32; };

@@ -875,6 +875,10 @@ __global__ __launch_bounds__(LAYOUT == kRowPair ? RCfg<D>::THREADS : 2 * NRG * 6
 template <int D, int MODE, int LAYOUT, int NRG = 4>
 hipError_t launch_stream(const PassParams& p, hipStream_t s) {
   using C = std::conditional_t<LAYOUT == kRowPair, RCfg<D>, SCfg<D, LAYOUT, (MODE == kPassSparseRefresh) ? 2 : 1, NRG>>;
+  // row pairs: the shortest range has to hold what is loaded ahead (the routes here ask for more); per-head refresh: two splits
+  // share a range
+  if (LAYOUT == kRowPair && (p.nkeys + C::KT - 1) / C::KT < kRowsTiles * (MODE == kPassDenseHeads ? (p.nsplit + 1) / 2 : p.nsplit))
+    return hipErrorInvalidValue;
   auto kern = attn_stream_kernel<D, MODE, LAYOUT, NRG>;
   static LdsLimit lim;
   hipError_t e = raise_lds_limit(kern, C::LDS, lim, C::LDS);
