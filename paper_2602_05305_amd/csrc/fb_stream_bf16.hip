@@ -19,6 +19,9 @@
 //              At head_dim 64 two tiles per barrier.
 //   kTileSplit the same with whole tiles: half h takes every other tile, two tiles per barrier.
 //   kRowPair   256 rows, 4 wavefronts of 64 rows and whole tiles (many rows per KV head): fb_rows_bf16.h.
+//   kRowPairShort  256 rows, wavefront w owns rows [32 w, +32) and whole tiles, two tiles per barrier: dense streams too short for
+//              kRowPair, whose ends cost more (its first scores stand alone, it scores a tile past the last one, and four
+//              wavefronts store what eight do here).
 //   Per tile and wavefront: S^T = K Q^T on v_mfma_f32_32x32x16_bf16 (A = K rows from LDS, B = Q^T in
 //   registers), in-lane online softmax with a lazily moved reference, O^T += V^T P^T with the lane's own
 //   probabilities as the B operand (register layout reasoning: fb_attn_bf16.hip, which is the same).
@@ -40,7 +43,7 @@ namespace fb {
 namespace {
 
 // (kKeySplitSingle: the key split with one tile per barrier at head_dim 64 as well)
-enum StreamLayout : int { kKeySplit = 0, kTileSplit = 1, kRowPair = 2, kKeySplitSingle = 3 };
+enum StreamLayout : int { kKeySplit = 0, kTileSplit = 1, kRowPair = 2, kKeySplitSingle = 3, kRowPairShort = 4 };
 constexpr bool key_split(int layout) { return layout == kKeySplit || layout == kKeySplitSingle; }
 
 // Key split at head_dim 64: two tiles per barrier, their scores and weights computed together, because a tile's fixed cost
@@ -56,7 +59,8 @@ constexpr bool paired_halves(int D, int layout) { return D == 64 && layout == kK
 // wavefronts: the small blocks of 4- and 8-token diffusion steps, where more row groups would compute padding rows)
 template <int D, int LAYOUT, int NSETS = 1, int NRG = 4>
 struct SCfg {
-  static constexpr int NW = 2 * NRG;                  // wavefronts per workgroup
+  static constexpr bool RP = LAYOUT == kRowPairShort;
+  static constexpr int NW = RP ? 8 : 2 * NRG;         // wavefronts per workgroup
   static constexpr int THREADS = 64 * NW;
   static constexpr int KT = 64;                       // keys per tile
   static constexpr int ROWB = D * 2;                  // bytes per key row
@@ -66,14 +70,14 @@ struct SCfg {
   static constexpr int NLOAD = OPB / (THREADS * 16);  // direct-to-LDS loads per lane, operand and tile
   static constexpr int LSTEP = NW * 1024;             // LDS bytes one load of every wavefront covers
   static constexpr int LPT = 2 * NLOAD;               // loads per lane and tile
-  static constexpr int NS = (D == 128) ? 4 : LAYOUT == kKeySplitSingle ? 6 : 8;       // ring stages
+  static constexpr int NS = (D == 128) ? 4 : (RP || LAYOUT == kKeySplitSingle) ? 6 : 8;       // ring stages
   static constexpr int NKS = D / 16;                  // MFMA k-steps of the score product
   static constexpr int NDB = D / 32;                  // 32-wide output column blocks
-  static constexpr int ROWS = 32 * NRG;
+  static constexpr int ROWS = RP ? 256 : 32 * NRG;
   static constexpr int NKB = key_split(LAYOUT) ? 1 : 2;    // 32-key blocks of a tile one wavefront computes
   static constexpr int QPARTS = (ROWS + 63) / 64;             // the query rows are loaded 64 at a time, like a K operand
   static constexpr int QSTAGES = (QPARTS * OPB + STAGE - 1) / STAGE;   // ring stages they pass through at start
-  static constexpr int MERGE = NSETS * NRG * 2 * (NDB / 2 * 16 + 2) * 64 * 4;   // key-half exchange
+  static constexpr int MERGE = RP ? 0 : NSETS * NRG * 2 * (NDB / 2 * 16 + 2) * 64 * 4;   // key-half exchange
   static constexpr int RING = NS * STAGE;
   static constexpr int FIFO = RING > MERGE ? RING : MERGE;
   static constexpr int LDS = FIFO;
@@ -350,22 +354,24 @@ struct TileDesc {
   const unsigned char* vt;
 };
 
-// Two wavefronts per row group (every layout but kRowPair).
+// Every layout but kRowPair: two wavefronts per row group, or one (kRowPairShort).
 template <int D, int MODE, int LAYOUT, int NRG>
 __device__ __forceinline__ void halves_pass(const PassParams& p, unsigned char* ring) {
   constexpr int NSETS = (MODE == kPassSparseRefresh) ? 2 : 1;
   using C = SCfg<D, LAYOUT, NSETS, NRG>;
   static_assert(MODE == kPassDense || MODE == kPassDenseHeads || MODE == kPassDensePaged || MODE == kPassSparseReuse ||
                     MODE == kPassSparseRefresh, "modes of this form");
-  // Tile split and head_dim 64: two tiles per barrier (tiles t, t+1 are computed while t+2, t+3 are in flight); key split at 128:
+  constexpr bool kHalves = LAYOUT != kRowPairShort;
+  static_assert(kHalves || MODE == kPassDense, "one wavefront per row group: dense pass");
+  // Whole tiles and head_dim 64: two tiles per barrier (tiles t, t+1 are computed while t+2, t+3 are in flight); key split at 128:
   // one tile per barrier, NS - 1 in flight.
   constexpr bool kPairs = !key_split(LAYOUT) || paired_halves(D, LAYOUT);
   constexpr int AHEAD = kPairs ? C::NS - 2 : C::NS - 1;
   static_assert(!kPairs || C::NS % 2 == 0, "pairs of tiles: an even number of stages");
   const int lane = threadIdx.x & 63, l32 = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));     // wavefront-uniform (scalar)
-  const int rg = wave % NRG;                                   // 32-row group
-  const int half = wave / NRG;                                 // keys of this wavefront: half of every tile, or every other tile
+  const int rg = kHalves ? wave % NRG : wave;                  // 32-row group
+  const int half = kHalves ? wave / NRG : 0;                   // keys of this wavefront: half of every tile, or every other tile
   const int kb0 = key_split(LAYOUT) ? half : 0;              // first 32-key block of a tile
 
   // ---- workgroup -> (row tile, batch, KV head, split).  Hardware deals consecutive workgroup ids round-robin
@@ -601,13 +607,14 @@ __device__ __forceinline__ void halves_pass(const PassParams& p, unsigned char* 
         qmask[i] = d.mask;
       }
   }
-  // table words of the next tile to be issued, fetched one iteration ahead (lookups off the critical path)
+  // table words of the next tile to be issued, fetched one iteration ahead (lookups off the critical path; one wavefront per row
+  // group: no table, and computing the tile ahead only lengthens the loop)
   constexpr int NNEXT = kPairs ? 2 : 1;
   TileRaw rnext[NNEXT];
 #pragma unroll
   for (int u = 0; u < NNEXT; ++u) {
     rnext[u].e = 0; rnext[u].word = 0; rnext[u].mask = 0u;
-    if (AHEAD + u < ntiles) rnext[u] = tile_raw(AHEAD + u);
+    if (kHalves && AHEAD + u < ntiles) rnext[u] = tile_raw(AHEAD + u);
   }
 
   // per-lane LDS read addresses inside a stage
@@ -643,11 +650,11 @@ __device__ __forceinline__ void halves_pass(const PassParams& p, unsigned char* 
   // follows in this slot; the queue then holds tiles t .. t + AHEAD + u
   auto refill = [&](int t, int u) {
     if (t + AHEAD + u < ntiles) {
-      const TileDesc d = tile_desc(rnext[u]);
+      const TileDesc d = tile_desc(kHalves ? rnext[u] : tile_raw(t + AHEAD + u));
       issue_tile(t + AHEAD + u, d);
       qk0[AHEAD + u] = d.k0;
       qmask[AHEAD + u] = d.mask;
-      if (t + AHEAD + u + NNEXT < ntiles) rnext[u] = tile_raw(t + AHEAD + u + NNEXT);
+      if (kHalves && t + AHEAD + u + NNEXT < ntiles) rnext[u] = tile_raw(t + AHEAD + u + NNEXT);
     }
   };
   auto advance = [&]() {
@@ -723,7 +730,23 @@ __device__ __forceinline__ void halves_pass(const PassParams& p, unsigned char* 
     }
   };
 
-  if constexpr (LAYOUT == kTileSplit) {
+  if constexpr (!kHalves) {
+    for (int t = 0; t < ntiles; t += 2) {
+      wait_tiles<C::LPT>(min(AHEAD - 2, max(ntiles - 2 - t, 0)));   // tiles issued after tile t+1 so far
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < 2; ++u) refill(t, u);
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        if (t + u < ntiles) {
+          const unsigned char* stage = ring + ((t + u) % C::NS) * C::STAGE;
+          f32x16 s[C::NKB];
+          tile_scores<D, C::NKB>(s, qreg, stage, kaddr, kb0);
+          tile_softmax_pv<D, C::NKB>(acc, s, stage, vaddr, kb0, p.scale_log2, true, min(C::KT, nkeys - qk0[u]), h);
+        }
+      advance();
+    }
+  } else if constexpr (LAYOUT == kTileSplit) {
     for (int t = 0; t < ntiles; t += 2) {
       wait_tiles<C::LPT>(min(AHEAD - 2, max(ntiles - 2 - t, 0)));   // tiles issued after tile t+1 so far
       __syncthreads();
@@ -760,12 +783,12 @@ __device__ __forceinline__ void halves_pass(const PassParams& p, unsigned char* 
     }
   }
 
-  // Output column blocks this wavefront finishes and stores: the two wavefronts of a row group exchange halves, so that both
-  // take part in the merge and in the stores (the wavefront of key half 0 keeps the lower column blocks, the other one the
-  // upper ones).
-  constexpr int NDBK = C::NDB / 2;
+  // Output column blocks this wavefront finishes and stores: all of them, or, where two wavefronts share a row group, half: they
+  // exchange halves, so that both take part in the merge and in the stores (the wavefront of key half 0 keeps the lower column
+  // blocks, the other one the upper ones).
+  constexpr int NDBK = kHalves ? C::NDB / 2 : C::NDB;
   const int db_keep = half * NDBK;
-  {
+  if constexpr (kHalves) {
     // ---- merge the two key halves through LDS.  Record per (set, row group, key half): the NDBK column blocks the
     // wavefront gives away, then its m and l; [register][lane] so that neighbouring lanes hit neighbouring banks.
     constexpr int REC = NDBK * 16 + 2;
@@ -866,7 +889,7 @@ __device__ __forceinline__ void halves_pass(const PassParams& p, unsigned char* 
 }
 
 template <int D, int MODE, int LAYOUT, int NRG>
-__global__ __launch_bounds__(LAYOUT == kRowPair ? RCfg<D>::THREADS : 2 * NRG * 64, 1) void attn_stream_kernel(const PassParams p) {
+__global__ __launch_bounds__(LAYOUT == kRowPair ? RCfg<D>::THREADS : LAYOUT == kRowPairShort ? 512 : 2 * NRG * 64, 1) void attn_stream_kernel(const PassParams p) {
   extern __shared__ __align__(16) unsigned char ring[];
   if constexpr (LAYOUT == kRowPair) rows_pass<D, MODE>(p, ring);
   else halves_pass<D, MODE, LAYOUT, NRG>(p, ring);
@@ -924,12 +947,22 @@ hipError_t launch_key_split(const PassParams& p, hipStream_t s) {
   return launch_stream<D, MODE, kKeySplit, 4>(p, s);
 }
 
+// Dense row pairs: 32 rows per wavefront (kRowPairShort) below 14 tiles per split, 64 (kRowPair) from there on.  External pass, us, 32 against
+// 64 rows per wavefront, a ragged last tile: 8 / 64 heads of 32 rows, one split, 8 / 10 / 12 / 14 / 16 / 32 tiles 19.2 / 22.1 / 25.0 / 28.0 /
+// 30.9 / 54.1 and 21.0 / 23.3 / 25.3 / 28.2 / 30.1 / 49.5; 16 splits, 8 / 12 / 14 / 24 tiles 26.3 / 32.8 / 35.7 / 50.7 and 27.7 / 32.6 / 35.3 / 47.2;
+// batch 16 in 2 splits, all CUs, 8 / 16 tiles 32.9 / 47.7 and 32.5 / 45.1; head_dim 64, 8 heads of 1500 rows, 8 / 12 / 16 / 32 tiles 14.7 / 19.3 /
+// 23.8 / 41.5 and 15.8 / 19.7 / 23.5 / 39.2.
+constexpr int kShortRowTiles = 14;
+inline bool short_row_pairs(const PassParams& p) {
+  return (p.nkeys + kKeyTile - 1) / kKeyTile < kShortRowTiles * p.nsplit;
+}
+
 template <int D>
 hipError_t launch_stream_d(const PassParams& p, PassMode mode, hipStream_t s) {
   const int nrows = p.G * p.Bq;
   switch (mode) {
     case kPassDense:
-      if (dense_row_pairs(nrows, D)) return launch_stream<D, kPassDense, kRowPair>(p, s);
+      if (dense_row_pairs(nrows, D)) return short_row_pairs(p) ? launch_stream<D, kPassDense, kRowPairShort>(p, s) : launch_stream<D, kPassDense, kRowPair>(p, s);
       if (p.whole_tiles) {
         if (nrows <= 32) return launch_stream<D, kPassDense, kTileSplit, 1>(p, s);
         if (nrows <= 64) return launch_stream<D, kPassDense, kTileSplit, 2>(p, s);
@@ -980,7 +1013,8 @@ bool stream_bf16_covers(const PassParams& p, int D, PassMode mode) {
 int stream_bf16_name(const PassParams& p, int D, PassMode mode, char* buf, size_t n) {
   const bool rp = (mode == kPassDense && dense_row_pairs(p.G * p.Bq, D)) || mode == kPassInternal;
   const int nrows = p.G * p.Bq;
-  return snprintf(buf, n, "attn_stream_kernel<%d, %d, %d, %d>", D, (int)mode, rp ? (int)kRowPair : (int)kKeySplit,
+  return snprintf(buf, n, "attn_stream_kernel<%d, %d, %d, %d>", D, (int)mode,
+                  !rp ? (int)kKeySplit : mode == kPassDense && short_row_pairs(p) ? (int)kRowPairShort : (int)kRowPair,
                   (rp || nrows > 64) ? 4 : nrows > 32 ? 2 : 1);
 }
 

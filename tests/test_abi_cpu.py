@@ -348,3 +348,13 @@ def test_external_kernel_name_follows_the_launch_rules():
     assert name(1, 4, 4, 64, 16, 256, "f32") == "attn_f32_kernel<64, 0>"
     bad = fb.make_shape(1, 4, 3, 64, 16, 256, "f32")
     assert fb.fb_external_kernel_name(bad) == ""
+
+
+@pytest.mark.parametrize("kw,layout", [
+    (dict(prefix_len=13 * 64), 4), (dict(prefix_len=13 * 64 + 1), 2),        # one split: 13 and 14 tiles
+    (dict(prefix_len=27 * 64), 4),                                           # three splits of 9
+    (dict(head_dim=64, block_len=200, prefix_len=13 * 64), 4), (dict(head_dim=64, block_len=200, prefix_len=40000), 2),
+])
+def test_dense_row_pairs_by_tiles_per_split(kw, layout):
+    shape = _ok_shape(**dict(dict(n_q_heads=64, n_kv_heads=8, head_dim=128, block_len=32, dtype="bf16"), **kw))
+    assert fb.fb_external_kernel_name(shape) == f"attn_stream_kernel<{shape.head_dim}, 0, {layout}, 4>"

@@ -1,8 +1,8 @@
-"""Row-pair layout of the streaming kernel (256 rows, 64 per wavefront, four written-out tiles a trip, operands and loads of the
-next tiles requested inside the present one): where its tile walk can go wrong.  Streams of 8 tiles to a few more than two trips,
-ending with a whole tile, with one key, with one key missing; every remainder modulo the trip; the ragged tile first,
-in the middle and last in the rotated order (several KV heads and splits rotate differently); row counts around a wavefront's 64
-and a workgroup's 256.  Scores spread over many log2 units with planted outliers, so that the reference moves in mid-stream.
+"""Row-pair layouts of the streaming kernel: 32 rows per wavefront and two tiles a trip for streams of 8 to 13 tiles, 64 rows and four
+written-out tiles a trip, operands and loads of the next tiles requested inside the present one, from 14 on.  Where their tile
+walks can go wrong: streams ending with a whole tile, with one key, with one key missing; every remainder modulo the trip; the
+ragged tile first, in the middle and last in the rotated order (several KV heads and splits rotate differently); row counts
+around a wavefront's 64 and a workgroup's 256.  Scores spread over many log2 units with planted outliers, so that the reference moves in mid-stream.
 Against the numpy float64 oracle, tolerances of bf16 storage (fb_testlib)."""
 import numpy as np
 import pytest
@@ -35,3 +35,19 @@ def test_external_partial(Hq, Hkv, d, P, Bq, n_splits):
     assert orc.scores(steps[0][0], Kp, 0.7).std() / np.log(2.0) >= 5.0
     T.check_partial(gpu[0]["ext"], ora[0]["ext"], "bf16", w.name + " ext")
     T.assert_close(gpu[0]["out"], ora[0]["out"], "bf16", w.name + " out")
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,P,Bq,n_splits", [
+    (4, 2, 128, 832, 65, 1),          # 13 whole tiles: the longest of the short layout
+    (4, 2, 128, 896, 65, 1),          # 14 whole tiles; 130 rows: two of the third wavefront
+    (4, 2, 128, 897, 96, 1),          # 15 tiles, one key in the last; 192 rows: three whole wavefronts
+    (6, 3, 128, 1023, 97, 1),         # 16 tiles, one key missing
+    (5, 5, 128, 1084, 257, 1),        # 17 tiles; one row in the second row tile
+    (3, 3, 128, 1800, 256, 2),        # splits of 15 and 14 tiles
+    (8, 8, 128, 1217, 129, 1),        # 20 tiles, eight rotations
+    (20, 20, 128, 961, 130, 1),       # 16 tiles, every rotation
+    (2, 2, 64, 1027, 1025, 1),        # head_dim 64: 17 tiles, one row in the fifth row tile
+    (2, 1, 64, 1919, 600, 2),         # two splits of 15 tiles
+])
+def test_external_partial_around_14_tiles(Hq, Hkv, d, P, Bq, n_splits):
+    test_external_partial(Hq, Hkv, d, P, Bq, n_splits)
