@@ -605,7 +605,7 @@ fb_status fb_refresh_step_prof(const fb_shape* shape, const void* q, const void*
     const fb::PassParams d = base_pass(shape, q, k_prefix, v_prefix, shape->prefix_len, 1);
     fb::PassParams in = base_pass(shape, q, k_block, v_block, shape->block_len, 1);
     if (fb::dense_row_pairs(d.G * d.Bq, shape->head_dim) && fb::stream_bf16_covers(d, shape->head_dim, fb::kPassDense) &&
-        fb::stream_bf16_covers(in, shape->head_dim, fb::kPassInternal)) {
+        fb::internal_many_rows(in) && shape->block_len > 7 * fb::kKeyTile) {
       st = external_partial_impl(shape, q, k_prefix, v_prefix, nullptr, nullptr, false, 0, o_part, m_part, lse_part, 1, workspace,
                                  workspace_bytes, ev_begin, ev_attn_end, nullptr, hip_stream);
       if (st != FB_OK) return st;

@@ -268,6 +268,12 @@ inline bool dense_row_pairs(int nrows, int head_dim) {
   return nrows >= 1024 || (head_dim >= 128 && nrows > kRowsPerWgBf16);
 }
 
+// Compute-bound internal pass: many rows per KV head, a 256-row workgroup for (almost) every CU.
+inline bool internal_many_rows(const PassParams& p) {
+  const int nrows = p.G * p.Bq;
+  return nrows >= 1024 && (long long)p.B * p.Hkv * ((nrows + 255) / 256) >= 128;
+}
+
 // ---- device helpers shared by the attention kernels -------------------------------------
 // One 16-byte direct-to-LDS load per lane: lane l's chunk lands at LDS byte lds_base + 16 l.  Global address =
 // base (wavefront-uniform) + off (per lane, unsigned 32-bit).  A direct-to-LDS load needs one wait state after a scalar write of

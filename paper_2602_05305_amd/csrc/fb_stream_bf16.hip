@@ -1000,11 +1000,12 @@ bool stream_bf16_covers(const PassParams& p, int D, PassMode mode) {
     case kPassSparseReuse:
     case kPassSparseRefresh:
       return nrows <= 128 && tiles >= 8 * p.nsplit;
-    case kPassInternal: {
-      // compute-bound internal pass: many rows per KV head and a 256-row workgroup for (almost) every CU
-      const long long wgs = (long long)p.B * p.Hkv * ((nrows + 255) / 256);
-      return nrows >= 1024 && wgs >= 128 && tiles >= 8;
-    }
+    case kPassInternal:
+      // From 16 tiles on: shorter streams of several rounds of workgroups are the register-staged kernel's, whose start and end cost
+      // less (us, there and here: 128 KV heads of 2048 rows, blocks of 512 / 520 / 704 / 900 / 1100 / 1280 117 / 143 / 202 / 322 /
+      // 423 / 520 and 134 / 163 / 219 / 330 / 427 / 513; head_dim 64, two rows a key, 512 / 704 / 1100 / 1280 36.4 / 61.5 / 140 /
+      // 158 and 39.9 / 65.1 / 141 / 155; one round, 32 heads of 1024 / 1536 rows 40.7 / 53.7 and 38.9 / 52.0).
+      return internal_many_rows(p) && tiles >= 16;
     default: return false;
   }
 }

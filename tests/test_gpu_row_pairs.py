@@ -202,3 +202,12 @@ def test_hint_on_a_short_stream(Hq, Hkv, d, P, Bq, mask):
                                      part.lse, torch.empty(size, device=T.DEV, dtype=torch.uint8), hint)
         torch.cuda.synchronize()
         T.check_partial({k: v[:, on, ::17] for k, v in part.numpy().items()}, want, "bf16", f"{w.name} {size}")
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,P,Bq", [
+    (36, 18, 128, 600, 960),              # a block of 15 whole tiles: register-staged internal pass
+    (32, 16, 128, 900, 961),              # 16 tiles, one key in the last: the streaming kernel, its prefix pass as well (15 tiles)
+    (32, 16, 64, 600, 1024),
+])
+def test_internal_pass_around_16_tiles(Hq, Hkv, d, P, Bq):
+    test_refresh_step_without_splits_is_two_row_pair_passes(Hq, Hkv, d, P, Bq)
