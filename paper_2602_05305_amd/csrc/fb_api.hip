@@ -224,6 +224,7 @@ HeadsPlan heads_plan(const fb_shape* s, int active_heads, int ns) {
   // heads, 141 tiles: 310 -> 297; 8 of 10 heads of 3111 rows, 94 tiles: 191 -> 201)
   const long long wgs = (long long)s->batch * std::min(active_heads, s->n_kv_heads) * ((nrows + fb::kRowsPerWgBf16 - 1) / fb::kRowsPerWgBf16);
   if (tiles < 48 * ns || (ns == 1 && wgs >= 128 && tiles < 128) || 2 * ns > FB_MAX_SPLITS) return h;
+  if (nrows * s->head_dim * 2 >= (1ll << 32)) return h;      // 32-bit query offsets between the heads of a group
   h.ns = 2 * ns;
   h.cap = std::min(active_heads, s->n_kv_heads);
   const size_t n = (size_t)h.ns * s->batch * h.cap * nrows;

@@ -146,7 +146,8 @@ struct PassParams {
   FastDiv div_rowtiles, div_nsplit, div_hkv;   // bf16 pass: decomposition of the linear workgroup index
   FastDiv div_page;                            // bf16 paged pass: key index -> page slot
   FastDiv div_bias;                            // streaming bf16 pass, xcd_bias: by 64 * nsplit
-  FastDiv div_tpb;                             // streaming sparse passes: tile index -> key block (tiles per key block)
+  FastDiv div_tpb;                             // streaming sparse passes: tile index -> key block (tiles per key block); per-head
+                                               // refresh by rank: row -> head (block_len)
 };
 
 // Fold split partials (and optionally a cached residual) into final (o, m, lse) partials.

@@ -183,20 +183,30 @@ __device__ __forceinline__ void rows_pass(const PassParams& p, unsigned char* ri
   const int nkeys = p.nkeys;                                 // at least kRowsTiles tiles to a range (launch_stream sees to it)
   const int row0 = rt * C::ROWS;
   const size_t grow_base = (size_t)(b * p.Hq + kvh * p.G) * p.Bq;
-  auto row_of = [&](int g) { return row0 + wave * 64 + g * 32 + l32; };
-  auto row_active = [&](int g) {                             // per-head refresh: rows of other heads are computed along, not stored
-    const int row = row_of(g);
-    return row < nrows && (!kHeads || p.head_on[b * p.Hq + kvh * p.G + row / p.Bq] != 0);
-  };
+  // Per-head refresh: row tiles are cut from the rows of the group's flagged heads, one head after the other; workgroups past the last
+  // one leave, and wavefronts past it only load.  (Cut from all rows, a tile computed those of other heads along: 1 of 4 heads of
+  // 64 rows flagged in each of 8 KV groups, batch 2, 40000 keys, 99.5 us, where wavefronts of 32 rows that skip theirs take 82.3;
+  // so 73.5.  Every other of 8 heads of 373 rows, 4 KV groups, batch 3, 6877 keys 171, 149, 117.5.)
+  int nflagged = nrows, head_of = 0;                         // rows of flagged heads; lane k: the k-th flagged head of the group
+  bool gaps = false;
   if constexpr (kHeads) {
-    // (not __syncthreads_or, which has LDS of its own: the ring takes all there is)
-    const bool any = __any(row_active(0) || row_active(1));
-    if (lane == 0) ((int*)ring)[wave] = any ? 1 : 0;
-    __syncthreads();
-    const int4 on = *(const int4*)ring;
-    if ((on.x | on.y | on.z | on.w) == 0) return;
-    __syncthreads();                                         // before the first load into the ring
+    const unsigned long long on = __ballot(lane < p.G && p.head_on[b * p.Hq + kvh * p.G + min(lane, p.G - 1)] != 0);
+    int k = 0;
+    for (int g = 0; g < p.G; ++g)
+      if ((on >> g) & 1) {
+        head_of = lane == k ? g : head_of;
+        ++k;
+      }
+    nflagged = k * p.Bq;
+    gaps = k < p.G;
+    if (row0 >= nflagged) return;                            // workgroup-uniform
   }
+  // the r-th of the rows that are computed, r < nflagged, as a row of the group (every lane takes part)
+  auto group_row = [&](int r) __attribute__((always_inline)) {
+    if (!kHeads || !gaps) return r;
+    const int k = (int)fastdiv((uint32_t)r, p.div_tpb);      // (divisor here: block_len)
+    return r + (__shfl(head_of, k, 64) - k) * p.Bq;
+  };
 
   const unsigned char* __restrict__ Kg = (const unsigned char*)p.k + (size_t)bk * nkeys * C::ROWB;
   const unsigned char* __restrict__ Vg = (const unsigned char*)p.v + (size_t)bk * nkeys * C::ROWB;
@@ -294,13 +304,15 @@ __device__ __forceinline__ void rows_pass(const PassParams& p, unsigned char* ri
 
   // prologue
   {
-    const unsigned char* qg = (const unsigned char*)p.q + (grow_base + row0) * C::ROWB;
-    const int qvalid = nrows - row0;
+    const int at = kHeads ? __builtin_amdgcn_readfirstlane(group_row(row0)) : row0;
+    const unsigned char* qg = (const unsigned char*)p.q + (grow_base + at) * C::ROWB;
+    const int qvalid = nflagged - row0;
 #pragma unroll
     for (int part = 0; part < 4; ++part)
 #pragma unroll
       for (int j = 0; j < C::NLOAD; ++j) {
-        const int r = min(64 * part + ld_row[j], qvalid - 1);
+        int r = min(64 * part + ld_row[j], qvalid - 1);
+        if constexpr (kHeads) r = group_row(row0 + r) - at;
         dma16(qg, (uint32_t)(r * C::ROWB + ck[j] * 16), ring_base + C::QOFF + part * C::OPB + wave * 1024 + j * 4096);
       }
   }
@@ -311,6 +323,31 @@ __device__ __forceinline__ void rows_pass(const PassParams& p, unsigned char* ri
     wait_vm<0>();
   }
   __syncthreads();
+  if constexpr (kHeads) {
+    if (row0 + wave * 64 >= nflagged) {
+      // no rows for this wavefront: its share of the loads, at the barriers of the loop below, and nothing else
+      if (ntiles > 0) {
+        wait_vm<3 * C::NLOAD>();
+        __syncthreads();
+        issue_v(Int<2>{});
+        issue_k(Int<4>{});
+        for (int t = 0; t < ntiles; ++t) {
+          wait_vm<3 * C::NLOAD>();
+          __syncthreads();
+          step_stream(vst);
+          aim(off_v, cv, t + 3 == t_ragged);
+#pragma unroll
+          for (int j = 0; j < C::NLOAD; ++j) dma16(vst.src, off_v[j], dst_base + VOFF + (t + 3) % C::NS * C::OPB + j * 4096);
+          step_stream(kst);
+          aim(off_k, ck, t + 5 == t_ragged);
+#pragma unroll
+          for (int j = 0; j < C::NLOAD; ++j) dma16(kst.src, off_k[j], dst_base + (t + 5) % C::NS * C::OPB + j * 4096);
+        }
+      }
+      wait_vm<0>();
+      return;
+    }
+  }
   bf16x8 qreg[2][C::NKS];
 #pragma unroll
   for (int g = 0; g < 2; ++g) {
@@ -545,8 +582,9 @@ __device__ __forceinline__ void rows_pass(const PassParams& p, unsigned char* ri
   settle_o<C::NDB>(o);
 #pragma unroll
   for (int g = 0; g < 2; ++g) {
-    const int row = row_of(g);
-    const bool row_ok = row < nrows;
+    const int r = row0 + wave * 64 + g * 32 + l32;
+    const bool row_ok = r < nflagged;                        // the others repeat the last one
+    const int row = kHeads ? group_row(min(r, nflagged - 1)) : r;
     const size_t grow = grow_base + row;
     const float l_row = sum_halves(l[g]);
     if constexpr (MODE == kPassInternal) {
@@ -585,7 +623,7 @@ __device__ __forceinline__ void rows_pass(const PassParams& p, unsigned char* ri
       }
     } else if (direct) {
       // the final partial: natural-log units, o rescaled to the reference that consumers recover from the rounded m
-      if (row_active(g)) {
+      if (row_ok) {
         float mo = -INFINITY, lo = -INFINITY, adj = 0.f;
         if (l_row > 0.f) {
           mo = mold[g] * kLn2;

@@ -914,7 +914,7 @@ hipError_t launch_stream(const PassParams& p, hipStream_t s) {
   if (nwg >= (1ll << 31)) return hipErrorInvalidValue;
   PassParams q = p;
   if (MODE == kPassDensePaged) q.div_page = make_fastdiv((uint32_t)p.page_size);
-  q.div_tpb = make_fastdiv((uint32_t)(p.key_block > 0 ? p.key_block / kKeyTile : 1));
+  q.div_tpb = make_fastdiv((uint32_t)((MODE == kPassDenseHeads && LAYOUT == kRowPair) ? p.Bq : p.key_block > 0 ? p.key_block / kKeyTile : 1));
   {
     // long streams only: below 64 tiles per split a 1/64 bias rounds away
     const int tiles = (p.nkeys + kKeyTile - 1) / kKeyTile;

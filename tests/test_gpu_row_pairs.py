@@ -211,3 +211,34 @@ def test_hint_on_a_short_stream(Hq, Hkv, d, P, Bq, mask):
 ])
 def test_internal_pass_around_16_tiles(Hq, Hkv, d, P, Bq):
     test_refresh_step_without_splits_is_two_row_pair_passes(Hq, Hkv, d, P, Bq)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,P,Bq,masks,hint,step", [
+    # 260 rows of 4 heads: the flagged ones' fill one row tile, a part of it, two (all four heads)
+    (32, 8, 128, 36000, 65, ["0000", "1000", "0001", "0101", "1111", "0010", "1101", "0000"], 8, 7),
+    # 320 rows of 8 heads: every other head; all but one (280 rows: 24 in the second tile); the last head alone
+    (32, 4, 128, 74000, 40, ["00000000", "01010101", "11111011", "00000001"], 4, 7),
+    (16, 2, 64, 49000, 140, ["00000000", "10010110"], 2, 31),
+    (16, 4, 128, 19000, 700, ["0000", "0101", "1000", "0110"], 2, 61),      # hint too low: the third flagged group unsplit, with gaps
+])
+def test_head_wise_refresh_by_rank_with_gaps(Hq, Hkv, d, P, Bq, masks, hint, step):
+    """Several query heads per KV head, some of them flagged: row tiles are cut from the flagged heads' rows.  Every step-th row is
+    compared; no row of another head is written, in the workspace either."""
+    w = _wl(1, Hq, Hkv, d, P, Bq)
+    Kp, Vp = wl.make_prefix(w, 419)
+    (Q, _, _), _ = wl.make_block_steps(w, 419)
+    on = np.array([[int(c) for c in "".join(masks)]], dtype=bool)
+    shape, part, G = T.shape_of(w), T.Partial(w), Hq // Hkv
+    part.o.fill_(7), part.m.fill_(8), part.lse.fill_(9)
+    n = fb.fb_workspace_bytes(shape, 0, 0, fb.fb_external_heads_splits(shape, hint))
+    ws = torch.full((n,), 0xA5, device=T.DEV, dtype=torch.uint8)
+    fb.fb_external_partial_heads(shape, T.to_dev(Q, "bf16"), T.to_dev(Kp, "bf16"), T.to_dev(Vp, "bf16"),
+                                 torch.from_numpy(on.astype(np.uint8)).to(T.DEV), part.o, part.m, part.lse, ws, hint)
+    torch.cuda.synchronize()
+    # the first flagged group's partials of the first split stand at the beginning of the workspace, by row of the group
+    rank0 = (ws[:G * Bq * d * 4].view(G, Bq * d * 4) != 0xA5).any(1).cpu().numpy()
+    first = next(m for m in masks if "1" in m)
+    assert rank0.tolist() == [c == "1" for c in first]
+    got, want = {k: v[:, :, ::step] for k, v in part.numpy().items()}, orc.partial(Q[:, :, ::step], Kp, Vp)
+    T.check_partial({k: v[on] for k, v in got.items()}, {k: v[on] for k, v in want.items()}, "bf16", w.name)
+    assert (got["o"][~on] == 7).all() and (got["m"][~on] == 8).all() and (got["lse"][~on] == 9).all()
