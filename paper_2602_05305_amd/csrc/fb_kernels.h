@@ -239,15 +239,21 @@ inline bool f32_few_keys(long long rows, long long group_rows, int nkeys) {
   return nkeys >= 1 && nkeys <= kFewKeysF32 && (rows <= 4096 || group_rows <= 32);
 }
 // fp32 refresh step in one launch (kPassRefreshOne): 16-row workgroups, one round of them, that run prefix and block tiles
-// themselves (head_dim 64: two tiles side by side, every tile with a stage of its own; 128: one after the other, 1.8 us each),
-// against splits, a combine and its launch.  A refresh step, us, before -> so: head_dim 64, 4 heads of 16 rows, 64 / 256 keys 7.1 ->
-// 6.1 / 8.2 -> 8.6 (9.0 where the host's two launches take longer; a block of 4 steps 23.4 -> 19.1), batch 2, 8 x 120 rows, 256 keys
-// 11.5 -> 9.0; a refresh and a reuse step, head_dim 128, 32 / 8 heads of 32 rows, 100 keys 18.6 -> 15.2, 8 x 384 rows, 128 keys
-// 18.6 -> 16.9.  One tile more: head_dim 64, 512 keys, tiles one after the other, 8.8 -> 13.8; 128, 256 keys 11.7 -> 15.
+// themselves (head_dim 64: two tiles side by side, every tile with a stage of its own; 128: one after the other), against splits, a
+// combine and its launch.  What it saves everybody is that launch's host time; what it costs or saves on the device depends on the
+// tiles (all of the prefix and the block) and on the workgroups, of which the splits need several rounds where they are many.
+// A refresh step replayed from a graph, us, splits -> one launch:
+//   head_dim 64, 16 workgroups: 2 tiles 7.3 -> 6.6, 3 8.3 -> 7.4, 4 8.2 -> 8.2, 5 8.1 -> 9.0; 64: 5 8.8 -> 9.2; 80: 5 11.1 -> 9.2;
+//     256: 2 9.9 -> 7.0, 5 15.4 -> 9.5
+//   head_dim 128, 8 workgroups: 2 tiles 9.1 -> 9.3, 3 10.7 -> 11.4; 96: 3 11.5 -> 11.7; 112: 3 11.7 -> 11.5; 144: 3 15.9 -> 11.8
+// and issued call by call with a reuse step behind it: head_dim 64, 2 to 64 workgroups, 3 / 5 tiles 11-14 -> 10 / 12.6-14.5 -> 10.9-12;
+// head_dim 128, 2 / 3 tiles 14.3 -> 12 / 14.2-14.8 -> 14.2-14.9.  So the fifth tile of head_dim 64 trades up to 1 us on the device for
+// 2 us of host time at up to 64 workgroups, and the third of 128 is taken only where the device gains.  One tile more: head_dim 64,
+// 512 keys, 8.8 -> 13.8; 128, 256 keys 11.7 -> 15.
 constexpr int kOneTiles = 5;         // at head_dim 64: one LDS stage each
 inline bool f32_refresh_one(long long wgs16, int head_dim, int prefix_len, int block_len) {
   const int tiles = (prefix_len + kKeyTile - 1) / kKeyTile + (block_len + kKeyTile - 1) / kKeyTile;
-  return head_dim == 64 ? tiles <= kOneTiles && wgs16 <= 256 : tiles <= 3 && wgs16 <= 256;
+  return wgs16 <= 256 && tiles <= (head_dim == 64 ? kOneTiles : wgs16 > 100 ? 3 : 2);
 }
 
 // Whether the internal pass writes over any of its inputs: rows' bytes of storage type and of fp32.

@@ -29,7 +29,7 @@ def _wl(B, Hq, Hkv, d, P, Bq):
     (1, 4, 4, 64, 0, 16),         # empty prefix: nothing but the block
     (1, 4, 4, 64, 256, 16),       # 4 + 1 tiles, the most at head_dim 64
     (1, 4, 4, 64, 257, 16),       # one more: splits
-    (1, 2, 2, 128, 128, 20),      # 2 + 1 tiles, the most at head_dim 128
+    (1, 2, 2, 128, 128, 20),      # 2 + 1 tiles
     (1, 2, 2, 128, 1, 70),        # a prefix of one key, a block of two tiles
 ])
 def test_block(B, Hq, Hkv, d, P, Bq):
@@ -94,3 +94,29 @@ def test_one_denominator_per_row(n, d):
         torch.cuda.synchronize()
         uneven = (out != out[..., :1]).any(-1).sum().item()
         assert uneven == 0, f"{uneven} of {B * H * Bq} rows"
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,P,Bq,one", [
+    (1, 2, 2, 128, 64, 20, True),         # 2 tiles
+    (1, 2, 2, 128, 128, 20, False),       # 3 tiles, 4 workgroups of 16 rows
+    (4, 8, 8, 128, 128, 49, True),        # 3 tiles, 128 workgroups
+    (2, 8, 8, 128, 64, 100, True),        # a block of two tiles, 112 workgroups
+    (4, 8, 8, 128, 129, 49, False),       # 4 tiles
+    (4, 4, 4, 64, 200, 70, False),        # head_dim 64: 6 tiles
+    (2, 8, 2, 64, 190, 70, True),         # 5 tiles
+])
+def test_refresh_step_in_one_launch(B, Hq, Hkv, d, P, Bq, one):
+    """One launch leaves the workspace alone, the splits and their combine do not; both against the oracle."""
+    w = _wl(B, Hq, Hkv, d, P, Bq)
+    Kp, Vp = wl.make_prefix(w, 615)
+    steps = wl.make_block_steps(w, 615)
+    ora = orc.run_block_dense(Kp, Vp, steps, 2)
+    shape, ext, dev = T.shape_of(w), T.Partial(w), lambda x: T.to_dev(x, "f32")
+    ws = torch.full((fb.fb_workspace_bytes(shape),), 0xA5, device=T.DEV, dtype=torch.uint8)
+    Q, Kb, Vb = steps[0]
+    q, out = dev(Q), torch.empty_like(dev(Q))
+    fb.fb_refresh_step(shape, q, dev(Kp), dev(Vp), dev(Kb), dev(Vb), ext.o, ext.m, ext.lse, out, None, ws)
+    torch.cuda.synchronize()
+    assert bool((ws == 0xA5).all()) == one
+    T.assert_close(out.double().cpu().numpy(), ora[0]["out"], "f32", f"{w.name} out")
+    T.check_partial(ext.numpy(), ora[0]["ext"], "f32", w.name + " ext")
