@@ -25,8 +25,12 @@ pytestmark = pytest.mark.gpu
 ])
 def test_selection(B, Hq, Hkv, d, Bq, nblk, topk, dtype):
     rng = np.random.default_rng([B, Hq, Bq, nblk])
-    # rows of a head alike and small: means, products and sums are small integers
-    q = np.repeat(rng.integers(-2, 3, (B, Hq, 1, d)), Bq, axis=2).astype(np.float64)
+    # every row of a head different, small integers whose column sums are multiples of the row count (the last row makes up for
+    # the rest, at most Bq - 1 <= 64 and so exact in bf16): means, products and sums are small integers
+    q = rng.integers(-2, 3, (B, Hq, 1, d)) + rng.integers(-2, 3, (B, Hq, Bq, d))
+    q[:, :, -1] -= q.sum(2) % Bq
+    mean = q.sum(2) // Bq
+    q = q.astype(np.float64)
     kp = rng.integers(-1, 2, (B, Hkv, nblk, d)).astype(np.float64)
     kp[:, :, :, 8:] = 0                          # few distinct scores
     shape = fb.make_shape(B, Hq, Hkv, d, Bq, nblk * 64, dtype)
@@ -42,6 +46,6 @@ def test_selection(B, Hq, Hkv, d, Bq, nblk, topk, dtype):
     k = min(topk, nblk)
     for b in range(B):
         for h in range(Hq):
-            score = kp[b, h // (Hq // Hkv)] @ q[b, h, 0]
+            score = kp[b, h // (Hq // Hkv)] @ mean[b, h]
             want = np.sort(np.lexsort((np.arange(nblk), -score))[:k])
             assert (got[0][b, h, :k] == want).all() and (got[0][b, h, k:] == -1).all()
