@@ -327,6 +327,10 @@ __global__ __launch_bounds__(256 * WR * TG, 1) void attn_f32_kernel(const PassPa
       // the rows of its own 16 keys and clears them itself.
       for (int c = max(nvalid, 16 * wk) * C::CPR + lane; c < (16 * wk + 16) * C::CPR; c += 64)
         *(f32x4*)(stage + C::OPB + c * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
+      // other lanes of the wavefront read them: LDS keeps the order by itself, the compiler is told (no instruction)
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
     const int key0 = 16 * wk + 4 * g4;
     if (NSETS > 1 && !t0.is_sel)
