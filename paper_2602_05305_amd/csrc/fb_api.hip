@@ -115,7 +115,7 @@ int auto_splits(const fb_shape* s, int active_heads = 0) {
 
 // Split counts of the sparse passes (bf16): one workgroup per CU in both modes - 8 wavefronts in
 // the reuse pass, 4 wavefronts with two accumulator sets in the refresh pass.
-// Splits of the plain dense external pass.  KV groups above 128 rows run 256-row, 8-wavefront workgroups, one per
+// Splits of the plain dense external pass.  KV groups above 128 rows run 256-row workgroups, one per
 // CU: as many splits as keep the workgroup count within the 256 CUs (one round), each with at least 8 tiles.
 int dense_splits(const fb_shape* s) {
   const int G = s->n_q_heads / s->n_kv_heads;
@@ -221,7 +221,9 @@ HeadsPlan heads_plan(const fb_shape* s, int active_heads, int ns) {
   // twice the split partials have to be earned: from 24 tiles per split on (12 heads of 4680 rows, 1 flagged: 26 tiles a
   // split 222 -> 218 us, 12 tiles 193 -> 194; 3 of 8 heads of 2500 rows, 10 tiles, 89 -> 95), and where the 128-row
   // workgroups fill half the chip unsplit and would write the final partial themselves, from 128 tiles on (6 of 12
-  // heads, 141 tiles: 310 -> 297; 8 of 10 heads of 3111 rows, 94 tiles: 191 -> 201)
+  // heads, 141 tiles: 310 -> 297; 8 of 10 heads of 3111 rows, 94 tiles: 191 -> 201).  (Measured with 32 rows per wavefront.  With 64
+  // the plan gains more where it is taken: 12 heads of 4680 rows, 1 flagged, 24.5 tiles a split 76.4 -> 65.3, 6 flagged, 141 tiles
+  // 158 -> 139; 8 of 10 heads of 3111 rows, 130 tiles 142 -> 121; 6 of 12 heads of 3000 rows, head_dim 64, 106 -> 90)
   const long long wgs = (long long)s->batch * std::min(active_heads, s->n_kv_heads) * ((nrows + fb::kRowsPerWgBf16 - 1) / fb::kRowsPerWgBf16);
   if (tiles < 48 * ns || (ns == 1 && wgs >= 128 && tiles < 128) || 2 * ns > FB_MAX_SPLITS) return h;
   if (nrows * s->head_dim * 2 >= (1ll << 32)) return h;      // 32-bit query offsets between the heads of a group

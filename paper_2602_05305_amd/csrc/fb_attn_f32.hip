@@ -1,4 +1,4 @@
-// fp32 attention pass for gfx950: fp32 matrix instructions, wavefront-shuffle softmax statistics.
+// fp32 attention pass for gfx950: fp32 matrix instructions, softmax statistics exchanged between lanes in registers.
 //
 // Computes the per-row statistics of Eq. 3-4/6 (arxiv 2602.05305, Section 4.2) over a key range, for storage
 // type float.  This is the exactness path (max-abs 1e-5 against a float64 reference): products and sums are fp32

@@ -559,7 +559,8 @@ __device__ __forceinline__ float chunk_dot(const float4 a, const float4 q4) {
   return fmaf(a.w, q4.w, fmaf(a.z, q4.z, fmaf(a.y, q4.y, a.x * q4.x)));
 }
 
-// grid (B*Hq), 256 threads: qbar_out[bh][D] = mean query of the head (first kernel of the three-kernel selection).
+// grid (B*Hq), 256 threads: qbar_out[bh][D] = mean query of the head (first kernel of the selection with a workspace,
+// where qbar_scores_kernel does not take its place).
 __global__ __launch_bounds__(256) void head_qbar_kernel(const SelectParams p) {
   __shared__ float qbar[128];
   __shared__ float red[256 * 8];
@@ -569,7 +570,7 @@ __global__ __launch_bounds__(256) void head_qbar_kernel(const SelectParams p) {
 
 // grid (ceil(nblk / rows per workgroup), B*Hkv), 256 threads: scores of a run of key blocks for the G heads of
 // a KV group: every pooled row is read once for the whole group.  A wavefront instruction covers 64 / (D/4)
-// rows; kScoreU of them are in flight; a row's partial sums meet by xor-shuffles inside its lane group (the
+// rows; kScoreU of them are in flight; a row's partial sums meet by lane exchanges inside its lane group (the
 // same arithmetic, in the same order, as the one-kernel selection).
 constexpr int kScoreU = 4;
 __global__ __launch_bounds__(256) void block_scores_kernel(const SelectParams p) {
@@ -727,13 +728,13 @@ __global__ __launch_bounds__(256) void select_topk_kernel(const SelectParams p) 
       if (p.score_out != nullptr) p.score_out[(size_t)bh * nblk + c] = s;
     }
   } else if (p.scores_ws != nullptr) {
-    // scores already computed by block_scores_kernel
+    // scores already computed by block_scores_kernel or qbar_scores_kernel
     const float* sc = p.scores_ws + (size_t)bh * nblk;
     for (int c = tid; c < nblk; c += 256) key[c] = order_key(sc[c]);
   } else {
     head_qbar(p.q, bh, p.Bq, D, p.is_bf16, qbar, red, tid);
     // score = qbar . pooled key of the block.  A wavefront reads 64 consecutive 16-byte chunks per
-    // instruction (2 rows at D = 128, 4 at D = 64); a row's partial sums meet by xor-shuffles inside
+    // instruction (2 rows at D = 128, 4 at D = 64); a row's partial sums meet by lane exchanges inside
     // its lane group; 8 such loads are in flight per wavefront.
     const float* kp = p.k_pooled + (size_t)(b * p.Hkv + kvh) * nblk * D;
     const int cpr = D / 4, rpw = 64 / cpr;            // chunks per row, rows per wavefront instruction

@@ -267,10 +267,11 @@ inline bool internal_in_place(const PassParams& p, int D, size_t esize) {
   return false;
 }
 
-// bf16 dense external pass: KV groups of more than 128 rows run row-pair workgroups (8 wavefronts, 256 rows, one
-// shared tile stream), so every K/V tile is staged once per 256 rows.  At head_dim 64 that measures the same as
-// 128-row workgroups (32.6 vs 33.8 us at 256 rows, 32K keys) but leaves twice the splits to fold, so there only
-// from 1024 rows on, where the pass is compute-bound.  Shared by the split heuristic and the launcher.
+// bf16 dense external pass: KV groups of more than 128 rows run 256-row workgroups (row pairs, one shared tile stream), so every
+// K/V tile is staged once per 256 rows.  At head_dim 64 only from 1024 rows on: below, on streams of up to some 16000 keys, they
+// are slower with the splits they get (us, 128-row workgroups and row pairs: 64 / 8 heads of 32 rows, 1000 / 4111 / 16384 keys 12.7 / 15.3 / 24.1
+// and 18.4 / 21.5 / 25.3), though faster on long ones (32768 / 100000 keys 35.5 / 82.2 and 34.9 / 68.8; 8 heads of 300 rows 76 / 203 and
+// 48 / 116), which a rule by length does not tell apart yet.  Shared by the split heuristic and the launcher.
 inline bool dense_row_pairs(int nrows, int head_dim) {
   return nrows >= 1024 || (head_dim >= 128 && nrows > kRowsPerWgBf16);
 }

@@ -19,7 +19,8 @@
 //     moved, ragged tile) is one branch at its top.
 // Measured (12 heads of 4680 rows, 37440 keys, against 32 rows per wavefront, alternating): 1015 -> 886 us, 2.26 M cycles at 2.23
 // GHz -> 1.78 M at 2.02 (the part lowers its clock as the matrix cores get busier, so time falls less than cycles); reuse step
-// of 4680 keys 147 -> 131 us.  Results are the same bit for bit: same tiles, order and references per row.
+// of 4680 keys 147 -> 131 us.  Same tiles, order and references per row: results are the same up to the contraction of the row
+// sum in the epilogue.  Its ends cost more, so short streams keep the 32 rows (short_row_pairs in fb_stream_bf16.hip).
 #pragma once
 
 #include <type_traits>
