@@ -113,14 +113,25 @@ int auto_splits(const fb_shape* s, int active_heads = 0) {
   return f32_splits(s, false);
 }
 
-// Split counts of the sparse passes (bf16): one workgroup per CU in both modes - 8 wavefronts in
-// the reuse pass, 4 wavefronts with two accumulator sets in the refresh pass.
+// Pieces that the streaming kernel cuts the prefix of up to 128 rows per KV head into, where the nseg splits of auto_splits, one
+// more than fit 256 workgroups, would leave a second round with a few of them: one round, and the splits stay as the reference
+// segments of the walk (fb_stream_bf16.hip), so that results do not change with the cut.  (A refresh step, 11 splits -> 10 pieces, batch 3,
+// 8 heads of 9 rows, head_dim 128 / 64, 8 / 12 / 24 tiles a split 30.1 / 38.1 / 73.2 -> 24.8 / 29.1 / 49.2 us and 22.7 / 27.9 / 43.7 -> 20.8 /
+// 24.1 / 33.7; 3 -> 2 pieces, batch 15, 50 rows of 2 heads a group, 8 / 16 tiles 44.1 / 68.3 -> 36.9 / 57.7; never slower.)
+int dense_parts(const fb_shape* s, int nseg) {
+  const int tiles = (s->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile;
+  const long long groups = (long long)s->batch * s->n_kv_heads;
+  const long long nrows = (long long)(s->n_q_heads / s->n_kv_heads) * s->block_len;
+  if (s->dtype != FB_BF16 || nrows > fb::kRowsPerWgBf16 || tiles < 8 * nseg || groups * nseg <= 256 || 256 / groups < 2) return nseg;
+  return (int)(256 / groups);
+}
+
 // Splits of the plain dense external pass.  KV groups above 128 rows run 256-row workgroups, one per
 // CU: as many splits as keep the workgroup count within the 256 CUs (one round), each with at least 8 tiles.
 int dense_splits(const fb_shape* s) {
   const int G = s->n_q_heads / s->n_kv_heads;
   const long long nrows = (long long)G * s->block_len;
-  if (s->dtype != FB_BF16 || !fb::dense_row_pairs((int)std::min<long long>(nrows, 1 << 30), s->head_dim)) return auto_splits(s);
+  if (s->dtype != FB_BF16 || !fb::dense_row_pairs((int)std::min<long long>(nrows, 1 << 30), s->head_dim)) return dense_parts(s, auto_splits(s));
   const int tiles = (s->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile;
   const long long groups = (long long)s->batch * s->n_kv_heads * ((nrows + 2 * fb::kRowsPerWgBf16 - 1) / (2 * fb::kRowsPerWgBf16));
   long long ns = 256 / groups;
@@ -128,6 +139,12 @@ int dense_splits(const fb_shape* s) {
   if (ns > FB_MAX_SPLITS) ns = FB_MAX_SPLITS;
   if (ns < 1) ns = 1;
   return (int)ns;
+}
+
+// Reference segments of the plain dense pass.
+int dense_segments(const fb_shape* s) {
+  const long long nrows = (long long)(s->n_q_heads / s->n_kv_heads) * s->block_len;
+  return s->dtype == FB_BF16 && nrows <= fb::kRowsPerWgBf16 ? auto_splits(s) : dense_splits(s);
 }
 
 // Splits of the per-head refresh.  fp32: one query head per workgroup.
@@ -147,6 +164,8 @@ int heads_splits(const fb_shape* s, int active_heads) {
   return std::max({ns, auto_splits(s), std::min(tiles / 8, 7)});
 }
 
+// Split counts of the sparse passes (bf16): one workgroup per CU in both modes - 8 wavefronts in
+// the reuse pass, 4 wavefronts with two accumulator sets in the refresh pass.
 int sparse_splits(const fb_shape* s, bool refresh) {
   (void)refresh;
   if (s->dtype != FB_BF16) return f32_splits(s, true);
@@ -330,7 +349,8 @@ const char* fb_external_kernel_name(const fb_shape* shape) {
     snprintf(name, sizeof(name), "attn_f32_%skernel<%d, %d>", few ? "few_" : "", shape->head_dim, (int)fb::kPassDense);
     return name;
   }
-  const fb::PassParams p = base_pass(shape, nullptr, nullptr, nullptr, shape->prefix_len, dense_splits(shape));
+  fb::PassParams p = base_pass(shape, nullptr, nullptr, nullptr, shape->prefix_len, dense_splits(shape));
+  p.nseg = dense_segments(shape);
   fb::attn_bf16_dense_name(p, shape->head_dim, name, sizeof(name));
   return name;
 }
@@ -392,13 +412,15 @@ fb_status external_partial_impl(const fb_shape* shape, const void* q, const void
   // per-head refresh, bf16: a buffer below the documented size that holds the splits of auto_splits is taken with those
   if (use_head_mask && shape->dtype == FB_BF16 && workspace_bytes < ws_layout(shape, ns, 1, 0).total)
     ns = auto_splits(shape, n_active_heads);
+  const int nseg = (n_splits > 0 || paged || use_head_mask) ? ns : dense_segments(shape);
+  if (!workspace || workspace_bytes < ws_layout(shape, nseg, 1, 0).total) return FB_ERR_WORKSPACE;
   const WsLayout w = ws_layout(shape, ns, 1, 0);
-  if (!workspace || workspace_bytes < w.total) return FB_ERR_WORKSPACE;
 
   hipStream_t stream = (hipStream_t)hip_stream;
   char* ws = (char*)workspace;
   fb::PassParams p = base_pass(shape, q, k_prefix, v_prefix, shape->prefix_len, ns);
   p.ws_o = (float*)(ws + w.o[0]); p.ws_m = (float*)(ws + w.m[0]); p.ws_l = (float*)(ws + w.l[0]);
+  p.nseg = nseg;
   p.head_on = use_head_mask ? head_mask : nullptr;
   fb::PassMode mode = use_head_mask ? fb::kPassDenseHeads : fb::kPassDense;
   if (use_head_mask) {
@@ -595,9 +617,17 @@ fb_status fb_refresh_step_prof(const fb_shape* shape, const void* q, const void*
   // count); one fold kernel (4 rows per workgroup) folds the splits, computes the rows' block-internal
   // attention and merges.
   // (fp32: the block's own keys are one more workgroup of the pass, which then needs a place in the single round)
-  const bool small_block = shape->dtype == FB_BF16 && shape->block_len <= fb::kMaxInlineBlock &&
-                           shape->block_len % fb::kFoldRows == 0 && dense_splits(shape) >= 8;
-  const int ns = small_block ? dense_splits(shape) : std::max(1, auto_splits(shape) - (shape->dtype == FB_F32 ? 1 : 0));
+  const int segs = dense_segments(shape);
+  const bool few_rows = (long long)(shape->n_q_heads / shape->n_kv_heads) * shape->block_len <= fb::kRowsPerWgBf16;
+  // (blocks that are no multiple of the fold kernel's rows used to be the register-staged pass and the combine only, and still are
+  // where these are the faster end: by tiles per split, 8 / 16 / 24 / 48 of them, batch 2 and 4, 56 rows of 8 KV heads, head_dim 128 22.6 /
+  // 32.9 / 49.6 / 87.0 and 23.9 / 33.5 / 49.1 / 83.7 us; head_dim 64, 16 / 24 / 32 / 48 22.1 / 27.5 / 33.9 / 51.6 and 22.3 / 26.4 / 31.3 /
+  // 46.7, 108 rows level at 32.  Where one round in pieces replaces two, it always wins)
+  const bool fours = shape->block_len % fb::kFoldRows == 0;
+  const int odd_tiles = dense_parts(shape, segs) < segs ? 8 : shape->head_dim == 128 ? 24 : 32;
+  const bool small_block = shape->dtype == FB_BF16 && shape->block_len <= fb::kMaxInlineBlock && segs >= 8 &&
+                           (fours || (few_rows && (shape->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile >= odd_tiles * segs));
+  const int ns = small_block ? segs : std::max(1, auto_splits(shape) - (shape->dtype == FB_F32 ? 1 : 0));
   const WsLayout w = ws_layout(shape, ns, 2, 0, 1);
   const size_t need = shape->dtype == FB_F32 ? fb_workspace_bytes(shape, 0, 0, 0) : w.total;
   if (!workspace || workspace_bytes < need) return FB_ERR_WORKSPACE;
@@ -645,15 +675,20 @@ fb_status fb_refresh_step_prof(const fb_shape* shape, const void* q, const void*
   // 128: batch 6, 31 rows, 9000 keys 90.8 -> 83.3 us; batch 8, 32 rows, 20000 keys 146 -> 138).  head_dim 64 by tiles per split
   // (a refresh step): more than one round of workgroups from 32 on (36 tiles, 288 workgroups, blocks of 9 62.5 -> 58.5); one
   // round from 44 on (64 KV heads, blocks of 24, 36 tiles 36.4 -> 37.4, 48 44.2 -> 44.2, 64 57.2 -> 53.7), blocks of more than
-  // one 32-key tile from 64 on (blocks of 61, 36 tiles 39.5 -> 41.7, 56 54.1 -> 54.6, 64 63.7 -> 60.6)
-  const int d64_tiles = (long long)p.B * p.Hkv * ns > 256 ? 32 : p.Bq <= 32 ? 44 : 64;
+  // one 32-key tile from 64 on (blocks of 61, 36 tiles 39.5 -> 41.7, 56 54.1 -> 54.6, 64 63.7 -> 60.6
+  // us); always where one round in pieces replaces two (3 splits -> 2, 8 / 16 tiles a split 28.4 / 39.0 -> 25.6 / 35.0)
+  const int d64_tiles = dense_parts(shape, ns) < ns ? 8 : (long long)p.B * p.Hkv * ns > 256 ? 32 : p.Bq <= 32 ? 44 : 64;
   fb::PassParams in = base_pass(shape, q, k_block, v_block, shape->block_len, 1);
   in.fold_ns = ns;
   const bool fold_internal = shape->dtype == FB_BF16 && !small_block && ns > 1 && p.G * p.Bq <= 128 &&
                              p.Bq <= fb::kKeyTile && fb::stream_bf16_covers(p, shape->head_dim, fb::kPassDense) &&
                              (shape->head_dim == 128 || shape->prefix_len >= (long long)d64_tiles * fb::kKeyTile * ns) &&
                              fb::internal_fold_covers(in, shape->head_dim);
-  p.whole_tiles = fold_internal ? 1 : 0;
+  p.whole_tiles = fold_internal || (small_block && !fours) ? 1 : 0;
+  if (small_block || fold_internal) {
+    p.nseg = ns;
+    p.nsplit = in.fold_ns = dense_parts(shape, ns);
+  }
   p.ws_o = (float*)(ws + w.o[0]); p.ws_m = (float*)(ws + w.m[0]); p.ws_l = (float*)(ws + w.l[0]);
   p.ws_o2 = (float*)(ws + w.o[1]); p.ws_m2 = (float*)(ws + w.m[1]); p.ws_l2 = (float*)(ws + w.l[1]);
   hipError_t e = timed_attn(shape, p, small_block || fold_internal ? fb::kPassDense : fb::kPassRefreshFused, stream, ev_begin, ev_attn_end);
@@ -661,7 +696,7 @@ fb_status fb_refresh_step_prof(const fb_shape* shape, const void* q, const void*
 
   fb::CombineParams c;
   memset(&c, 0, sizeof(c));
-  c.rows = (int)rows_of(shape); c.D = shape->head_dim; c.nsplit = ns;
+  c.rows = (int)rows_of(shape); c.D = shape->head_dim; c.nsplit = p.nsplit;
   c.ws_o = p.ws_o; c.ws_m = p.ws_m; c.ws_l = p.ws_l;
   c.o = o_part; c.m = m_part; c.lse = lse_part;
   c.Bq = shape->block_len;
@@ -704,8 +739,7 @@ fb_status fb_refresh_step_paged(const fb_shape* shape, const void* q, const fb_p
   fb::PassParams in = base_pass(shape, q, k_block, v_block, shape->block_len, 1);
   in.out = out; in.lse_out = lse_out;
   in.fold_ns = n_splits > 0 ? n_splits : paged_splits(shape);
-  const bool fold_kernel = shape->block_len <= fb::kMaxInlineBlock && shape->block_len % fb::kFoldRows == 0 &&
-                           rows_of(shape) <= kFoldKernelMaxRows;
+  const bool fold_kernel = shape->block_len <= fb::kMaxInlineBlock && rows_of(shape) <= kFoldKernelMaxRows;
   const bool one_round = (long long)in.B * in.Hkv * ((in.G * in.Bq + 31) / 32) <= 256;
   const bool fold_internal = !fold_kernel && shape->dtype == FB_BF16 && in.fold_ns > 1 &&
                              (shape->head_dim == 64 || in.Bq <= 32 || one_round) &&

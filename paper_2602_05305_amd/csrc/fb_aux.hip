@@ -239,21 +239,24 @@ __device__ __forceinline__ float4 load4(const void* base, size_t i, int is_bf16)
 template <int D>
 __global__ __launch_bounds__(256) void refresh_fold_kernel(const CombineParams p) {
   constexpr int RW = kFoldRows;
-  static_assert(RW % 4 == 0 && RW <= 4, "block length is a multiple of RW: the value loop below steps by 4 keys; one wavefront per row");
+  static_assert(RW <= 4, "one wavefront per row");
   constexpr int per_row = D / 4, nsl = 256 / per_row;
   constexpr int ST = D + 4;                        // floats per K / V row in LDS: conflict-free 128-bit row reads
   constexpr int ES = D + 4;                        // folded external row: o[D], m2, l
   constexpr int NACC = D / 64;
   extern __shared__ __align__(16) float lds_f[];
   float* k_s = lds_f;                              // [Bq][ST]
-  float* v_s = k_s + p.Bq * ST;                    // [Bq][ST]
-  float* q_s = v_s + p.Bq * ST;                    // [RW][D]
+  float* v_s = k_s + p.Bq * ST;                    // [Bq rounded up to 4][ST]
+  float* q_s = v_s + (p.Bq + 3) / 4 * 4 * ST;      // [RW][D]
   float* e_s = q_s + RW * D;                       // [RW][ES]
   Folded* sh = (Folded*)(e_s + RW * ES);           // [RW][256]
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int sl = tid / per_row, c4 = tid % per_row;
-  const size_t row0 = (size_t)xcd_contiguous(blockIdx.x, gridDim.x) * RW;     // Bq % RW == 0: the RW rows belong to one query head
+  // RW rows of one query head, fewer at its end (those loads read the head's last row)
+  const uint32_t unit = xcd_contiguous(blockIdx.x, gridDim.x), bh_u = fastdiv(unit, p.div_fold);
+  const int at = (int)(unit - bh_u * p.div_fold.d) * RW, left = p.Bq - at;
+  const size_t row0 = (size_t)bh_u * p.Bq + at;
 
   // first CH splits of this thread for all RW rows: every load is issued before any is used, and the
   // block's K / V / q staging below runs while they are in flight
@@ -270,7 +273,7 @@ __global__ __launch_bounds__(256) void refresh_fold_kernel(const CombineParams p
         lv[r][c] = 0.f;
         ov[r][c] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (sp < p.nsplit) {
-          const size_t g = (size_t)sp * p.rows + row0 + r;
+          const size_t g = (size_t)sp * p.rows + row0 + min(r, left - 1);
           mv[r][c] = p.ws_m[g];
           lv[r][c] = p.ws_l[g];
           ov[r][c] = *(const float4*)(p.ws_o + g * D + c4 * 4);
@@ -280,11 +283,11 @@ __global__ __launch_bounds__(256) void refresh_fold_kernel(const CombineParams p
     // (a load-then-store loop would wait for every load in flight, the split loads included, on
     // each trip); chunks past the block's end are clamped to its last chunk and not stored.
     // (the head arithmetic needs integer divisions: it comes after the split loads have been issued)
-    const int bh = (int)(row0 / p.Bq), b = bh / p.Hq, kvh = (bh % p.Hq) / p.G;
+    const int bh = (int)bh_u, b = bh / p.Hq, kvh = (bh % p.Hq) / p.G;
     const size_t kvbase = (size_t)(b * p.Hkv + kvh) * p.Bq * D;
     constexpr int NST = kMaxInlineBlock * per_row / 256;      // staging trips at the largest block
     const int nchunk = p.Bq * per_row;
-    const size_t qoff = (row0 + (size_t)((tid % (RW * per_row)) / per_row)) * D + (tid % per_row) * 4;
+    const size_t qoff = (row0 + (size_t)min((tid % (RW * per_row)) / per_row, left - 1)) * D + (tid % per_row) * 4;
     if (p.fin_bf16) {
       uint2 kr[NST], vr[NST];
 #pragma unroll
@@ -349,13 +352,16 @@ __global__ __launch_bounds__(256) void refresh_fold_kernel(const CombineParams p
         }
       }
       if (p.nsplit > CH * nsl)     // more splits than one chunk per thread covers
-        f = fold_two(f, fold_strided(p.ws_o, p.ws_m, p.ws_l, p.nsplit, p.rows, row0 + r, D, c4, sl + CH * nsl, nsl));
+        f = fold_two(f, fold_strided(p.ws_o, p.ws_m, p.ws_l, p.nsplit, p.rows, row0 + min(r, left - 1), D, c4, sl + CH * nsl, nsl));
       sh[r * 256 + tid] = f;
     }
   }
+  // value rows up to the next multiple of 4: the value loop steps by 4 keys, and a weight of 0 must meet a number
+  if (p.Bq % 4 != 0 && tid < (4 - p.Bq % 4) * per_row)
+    *(float4*)(v_s + (p.Bq + tid / per_row) * ST + (tid % per_row) * 4) = make_float4(0.f, 0.f, 0.f, 0.f);
   __syncthreads();
 
-  const bool has_row = wave < RW;                  // wavefronts beyond the workgroup's rows only took part in the loads
+  const bool has_row = wave < min(RW, left);       // wavefronts beyond the workgroup's rows only took part in the loads
   const size_t row = row0 + (has_row ? wave : 0);
   if (has_row && lane < per_row) {                 // finish this wavefront's row: fold the split groups in order
     Folded ext = sh[wave * 256 + lane];
@@ -393,7 +399,7 @@ __global__ __launch_bounds__(256) void refresh_fold_kernel(const CombineParams p
   float acc[NACC];
 #pragma unroll
   for (int i = 0; i < NACC; ++i) acc[i] = 0.f;
-  for (int j = 0; j < p.Bq; j += 4) {             // Bq % 4 == 0 on this path; four keys' LDS reads in flight per trip
+  for (int j = 0; j < p.Bq; j += 4) {             // four keys' LDS reads in flight per trip; keys past the end weigh 0
     float pj[4], vv[4][NACC];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -956,15 +962,18 @@ hipError_t launch_pool_keys(const PoolParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_refresh_fold(const CombineParams& p, hipStream_t s) {
+hipError_t launch_refresh_fold(const CombineParams& c, hipStream_t s) {
+  CombineParams p = c;
   if (p.rows == 0) return hipSuccess;
-  if (p.Bq > kMaxInlineBlock || p.Bq % kFoldRows != 0 || p.blk_q == nullptr || p.nsplit < 1) return hipErrorInvalidValue;
-  const size_t lds = ((size_t)2 * p.Bq * (p.D + 4) + kFoldRows * p.D + kFoldRows * (p.D + 4)) * sizeof(float) +
+  if (p.Bq < 1 || p.Bq > kMaxInlineBlock || p.blk_q == nullptr || p.nsplit < 1) return hipErrorInvalidValue;
+  const uint32_t per_head = (uint32_t)((p.Bq + kFoldRows - 1) / kFoldRows);
+  p.div_fold = make_fastdiv(per_head);
+  const size_t lds = ((size_t)(p.Bq + (p.Bq + 3) / 4 * 4) * (p.D + 4) + kFoldRows * p.D + kFoldRows * (p.D + 4)) * sizeof(float) +
                      (size_t)kFoldRows * 256 * sizeof(Folded);
   static LdsLimit lim64, lim128;
   hipError_t e = p.D == 64 ? raise_lds_limit(refresh_fold_kernel<64>, lds, lim64, kLdsLimitMax) : raise_lds_limit(refresh_fold_kernel<128>, lds, lim128, kLdsLimitMax);
   if (e != hipSuccess) return e;
-  const dim3 grid((unsigned)(p.rows / kFoldRows));
+  const dim3 grid((unsigned)(p.rows / p.Bq) * per_head);
   if (p.D == 64) hipLaunchKernelGGL(refresh_fold_kernel<64>, grid, dim3(256), lds, s, p);
   else hipLaunchKernelGGL(refresh_fold_kernel<128>, grid, dim3(256), lds, s, p);
   return hipGetLastError();

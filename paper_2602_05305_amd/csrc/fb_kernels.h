@@ -143,6 +143,9 @@ struct PassParams {
   // streaming bf16 pass: 1 = splits alternate between the even and the odd XCD of a pair and the odd XCDs' splits are a
   // little shorter (see biased_range)
   int xcd_bias;
+  // dense pass of up to 128 rows, nseg > 0 and != nsplit: reference segments (halves_pass), cut and ordered as nseg splits would
+  // be, with their bias
+  int nseg, seg_bias;
   FastDiv div_rowtiles, div_nsplit, div_hkv;   // bf16 pass: decomposition of the linear workgroup index
   FastDiv div_page;                            // bf16 paged pass: key index -> page slot
   FastDiv div_bias;                            // streaming bf16 pass, xcd_bias: by 64 * nsplit
@@ -168,6 +171,7 @@ struct CombineParams {
   // fin_bf16): the fold kernel computes the block-internal attention of its rows itself
   const void* blk_q; const void* blk_k; const void* blk_v;
   int Hq, Hkv, G; float scale_log2;
+  FastDiv div_fold;                 // fold kernel: workgroups of a query head
 };
 
 struct SelectParams {
@@ -210,7 +214,7 @@ bool internal_fold_covers(const PassParams& p, int D);
 // Name of the kernel launch_attn_bf16 runs for the dense external pass of p (profiler spelling, no namespace).
 int attn_bf16_dense_name(const PassParams& p, int D, char* buf, size_t n);
 hipError_t launch_combine(const CombineParams& p, hipStream_t s);
-// Fold + block-internal attention + merge in one kernel; needs blk_q/k/v, Bq <= kMaxInlineBlock, Bq % kFoldRows == 0.
+// Fold + block-internal attention + merge in one kernel; needs blk_q/k/v, Bq <= kMaxInlineBlock.
 hipError_t launch_refresh_fold(const CombineParams& p, hipStream_t s);
 constexpr int kMaxInlineBlock = 64;
 constexpr int kFoldRows = 4;

@@ -43,7 +43,10 @@ namespace fb {
 namespace {
 
 // (kKeySplitSingle: the key split with one tile per barrier at head_dim 64 as well)
-enum StreamLayout : int { kKeySplit = 0, kTileSplit = 1, kRowPair = 2, kKeySplitSingle = 3, kRowPairShort = 4 };
+// kKeySplitParts, kTileSplitParts: the first two where the workgroups' ranges are not the reference segments (PassParams::nseg)
+enum StreamLayout : int { kKeySplit = 0, kTileSplit = 1, kRowPair = 2, kKeySplitSingle = 3, kRowPairShort = 4, kKeySplitParts = 5, kTileSplitParts = 6 };
+constexpr bool in_parts(int layout) { return layout == kKeySplitParts || layout == kTileSplitParts; }
+constexpr int whole_layout(int layout) { return layout == kKeySplitParts ? kKeySplit : layout == kTileSplitParts ? kTileSplit : layout; }
 constexpr bool key_split(int layout) { return layout == kKeySplit || layout == kKeySplitSingle; }
 
 // Key split at head_dim 64: two tiles per barrier, their scores and weights computed together, because a tile's fixed cost
@@ -155,12 +158,15 @@ __device__ __forceinline__ void tile_scores(f32x16 (&s)[NKB], const bf16x8 (&qre
   }
 }
 
+// A reference that moves down scales what is accumulated up, by at most this many powers of two.
+constexpr float kMostDown = 64.f;
+
 // Online softmax update with the tile's scores: moves the running reference if needed (rescaling the accumulators),
 // adds the row sums, and leaves the tile's probabilities, rounded to bf16, in pb (B operands of the value product).
 //   s[kb][r] = raw dot product of query row lane%32 with key 32 (kb0 + kb) + 8 (r/4) + 4 h + r%4
 template <int D, int NKB>
 __device__ __forceinline__ void tile_softmax(WaveAcc<D / 32>& st, f32x16 (&s)[NKB], bf16x8 (&pb)[2 * NKB], int kb0,
-                                             float scale_log2, bool lane_on, int nvalid, int h) {
+                                             float scale_log2, bool lane_on, int nvalid, int h, bool fresh = false) {
   constexpr int NDB = D / 32;
   if (nvalid < 64) {
     // the empty asm keeps this a real (wavefront-uniform) branch instead of per-score selects on every tile
@@ -183,7 +189,8 @@ __device__ __forceinline__ void tile_softmax(WaveAcc<D / 32>& st, f32x16 (&s)[NK
   // Lazy reference: m moves only when the tile maximum exceeds it by more than kLazy (log2 units); weights
   // stay below 2^kLazy, (o, l, m) remain exactly paired, and the accumulators are rescaled on few tiles only.
   constexpr float kLazy = 8.f;
-  const float m_new = (tmax > st.m + kLazy) ? tmax : st.m;
+  // fresh: the first tile of a reference segment moves it always (down as well, unless what is kept would leave fp32's range)
+  const float m_new = (tmax > st.m + kLazy || (fresh && tmax > st.m - kMostDown)) ? tmax : st.m;
   const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
   const float alpha = __builtin_amdgcn_exp2f(st.m - m_use);
   float lsum = 0.f;
@@ -237,10 +244,22 @@ template <int D, int NKB>
 __device__ __forceinline__ void tile_softmax_pv(WaveAcc<D / 32>& st, f32x16 (&s)[NKB],
                                                 const unsigned char* __restrict__ stage,
                                                 const uint32_t (&vaddr)[D / 32], int kb0, float scale_log2,
-                                                bool lane_on, int nvalid, int h) {
+                                                bool lane_on, int nvalid, int h, bool fresh = false) {
   bf16x8 pb[2 * NKB];
-  tile_softmax<D, NKB>(st, s, pb, kb0, scale_log2, lane_on, nvalid, h);
+  tile_softmax<D, NKB>(st, s, pb, kb0, scale_log2, lane_on, nvalid, h, fresh);
   tile_pv<D, NKB>(st, pb, stage, vaddr, kb0);
+}
+
+// The reference a stream would have after this tile as its first one; nothing is accumulated yet.
+template <int NDB, int NKB>
+__device__ __forceinline__ void tile_reference(WaveAcc<NDB>& st, const f32x16 (&s)[NKB], int kb0, float scale_log2, int nvalid, int h) {
+  float tmax = -INFINITY;
+#pragma unroll
+  for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if ((kb0 + kb) * 32 + 8 * (r / 4) + 4 * h + (r % 4) < nvalid) tmax = fmaxf(tmax, s[kb][r]);
+  st.m = max_halves(tmax * scale_log2);
 }
 
 // One tile of a wavefront for every accumulator set that any of its rows feeds (on).
@@ -354,9 +373,14 @@ struct TileDesc {
   const unsigned char* vt;
 };
 
-// Every layout but kRowPair: two wavefronts per row group, or one (kRowPairShort).
-template <int D, int MODE, int LAYOUT, int NRG>
+// What a workgroup does with an entry of its stream (TileRaw::mask) where its range is not a reference segment.
+constexpr uint32_t kSegFirst = 1u, kSegReference = 2u, kSegPad = 4u;
+
+// Every layout but kRowPair: two wavefronts per row group, or one (kRowPairShort).  PARTS: the stream of a (batch element, KV head) is
+// p.nseg reference segments, each visited in an order of its own, and the workgroups take p.nsplit even pieces of that walk.
+template <int D, int MODE, int LAYOUT, int NRG, bool PARTS>
 __device__ __forceinline__ void halves_pass(const PassParams& p, unsigned char* ring) {
+  static_assert(!PARTS || (MODE == kPassDense && (LAYOUT == kKeySplit || LAYOUT == kTileSplit)), "reference segments: dense pass");
   constexpr int NSETS = (MODE == kPassSparseRefresh) ? 2 : 1;
   using C = SCfg<D, LAYOUT, NSETS, NRG>;
   static_assert(MODE == kPassDense || MODE == kPassDenseHeads || MODE == kPassDensePaged || MODE == kPassSparseReuse ||
@@ -470,12 +494,107 @@ __device__ __forceinline__ void halves_pass(const PassParams& p, unsigned char* 
     tr.begin = min(tr.begin, total);
     tr.end = min(tr.end, total);
   }
-  const int ntiles = tr.end - tr.begin;
-  const int rot = ntiles <= 0 ? 0 : (int)((rsrc * 13u + (rsrc >> 5) * 7u) % (unsigned)ntiles);
+  int ntiles = tr.end - tr.begin;
+  // PARTS.  A weight is rounded to bf16 against the running reference, so the tile a reference starts from decides single roundings.
+  // Segments fix those tiles whatever the number of workgroups: each has its tiles, its order and its first tile; a workgroup that
+  // starts inside one takes its reference from that first tile (streamed once more, nothing accumulated), one that
+  // walks into the next starts a new reference there.  Segments are cut and rotated as nsplit = nseg would cut them.
+  int seg = 0, seg_begin = 0, seg_len = 1, seg_rot = 0, seg_pos = 0, part_left = 0, ref_at = 0, nref = 0, last_e = 0;
+  bool pad_next = false;
+  constexpr int kFirst = LAYOUT == kTileSplit ? 2 : 1;          // tiles that start a reference: one for each wavefront half
+  int seg_base = 0, seg_rem = 0, seg_q8 = 0;                     // the cut of split_range, and of the grid of nseg splits over the XCDs
+  if constexpr (PARTS) {
+    const int all = total + (LAYOUT == kTileSplit ? p.blk_cost : 0);
+    seg_base = all / p.nseg;
+    seg_rem = all - seg_base * p.nseg;
+    seg_q8 = (p.B * p.Hkv * p.nseg) >> 3;
+  }
+  auto seg_range = [&](int i) -> TileRange {
+    if (LAYOUT == kKeySplit && p.seg_bias) return biased_range(total, p.div_bias, i);
+    const int begin = i * seg_base + min(i, seg_rem);
+    return {min(begin, total), min(begin + seg_base + (i < seg_rem ? 1 : 0), total)};
+  };
+  auto seg_open = [&](int i) {
+    const TileRange r = seg_range(i);
+    seg = i;
+    seg_begin = r.begin;
+    seg_len = max(r.end - r.begin, 1);
+    // the workgroup that nsplit = nseg would give it, whose number rotates the order
+    const uint32_t w = r2 * (uint32_t)p.nseg + (uint32_t)i;
+    uint32_t bid;
+    if (p.seg_bias) {
+      const uint32_t q2 = 2u * (uint32_t)seg_q8, pair = w / q2, r1 = w - pair * q2;
+      bid = (r1 >> 1) * 8 + 2 * pair + (r1 & 1);
+    } else {
+      const uint32_t r8 = (uint32_t)(p.B * p.Hkv * p.nseg) & 7u, lim = r8 * (uint32_t)(seg_q8 + 1);
+      const uint32_t from = w < lim ? w : w - lim, q = (uint32_t)seg_q8 + (w < lim ? 1u : 0u), x = from / q;
+      bid = (from - x * q) * 8 + (w < lim ? 0u : r8) + x;
+    }
+    seg_rot = (int)((bid * 13u + (bid >> 5) * 7u) % (uint32_t)seg_len);
+  };
+  if constexpr (PARTS) {
+    auto seg_of = [&](int x) -> int {
+      int i = min((int)((float)x * (float)p.nseg / (float)total), p.nseg - 1);
+      while (i > 0 && seg_range(i).begin > x) --i;
+      while (i + 1 < p.nseg && seg_range(i).end <= x) ++i;
+      return i;
+    };
+    auto cut = [&](int i) -> int {                               // where piece i of the walk begins
+      if (i >= p.nsplit) return total;
+      const int x = split_range(total, p.div_nsplit, i).begin;
+      if (LAYOUT == kKeySplit) return x;
+      const int b0 = seg_range(seg_of(x)).begin;                 // pairs of tiles stay together
+      return b0 + ((x - b0) & ~1);
+    };
+    const int begin = cut(split), end = cut(split + 1);
+    part_left = end - begin;
+    const int first = seg_of(begin);
+    seg_open(first);
+    seg_pos = begin - seg_begin;
+    nref = seg_pos > 0 ? kFirst : 0;
+    ntiles = nref + part_left;
+    if (LAYOUT == kTileSplit) {
+      // a segment's last tile alone: the next one starts with a new pair
+      for (int i = first; i + 1 < p.nseg; ++i) {
+        const TileRange r = seg_range(i);
+        if (r.end >= end) break;
+        ntiles += (r.end - r.begin) & 1;
+      }
+    }
+  }
+  auto next_entry = [&]() -> TileRaw {
+    TileRaw r;
+    r.word = 0;
+    if (ref_at < nref) {
+      int j = ref_at++ + seg_rot;
+      if (j >= seg_len) j -= seg_len;
+      r.e = seg_begin + j;
+      r.mask = kSegReference;
+    } else if (pad_next) {
+      pad_next = false;
+      r.e = last_e;
+      r.mask = kSegPad;
+    } else {
+      int j = seg_pos + seg_rot;
+      if (j >= seg_len) j -= seg_len;
+      r.e = last_e = seg_begin + j;
+      r.mask = seg_pos < kFirst ? kSegFirst : 0u;
+      ++seg_pos;
+      --part_left;
+      if (seg_pos >= seg_len && part_left > 0) {
+        pad_next = LAYOUT == kTileSplit && (seg_len & 1) != 0;
+        seg_open(seg + 1);
+        seg_pos = 0;
+      }
+    }
+    return r;
+  };
+  const int rot = PARTS || ntiles <= 0 ? 0 : (int)((rsrc * 13u + (rsrc >> 5) * 7u) % (unsigned)ntiles);
   const uint32_t* __restrict__ bmask = p.blk_mask ? p.blk_mask + (size_t)bk * p.nblk : nullptr;
   const int32_t* __restrict__ ulist = p.union_list ? p.union_list + (size_t)bk * p.nblk : nullptr;
   const uint32_t* __restrict__ umask = p.union_mask ? p.union_mask + (size_t)bk * p.nblk : nullptr;
-  auto tile_raw = [&](int i) -> TileRaw {        // i-th tile of this workgroup: table lookups only
+  auto tile_raw = [&](int i) -> TileRaw {        // i-th tile of this workgroup (asked for in order): table lookups only
+    if constexpr (PARTS) return next_entry();
     int j = i + rot;
     if (j >= ntiles) j -= ntiles;
     TileRaw r;
@@ -665,8 +784,14 @@ __device__ __forceinline__ void halves_pass(const PassParams& p, unsigned char* 
     }
   };
   // one tile of a wavefront whose row group is shared by two (key halves)
+  bool seg_waits = false;          // PARTS: the segment's first tile has no key for this half (the ragged last tile): the next one counts
   auto half_tile = [&](const unsigned char* stage, int k0, uint32_t mask) __attribute__((always_inline)) {
+    if constexpr (PARTS) {
+      if (mask & kSegPad) return;
+    }
     const int nvalid = min(C::KT, nkeys - k0);
+    const bool fresh = PARTS && ((mask & kSegFirst) != 0u || seg_waits);
+    if constexpr (PARTS) seg_waits = fresh && nvalid <= 32 * kb0;
     if constexpr (MODE == kPassSparseReuse) {
       if (nvalid <= 0) return;                               // a list entry past the end of the keys
     }
@@ -686,10 +811,16 @@ __device__ __forceinline__ void halves_pass(const PassParams& p, unsigned char* 
     } else {
       f32x16 s[C::NKB];
       tile_scores<D, C::NKB>(s, qreg, stage, kaddr, kb0);
+      if constexpr (PARTS) {
+        if (mask & kSegReference) {
+          tile_reference<C::NDB, C::NKB>(acc, s, kb0, p.scale_log2, nvalid, h);
+          return;
+        }
+      }
 #pragma unroll
       for (int i = 0; i < NSETS; ++i) {
         if (NSETS > 1 && !__any(on[i])) continue;
-        tile_softmax_pv<D, C::NKB>(accs[i], s, stage, vaddr, kb0, p.scale_log2, on[i], nvalid, h);
+        tile_softmax_pv<D, C::NKB>(accs[i], s, stage, vaddr, kb0, p.scale_log2, on[i], nvalid, h, fresh);
       }
     }
   };
@@ -698,6 +829,13 @@ __device__ __forceinline__ void halves_pass(const PassParams& p, unsigned char* 
   // bit, but the scores, the cross-lane maxima and the weights of both in one go
   auto two_tiles = [&](const unsigned char* stage_a, int k0a, uint32_t mask_a, const unsigned char* stage_b, int k0b,
                        uint32_t mask_b) __attribute__((always_inline)) {
+    if constexpr (PARTS) {
+      if ((mask_a | mask_b) != 0u || seg_waits) {
+        half_tile(stage_a, k0a, mask_a);
+        half_tile(stage_b, k0b, mask_b);
+        return;
+      }
+    }
     const int nva = min(C::KT, nkeys - k0a), nvb = min(C::KT, nkeys - k0b);
     bool ona[NSETS], onb[NSETS];
     bool any_a = false, any_b = false;
@@ -892,12 +1030,12 @@ template <int D, int MODE, int LAYOUT, int NRG>
 __global__ __launch_bounds__(LAYOUT == kRowPair ? RCfg<D>::THREADS : LAYOUT == kRowPairShort ? 512 : 2 * NRG * 64, 1) void attn_stream_kernel(const PassParams p) {
   extern __shared__ __align__(16) unsigned char ring[];
   if constexpr (LAYOUT == kRowPair) rows_pass<D, MODE>(p, ring);
-  else halves_pass<D, MODE, LAYOUT, NRG>(p, ring);
+  else halves_pass<D, MODE, whole_layout(LAYOUT), NRG, in_parts(LAYOUT)>(p, ring);
 }
 
 template <int D, int MODE, int LAYOUT, int NRG = 4>
 hipError_t launch_stream(const PassParams& p, hipStream_t s) {
-  using C = std::conditional_t<LAYOUT == kRowPair, RCfg<D>, SCfg<D, LAYOUT, (MODE == kPassSparseRefresh) ? 2 : 1, NRG>>;
+  using C = std::conditional_t<LAYOUT == kRowPair, RCfg<D>, SCfg<D, whole_layout(LAYOUT), (MODE == kPassSparseRefresh) ? 2 : 1, NRG>>;
   // row pairs: the shortest range has to hold what is loaded ahead (the routes here ask for more); per-head refresh: two splits
   // share a range
   if (LAYOUT == kRowPair && (p.nkeys + C::KT - 1) / C::KT < kRowsTiles * (MODE == kPassDenseHeads ? (p.nsplit + 1) / 2 : p.nsplit))
@@ -918,9 +1056,20 @@ hipError_t launch_stream(const PassParams& p, hipStream_t s) {
   {
     // long streams only: below 64 tiles per split a 1/64 bias rounds away
     const int tiles = (p.nkeys + kKeyTile - 1) / kKeyTile;
-    q.xcd_bias = (key_split(LAYOUT) && (MODE == kPassDense || MODE == kPassSparseRefresh) && ntile_rows == 1 && p.nsplit % 2 == 0 &&
-                  nwg % 8 == 0 && tiles >= 64 * p.nsplit && (long long)tiles * 64 * p.nsplit < (1ll << 31)) ? 1 : 0;
-    q.div_bias = make_fastdiv(64u * (uint32_t)p.nsplit);
+    auto biased = [&](int n, long long wgs) {
+      return key_split(whole_layout(LAYOUT)) && (MODE == kPassDense || MODE == kPassSparseRefresh) && ntile_rows == 1 && n % 2 == 0 &&
+             wgs % 8 == 0 && tiles >= 64 * n && (long long)tiles * 64 * n < (1ll << 31);
+    };
+    if constexpr (in_parts(LAYOUT)) {
+      const long long segs = (long long)p.B * p.Hkv * p.nseg;
+      if (ntile_rows != 1 || p.nseg < 1 || tiles < 8 * p.nseg || tiles < 8 * p.nsplit || segs < 8 || segs >= (1ll << 31)) return hipErrorInvalidValue;
+      q.seg_bias = biased(p.nseg, segs) ? 1 : 0;
+      q.xcd_bias = 0;
+      q.div_bias = make_fastdiv(64u * (uint32_t)p.nseg);
+    } else {
+      q.xcd_bias = biased(p.nsplit, nwg) ? 1 : 0;
+      q.div_bias = make_fastdiv(64u * (uint32_t)p.nsplit);
+    }
   }
   q.div_rowtiles = make_fastdiv((uint32_t)ntile_rows);
   q.div_nsplit = make_fastdiv((uint32_t)p.nsplit);
@@ -947,6 +1096,14 @@ hipError_t launch_key_split(const PassParams& p, hipStream_t s) {
   return launch_stream<D, MODE, kKeySplit, 4>(p, s);
 }
 
+template <int D, int LAYOUT>
+hipError_t launch_parts(const PassParams& p, hipStream_t s) {
+  const int nrows = p.G * p.Bq;
+  if (nrows <= 32) return launch_stream<D, kPassDense, LAYOUT, 1>(p, s);
+  if (nrows <= 64) return launch_stream<D, kPassDense, LAYOUT, 2>(p, s);
+  return launch_stream<D, kPassDense, LAYOUT, 4>(p, s);
+}
+
 // Dense row pairs: 32 rows per wavefront (kRowPairShort) below 14 tiles per split, 64 (kRowPair) from there on.  External pass, us, 32 against
 // 64 rows per wavefront, a ragged last tile: 8 / 64 heads of 32 rows, one split, 8 / 10 / 12 / 14 / 16 / 32 tiles 19.2 / 22.1 / 25.0 / 28.0 /
 // 30.9 / 54.1 and 21.0 / 23.3 / 25.3 / 28.2 / 30.1 / 49.5; 16 splits, 8 / 12 / 14 / 24 tiles 26.3 / 32.8 / 35.7 / 50.7 and 27.7 / 32.6 / 35.3 / 47.2;
@@ -963,6 +1120,10 @@ hipError_t launch_stream_d(const PassParams& p, PassMode mode, hipStream_t s) {
   switch (mode) {
     case kPassDense:
       if (dense_row_pairs(nrows, D)) return short_row_pairs(p) ? launch_stream<D, kPassDense, kRowPairShort>(p, s) : launch_stream<D, kPassDense, kRowPair>(p, s);
+      if (p.nseg > 0 && p.nseg != p.nsplit) {
+        if (p.whole_tiles) return launch_parts<D, kTileSplitParts>(p, s);
+        return launch_parts<D, kKeySplitParts>(p, s);
+      }
       if (p.whole_tiles) {
         if (nrows <= 32) return launch_stream<D, kPassDense, kTileSplit, 1>(p, s);
         if (nrows <= 64) return launch_stream<D, kPassDense, kTileSplit, 2>(p, s);
@@ -1015,7 +1176,7 @@ int stream_bf16_name(const PassParams& p, int D, PassMode mode, char* buf, size_
   const bool rp = (mode == kPassDense && dense_row_pairs(p.G * p.Bq, D)) || mode == kPassInternal;
   const int nrows = p.G * p.Bq;
   return snprintf(buf, n, "attn_stream_kernel<%d, %d, %d, %d>", D, (int)mode,
-                  !rp ? (int)kKeySplit : mode == kPassDense && short_row_pairs(p) ? (int)kRowPairShort : (int)kRowPair,
+                  !rp ? (int)(mode == kPassDense && p.nseg > 0 && p.nseg != p.nsplit ? kKeySplitParts : kKeySplit) : mode == kPassDense && short_row_pairs(p) ? (int)kRowPairShort : (int)kRowPair,
                   (rp || nrows > 64) ? 4 : nrows > 32 ? 2 : 1);
 }
 

@@ -1,0 +1,81 @@
+"""Dense passes whose workgroups take even pieces of a walk through reference segments (24 KV groups: 10 pieces of 11 segments), and the
+fold kernel over blocks that are no multiple of its four rows: against the same pass with one workgroup per segment, and against
+the numpy float64 oracle."""
+import pytest
+import torch
+
+from oracle import flashblock_oracle as orc
+from paper_2602_05305_amd import flashblock as fb
+from paper_2602_05305_amd import workloads as wl
+
+import fb_testlib as T
+
+pytestmark = pytest.mark.gpu
+
+
+def _normalised(e):
+    return e.o.double() * (e.m - e.lse).double().exp()[..., None]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("B,G,Bq,P", [
+    (3, 1, 8, 64 * 88),              # the shortest segments: 8 tiles
+    (3, 2, 31, 64 * 97 - 31),        # 62 rows, a ragged last tile with one key for the second key half
+    (3, 4, 25, 64 * 163 + 5),        # 100 rows, segments of 14 and 15 tiles
+    (5, 1, 32, 64 * 131 + 40),       # 40 groups: 6 pieces of 7 segments
+])
+def test_pieces_keep_the_segments_references(B, G, Bq, P, d):
+    """Weights are rounded against the same references, so the two ways differ by fp32 sums only: 1e-5 of the RMS, where another
+    reference moves single values by some 1e-2 of it."""
+    w = wl.Workload(f"sg_{B}_{G}_{P}_{d}", B, 8 * G, 8, d, P, Bq, 1, 1, "bf16", 1.0)
+    Kp, Vp = wl.make_prefix(w, 601)
+    q = T.to_dev(wl.make_block_steps(w, 601)[0][0], "bf16")
+    k, v = T.to_dev(Kp, "bf16"), T.to_dev(Vp, "bf16")
+    shape, pieces, segments = T.shape_of(w), T.Partial(w), T.Partial(w)
+    nseg = -(-256 // (8 * B))
+    assert fb.fb_external_splits(shape) == 256 // (8 * B) == nseg - 1
+    fb.fb_external_partial(shape, q, k, v, pieces.o, pieces.m, pieces.lse, T.workspace(shape))
+    fb.fb_external_partial_ex(shape, q, k, v, segments.o, segments.m, segments.lse, nseg, T.workspace(shape, n_splits=nseg))
+    a, b = _normalised(pieces), _normalised(segments)
+    assert float((a - b).abs().max()) <= 1e-5 * float(b.square().mean().sqrt())
+    assert float((pieces.lse - segments.lse).abs().max()) <= 2e-6 * max(1.0, float(segments.lse.abs().max()))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,Bq,P", [(1, 1, 64 * 88), (4, 3, 64 * 90 + 1), (2, 33, 64 * 91 - 1), (4, 31, 64 * 109 + 7), (1, 63, 64 * 93)])
+def test_refresh_step_of_odd_blocks(G, Bq, P, d):
+    w = wl.Workload(f"so_{G}_{Bq}_{P}_{d}", 3, 8 * G, 8, d, P, Bq, 2, 2, "bf16", 1.0)
+    Kp, Vp = wl.make_prefix(w, 603)
+    steps = wl.make_block_steps(w, 603)
+    shape, ext = T.shape_of(w), T.Partial(w)
+    ws, k, v = T.workspace(shape), T.to_dev(Kp, "bf16"), T.to_dev(Vp, "bf16")
+    for (Q, Kb, Vb), want in zip(steps, orc.run_block_dense(Kp, Vp, steps, 2)):
+        q, kb, vb = (T.to_dev(x, "bf16") for x in (Q, Kb, Vb))
+        out, lse = torch.empty_like(q), torch.empty(q.shape[:3], device=T.DEV)
+        if Q is steps[0][0]:
+            fb.fb_refresh_step(shape, q, k, v, kb, vb, ext.o, ext.m, ext.lse, out, lse, ws)
+        else:
+            fb.fb_internal_merge(shape, q, kb, vb, ext.o, ext.m, ext.lse, out, lse)
+        T.assert_close(out.double().cpu().numpy(), want["out"], "bf16", w.name + " out")
+        T.check_partial(ext.numpy(), want["ext"], "bf16", w.name + " ext")
+
+
+@pytest.mark.parametrize("factor", [2.0, 8.0])
+@pytest.mark.parametrize("Bq", [8, 5])
+def test_references_that_move_between_segments(Bq, factor):
+    """Some keys outweigh the others by 30 or 130 powers of two for one row: the next segment's reference lies as far below, and what a
+    workgroup that walks on has accumulated is scaled up (or, farther apart than 64, its reference stays)."""
+    w = wl.Workload(f"sm_{Bq}_{factor}", 3, 8, 8, 128, 64 * 88, Bq, 1, 1, "bf16", 1.0)
+    Kp, Vp = wl.make_prefix(w, 605)
+    steps = wl.make_block_steps(w, 605)
+    for at in range(7, w.prefix_len, 64 * 8 + 11):
+        Kp[:, :, at] = wl.round_storage(factor * steps[0][0][:, :, 1], "bf16")
+    shape, ext = T.shape_of(w), T.Partial(w)
+    q, kb, vb, k, v = (T.to_dev(x, "bf16") for x in (*steps[0], Kp, Vp))
+    want = orc.run_block_dense(Kp, Vp, steps, 1)[0]
+    fb.fb_external_partial(shape, q, k, v, ext.o, ext.m, ext.lse, T.workspace(shape))
+    T.check_partial(ext.numpy(), want["ext"], "bf16", w.name + " ext")
+    out = torch.empty_like(q)
+    fb.fb_refresh_step(shape, q, k, v, kb, vb, ext.o, ext.m, ext.lse, out, None, T.workspace(shape))
+    T.assert_close(out.double().cpu().numpy(), want["out"], "bf16", w.name + " out")
+    T.check_partial(ext.numpy(), want["ext"], "bf16", w.name + " ext of the step")
