@@ -266,6 +266,35 @@ int heads_ws_splits(const fb_shape* s, int active_heads) {
   return n;
 }
 
+// Refresh step of more than 128 rows per KV head in ns >= 2 splits (bf16) by the row-pair kernel: every split as two streams, the even
+// and the odd tiles, which are the tile groups of the register-staged pass, so that weights round alike; the block's own keys as two more
+// (from 640 tokens on), or by the fold kernel or the internal pass (one tile).  0: not this route.  By tiles per split, against the
+// register-staged pass and the combine (us a refresh step, head_dim 128): blocks of many tokens always (5 heads of 4300 rows, 3 splits, 12 /
+// 24 / 60 tiles 201 / 257 / 351 and 104 / 145 / 249; 12 heads of 1023, 5 splits, 75 / 108 / 156 and 57 / 77 / 112; head_dim 64, 4 heads of
+// 2728 rows, 5 splits, 65 / 86 / 115 and 54 / 63 / 87).  One tile: twice the partials have to be earned where the fold kernel reads them
+// (up to 4096 rows: batch 3, 168 rows of 8 heads, 6 splits, 24 / 36 / 60 tiles 72 / 104 / 159 and 77 / 96 / 131; head_dim 64 48 / 64 / 97
+// and 51 / 62 / 87), not where combine and internal pass do (batch 7, 152 rows, 3 splits, 12 / 24 tiles 50 / 78 and 47 / 66;
+// batch 3, 212 rows, 6 splits, 14 tiles, blocks of 53, 55 and 63).
+int step_streams(const fb_shape* s, int ns) {
+  const long long nrows = (long long)(s->n_q_heads / s->n_kv_heads) * s->block_len;
+  const int tiles = (s->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile;
+  if (s->dtype != FB_BF16 || ns < 2 || nrows <= fb::kRowsPerWgBf16 || 2 * ns > FB_MAX_SPLITS) return 0;
+  if (s->block_len > fb::kKeyTile && s->block_len < 640) return 0;
+  if (s->block_len <= fb::kKeyTile) return tiles >= (rows_of(s) > kFoldKernelMaxRows ? 6 + 4 * ns : 36) * ns ? 2 * ns : 0;
+  if (tiles < 10 * ns) return 0;
+  // Both ways by their rounds of 256 workgroups, in tiles of 256 rows: a tile of 128 rows takes the register-staged kernel as long as one of 256
+  // the row-pair kernel, a start and an end 4 and 5 tiles; the last split's workgroup runs the block too, here the block's streams
+  // fill what the prefix's leave; and ns + 1 more partials are written and read.  (4 heads of 2026 rows, 11933 keys, one full round
+  // there and a second one of the block's streams here: 75 us there, 80 here.)
+  const int btiles = (s->block_len + fb::kKeyTile - 1) / fb::kKeyTile, per = tiles / ns;
+  const long long heads = (long long)s->batch * s->n_kv_heads, wgs = heads * ((nrows + 127) / 128) * ns, rows256 = (nrows + 255) / 256;
+  const long long there = (wgs + 255) / 256 * (std::max(per, per - std::min(2 + btiles, per / 2) + btiles) + 4);
+  const long long a = per / 2 + 5, b = btiles / 2 + 5, na = heads * rows256 * 2 * ns, nb = heads * rows256 * 2, busy = na % 256;
+  const long long fit = busy ? (256 - busy) * (a / b) : 0;
+  const long long here = (na + 255) / 256 * a + (std::max(nb - fit, 0ll) + 255) / 256 * b + heads * nrows * (ns + 1) / (s->head_dim == 128 ? 6700 : 13400) ;
+  return here + here / 5 < there ? 2 * ns : 0;
+}
+
 fb_status check_key_block(const fb_shape* s, int32_t key_block, int32_t topk, int* nblk) {
   if (key_block <= 0 || topk < 0) return FB_ERR_SHAPE;
   if (key_block % fb::kKeyTile != 0) return FB_ERR_UNSUPPORTED;
@@ -284,6 +313,12 @@ fb::PassParams base_pass(const fb_shape* s, const void* q, const void* k, const 
   p.scale_log2 = eff_scale(s) * kLog2e;
   p.key_block = fb::kKeyTile;
   return p;
+}
+
+// Split partials of the dense passes, and one block-internal partial for fb_refresh_step.
+size_t pass_workspace(const fb_shape* s, int n_splits) {
+  const int ns = n_splits > 0 ? n_splits : std::max({auto_splits(s), dense_splits(s), heads_splits(s, 0)});
+  return ws_layout(s, ns, 2, 0, 1).total;
 }
 
 hipError_t launch_attn(const fb_shape* s, const fb::PassParams& p, fb::PassMode mode, hipStream_t st) {
@@ -363,8 +398,10 @@ int32_t fb_paged_splits(const fb_shape* shape) {
 size_t fb_workspace_bytes(const fb_shape* shape, int32_t key_block, int32_t topk, int32_t n_splits) {
   if (check_shape(shape) != FB_OK) return 0;
   if (n_splits < 0 || n_splits > FB_MAX_SPLITS) return 0;
-  const int ns = n_splits > 0 ? n_splits : std::max({auto_splits(shape), dense_splits(shape), heads_splits(shape, 0)});
-  size_t t = ws_layout(shape, ns, 2, 0, 1).total;   // + one block-internal partial for fb_refresh_step
+  size_t t = pass_workspace(shape, n_splits);
+  if (n_splits == 0) {
+    if (const int streams = step_streams(shape, auto_splits(shape))) t = std::max(t, ws_layout(shape, streams, 2, 0, 2).total);
+  }
   if (key_block != 0) {
     int nblk = 0;
     if (check_key_block(shape, key_block, topk, &nblk) != FB_OK) return 0;
@@ -558,7 +595,7 @@ fb_status fb_external_partial_builtin_ws(const fb_shape* shape, const void* q, c
                                          void* hip_stream) {
   fb_status st = check_shape(shape);
   if (st != FB_OK) return st;
-  if (fb_workspace_bytes(shape, 0, 0, 0) > kBuiltinWsBytes) return FB_ERR_WORKSPACE;   // too large for the built-in scratch
+  if (pass_workspace(shape, 0) > kBuiltinWsBytes) return FB_ERR_WORKSPACE;   // too large for the built-in scratch
   if (!q || !o_part || !m_part || !lse_part) return FB_ERR_NULL;      // host-side checks before any HIP call
   if (shape->prefix_len > 0 && (!k_prefix || !v_prefix)) return FB_ERR_NULL;
   void* ws = nullptr;
@@ -629,7 +666,7 @@ fb_status fb_refresh_step_prof(const fb_shape* shape, const void* q, const void*
                            (fours || (few_rows && (shape->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile >= odd_tiles * segs));
   const int ns = small_block ? segs : std::max(1, auto_splits(shape) - (shape->dtype == FB_F32 ? 1 : 0));
   const WsLayout w = ws_layout(shape, ns, 2, 0, 1);
-  const size_t need = shape->dtype == FB_F32 ? fb_workspace_bytes(shape, 0, 0, 0) : w.total;
+  const size_t need = shape->dtype == FB_F32 ? pass_workspace(shape, 0) : w.total;
   if (!workspace || workspace_bytes < need) return FB_ERR_WORKSPACE;
   if (shape->dtype == FB_BF16 && !small_block && ns == 1) {
     // Many rows per KV head, unsplit: the row-pair streaming kernel, once over the prefix (it writes the partial itself) and
@@ -691,6 +728,16 @@ fb_status fb_refresh_step_prof(const fb_shape* shape, const void* q, const void*
   }
   p.ws_o = (float*)(ws + w.o[0]); p.ws_m = (float*)(ws + w.m[0]); p.ws_l = (float*)(ws + w.l[0]);
   p.ws_o2 = (float*)(ws + w.o[1]); p.ws_m2 = (float*)(ws + w.m[1]); p.ws_l2 = (float*)(ws + w.l[1]);
+  const int streams = small_block || fold_internal ? 0 : step_streams(shape, ns);
+  const WsLayout w2 = ws_layout(shape, streams, 2, 0, 2);
+  const bool by_parity = streams > 0 && workspace_bytes >= w2.total;     // (below: a buffer of before, with the route of before)
+  if (by_parity) {
+    p.by_parity = 1;
+    p.nsplit = streams;
+    if (p.Bq <= fb::kKeyTile) p.k2 = p.v2 = nullptr;
+    p.ws_o = (float*)(ws + w2.o[0]); p.ws_m = (float*)(ws + w2.m[0]); p.ws_l = (float*)(ws + w2.l[0]);
+    p.ws_o2 = (float*)(ws + w2.o[1]); p.ws_m2 = (float*)(ws + w2.m[1]); p.ws_l2 = (float*)(ws + w2.l[1]);
+  }
   hipError_t e = timed_attn(shape, p, small_block || fold_internal ? fb::kPassDense : fb::kPassRefreshFused, stream, ev_begin, ev_attn_end);
   if (e != hipSuccess) return hip_fail(e);
 
@@ -706,13 +753,22 @@ fb_status fb_refresh_step_prof(const fb_shape* shape, const void* q, const void*
     in.o_final = o_part; in.m_final = m_part; in.l_final = lse_part;
     in.out = out; in.lse_out = lse_out;
     e = launch_attn(shape, in, fb::kPassInternal, stream);
-  } else if (small_block) {
+  } else if (by_parity && p.k2 == nullptr && rows_of(shape) > kFoldKernelMaxRows) {
+    c.fin_out = nullptr;
+    e = fb::launch_combine(c, stream);
+    if (e != hipSuccess) return hip_fail(e);
+    in.fold_ns = 0;
+    in.ext_o = o_part; in.ext_m = m_part; in.ext_lse = lse_part;
+    in.out = out; in.lse_out = lse_out;
+    e = launch_attn(shape, in, fb::kPassInternal, stream);
+  } else if (small_block || (by_parity && p.k2 == nullptr)) {
     c.blk_q = q; c.blk_k = k_block; c.blk_v = v_block;
     c.Hq = shape->n_q_heads; c.Hkv = shape->n_kv_heads; c.G = shape->n_q_heads / shape->n_kv_heads;
     c.scale_log2 = p.scale_log2;
     e = fb::launch_refresh_fold(c, stream);
   } else {
     c.blk_o = p.ws_o2; c.blk_m = p.ws_m2; c.blk_l = p.ws_l2;
+    c.blk_ns = by_parity ? 2 : 1;
     e = fb::launch_combine(c, stream);
   }
   if (e != hipSuccess) return hip_fail(e);

@@ -77,6 +77,7 @@ __device__ __forceinline__ Folded empty_folded() {
 }
 
 // Everything after the split fold: residual in/out, total, emission (shared by both kernels).
+template <bool TWO = false>                        // two partials of the block's own keys
 __device__ __forceinline__ void finish_row(const CombineParams& p, const Folded& sel, Folded res,
                                            bool have_res_set, size_t row, int c4) {
   if (!have_res_set && p.res_in_o != nullptr) {   // reuse: cached residual, natural-log units
@@ -97,6 +98,14 @@ __device__ __forceinline__ void finish_row(const CombineParams& p, const Folded&
     in.m2 = p.blk_m[row];
     in.l = p.blk_l[row];
     in.o = *(const float4*)(p.blk_o + row * p.D + c4 * 4);
+    if constexpr (TWO) {
+      const size_t at = (size_t)p.rows + row;
+      Folded odd;
+      odd.m2 = p.blk_m[at];
+      odd.l = p.blk_l[at];
+      odd.o = *(const float4*)(p.blk_o + at * p.D + c4 * 4);
+      in = fold_two(in, odd);
+    }
     const Folded f = fold_two(total, in);
     const float inv = f.l > 0.f ? 1.f / f.l : 0.f;
     const float4 r = make_float4(f.o.x * inv, f.o.y * inv, f.o.z * inv, f.o.w * inv);
@@ -182,6 +191,7 @@ __device__ __forceinline__ bool fold_row(const CombineParams& p, size_t row, Fol
 }
 
 // Few splits: one thread per (row, 4 columns) walks the splits.
+template <bool TWO>
 __global__ __launch_bounds__(256) void combine_kernel(const CombineParams p) {
   const int per_row = p.D / 4;
   const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
@@ -195,7 +205,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineParams p) {
   if (p.ws_o != nullptr && p.nsplit > 0) sel = fold_strided(p.ws_o, p.ws_m, p.ws_l, p.nsplit, f.rows, f.row, p.D, c4, 0, 1);
   const bool have_res_set = p.ws_o2 != nullptr;
   if (have_res_set) res = fold_strided(p.ws_o2, p.ws_m2, p.ws_l2, p.nsplit, f.rows, f.row, p.D, c4, 0, 1);
-  finish_row(p, sel, res, have_res_set, row, c4);
+  finish_row<TWO>(p, sel, res, have_res_set, row, c4);
 }
 
 // Many splits: one workgroup per row; NSL = 256/(D/4) thread groups each fold every NSL-th split
@@ -945,11 +955,14 @@ hipError_t launch_head_similarity(const float* o_a, const float* o_b, float* sim
 hipError_t launch_combine(const CombineParams& p, hipStream_t s) {
   const size_t n = (size_t)p.rows * (p.D / 4);
   if (n == 0) return hipSuccess;
-  // (one workgroup per row: not for the per-head refresh of many rows, most of whose rows are left alone)
-  if (p.nsplit >= 8 && p.ws_o != nullptr && p.heads_cap == 0)
+  // (one workgroup per row: not for the per-head refresh of many rows, most of whose rows are left alone, nor for the refresh step of
+  // many rows)
+  if (p.nsplit >= 8 && p.ws_o != nullptr && p.heads_cap == 0 && p.blk_ns < 2)
     hipLaunchKernelGGL(combine_wide_kernel, dim3((unsigned)p.rows), dim3(256), 0, s, p);
+  else if (p.blk_ns > 1)
+    hipLaunchKernelGGL(combine_kernel<true>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p);
   else
-    hipLaunchKernelGGL(combine_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(combine_kernel<false>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p);
   return hipGetLastError();
 }
 

@@ -143,14 +143,17 @@ struct PassParams {
   // streaming bf16 pass: 1 = splits alternate between the even and the odd XCD of a pair and the odd XCDs' splits are a
   // little shorter (see biased_range)
   int xcd_bias;
-  // dense pass of up to 128 rows, nseg > 0 and != nsplit: reference segments (halves_pass), cut and ordered as nseg splits would
-  // be, with their bias
-  int nseg, seg_bias;
   FastDiv div_rowtiles, div_nsplit, div_hkv;   // bf16 pass: decomposition of the linear workgroup index
   FastDiv div_page;                            // bf16 paged pass: key index -> page slot
   FastDiv div_bias;                            // streaming bf16 pass, xcd_bias: by 64 * nsplit
   FastDiv div_tpb;                             // streaming sparse passes: tile index -> key block (tiles per key block); per-head
                                                // refresh by rank: row -> head (block_len)
+  // dense pass of up to 128 rows, nseg > 0 and != nsplit: reference segments (halves_pass), cut and ordered as nseg splits would
+  // be, with their bias
+  int nseg, seg_bias;
+  // fused refresh pass by the row-pair kernel (many rows per KV head): an even nsplit, splits 2i and 2i + 1 with the even and the odd tiles of the i-th
+  // range, and with k2 != null two partials of the block's own keys, likewise, in set 1
+  int by_parity;
 };
 
 // Fold split partials (and optionally a cached residual) into final (o, m, lse) partials.
@@ -172,6 +175,7 @@ struct CombineParams {
   const void* blk_q; const void* blk_k; const void* blk_v;
   int Hq, Hkv, G; float scale_log2;
   FastDiv div_fold;                 // fold kernel: workgroups of a query head
+  int blk_ns;                       // partials at blk_o / blk_m / blk_l, rows of them each
 };
 
 struct SelectParams {

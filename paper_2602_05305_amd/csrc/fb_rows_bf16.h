@@ -121,6 +121,9 @@ template <int D, int MODE>
 __device__ __forceinline__ void rows_pass(const PassParams& p, unsigned char* ring) {
   using C = RCfg<D>;
   constexpr bool kHeads = MODE == kPassDenseHeads;
+  // refresh step in several splits: every split as two streams (below), and two more over the block's own keys
+  constexpr bool kFused = MODE == kPassRefreshFused;
+  constexpr bool kParity = kHeads || kFused;
   const int lane = threadIdx.x & 63, l32 = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
 
@@ -129,8 +132,11 @@ __device__ __forceinline__ void rows_pass(const PassParams& p, unsigned char* ri
   const int nwg = gridDim.x;
   const int nrows = p.G * p.Bq;
   int w = blockIdx.x;
+  bool own_block = false;                                    // (the prefix's workgroups are the first of the grid)
   if constexpr (!kHeads) {
-    const int bid = blockIdx.x, q8 = nwg / 8, r8 = nwg % 8;
+    const int npre = kFused ? p.B * p.Hkv * p.nsplit * (int)p.div_rowtiles.d : nwg;
+    own_block = kFused && w >= npre;
+    const int bid = own_block ? w - npre : w, n = own_block ? nwg - npre : npre, q8 = n / 8, r8 = n % 8;
     const int xcd = bid % 8, j = bid / 8;
     w = (xcd < r8 ? xcd * (q8 + 1) : r8 * (q8 + 1) + (xcd - r8) * q8) + j;
   }
@@ -138,7 +144,10 @@ __device__ __forceinline__ void rows_pass(const PassParams& p, unsigned char* ri
   const int rt = w - (int)(rest * p.div_rowtiles.d);
   const uint32_t unit = rest;
   int split = 0;
-  if constexpr (MODE != kPassInternal) {
+  if (kFused && own_block) {
+    split = (int)(rest & 1);
+    rest >>= 1;
+  } else if constexpr (MODE != kPassInternal) {
     const uint32_t r2 = fastdiv(rest, p.div_nsplit);
     split = (int)(rest - r2 * p.div_nsplit.d);
     rest = r2;
@@ -181,7 +190,7 @@ __device__ __forceinline__ void rows_pass(const PassParams& p, unsigned char* ri
     kvh = (int)(rest - (uint32_t)b * p.div_hkv.d);
   }
   const int bk = b * p.Hkv + kvh;
-  const int nkeys = p.nkeys;                                 // at least kRowsTiles tiles to a range (launch_stream sees to it)
+  const int nkeys = own_block ? p.Bq : p.nkeys;              // at least kRowsTiles tiles to a range (launch_stream sees to it)
   const int row0 = rt * C::ROWS;
   const size_t grow_base = (size_t)(b * p.Hq + kvh * p.G) * p.Bq;
   // Per-head refresh: row tiles are cut from the rows of the group's flagged heads, one head after the other; workgroups past the last
@@ -209,15 +218,25 @@ __device__ __forceinline__ void rows_pass(const PassParams& p, unsigned char* ri
     return r + (__shfl(head_of, k, 64) - k) * p.Bq;
   };
 
-  const unsigned char* __restrict__ Kg = (const unsigned char*)p.k + (size_t)bk * nkeys * C::ROWB;
-  const unsigned char* __restrict__ Vg = (const unsigned char*)p.v + (size_t)bk * nkeys * C::ROWB;
+  const unsigned char* __restrict__ Kg = (const unsigned char*)(own_block ? p.k2 : p.k) + (size_t)bk * nkeys * C::ROWB;
+  const unsigned char* __restrict__ Vg = (const unsigned char*)(own_block ? p.v2 : p.v) + (size_t)bk * nkeys * C::ROWB;
 
-  // ---- tiles of this workgroup: positions first, first + stride, ... of a range, rotated (per-head refresh, partials by rank:
-  // splits 2i and 2i + 1 take the even and the odd tiles of the i-th range)
+  // ---- tiles of this workgroup: positions first, first + stride, ... of a range, rotated (per-head refresh, partials by rank, and refresh
+  // step: splits 2i and 2i + 1 take the even and the odd tiles of the i-th range, the two tile groups of the register-staged kernel,
+  // whose references these are)
   const int total = (nkeys + C::KT - 1) / C::KT;
   TileRange tr = (MODE == kPassInternal) ? TileRange{0, total} : split_range(total, p.div_nsplit, split);
   uint32_t rsrc = (p.div_rowtiles.d == 1) ? blockIdx.x : unit;
   int stride = 1, first = 0;
+  if constexpr (kFused) {
+    const int pairs = p.nsplit / 2, range_i = own_block ? pairs - 1 : split >> 1;
+    tr = own_block ? TileRange{0, total} : split_range(total + p.blk_cost, pairs, range_i);
+    tr.begin = min(tr.begin, total);
+    tr.end = min(tr.end, total);
+    stride = 2;
+    first = split & 1;
+    rsrc = (uint32_t)(bk * pairs + range_i);
+  }
   if constexpr (kHeads) {
     if (direct) {
       tr = TileRange{0, total};
@@ -230,7 +249,7 @@ __device__ __forceinline__ void rows_pass(const PassParams& p, unsigned char* ri
     }
   }
   const int range = tr.end - tr.begin;
-  const int ntiles = kHeads ? (range - first + stride - 1) / stride : range;
+  const int ntiles = kParity ? (range - first + stride - 1) / stride : range;
   const int rot = ((MODE == kPassInternal && !p.rotate) || range <= 0) ? 0 : (int)((rsrc * 13u + (rsrc >> 5) * 7u) % (unsigned)range);
   // the ragged tile: its keys, and which of this workgroup's tiles it is (far from every one if none)
   const int nvalid = nkeys - (total - 1) * C::KT;
@@ -238,7 +257,7 @@ __device__ __forceinline__ void rows_pass(const PassParams& p, unsigned char* ri
   if (nvalid < C::KT && tr.end == total) {
     const int x = range - 1 - rot - first;
     if (x >= 0 && x % stride == 0) t_ragged = x / stride;
-    if (!kHeads) again = t_ragged + range;
+    if (!kParity) again = t_ragged + range;
   }
 
   const uint32_t ring_base = (uint32_t)(uintptr_t)ring;
@@ -261,7 +280,7 @@ __device__ __forceinline__ void rows_pass(const PassParams& p, unsigned char* ri
     for (int j = 0; j < C::NLOAD; ++j) off[j] = (uint32_t)(min(ld_row[j], last) * C::ROWB + chunk[j] * 16);
   };
   // One stream of tiles per operand: the address of the next tile, in rotated order.  Past the last tile it goes on, through the
-  // first ones again (per-head refresh: with the first tile of the range, which is whole): every iteration requests the same
+  // first ones again (two streams to a range: with the first tile of the range, which is whole): every iteration requests the same
   // number of loads, and what these bring is never read.
   struct Stream {
     const unsigned char *next, *first, *src;
@@ -278,7 +297,7 @@ __device__ __forceinline__ void rows_pass(const PassParams& p, unsigned char* ri
   };
   Stream kst = open_stream(Kg), vst = open_stream(Vg);
   auto step_stream = [&](Stream& st) __attribute__((always_inline)) {
-    if constexpr (kHeads) {
+    if constexpr (kParity) {
       st.src = st.left > 0 ? st.next : st.first;
       --st.left;
       st.at += stride;
@@ -324,7 +343,7 @@ __device__ __forceinline__ void rows_pass(const PassParams& p, unsigned char* ri
     wait_vm<0>();
   }
   __syncthreads();
-  if constexpr (kHeads) {
+  if constexpr (kParity) {
     if (row0 + wave * 64 >= nflagged) {
       // no rows for this wavefront: its share of the loads, at the barriers of the loop below, and nothing else
       if (ntiles > 0) {
@@ -648,16 +667,17 @@ __device__ __forceinline__ void rows_pass(const PassParams& p, unsigned char* ri
       // (a branch of its own down to the stores: sharing them with the final partial's costs them their non-temporal hint, and these
       // partials, read once by the combine, then displace K and V in L2)
       const size_t wrow = ((size_t)(split * p.B + b) * (kHeads ? p.heads_cap : p.Hkv) + (kHeads ? rank : kvh)) * nrows + row;
+      float* __restrict__ w_o = own_block ? p.ws_o2 : p.ws_o;
 #pragma unroll
       for (int db = 0; db < C::NDB; ++db)
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
           const f32x4 o4 = {o[g][db][4 * q4], o[g][db][4 * q4 + 1], o[g][db][4 * q4 + 2], o[g][db][4 * q4 + 3]};
-          __builtin_nontemporal_store(o4, (f32x4*)(p.ws_o + wrow * D + 32 * db + 8 * q4 + 4 * h));
+          __builtin_nontemporal_store(o4, (f32x4*)(w_o + wrow * D + 32 * db + 8 * q4 + 4 * h));
         }
       if (h == 0) {
-        p.ws_m[wrow] = mold[g];
-        p.ws_l[wrow] = l_row;
+        (own_block ? p.ws_m2 : p.ws_m)[wrow] = mold[g];
+        (own_block ? p.ws_l2 : p.ws_l)[wrow] = l_row;
       }
     }
   }

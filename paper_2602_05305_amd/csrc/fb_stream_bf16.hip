@@ -1038,8 +1038,13 @@ hipError_t launch_stream(const PassParams& p, hipStream_t s) {
   using C = std::conditional_t<LAYOUT == kRowPair, RCfg<D>, SCfg<D, whole_layout(LAYOUT), (MODE == kPassSparseRefresh) ? 2 : 1, NRG>>;
   // row pairs: the shortest range has to hold what is loaded ahead (the routes here ask for more); per-head refresh: two splits
   // share a range
-  if (LAYOUT == kRowPair && (p.nkeys + C::KT - 1) / C::KT < kRowsTiles * (MODE == kPassDenseHeads ? (p.nsplit + 1) / 2 : p.nsplit))
+  if (LAYOUT == kRowPair && (p.nkeys + C::KT - 1) / C::KT < kRowsTiles * (MODE == kPassDenseHeads || MODE == kPassRefreshFused ? (p.nsplit + 1) / 2 : p.nsplit))
     return hipErrorInvalidValue;
+  if (MODE == kPassRefreshFused) {
+    // the last range, blk_cost tiles shorter, and the block's own
+    const int pairs = p.nsplit / 2, tiles = (p.nkeys + C::KT - 1) / C::KT, all = tiles + p.blk_cost;
+    if (p.nsplit % 2 != 0 || pairs < 1 || all / pairs - p.blk_cost < kRowsTiles || (p.k2 != nullptr && (p.Bq + C::KT - 1) / C::KT < kRowsTiles)) return hipErrorInvalidValue;
+  }
   auto kern = attn_stream_kernel<D, MODE, LAYOUT, NRG>;
   static LdsLimit lim;
   hipError_t e = raise_lds_limit(kern, C::LDS, lim, C::LDS);
@@ -1049,6 +1054,7 @@ hipError_t launch_stream(const PassParams& p, hipStream_t s) {
   long long nwg = (long long)p.B * p.Hkv * ntile_rows * p.nsplit;
   if (MODE == kPassDensePaged) nwg = (((long long)p.B * p.Hkv * p.nsplit + 7) / 8) * 8 * ntile_rows;
   if (MODE == kPassDenseHeads && LAYOUT == kRowPair) nwg = (long long)p.B * (p.heads_cap * p.nsplit + p.Hkv) * ntile_rows;
+  if (MODE == kPassRefreshFused && p.k2 != nullptr) nwg += (long long)p.B * p.Hkv * ntile_rows * 2;
   if (nwg >= (1ll << 31)) return hipErrorInvalidValue;
   PassParams q = p;
   if (MODE == kPassDensePaged) q.div_page = make_fastdiv((uint32_t)p.page_size);
@@ -1140,6 +1146,7 @@ hipError_t launch_stream_d(const PassParams& p, PassMode mode, hipStream_t s) {
     case kPassSparseRefresh: return launch_key_split<D, kPassSparseRefresh>(p, s);
     case kPassInternal:
       return launch_stream<D, kPassInternal, kRowPair>(p, s);
+    case kPassRefreshFused: return launch_stream<D, kPassRefreshFused, kRowPair>(p, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1167,6 +1174,7 @@ bool stream_bf16_covers(const PassParams& p, int D, PassMode mode) {
       // 423 / 520 and 134 / 163 / 219 / 330 / 427 / 513; head_dim 64, two rows a key, 512 / 704 / 1100 / 1280 36.4 / 61.5 / 140 /
       // 158 and 39.9 / 65.1 / 141 / 155; one round, 32 heads of 1024 / 1536 rows 40.7 / 53.7 and 38.9 / 52.0).
       return internal_many_rows(p) && tiles >= 16;
+    case kPassRefreshFused: return p.by_parity != 0;
     default: return false;
   }
 }

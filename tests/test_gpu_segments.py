@@ -79,3 +79,35 @@ def test_references_that_move_between_segments(Bq, factor):
     fb.fb_refresh_step(shape, q, k, v, kb, vb, ext.o, ext.m, ext.lse, out, None, T.workspace(shape))
     T.assert_close(out.double().cpu().numpy(), want["out"], "bf16", w.name + " out")
     T.check_partial(ext.numpy(), want["ext"], "bf16", w.name + " ext of the step")
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,P,Bq", [
+    (1, 8, 8, 128, 64 * 60, 700),        # 6 splits of 10 tiles, the least; the block's 11 tiles in two streams
+    (1, 8, 8, 64, 64 * 71 + 9, 641),     # a ragged last tile, a block of one row more than whole tiles
+    (1, 12, 6, 128, 64 * 97 - 1, 650),   # 1300 rows per KV head, 5 splits
+    (9, 24, 8, 128, 64 * 25 + 3, 43),    # 129 rows, 2 splits: combine and internal pass
+    (4, 24, 8, 64, 64 * 144 + 31, 43),   # 4 splits: fold kernel
+])
+def test_refresh_step_in_streams_of_even_and_odd_tiles(B, Hq, Hkv, d, P, Bq):
+    """More than 128 rows per KV head in several splits; a workspace without room for the streams gets the former route."""
+    w = wl.Workload(f"st_{B}_{Hq}_{d}_{P}", B, Hq, Hkv, d, P, Bq, 1, 1, "bf16", 1.0)
+    Kp, Vp = wl.make_prefix(w, 609)
+    step = wl.make_block_steps(w, 609)[0]
+    want = orc.run_block_dense(Kp, Vp, [step], 1)[0]
+    q, kb, vb, k, v = (T.to_dev(x, "bf16") for x in (*step, Kp, Vp))
+    shape = T.shape_of(w)
+    ns = -(-256 // (B * Hkv * -(-(Hq // Hkv * Bq) // 128)))
+    rows = B * Hq * Bq
+    small = sum(-(-n * rows * x * 4 // 256) * 256 for n in (ns, 1) for x in (d, 1, 1)) + 256
+    assert small < fb.fb_workspace_bytes(shape)
+    results = []
+    for size in (fb.fb_workspace_bytes(shape), small):
+        ext, ws = T.Partial(w), torch.zeros(size, device=T.DEV, dtype=torch.uint8)
+        out, lse = torch.empty_like(q), torch.empty(q.shape[:3], device=T.DEV)
+        fb.fb_refresh_step(shape, q, k, v, kb, vb, ext.o, ext.m, ext.lse, out, lse, ws)
+        T.assert_close(out.double().cpu().numpy(), want["out"], "bf16", w.name + " out")
+        T.assert_close(lse.double().cpu().numpy(), want["lse"], "bf16", w.name + " lse", lse=True)
+        T.check_partial(ext.numpy(), want["ext"], "bf16", w.name + " ext")
+        results.append(_normalised(ext))
+    # the same references: fp32 sums only
+    assert float((results[0] - results[1]).abs().max()) <= 1e-5 * float(results[1].square().mean().sqrt())
