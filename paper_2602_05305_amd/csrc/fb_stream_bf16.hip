@@ -17,7 +17,8 @@
 //              residual key blocks); a tile's scores are computed once and go to the set the row's head routes
 //              the tile's key block to, so the eight wavefronts stay evenly loaded whatever the selection.
 //              At head_dim 64 two tiles per barrier.
-//   kTileSplit the same with whole tiles: half h takes every other tile, two tiles per barrier.
+//   kTileSplit the same with whole tiles: half h takes every other tile, two tiles per barrier.  (Refresh step with few splits; internal
+//              pass of one round of workgroups.)
 //   kRowPair   256 rows, 4 wavefronts of 64 rows and whole tiles (many rows per KV head): fb_rows_bf16.h.
 //   kRowPairShort  256 rows, wavefront w owns rows [32 w, +32) and whole tiles, two tiles per barrier: dense streams too short for
 //              kRowPair, whose ends cost more (its first scores stand alone, it scores a tile past the last one, and four
@@ -384,7 +385,7 @@ __device__ __forceinline__ void halves_pass(const PassParams& p, unsigned char* 
   constexpr int NSETS = (MODE == kPassSparseRefresh) ? 2 : 1;
   using C = SCfg<D, LAYOUT, NSETS, NRG>;
   static_assert(MODE == kPassDense || MODE == kPassDenseHeads || MODE == kPassDensePaged || MODE == kPassSparseReuse ||
-                    MODE == kPassSparseRefresh, "modes of this form");
+                    MODE == kPassSparseRefresh || (MODE == kPassInternal && LAYOUT == kTileSplit), "modes of this form");
   constexpr bool kHalves = LAYOUT != kRowPairShort;
   static_assert(kHalves || MODE == kPassDense, "one wavefront per row group: dense pass");
   // Whole tiles and head_dim 64: two tiles per barrier (tiles t, t+1 are computed while t+2, t+3 are in flight); key split at 128:
@@ -589,7 +590,7 @@ __device__ __forceinline__ void halves_pass(const PassParams& p, unsigned char* 
     }
     return r;
   };
-  const int rot = PARTS || ntiles <= 0 ? 0 : (int)((rsrc * 13u + (rsrc >> 5) * 7u) % (unsigned)ntiles);
+  const int rot = PARTS || MODE == kPassInternal || ntiles <= 0 ? 0 : (int)((rsrc * 13u + (rsrc >> 5) * 7u) % (unsigned)ntiles);
   const uint32_t* __restrict__ bmask = p.blk_mask ? p.blk_mask + (size_t)bk * p.nblk : nullptr;
   const int32_t* __restrict__ ulist = p.union_list ? p.union_list + (size_t)bk * p.nblk : nullptr;
   const uint32_t* __restrict__ umask = p.union_mask ? p.union_mask + (size_t)bk * p.nblk : nullptr;
@@ -892,6 +893,13 @@ __device__ __forceinline__ void halves_pass(const PassParams& p, unsigned char* 
       for (int u = 0; u < 2; ++u) refill(t, u);
       const int k0 = half ? qk0[1] : qk0[0];
       const uint32_t mask = half ? qmask[1] : qmask[0];
+      if constexpr (MODE == kPassInternal) {
+        if (t == 0 && half) {                                        // one reference for both streams, that of the first tile
+          f32x16 s[C::NKB];
+          tile_scores<D, C::NKB>(s, qreg, ring, kaddr, kb0);
+          tile_reference<C::NDB, C::NKB>(acc, s, kb0, p.scale_log2, min(C::KT, nkeys - qk0[0]), h);
+        }
+      }
       advance();
       if (t + half < ntiles) half_tile(ring + ((t + half) % C::NS) * C::STAGE, k0, mask);
     }
@@ -973,7 +981,42 @@ __device__ __forceinline__ void halves_pass(const PassParams& p, unsigned char* 
 
   // ---- epilogue
   const float l_row = sum_halves(acc.l);
-  {
+  if constexpr (MODE == kPassInternal) {
+    // Eq. 8-9 with the cached pair expressed through (o, m, lse): A_out e^{L_out-M} = o e^{m-M}
+    if (!row_ok) return;
+    const bool has_ext = p.ext_o != nullptr;
+    float me2 = -INFINITY, le = 0.f;
+    f32x4 e[NDBK * 4];
+    if (has_ext) {
+#pragma unroll
+      for (int i = 0; i < NDBK * 4; ++i) e[i] = *(const f32x4*)(p.ext_o + grow * D + 32 * (db_keep + i / 4) + 8 * (i % 4) + 4 * h);
+      const float em = p.ext_m[grow], el = p.ext_lse[grow];
+      if (el != -INFINITY) {
+        me2 = em * kLog2e;
+        le = exp2f((el - em) * kLog2e);
+      }
+    }
+    const float M2 = fmaxf(me2, acc.m);
+    const float Mu = (M2 == -INFINITY) ? 0.f : M2;
+    const float we = exp2f(me2 - Mu), wi = exp2f(acc.m - Mu);
+    const float den = le * we + l_row * wi;
+    const float inv = den > 0.f ? 1.f / den : 0.f;
+    __bf16* out = (__bf16*)p.out + grow * D;
+#pragma unroll
+    for (int db = 0; db < NDBK; ++db)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const f32x4 x = has_ext ? e[db * 4 + q4] : f32x4{0.f, 0.f, 0.f, 0.f};
+        float r[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r[i] = (acc.o[db][4 * q4 + i] * wi + x[i] * we) * inv;
+        u32x2 pk;
+        pk.x = pack_bf16x2(r[0], r[1]);
+        pk.y = pack_bf16x2(r[2], r[3]);
+        *(u32x2*)(out + 32 * (db_keep + db) + 8 * q4 + 4 * h) = pk;
+      }
+    if (p.lse_out != nullptr && h == 0 && half == 0) p.lse_out[grow] = den > 0.f ? (M2 + log2f(den)) * kLn2 : -INFINITY;
+  } else {
     if (p.direct) {
       // single split: this is the final partial.  Same conversion as the split combine: m is rounded when
       // converted to natural-log units, o is rescaled to the reference consumers recover from it.
@@ -1120,6 +1163,21 @@ inline bool short_row_pairs(const PassParams& p) {
   return (p.nkeys + kKeyTile - 1) / kKeyTile < kShortRowTiles * p.nsplit;
 }
 
+// Internal pass in two streams of tiles per row group (kTileSplit, both with the reference of the first tile): the most workgroups that
+// are one round, of 1, 2 or 4 row groups; 0: another kernel.  Without splits a pass of this kind leaves most of the chip idle or, by
+// the register-staged kernel's column split, computes every score four times (us, there and here, head_dim 64 / 128: one row group, 4
+// heads of 700 / 1300 rows 14.1 / 23.9 and 11.2 / 16.9, 16.5 / 27.4 and 14.8 / 22.7; two, 4 heads of 2332 39 and 26, 65 and 36; four, 5 heads of
+// 4300 69 and 47, 84 and 67, 16 of 2048 (row pairs there) 40 and 27, 56 and 42).  Short blocks are over before the second stream
+// pays: one row group 4 / 5 tiles (3 tiles 7.6 and 8.4), two 6 / 3 (5 tiles at head_dim 64 8.5 and 8.6), four 6 (5 tiles 9.2 and 9.7).
+inline int internal_streams(const PassParams& p, int D) {
+  if (p.fold_ns > 0 || p.rotate) return 0;      // (rotated: another first tile)
+  const long long heads = (long long)p.B * p.Hkv, nrows = (long long)p.G * p.Bq;
+  const int tiles = (p.nkeys + kKeyTile - 1) / kKeyTile;
+  const int nrg = heads * ((nrows + 31) / 32) <= 256 ? 1 : heads * ((nrows + 63) / 64) <= 256 ? 2 : heads * ((nrows + 127) / 128) <= 256 ? 4 : 0;
+  const int least = nrg == 1 ? (D == 64 ? 4 : 5) : nrg == 2 ? (D == 64 ? 6 : 3) : 6;
+  return tiles >= least ? nrg : 0;
+}
+
 template <int D>
 hipError_t launch_stream_d(const PassParams& p, PassMode mode, hipStream_t s) {
   const int nrows = p.G * p.Bq;
@@ -1145,7 +1203,12 @@ hipError_t launch_stream_d(const PassParams& p, PassMode mode, hipStream_t s) {
     case kPassSparseReuse: return launch_key_split<D, kPassSparseReuse>(p, s);
     case kPassSparseRefresh: return launch_key_split<D, kPassSparseRefresh>(p, s);
     case kPassInternal:
-      return launch_stream<D, kPassInternal, kRowPair>(p, s);
+      switch (internal_streams(p, D)) {
+        case 1: return launch_stream<D, kPassInternal, kTileSplit, 1>(p, s);
+        case 2: return launch_stream<D, kPassInternal, kTileSplit, 2>(p, s);
+        case 4: return launch_stream<D, kPassInternal, kTileSplit, 4>(p, s);
+        default: return launch_stream<D, kPassInternal, kRowPair>(p, s);
+      }
     case kPassRefreshFused: return launch_stream<D, kPassRefreshFused, kRowPair>(p, s);
     default: return hipErrorInvalidValue;
   }
@@ -1173,7 +1236,7 @@ bool stream_bf16_covers(const PassParams& p, int D, PassMode mode) {
       // less (us, there and here: 128 KV heads of 2048 rows, blocks of 512 / 520 / 704 / 900 / 1100 / 1280 117 / 143 / 202 / 322 /
       // 423 / 520 and 134 / 163 / 219 / 330 / 427 / 513; head_dim 64, two rows a key, 512 / 704 / 1100 / 1280 36.4 / 61.5 / 140 /
       // 158 and 39.9 / 65.1 / 141 / 155; one round, 32 heads of 1024 / 1536 rows 40.7 / 53.7 and 38.9 / 52.0).
-      return internal_many_rows(p) && tiles >= 16;
+      return internal_streams(p, D) > 0 || (internal_many_rows(p) && tiles >= 16);
     case kPassRefreshFused: return p.by_parity != 0;
     default: return false;
   }
