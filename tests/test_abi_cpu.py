@@ -358,3 +358,50 @@ def test_external_kernel_name_follows_the_launch_rules():
 def test_dense_row_pairs_by_tiles_per_split(kw, layout):
     shape = _ok_shape(**dict(dict(n_q_heads=64, n_kv_heads=8, head_dim=128, block_len=32, dtype="bf16"), **kw))
     assert fb.fb_external_kernel_name(shape) == f"attn_stream_kernel<{shape.head_dim}, 0, {layout}, 4>"
+
+
+def test_native_calls_marshal_as_the_python_ones():
+    """The native form of the binding passes the same C arguments, in the same order, as the Python functions it stands for."""
+    import ctypes
+    import inspect
+    if fb._fbcall is None:
+        pytest.skip("fb_call.c is not built")
+
+    class Tensor:
+        def __init__(self, at):
+            self.at = at
+
+        def data_ptr(self):
+            return self.at
+
+        def numel(self):
+            return self.at // 16
+
+        def element_size(self):
+            return 4
+
+    python = {"__name__": fb.__name__, "__file__": fb.__file__, "__package__": fb.__package__}
+    exec(compile(inspect.getsource(fb).split("\n# The entry points in native form")[0], fb.__file__, "exec"), python)
+    seen = []
+    take = ctypes.CFUNCTYPE(ctypes.c_int, *[ctypes.c_int64] * 20)(lambda *a: seen.append(a) or 0)
+    shape, kv = _ok_shape(), fb.fb_paged_kv()
+    for name, kinds in fb._KINDS.items():
+        fn = python[name]
+        names = list(inspect.signature(fn).parameters)
+        values = {n: shape if n == "shape" else kv if n == "kv" else 7 + i if n in ("key_block", "topk", "mode", "n_splits", "n_active_heads", "stream")
+                  else Tensor(4096 * (i + 1)) for i, n in enumerate(names)}
+        for left_out in ([], ["lse_out", "mass_out", "o_part"], [n for n in names if n in ("workspace",) and name == "fb_select_topk"]):
+            args = {n: None if n in left_out else v for n, v in values.items()}
+            want = []
+
+            class Lib:
+                def __getattr__(self, _):
+                    return lambda *a: want.append(a) or 0
+            python["load_library"] = Lib
+            fn(**args)
+            kinds_, order = kinds if isinstance(kinds, tuple) else (kinds, " ".join(names))
+            native = fb._fbcall.Call(name, tuple(names), fn.__defaults__ or (), kinds_, tuple(names.index(x) for x in order.split()),
+                                     lambda _: ctypes.cast(take, ctypes.c_void_p).value, lambda: 0, fb._check, fb.fb_shape, fb.fb_paged_kv)
+            native(*args.values()) if not left_out else native(**args)
+            flat = [ctypes.addressof(a._obj) if hasattr(a, "_obj") else a or 0 for a in want[0]]
+            assert list(seen[-1][:len(flat)]) == flat and not any(seen[-1][len(flat):]), name
