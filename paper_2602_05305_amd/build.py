@@ -20,8 +20,8 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libflashblock.so")
 CALIB_LIB = os.path.join(HERE, "libfbcalib.so")
-CALIB_CALL_LIB = os.path.join(HERE, "_fbcall.so")          # host code only: the binding's native marshalling
-SOURCES = ["fb_calib.hip"]
+CALL_LIB = os.path.join(HERE, "_fbcall.so")          # host code only: the binding's native marshalling
+CALIB_SOURCES = ["fb_calib.hip"]
 SOURCES = ["fb_api.hip", "fb_attn_f32.hip", "fb_attn_bf16.hip", "fb_stream_bf16.hip", "fb_aux.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
