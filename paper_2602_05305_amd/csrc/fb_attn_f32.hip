@@ -73,29 +73,9 @@ struct FState {
   }
 };
 
-template <int D, int RB, int WR>
-__device__ __forceinline__ void f32_tile(FState<RB, D / 16>& st, const f32x4 (&q)[RB][D / 16],
-                                         const unsigned char* __restrict__ stage, const uint32_t (&kaddr)[D / 16],
-                                         const uint32_t (&vaddr)[D / 16], float scale_log2, int key0, int nvalid) {
-  using C = FCfg<D, RB, WR>;
-  // two accumulator chains at least: a chain's product waits for the one before it
-  constexpr int NC = RB == 1 ? 2 : 1;
-  f32x4 s[RB], part[NC][RB];
-#pragma unroll
-  for (int c = 0; c < NC; ++c)
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) part[c][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int j = 0; j < C::NQ; ++j) {
-    const f32x4 a = *(const f32x4*)(stage + kaddr[j]);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
-        part[i % NC][rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], q[rb][j][i], part[i % NC][rb], 0, 0, 0);
-  }
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) s[rb] = NC == 1 ? part[0][rb] : part[0][rb] + part[NC - 1][rb];
+// Online softmax with an exact running maximum; s becomes the weights.
+template <int RB, int NDB>
+__device__ __forceinline__ void f32_softmax(FState<RB, NDB>& st, f32x4 (&s)[RB], float scale_log2, int key0, int nvalid) {
   // s[rb][r] = raw dot product of row lane%16 with key key0 + r of the tile (key0 includes the lane's 4 (lane/16))
   if (nvalid < kKeyTile) {
 #pragma unroll
@@ -121,11 +101,138 @@ __device__ __forceinline__ void f32_tile(FState<RB, D / 16>& st, const f32x4 (&q
     st.m[rb] = m_new;
     if (__any(alpha != 1.f)) {
 #pragma unroll
-      for (int db = 0; db < C::NDB; ++db)
+      for (int db = 0; db < NDB; ++db)
 #pragma unroll
         for (int r = 0; r < 4; ++r) st.o[rb][db][r] *= alpha;
     }
   }
+}
+
+// An fp32 value as the sum of three bf16 values, exactly: its upper 8 bits, the next 8 (rounded), the rest.  Of the nine products of two
+// such sums the six largest are kept; what is left out is below 2^-23 of the product, with alternating signs.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+struct Parts {
+  u32x4 h, m, l;       // pairs of bf16
+};
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+  h = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
+  const float ra = a - __uint_as_float(ua & 0xffff0000u), rb = b - __uint_as_float(ub & 0xffff0000u);
+  bf16x2 mid;
+  mid[0] = (__bf16)ra;
+  mid[1] = (__bf16)rb;
+  m = __builtin_bit_cast(uint32_t, mid);
+  l = __builtin_amdgcn_perm(__float_as_uint(rb - __uint_as_float(m & 0xffff0000u)), __float_as_uint(ra - __uint_as_float(m << 16)), 0x07060302u);
+}
+__device__ __forceinline__ Parts split_parts(const f32x4& a, const f32x4& b) {
+  Parts p;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    uint32_t h, m, l;
+    split_pair(a[2 * i], a[2 * i + 1], h, m, l);
+    p.h[i] = h; p.m[i] = m; p.l[i] = l;
+    split_pair(b[2 * i], b[2 * i + 1], h, m, l);
+    p.h[2 + i] = h; p.m[2 + i] = m; p.l[2 + i] = l;
+  }
+  return p;
+}
+__device__ __forceinline__ f32x4 mfma_parts(const u32x4& a, const u32x4& b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// Two row blocks: products on the bf16 matrix cores.  The fp32 ones take 32 cycles for 16 x 16 x 4, the bf16 ones 16 for 16 x 16 x 32,
+// so that six of them and the splitting of K and V (11 vector instructions a pair of values, once for both row blocks) take half the
+// time of one: 32 / 8 heads, 128 rows a KV head, 4111 keys, head_dim 128, MEASURED.  With one row block the splitting costs what it saves.
+// Sums: the products of the upper parts in one chain, the small ones in another; its error against 64 bits is no larger (4111 keys
+// MEASURED).
+template <int D>
+struct QParts {
+  Parts q[2][D / 32];
+};
+template <int D, int WR>
+__device__ __forceinline__ void f32_tile_parts(FState<2, D / 16>& st, const QParts<D>& q, const unsigned char* __restrict__ stage,
+                                               const uint32_t (&kaddr)[D / 16], const uint32_t (&vaddr)[D / 16], float scale_log2,
+                                               int key0, int nvalid) {
+  using C = FCfg<D, 2, WR>;
+  f32x4 s[2], small[2];
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb) s[rb] = small[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < D / 32; ++j) {
+    // the lane's eight contraction elements of a step: columns 16 (2 j) + 4 g .. + 3 and 16 (2 j + 1) + 4 g .. + 3, as the queries have them
+    const Parts k = split_parts(*(const f32x4*)(stage + kaddr[2 * j]), *(const f32x4*)(stage + kaddr[2 * j + 1]));
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) s[rb] = mfma_parts(k.h, q.q[rb][j].h, s[rb]);
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) small[rb] = mfma_parts(k.h, q.q[rb][j].l, small[rb]);
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) small[rb] = mfma_parts(k.h, q.q[rb][j].m, small[rb]);
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) small[rb] = mfma_parts(k.m, q.q[rb][j].m, small[rb]);
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) small[rb] = mfma_parts(k.m, q.q[rb][j].h, small[rb]);
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) small[rb] = mfma_parts(k.l, q.q[rb][j].h, small[rb]);
+  }
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb) s[rb] += small[rb];
+  f32_softmax<2, C::NDB>(st, s, scale_log2, key0, nvalid);
+  // contraction elements 0 .. 3 of a lane: its four keys in one part, 4 .. 7: the same keys in another, so that a product of 32 takes
+  // two of the six: (h, m) x (h, h), (h, m) x (m, m), (l, h) x (h, l)
+  u32x4 p_hh[2], p_mm[2], p_hl[2];
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb) {
+    uint32_t h0, m0, l0, h1, m1, l1;
+    split_pair(s[rb][0], s[rb][1], h0, m0, l0);
+    split_pair(s[rb][2], s[rb][3], h1, m1, l1);
+    p_hh[rb] = u32x4{h0, h1, h0, h1};
+    p_mm[rb] = u32x4{m0, m1, m0, m1};
+    p_hl[rb] = u32x4{h0, h1, l0, l1};
+  }
+#pragma unroll
+  for (int db = 0; db < C::NDB; ++db) {
+    float v[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = *(const float*)(stage + C::OPB + vaddr[db] + r * C::ROWB);
+    uint32_t h0, m0, l0, h1, m1, l1;
+    split_pair(v[0], v[1], h0, m0, l0);
+    split_pair(v[2], v[3], h1, m1, l1);
+    const u32x4 hm = {h0, h1, m0, m1}, lh = {l0, l1, h0, h1};
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) st.o[rb][db] = mfma_parts(lh, p_hl[rb], st.o[rb][db]);
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) st.o[rb][db] = mfma_parts(hm, p_mm[rb], st.o[rb][db]);
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) st.o[rb][db] = mfma_parts(hm, p_hh[rb], st.o[rb][db]);
+  }
+}
+
+template <int D, int RB, int WR>
+__device__ __forceinline__ void f32_tile(FState<RB, D / 16>& st, const f32x4 (&q)[RB][D / 16],
+                                         const unsigned char* __restrict__ stage, const uint32_t (&kaddr)[D / 16],
+                                         const uint32_t (&vaddr)[D / 16], float scale_log2, int key0, int nvalid) {
+  using C = FCfg<D, RB, WR>;
+  // two accumulator chains at least: a chain's product waits for the one before it
+  constexpr int NC = RB == 1 ? 2 : 1;
+  f32x4 s[RB], part[NC][RB];
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) part[c][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < C::NQ; ++j) {
+    const f32x4 a = *(const f32x4*)(stage + kaddr[j]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+        part[i % NC][rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], q[rb][j][i], part[i % NC][rb], 0, 0, 0);
+  }
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) s[rb] = NC == 1 ? part[0][rb] : part[0][rb] + part[NC - 1][rb];
+  f32_softmax<RB, C::NDB>(st, s, scale_log2, key0, nvalid);
 #pragma unroll
   for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -282,11 +389,22 @@ __global__ __launch_bounds__(256 * WR * TG, 1) void attn_f32_kernel(const PassPa
 #pragma unroll
     for (int j = 0; j < C::NQ; ++j) q[rb][j] = *(const f32x4*)(qr + 16 * j);
   }
+  constexpr bool kParts = RB == 2;
+  QParts<D> qp;
+  if constexpr (kParts) {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int j = 0; j < D / 32; ++j) qp.q[rb][j] = split_parts(q[rb][2 * j], q[rb][2 * j + 1]);
+  }
   // the wait for the queries belongs here: in the loop it would also wait for the tiles in flight
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-    for (int j = 0; j < C::NQ; ++j) asm volatile("" ::"v"(q[rb][j]));
+    for (int j = 0; j < C::NQ; ++j) {
+      if constexpr (kParts) asm volatile("" ::"v"(qp.q[rb][j / 2].h));
+      else asm volatile("" ::"v"(q[rb][j]));
+    }
   bool have1 = have0 && next_tile(t1);
   if (have1) issue(t1, tg + TG);
 
@@ -333,10 +451,12 @@ __global__ __launch_bounds__(256 * WR * TG, 1) void attn_f32_kernel(const PassPa
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
     const int key0 = 16 * wk + 4 * g4;
-    if (NSETS > 1 && !t0.is_sel)
-      f32_tile<D, RB, WR>(sets[NSETS - 1], q, stage, kaddr, vaddr, p.scale_log2, key0, nvalid);
-    else
-      f32_tile<D, RB, WR>(sets[0], q, stage, kaddr, vaddr, p.scale_log2, key0, nvalid);
+    auto tile = [&](FState<RB, C::NDB>& st) __attribute__((always_inline)) {
+      if constexpr (kParts) f32_tile_parts<D, WR>(st, qp, stage, kaddr, vaddr, p.scale_log2, key0, nvalid);
+      else f32_tile<D, RB, WR>(st, q, stage, kaddr, vaddr, p.scale_log2, key0, nvalid);
+    };
+    if (NSETS > 1 && !t0.is_sel) tile(sets[NSETS - 1]);
+    else tile(sets[0]);
     const bool have2 = TG > 1 ? have3 : have1 && next_tile(t2);      // workgroup-uniform (several groups: group-uniform)
     if constexpr (TG > 1) {
       t2 = t3;
