@@ -116,14 +116,10 @@ struct Parts {
   u32x4 h, m, l;       // pairs of bf16
 };
 __device__ __forceinline__ void split_pair(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
   h = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
   const float ra = a - __uint_as_float(ua & 0xffff0000u), rb = b - __uint_as_float(ub & 0xffff0000u);
-  bf16x2 mid;
-  mid[0] = (__bf16)ra;
-  mid[1] = (__bf16)rb;
-  m = __builtin_bit_cast(uint32_t, mid);
+  asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(m) : "v"(ra), "v"(rb));      // (the compiler makes two of it)
   l = __builtin_amdgcn_perm(__float_as_uint(rb - __uint_as_float(m & 0xffff0000u)), __float_as_uint(ra - __uint_as_float(m << 16)), 0x07060302u);
 }
 __device__ __forceinline__ Parts split_parts(const f32x4& a, const f32x4& b) {
@@ -142,11 +138,15 @@ __device__ __forceinline__ f32x4 mfma_parts(const u32x4& a, const u32x4& b, cons
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// Two row blocks: products on the bf16 matrix cores.  The fp32 ones take 32 cycles for 16 x 16 x 4, the bf16 ones 16 for 16 x 16 x 32,
-// so that six of them and the splitting of K and V (11 vector instructions a pair of values, once for both row blocks) take half the
-// time of one: 32 / 8 heads, 128 rows a KV head, 4111 keys, head_dim 128, MEASURED.  With one row block the splitting costs what it saves.
+// 64-row workgroups: products on the bf16 matrix cores.  The fp32 ones take 32 cycles for 16 x 16 x 4, the bf16 ones 16 for 16 x 16 x
+// 32, so that six of them take 3072 of 8192 cycles a tile and SIMD; what bounds the tile now is the vector work of splitting K and V
+// (11 instructions a pair of values, once for both row blocks).  128 rows of 8 KV heads, 256 workgroups, 8 / 32 tiles each, head_dim
+// 128 92 / 172 -> 72 / 132 us, 64 50 -> 41; a refresh step over 4111 keys 33 -> 28.  With one row block, or in the 32-row workgroups,
+// whose short streams lose up to 3 % (32 rows, 4096 keys 17.8 -> 18.3), the splitting costs what it saves.  Tried: four row blocks to a
+// wavefront, one wavefront per SIMD (half the splitting, but its latencies show: 172 -> 174), operands in five slots, four under way
+// (level).
 // Sums: the products of the upper parts in one chain, the small ones in another; its error against 64 bits is no larger (4111 keys
-// MEASURED).
+// 6.8e-7 -> 5.5e-7, relative).
 template <int D>
 struct QParts {
   Parts q[2][D / 32];
@@ -176,6 +176,21 @@ __device__ __forceinline__ void f32_tile_parts(FState<2, D / 16>& st, const QPar
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) small[rb] = mfma_parts(k.l, q.q[rb][j].h, small[rb]);
   }
+  if constexpr (D == 128) {
+    // the next step's splitting between this one's products (head_dim 64: level or slower)
+    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);         // LDS reads
+    __builtin_amdgcn_sched_group_barrier(0x002, 44, 0);        // vector instructions
+#pragma unroll
+    for (int j = 0; j + 1 < D / 32; ++j) {
+      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+#pragma unroll
+      for (int i = 0; i < 12; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);     // product
+        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+      }
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, 12, 0);
+  }
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb) s[rb] += small[rb];
   f32_softmax<2, C::NDB>(st, s, scale_log2, key0, nvalid);
@@ -191,21 +206,42 @@ __device__ __forceinline__ void f32_tile_parts(FState<2, D / 16>& st, const QPar
     p_mm[rb] = u32x4{m0, m1, m0, m1};
     p_hl[rb] = u32x4{h0, h1, l0, l1};
   }
+  // at head_dim 128 two column blocks at a time: four chains of products instead of two that wait for themselves
+  constexpr int NB = D == 128 ? 2 : 1;
 #pragma unroll
-  for (int db = 0; db < C::NDB; ++db) {
-    float v[4];
+  for (int d0 = 0; d0 < C::NDB; d0 += NB) {
+    u32x4 hm[NB], lh[NB];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) v[r] = *(const float*)(stage + C::OPB + vaddr[db] + r * C::ROWB);
-    uint32_t h0, m0, l0, h1, m1, l1;
-    split_pair(v[0], v[1], h0, m0, l0);
-    split_pair(v[2], v[3], h1, m1, l1);
-    const u32x4 hm = {h0, h1, m0, m1}, lh = {l0, l1, h0, h1};
+    for (int i = 0; i < NB; ++i) {
+      float v[4];
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb) st.o[rb][db] = mfma_parts(lh, p_hl[rb], st.o[rb][db]);
+      for (int r = 0; r < 4; ++r) v[r] = *(const float*)(stage + C::OPB + vaddr[d0 + i] + r * C::ROWB);
+      uint32_t h0, m0, l0, h1, m1, l1;
+      split_pair(v[0], v[1], h0, m0, l0);
+      split_pair(v[2], v[3], h1, m1, l1);
+      hm[i] = u32x4{h0, h1, m0, m1};
+      lh[i] = u32x4{l0, l1, h0, h1};
+    }
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb) st.o[rb][db] = mfma_parts(hm, p_mm[rb], st.o[rb][db]);
+    for (int x = 0; x < 2 * NB; ++x) st.o[x % 2][d0 + x / 2] = mfma_parts(lh[x / 2], p_hl[x % 2], st.o[x % 2][d0 + x / 2]);
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb) st.o[rb][db] = mfma_parts(hm, p_hh[rb], st.o[rb][db]);
+    for (int x = 0; x < 2 * NB; ++x) st.o[x % 2][d0 + x / 2] = mfma_parts(hm[x / 2], p_mm[x % 2], st.o[x % 2][d0 + x / 2]);
+#pragma unroll
+    for (int x = 0; x < 2 * NB; ++x) st.o[x % 2][d0 + x / 2] = mfma_parts(hm[x / 2], p_hh[x % 2], st.o[x % 2][d0 + x / 2]);
+  }
+  if constexpr (D == 128) {
+    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+    __builtin_amdgcn_sched_group_barrier(0x002, 88, 0);
+#pragma unroll
+    for (int d0 = NB; d0 < C::NDB; d0 += NB) {
+      __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+      for (int i = 0; i < 12; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+      }
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, 12, 0);
   }
 }
 
@@ -389,7 +425,7 @@ __global__ __launch_bounds__(256 * WR * TG, 1) void attn_f32_kernel(const PassPa
 #pragma unroll
     for (int j = 0; j < C::NQ; ++j) q[rb][j] = *(const f32x4*)(qr + 16 * j);
   }
-  constexpr bool kParts = RB == 2;
+  constexpr bool kParts = RB == 2 && WR == 2;
   QParts<D> qp;
   if constexpr (kParts) {
 #pragma unroll
