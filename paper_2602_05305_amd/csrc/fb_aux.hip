@@ -122,12 +122,12 @@ __device__ __forceinline__ void finish_row(const CombineParams& p, const Folded&
 }
 
 // Fold of the splits first, first + stride, ... of one row (4 columns of it).
+template <int CH>
 __device__ __forceinline__ Folded fold_strided(const float* __restrict__ ws_o, const float* __restrict__ ws_m,
                                                const float* __restrict__ ws_l, int nsplit, size_t rows,
                                                size_t row, int D, int c4, int first, int stride) {
   // Chunks of CH splits: all loads of a chunk are independent (one memory round trip), then the
   // chunk is folded into the running result with an online reference update.
-  constexpr int CH = 4;
   Folded f = empty_folded();
   for (int s0 = first; s0 < nsplit; s0 += stride * CH) {
     float mv[CH], lv[CH];
@@ -202,14 +202,15 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineParams p) {
   if (!fold_row(p, row, f)) return;
   Folded sel = empty_folded(), res = empty_folded();
   // chunks of four splits with all loads in flight (one memory round trip for up to four splits)
-  if (p.ws_o != nullptr && p.nsplit > 0) sel = fold_strided(p.ws_o, p.ws_m, p.ws_l, p.nsplit, f.rows, f.row, p.D, c4, 0, 1);
+  if (p.ws_o != nullptr && p.nsplit > 0) sel = fold_strided<4>(p.ws_o, p.ws_m, p.ws_l, p.nsplit, f.rows, f.row, p.D, c4, 0, 1);
   const bool have_res_set = p.ws_o2 != nullptr;
-  if (have_res_set) res = fold_strided(p.ws_o2, p.ws_m2, p.ws_l2, p.nsplit, f.rows, f.row, p.D, c4, 0, 1);
+  if (have_res_set) res = fold_strided<4>(p.ws_o2, p.ws_m2, p.ws_l2, p.nsplit, f.rows, f.row, p.D, c4, 0, 1);
   finish_row<TWO>(p, sel, res, have_res_set, row, c4);
 }
 
 // Many splits: one workgroup per row; NSL = 256/(D/4) thread groups each fold every NSL-th split
 // (fold_strided above), then one group folds the NSL results in fixed order.
+template <int CH>
 __global__ __launch_bounds__(256) void combine_wide_kernel(const CombineParams p) {
   __shared__ Folded sh[2][256];
   const int per_row = p.D / 4, nsl = 256 / per_row;
@@ -218,8 +219,8 @@ __global__ __launch_bounds__(256) void combine_wide_kernel(const CombineParams p
   FoldRow f;
   if (!fold_row(p, row, f)) return;                                 // workgroup-uniform
   const bool have_res_set = p.ws_o2 != nullptr;
-  sh[0][tid] = fold_strided(p.ws_o, p.ws_m, p.ws_l, p.nsplit, f.rows, f.row, p.D, c4, sl, nsl);
-  if (have_res_set) sh[1][tid] = fold_strided(p.ws_o2, p.ws_m2, p.ws_l2, p.nsplit, f.rows, f.row, p.D, c4, sl, nsl);
+  sh[0][tid] = fold_strided<CH>(p.ws_o, p.ws_m, p.ws_l, p.nsplit, f.rows, f.row, p.D, c4, sl, nsl);
+  if (have_res_set) sh[1][tid] = fold_strided<CH>(p.ws_o2, p.ws_m2, p.ws_l2, p.nsplit, f.rows, f.row, p.D, c4, sl, nsl);
   __syncthreads();
   if (sl != 0) return;
   Folded sel = sh[0][c4], res = empty_folded();
@@ -235,7 +236,7 @@ __global__ __launch_bounds__(256) void combine_wide_kernel(const CombineParams p
 // Refresh step with a small block (at most kMaxInlineBlock keys): after the streaming pass over the
 // prefix, ONE kernel folds the split partials (Eq. 5), writes the folded external partial to the
 // caller's cache, computes the block-internal attention of its rows with plain FMAs (Eq. 7) and
-// writes the Eq. 8-9 merge as the step's output.  Workgroup = kFoldRows rows of one query head
+// writes the Eq. 8-9 merge as the step's output.  Workgroup = RW rows of one query head
 // (the block's K/V are staged in LDS once per workgroup); wavefront w owns row w for the
 // attention part, all 256 threads share the split loads of every row.
 __device__ __forceinline__ float4 load4(const void* base, size_t i, int is_bf16) {
@@ -246,9 +247,13 @@ __device__ __forceinline__ float4 load4(const void* base, size_t i, int is_bf16)
   }
   return *(const float4*)((const float*)base + i);
 }
-template <int D>
+// RW rows and CH splits per thread: 16 partial rows in flight.  4 x 4 covers 32 splits at head_dim 128 (64 at 64) in one memory round
+// trip; more splits (few KV groups, so few rows) take 2 x 8 or 1 x 16, where 4 rows x 4 splits took a trip for every row and every
+// further 32 splits one after the other.
+// WHOLE: block_len is a multiple of RW (no division in front of the first loads: the 32K language-model step 37.0 -> 36.6 us).
+template <int D, int RW, bool WHOLE>
 __global__ __launch_bounds__(256) void refresh_fold_kernel(const CombineParams p) {
-  constexpr int RW = kFoldRows;
+  constexpr int CH = 16 / RW;
   static_assert(RW <= 4, "one wavefront per row");
   constexpr int per_row = D / 4, nsl = 256 / per_row;
   constexpr int ST = D + 4;                        // floats per K / V row in LDS: conflict-free 128-bit row reads
@@ -264,14 +269,13 @@ __global__ __launch_bounds__(256) void refresh_fold_kernel(const CombineParams p
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int sl = tid / per_row, c4 = tid % per_row;
   // RW rows of one query head, fewer at its end (those loads read the head's last row)
-  const uint32_t unit = xcd_contiguous(blockIdx.x, gridDim.x), bh_u = fastdiv(unit, p.div_fold);
-  const int at = (int)(unit - bh_u * p.div_fold.d) * RW, left = p.Bq - at;
-  const size_t row0 = (size_t)bh_u * p.Bq + at;
+  const uint32_t unit = xcd_contiguous(blockIdx.x, gridDim.x), bh_u = WHOLE ? 0u : fastdiv(unit, p.div_fold);
+  const int at = WHOLE ? 0 : (int)(unit - bh_u * p.div_fold.d) * RW, left = WHOLE ? RW : p.Bq - at;
+  const size_t row0 = WHOLE ? (size_t)unit * RW : (size_t)bh_u * p.Bq + at;
 
   // first CH splits of this thread for all RW rows: every load is issued before any is used, and the
   // block's K / V / q staging below runs while they are in flight
   {
-    constexpr int CH = 4;
     float mv[RW][CH], lv[RW][CH];
     float4 ov[RW][CH];
 #pragma unroll
@@ -293,7 +297,7 @@ __global__ __launch_bounds__(256) void refresh_fold_kernel(const CombineParams p
     // (a load-then-store loop would wait for every load in flight, the split loads included, on
     // each trip); chunks past the block's end are clamped to its last chunk and not stored.
     // (the head arithmetic needs integer divisions: it comes after the split loads have been issued)
-    const int bh = (int)bh_u, b = bh / p.Hq, kvh = (bh % p.Hq) / p.G;
+    const int bh = WHOLE ? (int)(row0 / p.Bq) : (int)bh_u, b = bh / p.Hq, kvh = (bh % p.Hq) / p.G;
     const size_t kvbase = (size_t)(b * p.Hkv + kvh) * p.Bq * D;
     constexpr int NST = kMaxInlineBlock * per_row / 256;      // staging trips at the largest block
     const int nchunk = p.Bq * per_row;
@@ -362,7 +366,7 @@ __global__ __launch_bounds__(256) void refresh_fold_kernel(const CombineParams p
         }
       }
       if (p.nsplit > CH * nsl)     // more splits than one chunk per thread covers
-        f = fold_two(f, fold_strided(p.ws_o, p.ws_m, p.ws_l, p.nsplit, p.rows, row0 + min(r, left - 1), D, c4, sl + CH * nsl, nsl));
+        f = fold_two(f, fold_strided<4>(p.ws_o, p.ws_m, p.ws_l, p.nsplit, p.rows, row0 + min(r, left - 1), D, c4, sl + CH * nsl, nsl));
       sh[r * 256 + tid] = f;
     }
   }
@@ -958,7 +962,13 @@ hipError_t launch_combine(const CombineParams& p, hipStream_t s) {
   // (one workgroup per row: not for the per-head refresh of many rows, most of whose rows are left alone, nor for the refresh step of
   // many rows)
   if (p.nsplit >= 8 && p.ws_o != nullptr && p.heads_cap == 0 && p.blk_ns < 2)
-    hipLaunchKernelGGL(combine_wide_kernel, dim3((unsigned)p.rows), dim3(256), 0, s, p);
+  {
+    // as many splits in flight per thread as it folds (one memory round trip), up to 16
+    const int per_thread = (p.nsplit + 1024 / p.D - 1) / (1024 / p.D);
+    if (per_thread <= 4) hipLaunchKernelGGL(combine_wide_kernel<4>, dim3((unsigned)p.rows), dim3(256), 0, s, p);
+    else if (per_thread <= 8) hipLaunchKernelGGL(combine_wide_kernel<8>, dim3((unsigned)p.rows), dim3(256), 0, s, p);
+    else hipLaunchKernelGGL(combine_wide_kernel<16>, dim3((unsigned)p.rows), dim3(256), 0, s, p);
+  }
   else if (p.blk_ns > 1)
     hipLaunchKernelGGL(combine_kernel<true>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p);
   else
@@ -975,21 +985,38 @@ hipError_t launch_pool_keys(const PoolParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_refresh_fold(const CombineParams& c, hipStream_t s) {
+template <int D, int RW>
+hipError_t launch_fold(const CombineParams& c, hipStream_t s) {
   CombineParams p = c;
+  const uint32_t per_head = (uint32_t)((p.Bq + RW - 1) / RW);
+  p.div_fold = make_fastdiv(per_head);
+  const size_t lds = ((size_t)(p.Bq + (p.Bq + 3) / 4 * 4) * (D + 4) + RW * D + RW * (D + 4)) * sizeof(float) + (size_t)RW * 256 * sizeof(Folded);
+  const dim3 grid((unsigned)(p.rows / p.Bq) * per_head);
+  static LdsLimit lim[2];
+  hipError_t e;
+  if (p.Bq % RW == 0) {
+    e = raise_lds_limit(refresh_fold_kernel<D, RW, true>, lds, lim[0], kLdsLimitMax);
+    if (e == hipSuccess) hipLaunchKernelGGL((refresh_fold_kernel<D, RW, true>), grid, dim3(256), lds, s, p);
+  } else {
+    e = raise_lds_limit(refresh_fold_kernel<D, RW, false>, lds, lim[1], kLdsLimitMax);
+    if (e == hipSuccess) hipLaunchKernelGGL((refresh_fold_kernel<D, RW, false>), grid, dim3(256), lds, s, p);
+  }
+  if (e != hipSuccess) return e;
+  return hipGetLastError();
+}
+
+hipError_t launch_refresh_fold(const CombineParams& p, hipStream_t s) {
   if (p.rows == 0) return hipSuccess;
   if (p.Bq < 1 || p.Bq > kMaxInlineBlock || p.blk_q == nullptr || p.nsplit < 1) return hipErrorInvalidValue;
-  const uint32_t per_head = (uint32_t)((p.Bq + kFoldRows - 1) / kFoldRows);
-  p.div_fold = make_fastdiv(per_head);
-  const size_t lds = ((size_t)(p.Bq + (p.Bq + 3) / 4 * 4) * (p.D + 4) + kFoldRows * p.D + kFoldRows * (p.D + 4)) * sizeof(float) +
-                     (size_t)kFoldRows * 256 * sizeof(Folded);
-  static LdsLimit lim64, lim128;
-  hipError_t e = p.D == 64 ? raise_lds_limit(refresh_fold_kernel<64>, lds, lim64, kLdsLimitMax) : raise_lds_limit(refresh_fold_kernel<128>, lds, lim128, kLdsLimitMax);
-  if (e != hipSuccess) return e;
-  const dim3 grid((unsigned)(p.rows / p.Bq) * per_head);
-  if (p.D == 64) hipLaunchKernelGGL(refresh_fold_kernel<64>, grid, dim3(256), lds, s, p);
-  else hipLaunchKernelGGL(refresh_fold_kernel<128>, grid, dim3(256), lds, s, p);
-  return hipGetLastError();
+  const int per_thread = (p.nsplit + 1024 / p.D - 1) / (1024 / p.D);
+  // fewer rows to a workgroup load the block's keys more often, and a thousand workgroups the same ones: by rows times keys.  A refresh
+  // step, 4 rows x 4 splits -> fewer rows: 64 splits 29.0 -> 24.0 us (80 rows of 4 KV heads, blocks of 20), 40.6 -> 39.6 (192 rows, blocks of
+  // 48) but 44.5 -> 48.2 (256, blocks of 64); 128 splits 46.8 -> 40.3, 53.4 -> 52.9 (496 rows of 2, blocks of 62), 17.2 -> 13.5
+  // (24 rows, 64 wide); 16 rows of 2 KV heads, 70000 keys 33.4 -> 23.6.
+  const long long keys = (long long)p.rows * p.Bq;
+  const int rw = per_thread <= 4 ? 4 : per_thread <= 8 ? (keys <= 40000 ? 2 : 4) : keys <= 65536 ? 1 : 4;
+  if (p.D == 64) return rw == 4 ? launch_fold<64, 4>(p, s) : rw == 2 ? launch_fold<64, 2>(p, s) : launch_fold<64, 1>(p, s);
+  return rw == 4 ? launch_fold<128, 4>(p, s) : rw == 2 ? launch_fold<128, 2>(p, s) : launch_fold<128, 1>(p, s);
 }
 
 hipError_t launch_select_topk(const SelectParams& p, hipStream_t s) {

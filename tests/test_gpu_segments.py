@@ -111,3 +111,27 @@ def test_refresh_step_in_streams_of_even_and_odd_tiles(B, Hq, Hkv, d, P, Bq):
         results.append(_normalised(ext))
     # the same references: fp32 sums only
     assert float((results[0] - results[1]).abs().max()) <= 1e-5 * float(results[1].square().mean().sqrt())
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,P,Bq", [
+    (1, 4, 4, 128, 64 * 512 + 5, 8),     # 64 splits: two rows a workgroup
+    (3, 1, 1, 64, 64 * 688, 5),          # 85 pieces, two rows a workgroup, a block of odd length
+    (3, 2, 1, 128, 64 * 688 + 1, 5),     # 85 pieces, one row
+    (1, 2, 2, 128, 64 * 1024, 4),        # 128 splits, one row
+])
+def test_fold_of_many_splits(B, Hq, Hkv, d, P, Bq):
+    w = wl.Workload(f"fm_{B}_{Hkv}_{d}_{Bq}", B, Hq, Hkv, d, P, Bq, 1, 1, "bf16", 1.0)
+    Kp, Vp = wl.make_prefix(w, 611)
+    step = wl.make_block_steps(w, 611)[0]
+    want = orc.run_block_dense(Kp, Vp, [step], 1)[0]
+    q, kb, vb, k, v = (T.to_dev(x, "bf16") for x in (*step, Kp, Vp))
+    shape, ext, out, lse = T.shape_of(w), T.Partial(w), torch.empty_like(q), torch.empty(q.shape[:3], device=T.DEV)
+    assert fb.fb_external_splits(shape) > 4 * 1024 // d
+    for call in ("step", "external"):
+        if call == "step":
+            fb.fb_refresh_step(shape, q, k, v, kb, vb, ext.o, ext.m, ext.lse, out, lse, T.workspace(shape))
+            T.assert_close(out.double().cpu().numpy(), want["out"], "bf16", w.name + " out")
+            T.assert_close(lse.double().cpu().numpy(), want["lse"], "bf16", w.name + " lse", lse=True)
+        else:
+            fb.fb_external_partial(shape, q, k, v, ext.o, ext.m, ext.lse, T.workspace(shape))
+        T.check_partial(ext.numpy(), want["ext"], "bf16", w.name + " ext by " + call)
