@@ -237,14 +237,19 @@ HeadsPlan heads_plan(const fb_shape* s, int active_heads, int ns) {
   if (s->dtype != FB_BF16 || active_heads <= 0 || active_heads >= s->n_q_heads) return h;
   if (!fb::dense_row_pairs((int)std::min<long long>(nrows, 1 << 30), s->head_dim)) return h;
   const int tiles = (s->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile;
-  // twice the split partials have to be earned: from 24 tiles per split on (12 heads of 4680 rows, 1 flagged: 26 tiles a
-  // split 222 -> 218 us, 12 tiles 193 -> 194; 3 of 8 heads of 2500 rows, 10 tiles, 89 -> 95), and where the 128-row
-  // workgroups fill half the chip unsplit and would write the final partial themselves, from 128 tiles on (6 of 12
-  // heads, 141 tiles: 310 -> 297; 8 of 10 heads of 3111 rows, 94 tiles: 191 -> 201).  (Measured with 32 rows per wavefront.  With 64
-  // the plan gains more where it is taken: 12 heads of 4680 rows, 1 flagged, 24.5 tiles a split 76.4 -> 65.3, 6 flagged, 141 tiles
-  // 158 -> 139; 8 of 10 heads of 3111 rows, 130 tiles 142 -> 121; 6 of 12 heads of 3000 rows, head_dim 64, 106 -> 90)
-  const long long wgs = (long long)s->batch * std::min(active_heads, s->n_kv_heads) * ((nrows + fb::kRowsPerWgBf16 - 1) / fb::kRowsPerWgBf16);
-  if (tiles < 48 * ns || (ns == 1 && wgs >= 128 && tiles < 128) || 2 * ns > FB_MAX_SPLITS) return h;
+  // Twice the split partials have to be earned: from 12 tiles per stream on where the split count is 2 or more, from 24 unsplit, and from 40
+  // where the 128-row workgroups fill half the chip unsplit and would write the final partial themselves.  Us there and here: 9
+  // heads of 1140 rows, 5 flagged, 207 tiles, 5 splits 58.6 and 55.6; 11 of 3014, 5 flagged, 74 tiles, 2 splits 57.9 and 54.9; 8 of
+  // 3828, 7 flagged, 116 tiles 126 and 108; 8 of 4392, 4 flagged, 113 tiles 119 and 96; 9 of 4226, 7 flagged, 50 tiles 61.6 and 66.7.
+  // And not where twice the splits of half the row tiles spill into one round of workgroups more (tiles of 256 rows; a start and an
+  // end 5 of them, 4 there): of 5 splits and more always (4 of 1093, 3 flagged, 550 tiles, 9 splits 84 and 109; 5 of 3178, 2 flagged, 374
+  // tiles, 5 splits 98 and 131), of fewer on short streams (long ones gain all the same: 7 of 2608, 331 tiles, 3 splits 178 and 150).
+  const long long kvg = (long long)s->batch * std::min(active_heads, s->n_kv_heads);
+  const long long wgs = kvg * ((nrows + fb::kRowsPerWgBf16 - 1) / fb::kRowsPerWgBf16), wgs256 = kvg * ((nrows + 2 * fb::kRowsPerWgBf16 - 1) / (2 * fb::kRowsPerWgBf16));
+  const bool all_rows = s->n_q_heads == s->n_kv_heads;       // else row tiles are cut from flagged heads' rows, fewer than counted here
+  const bool spills = all_rows && (wgs256 * 2 * ns + 255) / 256 * (tiles / ns / 2 + 5) > (wgs * ns + 255) / 256 * (tiles / ns + 4);
+  const bool is_long = tiles >= 48 * ns && !(ns == 1 && wgs >= 128 && tiles < 128);
+  if (tiles < (ns > 1 ? 24 * ns : wgs >= 128 ? 80 : 48) || (spills && (ns >= 5 || !is_long)) || 2 * ns > FB_MAX_SPLITS) return h;
   if (nrows * s->head_dim * 2 >= (1ll << 32)) return h;      // 32-bit query offsets between the heads of a group
   h.ns = 2 * ns;
   h.cap = std::min(active_heads, s->n_kv_heads);
