@@ -114,8 +114,9 @@ int32_t fb_external_splits(const fb_shape* shape);
 const char* fb_external_kernel_name(const fb_shape* shape);
 
 /* Bytes of device workspace one call needs on this shape.  n_splits = 0 sizes for the
- * library's own split choice (what fb_external_partial and fb_sparse_external_residual use),
- * otherwise for fb_external_partial_ex with that split count.  key_block = 0 sizes the dense
+ * library's own split choice (what fb_external_partial, fb_refresh_step and fb_sparse_external_residual
+ * use; a refresh step of many rows wants more than the external pass, and takes a slower route in a
+ * buffer that holds only the external pass's splits and one more partial), otherwise for fb_external_partial_ex with that split count.  key_block = 0 sizes the dense
  * external pass only; key_block > 0 sizes both sparse modes as well.  Host only.  Returns 0 on
  * invalid arguments, otherwise at least 256. */
 #define FB_MAX_SPLITS 256
@@ -146,8 +147,8 @@ fb_status fb_external_partial_ex(const fb_shape* shape, const void* q, const voi
  * operation, arguments and results as fb_external_partial (library's own split count); the split
  * partials go through a scratch array built into the library (device memory of
  * fb_builtin_workspace_bytes() = 20 MiB per GPU, held until the process ends) instead of a caller
- * workspace.  The call allocates and frees nothing.  Shapes whose fb_workspace_bytes(shape, 0, 0, 0)
- * exceeds that size are rejected with FB_ERR_WORKSPACE before anything is launched (every batch-1
+ * workspace.  The call allocates and frees nothing.  Shapes whose split partials (and one more)
+ * exceed that size are rejected with FB_ERR_WORKSPACE before anything is launched (every batch-1
  * LLM-shaped configuration up to 128K context fits; batch 4 at 128K and the video shape do not).
  * All calls on one GPU share the one array: calls that may overlap in time (different streams, or
  * different threads) race on it and must be ordered by the caller; nothing in it has to be cleared
@@ -227,7 +228,7 @@ fb_status fb_external_partial_paged(const fb_shape* shape, const void* q, const 
  * A whole refresh step on the paged cache: fb_external_partial_paged followed by the step's block-internal
  * attention and Eq. 8-9 merge (what fb_internal_merge would return), in two launches where the shape allows it:
  * with one split the paged pass writes the partial itself and the internal pass follows; with several
- * splits and a block of at most 64 rows (a multiple of 4) one kernel folds the splits, computes the rows'
+ * splits and a block of at most 64 rows one kernel folds the splits, computes the rows'
  * block-internal attention and merges; with fewer than 8 splits and few rows per KV head otherwise (bf16) the
  * internal pass folds them; else split combine + internal pass (three launches).
  * Arguments as in fb_external_partial_paged and fb_internal_merge; lse_out may be NULL.  Workspace as for
@@ -264,7 +265,7 @@ fb_status fb_internal_merge(const fb_shape* shape, const void* q, const void* k_
                             const float* lse_part, void* out, float* lse_out, void* hip_stream);
 
 /*
- * A whole refresh step in two launches: the single-pass formulation of Section 4.4 (one attention
+ * A whole refresh step in two launches (three for some shapes of more than 4096 rows): the single-pass formulation of Section 4.4 (one attention
  * pass over [prefix || block] whose block-external statistics are kept at the block boundary), cut
  * into splits for a 256-CU part.  The first launch streams the prefix splits, where the shape makes that
  * the faster form with the block's own keys as one more split; the second folds the splits into the

@@ -269,8 +269,9 @@ __global__ __launch_bounds__(256) void refresh_fold_kernel(const CombineParams p
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int sl = tid / per_row, c4 = tid % per_row;
   // RW rows of one query head, fewer at its end (those loads read the head's last row)
-  const uint32_t unit = xcd_contiguous(blockIdx.x, gridDim.x), bh_u = WHOLE ? 0u : fastdiv(unit, p.div_fold);
-  const int at = WHOLE ? 0 : (int)(unit - bh_u * p.div_fold.d) * RW, left = WHOLE ? RW : p.Bq - at;
+  const uint32_t per_head = (uint32_t)(p.Bq + RW - 1) / RW;
+  const uint32_t unit = xcd_contiguous(blockIdx.x, gridDim.x), bh_u = WHOLE ? 0u : unit / per_head;
+  const int at = WHOLE ? 0 : (int)(unit - bh_u * per_head) * RW, left = WHOLE ? RW : p.Bq - at;
   const size_t row0 = WHOLE ? (size_t)unit * RW : (size_t)bh_u * p.Bq + at;
 
   // first CH splits of this thread for all RW rows: every load is issued before any is used, and the
@@ -986,10 +987,8 @@ hipError_t launch_pool_keys(const PoolParams& p, hipStream_t s) {
 }
 
 template <int D, int RW>
-hipError_t launch_fold(const CombineParams& c, hipStream_t s) {
-  CombineParams p = c;
+hipError_t launch_fold(const CombineParams& p, hipStream_t s) {
   const uint32_t per_head = (uint32_t)((p.Bq + RW - 1) / RW);
-  p.div_fold = make_fastdiv(per_head);
   const size_t lds = ((size_t)(p.Bq + (p.Bq + 3) / 4 * 4) * (D + 4) + RW * D + RW * (D + 4)) * sizeof(float) + (size_t)RW * 256 * sizeof(Folded);
   const dim3 grid((unsigned)(p.rows / p.Bq) * per_head);
   static LdsLimit lim[2];

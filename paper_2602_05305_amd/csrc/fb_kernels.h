@@ -121,17 +121,24 @@ struct PassParams {
   // tiles of the i-th range; their partials are stored by rank among the flagged KV groups, [split][B][heads_cap][G*Bq] rows;
   // groups of a higher rank run unsplit and write the final partial
   int heads_cap;
+  // dense pass of up to 128 rows, nseg > 0 and != nsplit: reference segments (halves_pass), cut and ordered as nseg splits would
+  // be, with their bias (seg_bias).  (These and by_parity stand where the pointers' alignment leaves room: eight bytes more of
+  // arguments cost 0.1 us between two kernels, 0.5 % of a sparse block.)
+  int nseg;
   float* o_final; float* m_final; float* l_final;
   // internal pass, fold_ns > 0: the external statistics are fold_ns split partials in ws_o / ws_m / ws_l, which the pass
   // folds, writes to o_final / m_final / l_final (natural-log units) and merges
   int fold_ns;
   // streaming kernel, refresh step: whole tiles for the two wavefronts of a row group, splits cut with blk_cost; and the
   // many-row internal pass visits its tiles in rotated order
-  int whole_tiles, rotate;
+  int whole_tiles, rotate, seg_bias;
   // paged pass: k/v point at the pools [num_pages, Hkv, page_size, D]
   const int32_t* block_table; // [B, max_pages] page ids
   const int32_t* prefix_lens; // [B] keys per sequence (<= nkeys)
   int page_size, max_pages, num_pages;
+  // fused refresh pass by the row-pair kernel (many rows per KV head): an even nsplit, splits 2i and 2i + 1 with the even and the odd
+  // tiles of the i-th range, and with k2 != null two partials of the block's own keys, likewise, in set 1
+  int by_parity;
   const int32_t* seq_order;   // [B] sequences by descending prefix length (longest work is dispatched first), or null
   int order_inline;           // seq_order == null and 1: each workgroup ranks the (few) sequences itself
   // fused refresh pass: the block's own K/V [B,Hkv,Bq,D] go into partial set 1 (bf16: second phase of the last
@@ -148,17 +155,12 @@ struct PassParams {
   FastDiv div_bias;                            // streaming bf16 pass, xcd_bias: by 64 * nsplit
   FastDiv div_tpb;                             // streaming sparse passes: tile index -> key block (tiles per key block); per-head
                                                // refresh by rank: row -> head (block_len)
-  // dense pass of up to 128 rows, nseg > 0 and != nsplit: reference segments (halves_pass), cut and ordered as nseg splits would
-  // be, with their bias
-  int nseg, seg_bias;
-  // fused refresh pass by the row-pair kernel (many rows per KV head): an even nsplit, splits 2i and 2i + 1 with the even and the odd tiles of the i-th
-  // range, and with k2 != null two partials of the block's own keys, likewise, in set 1
-  int by_parity;
 };
 
 // Fold split partials (and optionally a cached residual) into final (o, m, lse) partials.
 struct CombineParams {
   int rows, D, nsplit;
+  int blk_ns;                       // partials at blk_o / blk_m / blk_l, `rows` rows each
   const float* ws_o;  const float* ws_m;  const float* ws_l;    // selected / dense set, may be null when nsplit==0
   const float* ws_o2; const float* ws_m2; const float* ws_l2;   // residual set (refresh) or null
   const float* res_in_o; const float* res_in_m; const float* res_in_lse;   // cached residual (reuse) or null
@@ -174,8 +176,6 @@ struct CombineParams {
   // fin_bf16): the fold kernel computes the block-internal attention of its rows itself
   const void* blk_q; const void* blk_k; const void* blk_v;
   int Hq, Hkv, G; float scale_log2;
-  FastDiv div_fold;                 // fold kernel: workgroups of a query head
-  int blk_ns;                       // partials at blk_o / blk_m / blk_l, rows of them each
 };
 
 struct SelectParams {
