@@ -119,7 +119,10 @@ __device__ __forceinline__ void split_pair(float a, float b, uint32_t& h, uint32
   const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
   h = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
   const float ra = a - __uint_as_float(ua & 0xffff0000u), rb = b - __uint_as_float(ub & 0xffff0000u);
-  asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(m) : "v"(ra), "v"(rb));      // (the compiler makes two of it)
+  // (a conversion the compiler knows: a product that reads it needs two wait states, which inline assembly does not get)
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  m = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{ra, rb}, bf16x2));
   l = __builtin_amdgcn_perm(__float_as_uint(rb - __uint_as_float(m & 0xffff0000u)), __float_as_uint(ra - __uint_as_float(m << 16)), 0x07060302u);
 }
 __device__ __forceinline__ Parts split_parts(const f32x4& a, const f32x4& b) {
@@ -238,7 +241,7 @@ __device__ __forceinline__ void f32_tile_parts(FState<2, D / 16>& st, const QPar
 #pragma unroll
       for (int i = 0; i < 12; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
       }
     }
     __builtin_amdgcn_sched_group_barrier(0x008, 12, 0);

@@ -66,3 +66,40 @@ def test_split_partials_are_stored_non_temporally(tmp_path):
     assert len(stores) >= 20
     for func, (plain, hinted) in stores.items():
         assert plain == hinted, f"{func}: {hinted} of {plain + hinted} row stores are non-temporal"
+
+
+def _vector_registers(operand):
+    m = re.fullmatch(r"(-?\|?)([va])(?:(\d+)|\[(\d+):(\d+)\])\|?", operand.strip())
+    if not m:
+        return set()
+    first = int(m.group(3) if m.group(3) else m.group(4))
+    return {(m.group(2), r) for r in range(first, (first if m.group(3) else int(m.group(5))) + 1)}
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler in this installation")
+@pytest.mark.parametrize("lib", [fb_build.LIB, fb_build.CALIB_LIB])
+def test_products_read_what_vector_instructions_wrote_two_wait_states_later(lib, tmp_path):
+    """The hardware does not wait by itself; the compiler keeps the distance for the instructions it knows, not for the results of
+    inline assembly."""
+    if not os.path.exists(lib):
+        fb_build.build(force=True)
+    ins = _instructions(lib, tmp_path)
+    products, early = 0, []
+    for i, (func, text) in enumerate(ins):
+        if not text.startswith("v_mfma"):
+            continue
+        products += 1
+        operands = text.split(None, 1)[1].split(",")
+        reads = set().union(*(_vector_registers(x) for x in operands[1:4]))
+        waited = 0
+        for back, before in reversed(ins[max(0, i - 2):i]):
+            if back != func or waited >= 2:
+                break
+            nop = re.match(r"s_nop (\d+)", before)
+            if before.startswith("v_") and not before.startswith("v_mfma") and " " in before:
+                written = before.split(None, 1)[1].split(",")[:2 if "swap" in before else 1]
+                if reads & set().union(*(_vector_registers(x) for x in written)):
+                    early.append(f"{func}: {before}, {waited} wait states, {text}")
+            waited += int(nop.group(1)) + 1 if nop else 1
+    assert products > 0
+    assert not early, f"{len(early)} places, first: {early[0]}"
