@@ -50,7 +50,9 @@ struct FCfg {
   static constexpr int NDB = D / 16, NDBK = NDB / 4;    // 16-wide output column blocks; per finishing wavefront
   static constexpr int RING = (TG > 1 ? kOneTiles : 2) * STAGE;
   static constexpr int MERGE = NW * RB * (NDB * 1024 + 512);
-  static constexpr int LDS = RING > MERGE ? RING : MERGE;
+  static constexpr int FLAGS = RING > MERGE ? RING : MERGE;
+  static constexpr bool kParts = RB == 2 && WR == 2;    // products from bf16 parts (f32_tile_parts)
+  static constexpr int LDS = FLAGS + (kParts ? NW * 4 : 0);
   static_assert(LDS <= 160 * 1024 && 2 * NLOAD <= 63, "LDS size and load counter");
   __device__ static __forceinline__ int rot_k(int row) { return row; }
   __device__ static __forceinline__ int rot_v(int row) { return row & ~3; }
@@ -283,8 +285,13 @@ __device__ __forceinline__ void f32_tile(FState<RB, D / 16>& st, const f32x4 (&q
     }
 }
 
-template <int D, int MODE, int RB, int WR, int TG = 1>
-__global__ __launch_bounds__(256 * WR * TG, 1) void attn_f32_kernel(const PassParams p) {
+// Products of a pass: fp32; of bf16 parts; fp32 again, half of the rows at a time, where those of parts gave a NaN.
+enum F32Products : int { kProductsF32, kProductsParts, kProductsAgain };
+
+// The pass of one workgroup.  kProductsParts: false, and nothing stored, where a NaN came out.  half: of the rows, kProductsAgain.
+template <int D, int MODE, int RB, int WR, int TG, int PRODUCTS>
+__device__ __forceinline__ bool f32_pass(const PassParams& p, unsigned char* ring, int half = 0) {
+  constexpr bool PARTS = PRODUCTS == kProductsParts;
   using C = FCfg<D, RB, WR, TG>;
   constexpr bool kPerHead = f32_per_head(MODE);
   // kPassRefreshOne, a whole refresh step in one launch: the prefix's tiles and then the block's own are one stream with two sets
@@ -292,8 +299,17 @@ __global__ __launch_bounds__(256 * WR * TG, 1) void attn_f32_kernel(const PassPa
   constexpr bool kOne = (MODE == kPassRefreshOne);
   constexpr int NSETS = (MODE == kPassSparseRefresh || kOne) ? 2 : 1;
   constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
-  extern __shared__ __align__(16) unsigned char ring[];
-  const int lane = threadIdx.x & 63, l16 = lane & 15, g4 = lane >> 4;
+  // the lane's number anew, so that nothing made of it is kept in a register meanwhile
+  auto lane_again = [](int& x) __attribute__((always_inline)) {
+    x = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    asm volatile("" : "+v"(x));
+  };
+  int lane = threadIdx.x & 63, wg = blockIdx.x;
+  if constexpr (PRODUCTS == kProductsAgain) {
+    lane_again(lane);
+    asm volatile("" : "+s"(wg));
+  }
+  int l16 = lane & 15, g4 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int wk = wave & 3, wr = (wave >> 2) % WR, tg = TG == 1 ? 0 : wave / C::GW, gwave = TG == 1 ? wave : wave % C::GW;
   static_assert(TG == 1 || MODE == kPassRefreshOne, "tile groups");
@@ -303,13 +319,13 @@ __global__ __launch_bounds__(256 * WR * TG, 1) void attn_f32_kernel(const PassPa
   int rt;
   uint32_t rest;
   if constexpr (MODE == kPassDensePaged) {
-    const uint32_t j = blockIdx.x >> 3, xcd = blockIdx.x & 7;
+    const uint32_t j = (uint32_t)wg >> 3, xcd = wg & 7;
     const uint32_t jq = fastdiv(j, p.div_rowtiles);
     rt = (int)(j - jq * p.div_rowtiles.d);
     rest = jq * 8 + xcd;
-    if (rest >= (uint32_t)(p.B * p.Hkv * p.nsplit)) return;   // workgroup-uniform
+    if (rest >= (uint32_t)(p.B * p.Hkv * p.nsplit)) return true;   // workgroup-uniform
   } else {
-    const int bid = blockIdx.x, q8 = gridDim.x / 8, r8 = gridDim.x % 8, xcd = bid % 8;
+    const int bid = wg, q8 = gridDim.x / 8, r8 = gridDim.x % 8, xcd = bid % 8;
     const int w = (xcd < r8 ? xcd * (q8 + 1) : r8 * (q8 + 1) + (xcd - r8) * q8) + bid / 8;
     rest = fastdiv((uint32_t)w, p.div_rowtiles);
     rt = w - (int)(rest * p.div_rowtiles.d);
@@ -325,7 +341,7 @@ __global__ __launch_bounds__(256 * WR * TG, 1) void attn_f32_kernel(const PassPa
   const int nrows = kPerHead ? p.Bq : p.G * p.Bq;
   const size_t grow_base = (size_t)(b * p.Hq + (kPerHead ? unit_h : unit_h * p.G)) * p.Bq;
   if constexpr (MODE == kPassDenseHeads) {
-    if (p.head_on[b * p.Hq + unit_h] == 0) return;            // this head keeps its cached partial
+    if (p.head_on[b * p.Hq + unit_h] == 0) return true;       // this head keeps its cached partial
   }
   const int bk = b * p.Hkv + kvh;
   const bool own_block = (MODE == kPassRefreshFused) && (split == p.nsplit);
@@ -420,7 +436,7 @@ __global__ __launch_bounds__(256 * WR * TG, 1) void attn_f32_kernel(const PassPa
   bool have0 = next_tile(t0);
   if (have0) issue(t0, tg);
   // queries: rows past the end read the group's last row; what they compute is never stored
-  const int row0 = rt * C::ROWS + wr * 16 * RB;
+  const int row0 = (PRODUCTS == kProductsAgain ? 2 * rt + half : rt) * C::ROWS + wr * 16 * RB;
   f32x4 q[RB][C::NQ];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
@@ -428,9 +444,8 @@ __global__ __launch_bounds__(256 * WR * TG, 1) void attn_f32_kernel(const PassPa
 #pragma unroll
     for (int j = 0; j < C::NQ; ++j) q[rb][j] = *(const f32x4*)(qr + 16 * j);
   }
-  constexpr bool kParts = RB == 2 && WR == 2;
   QParts<D> qp;
-  if constexpr (kParts) {
+  if constexpr (PARTS) {
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
@@ -441,7 +456,7 @@ __global__ __launch_bounds__(256 * WR * TG, 1) void attn_f32_kernel(const PassPa
   for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
     for (int j = 0; j < C::NQ; ++j) {
-      if constexpr (kParts) asm volatile("" ::"v"(qp.q[rb][j / 2].h));
+      if constexpr (PARTS) asm volatile("" ::"v"(qp.q[rb][j / 2].h));
       else asm volatile("" ::"v"(q[rb][j]));
     }
   bool have1 = have0 && next_tile(t1);
@@ -491,7 +506,7 @@ __global__ __launch_bounds__(256 * WR * TG, 1) void attn_f32_kernel(const PassPa
     }
     const int key0 = 16 * wk + 4 * g4;
     auto tile = [&](FState<RB, C::NDB>& st) __attribute__((always_inline)) {
-      if constexpr (kParts) f32_tile_parts<D, WR>(st, qp, stage, kaddr, vaddr, p.scale_log2, key0, nvalid);
+      if constexpr (PARTS) f32_tile_parts<D, WR>(st, qp, stage, kaddr, vaddr, p.scale_log2, key0, nvalid);
       else f32_tile<D, RB, WR>(st, q, stage, kaddr, vaddr, p.scale_log2, key0, nvalid);
     };
     if (NSETS > 1 && !t0.is_sel) tile(sets[NSETS - 1]);
@@ -508,6 +523,26 @@ __global__ __launch_bounds__(256 * WR * TG, 1) void attn_f32_kernel(const PassPa
     t1 = t2;
     have0 = have1;
     have1 = have2;
+  }
+
+  [[maybe_unused]] int* flags = (int*)(ring + C::FLAGS);
+  if constexpr (PARTS) {
+    lane_again(lane);
+    l16 = lane & 15;
+    g4 = lane >> 4;
+    // a NaN in the row sums: a score was one; in the accumulators: a value had no parts, and that shows in every row of the wavefront
+    float x = 0.f;
+#pragma unroll
+    for (int i = 0; i < NSETS; ++i) {
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) x = __builtin_elementwise_maximum(x, sets[i].l[rb]);
+#pragma unroll
+      for (int db = 0; db < C::NDB; ++db)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x = __builtin_elementwise_maximum(x, sets[i].o[0][db][r]);
+    }
+    const int nan = __any(x != x);
+    if (lane == 0) flags[wave] = nan;
   }
 
   // ---- the four key quarters of a row block meet in LDS: records [wavefront][row block][column block][lane], then
@@ -528,6 +563,9 @@ __global__ __launch_bounds__(256 * WR * TG, 1) void attn_f32_kernel(const PassPa
       rec_ml[(wave * RB + rb) * 64 + lane] = make_float2(sets[i].m[rb], l);
     }
     __syncthreads();
+    if constexpr (PARTS) {
+      if (i == 0 && __any(flags[lane & (C::NW - 1)])) return false;        // workgroup-uniform
+    }
     if (TG > 1 && tg != 0) continue;                          // the first group finishes
     constexpr int NR = 4 * TG;                                // records of a row block: key quarter by quarter, group by group
 #pragma unroll
@@ -630,6 +668,29 @@ __global__ __launch_bounds__(256 * WR * TG, 1) void attn_f32_kernel(const PassPa
         }
       }
     }
+  }
+  return true;
+}
+
+// 64-row workgroups: an infinity has no parts (its remainder is NaN), a part of 0 must not meet one, and parts of opposite signs may
+// overflow where their sum does not.  All of it leaves a NaN in the row sums or the accumulators of the pass by parts; such a
+// workgroup does its pass over again with the fp32 products, so that a value counts for what it does in the other workgroups.
+template <int D, int MODE, int RB, int WR, int TG = 1>
+__global__ __launch_bounds__(256 * WR * TG, 1) void attn_f32_kernel(const PassParams p) {
+  extern __shared__ __align__(16) unsigned char ring[];
+  if constexpr (FCfg<D, RB, WR, TG>::kParts) {
+    if (f32_pass<D, MODE, RB, WR, TG, kProductsParts>(p, ring)) return;
+    // (p is the only argument: read again from where the arguments are, instead of kept in registers throughout the first pass)
+    typedef const __attribute__((address_space(4))) PassParams* Args;
+    Args args = (Args)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+#pragma unroll 1
+    for (int half = 0; half < 2; ++half) {
+      __syncthreads();                                          // the flags, and the first half's records, have been read
+      f32_pass<D, MODE, RB / 2, WR, TG, kProductsAgain>(*(const PassParams*)args, ring, half);
+    }
+  } else {
+    f32_pass<D, MODE, RB, WR, TG, kProductsF32>(p, ring);
   }
 }
 
