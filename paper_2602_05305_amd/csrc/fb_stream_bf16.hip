@@ -159,8 +159,11 @@ __device__ __forceinline__ void tile_scores(f32x16 (&s)[NKB], const bf16x8 (&qre
   }
 }
 
-// A reference that moves down scales what is accumulated up, by at most this many powers of two.
-constexpr float kMostDown = 64.f;
+// A reference that moves down scales what is accumulated up, by at most this many powers of two.  All that a segment farther below
+// adds to a row, 2^17 keys of it, is below 2^-15 of the row's sum and its rounding to bf16 below 2^-24 of it, so where its reference
+// lies no longer shows.  And 2^17 keys of weight 2^8 leave less than 2^57 times a value, the squares of 128 such sums fp32 can add (the
+// similarity of two partials does).
+constexpr float kMostDown = 32.f;
 
 // Online softmax update with the tile's scores: moves the running reference if needed (rescaling the accumulators),
 // adds the row sums, and leaves the tile's probabilities, rounded to bf16, in pb (B operands of the value product).
@@ -190,7 +193,7 @@ __device__ __forceinline__ void tile_softmax(WaveAcc<D / 32>& st, f32x16 (&s)[NK
   // Lazy reference: m moves only when the tile maximum exceeds it by more than kLazy (log2 units); weights
   // stay below 2^kLazy, (o, l, m) remain exactly paired, and the accumulators are rescaled on few tiles only.
   constexpr float kLazy = 8.f;
-  // fresh: the first tile of a reference segment moves it always (down as well, unless what is kept would leave fp32's range)
+  // fresh: the first tile of a reference segment moves it always (down as well, by up to kMostDown)
   const float m_new = (tmax > st.m + kLazy || (fresh && tmax > st.m - kMostDown)) ? tmax : st.m;
   const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
   const float alpha = __builtin_amdgcn_exp2f(st.m - m_use);

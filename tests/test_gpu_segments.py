@@ -64,7 +64,7 @@ def test_refresh_step_of_odd_blocks(G, Bq, P, d):
 @pytest.mark.parametrize("Bq", [8, 5])
 def test_references_that_move_between_segments(Bq, factor):
     """Some keys outweigh the others by 30 or 130 powers of two for one row: the next segment's reference lies as far below, and what a
-    workgroup that walks on has accumulated is scaled up (or, farther apart than 64, its reference stays)."""
+    workgroup that walks on has accumulated is scaled up (or, farther apart than 32, its reference stays)."""
     w = wl.Workload(f"sm_{Bq}_{factor}", 3, 8, 8, 128, 64 * 88, Bq, 1, 1, "bf16", 1.0)
     Kp, Vp = wl.make_prefix(w, 605)
     steps = wl.make_block_steps(w, 605)
@@ -79,6 +79,30 @@ def test_references_that_move_between_segments(Bq, factor):
     fb.fb_refresh_step(shape, q, k, v, kb, vb, ext.o, ext.m, ext.lse, out, None, T.workspace(shape))
     T.assert_close(out.double().cpu().numpy(), want["out"], "bf16", w.name + " out")
     T.check_partial(ext.numpy(), want["ext"], "bf16", w.name + " ext of the step")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("factor", [2.0, 3.0, 4.0, 4.5])
+def test_similarity_of_partials_whose_reference_moved_down(factor, d):
+    """One tile outweighs all others, for every row by another 25 to 75 powers of two, and a workgroup that has passed it walks into
+    the next segment: what it leaves can be squared and summed in fp32, and is what one workgroup per segment leaves, up to fp32 sums."""
+    w = wl.Workload(f"sd_{factor}_{d}", 3, 8, 8, d, 64 * 88, 8, 1, 1, "bf16", 1.0)
+    Kp, Vp = wl.make_prefix(w, 613)
+    (Q, _, _), = wl.make_block_steps(w, 613)
+    for r in range(8):
+        Kp[:, :, 64 * 35 + 7 * r] = wl.round_storage(factor * (128 / d) ** 0.5 * Q[:, :, r], "bf16")
+    q, k, v = (T.to_dev(x, "bf16") for x in (Q, Kp, Vp))
+    shape, pieces, segments = T.shape_of(w), T.Partial(w), T.Partial(w)
+    fb.fb_external_partial(shape, q, k, v, pieces.o, pieces.m, pieces.lse, T.workspace(shape))
+    fb.fb_external_partial_ex(shape, q, k, v, segments.o, segments.m, segments.lse, 11, T.workspace(shape, n_splits=11))
+    a, b = _normalised(pieces), _normalised(segments)
+    # (m and lse of either are rounded to 2^-24 of themselves, and enter the normalised row through e^(m - lse))
+    bound = 1e-5 * b.square().mean().sqrt() + b.abs() * segments.lse.double().abs()[..., None] * 2.0 ** -22
+    assert bool(((a - b).abs() <= bound).all()), float(((a - b).abs() - bound).max())
+    for left, right in ((pieces, pieces), (pieces, segments)):
+        sim = torch.empty(3, 8, device=T.DEV)
+        fb.fb_head_similarity(shape, left.o, right.o, sim)
+        assert float((sim - 1).abs().max()) <= 1e-5, f"{sim}"
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,d,P,Bq", [
