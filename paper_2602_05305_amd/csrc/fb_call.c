@@ -1,6 +1,7 @@
 // Native form of the binding's calls (paper_2602_05305_amd/flashblock.py): takes the Python arguments of an entry point, makes the
 // C arguments of it and calls it.  Nothing else: which entry points there are, their arguments and what a status means stay with the
-// Python module.
+// Python module.  Arguments that are not of the plain kinds below, or missing, or of an unknown name, go to the Python function that a
+// call stands for (its __wrapped__), which takes or refuses them as it always has.
 //
 // A reuse step is one kernel of some 3.3 us and its launch costs the host 2.3 us, so the marshalling around it shows: 1.4 us through
 // ctypes and Python functions, 0.5 us here.
@@ -11,7 +12,6 @@
 #include <stddef.h>
 #include <stdint.h>
 #include <string.h>
-#include <structmember.h>
 
 #define MAX_ARGS 20                          // C arguments of an entry point
 
@@ -25,6 +25,7 @@ typedef struct {
   PyObject *name, *names, *defaults;         // defaults: of the last arguments
   PyObject *resolve, *stream, *check;        // name -> address; () -> current stream's handle; (status, name) raises
   PyObject *shape, *paged;                   // types of S and K
+  PyObject *dict, *weakrefs;                 // attributes (functools.update_wrapper)
   char kinds[MAX_ARGS + 1];
   int order[MAX_ARGS];
   Py_ssize_t n;
@@ -32,7 +33,7 @@ typedef struct {
 } Call;
 
 static PyObject *g_device, *g_raw_stream;    // () -> current device, (device) -> its current stream's handle; or unset
-static PyObject *s_data_ptr, *s_numel, *s_element_size, *s_cuda_stream, *s_value;
+static PyObject *s_data_ptr, *s_numel, *s_element_size, *s_cuda_stream, *s_wrapped;
 
 typedef int64_t A;
 typedef int (*F)(A, A, A, A, A, A, A, A, A, A, A, A, A, A, A, A, A, A, A, A);
@@ -78,6 +79,10 @@ static int marshal(Call* c, PyObject* const* args, A* a) {
         break;
       case 'W':
         if (o == Py_None) {
+          if (c->order[i] < c->n - PyTuple_GET_SIZE(c->defaults)) {
+            PyErr_Format(PyExc_AttributeError, "%U: no workspace", c->name);
+            return -1;
+          }
           a[n++] = 0;
           a[n++] = 0;
         } else {
@@ -95,7 +100,7 @@ static int marshal(Call* c, PyObject* const* args, A* a) {
           Py_INCREF(o);
           r = o;
         } else if (o != Py_None) {
-          r = PyObject_GetAttr(o, PyObject_HasAttr(o, s_cuda_stream) ? s_cuda_stream : s_value);    // (value: a ctypes handle)
+          r = PyObject_GetAttr(o, s_cuda_stream);
         } else if (g_device) {
           PyObject* d = PyObject_CallNoArgs(g_device);
           r = d ? PyObject_CallOneArg(g_raw_stream, d) : NULL;
@@ -104,9 +109,7 @@ static int marshal(Call* c, PyObject* const* args, A* a) {
           r = PyObject_CallNoArgs(c->stream);
         }
         if (!r) return -1;
-        int e = 0;
-        if (r == Py_None) a[n++] = 0;        // (a ctypes null)
-        else e = as_int(r, &a[n++]);
+        const int e = as_int(r, &a[n++]);
         Py_DECREF(r);
         if (e < 0) return -1;
       }
@@ -115,31 +118,47 @@ static int marshal(Call* c, PyObject* const* args, A* a) {
   return n;
 }
 
+// Arguments by name and the defaults, into all[]; 0 with or without an exception: not a call of this function.
+static int bind(Call* c, PyObject* const* args, Py_ssize_t given, PyObject* kw, PyObject** all) {
+  const Py_ssize_t nkw = kw ? PyTuple_GET_SIZE(kw) : 0, nd = PyTuple_GET_SIZE(c->defaults);
+  for (Py_ssize_t i = 0; i < c->n; ++i) all[i] = i < given ? args[i] : NULL;
+  for (Py_ssize_t k = 0; k < nkw; ++k) {
+    PyObject* key = PyTuple_GET_ITEM(kw, k);
+    Py_ssize_t i = 0;
+    for (; i < c->n; ++i) {
+      PyObject* name = PyTuple_GET_ITEM(c->names, i);
+      if (name == key || PyUnicode_Compare(name, key) == 0) break;
+    }
+    if (i == c->n || all[i]) return 0;
+    all[i] = args[given + k];
+  }
+  for (Py_ssize_t i = 0; i < c->n; ++i)
+    if (!all[i]) {
+      if (i < c->n - nd) return 0;
+      all[i] = PyTuple_GET_ITEM(c->defaults, i - (c->n - nd));
+    }
+  return 1;
+}
+
+// The same call by the Python function.
+static PyObject* by_python(Call* c, PyObject* const* args, size_t nargsf, PyObject* kw) {
+  PyObject* fn = c->dict ? PyDict_GetItemWithError(c->dict, s_wrapped) : NULL;
+  if (!fn) return PyErr_Occurred() ? NULL : PyErr_Format(PyExc_TypeError, "%U: arguments that are not of the native call's kinds", c->name);
+  PyErr_Clear();
+  Py_INCREF(fn);
+  PyObject* r = PyObject_Vectorcall(fn, args, nargsf & ~PY_VECTORCALL_ARGUMENTS_OFFSET, kw);
+  Py_DECREF(fn);
+  return r;
+}
+
 static PyObject* call(PyObject* self, PyObject* const* args, size_t nargsf, PyObject* kw) {
   Call* c = (Call*)self;
-  const Py_ssize_t given = PyVectorcall_NARGS(nargsf), nkw = kw ? PyTuple_GET_SIZE(kw) : 0;
+  const Py_ssize_t given = PyVectorcall_NARGS(nargsf);
   PyObject* all[MAX_ARGS];
-  if (given > c->n) return PyErr_Format(PyExc_TypeError, "%U() takes %zd arguments but %zd were given", c->name, c->n, given);
-  if (given < c->n || nkw) {
-    const Py_ssize_t nd = PyTuple_GET_SIZE(c->defaults);
-    for (Py_ssize_t i = 0; i < c->n; ++i) all[i] = i < given ? args[i] : NULL;
-    for (Py_ssize_t k = 0; k < nkw; ++k) {
-      PyObject* key = PyTuple_GET_ITEM(kw, k);
-      Py_ssize_t i = 0;
-      for (; i < c->n; ++i) {
-        PyObject* name = PyTuple_GET_ITEM(c->names, i);
-        if (name == key || PyUnicode_Compare(name, key) == 0) break;
-      }
-      if (i == c->n) return PyErr_Format(PyExc_TypeError, "%U() got an unexpected keyword argument '%U'", c->name, key);
-      if (all[i]) return PyErr_Format(PyExc_TypeError, "%U() got multiple values for argument '%U'", c->name, key);
-      all[i] = args[given + k];
-    }
-    for (Py_ssize_t i = 0; i < c->n; ++i)
-      if (!all[i]) {
-        if (i < c->n - nd) return PyErr_Format(PyExc_TypeError, "%U() missing argument '%U'", c->name, PyTuple_GET_ITEM(c->names, i));
-        all[i] = PyTuple_GET_ITEM(c->defaults, i - (c->n - nd));
-      }
-    args = all;
+  PyObject* const* bound = args;
+  if (given != c->n || (kw && PyTuple_GET_SIZE(kw))) {
+    if (given > c->n || !bind(c, args, given, kw, all)) return by_python(c, args, nargsf, kw);
+    bound = all;
   }
   if (!c->fn) {                              // the first call: the library is loaded now
     PyObject* r = PyObject_CallOneArg(c->resolve, c->name);
@@ -150,7 +169,10 @@ static PyObject* call(PyObject* self, PyObject* const* args, size_t nargsf, PyOb
     c->fn = fn;
   }
   A a[MAX_ARGS] = {0};
-  if (marshal(c, args, a) < 0) return NULL;
+  if (marshal(c, bound, a) < 0) {
+    if (!PyErr_ExceptionMatches(PyExc_TypeError) && !PyErr_ExceptionMatches(PyExc_AttributeError)) return NULL;
+    return by_python(c, args, nargsf, kw);
+  }
   int status;
   Py_BEGIN_ALLOW_THREADS
   status = ((F)c->fn)(a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7], a[8], a[9], a[10], a[11], a[12], a[13], a[14], a[15], a[16], a[17], a[18], a[19]);
@@ -163,8 +185,26 @@ static PyObject* call(PyObject* self, PyObject* const* args, size_t nargsf, PyOb
   Py_RETURN_NONE;
 }
 
+// Pickled and copied as a function is: by its name in its module.
+static PyObject* call_reduce(PyObject* self, PyObject* unused) {
+  PyObject* name = ((Call*)self)->name;
+  Py_INCREF(name);
+  return name;
+}
+
+// On a class, a method, as a function is.
+static PyObject* call_get(PyObject* self, PyObject* of, PyObject* type) {
+  if (!of || of == Py_None) {
+    Py_INCREF(self);
+    return self;
+  }
+  return PyMethod_New(self, of);
+}
+
 static void call_dealloc(PyObject* self) {
   Call* c = (Call*)self;
+  if (c->weakrefs) PyObject_ClearWeakRefs(self);
+  Py_XDECREF(c->dict);
   Py_XDECREF(c->name); Py_XDECREF(c->names); Py_XDECREF(c->defaults);
   Py_XDECREF(c->resolve); Py_XDECREF(c->stream); Py_XDECREF(c->check); Py_XDECREF(c->shape); Py_XDECREF(c->paged);
   Py_TYPE(self)->tp_free(self);
@@ -219,7 +259,9 @@ static PyObject* set_stream_getters(PyObject* self, PyObject* args) {
 
 static PyMethodDef methods[] = {{"set_stream_getters", set_stream_getters, METH_VARARGS, NULL}, {NULL}};
 
-static PyMemberDef call_members[] = {{"__name__", T_OBJECT, offsetof(Call, name), READONLY, NULL}, {NULL}};
+static PyMethodDef call_methods[] = {{"__reduce__", call_reduce, METH_NOARGS, NULL}, {NULL}};
+
+static PyGetSetDef call_getset[] = {{"__dict__", PyObject_GenericGetDict, PyObject_GenericSetDict, NULL, NULL}, {NULL}};
 
 static PyTypeObject CallType = {
     PyVarObject_HEAD_INIT(NULL, 0).tp_name = "paper_2602_05305_amd._fbcall.Call",
@@ -229,7 +271,11 @@ static PyTypeObject CallType = {
     .tp_call = PyVectorcall_Call,
     .tp_vectorcall_offset = offsetof(Call, vectorcall),
     .tp_flags = Py_TPFLAGS_DEFAULT | Py_TPFLAGS_HAVE_VECTORCALL,
-    .tp_members = call_members,
+    .tp_methods = call_methods,
+    .tp_getset = call_getset,
+    .tp_dictoffset = offsetof(Call, dict),
+    .tp_weaklistoffset = offsetof(Call, weakrefs),
+    .tp_descr_get = call_get,
     .tp_new = call_new,
 };
 
@@ -241,8 +287,8 @@ PyMODINIT_FUNC PyInit__fbcall(void) {
   s_numel = PyUnicode_InternFromString("numel");
   s_element_size = PyUnicode_InternFromString("element_size");
   s_cuda_stream = PyUnicode_InternFromString("cuda_stream");
-  s_value = PyUnicode_InternFromString("value");
-  if (!s_value || !s_data_ptr || !s_numel || !s_element_size || !s_cuda_stream) return NULL;
+  s_wrapped = PyUnicode_InternFromString("__wrapped__");
+  if (!s_wrapped || !s_data_ptr || !s_numel || !s_element_size || !s_cuda_stream) return NULL;
   PyObject* m = PyModule_Create(&module);
   if (!m) return NULL;
   Py_INCREF(&CallType);

@@ -9,6 +9,7 @@ Python, and there is no fallback: if the HIP library is not built, loading fails
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from ctypes import POINTER, Structure, c_char_p, c_float, c_int, c_int32, c_size_t, c_uint32, c_void_p
 
@@ -319,7 +320,7 @@ def fb_sparse_external_residual(shape, mode, q, k_prefix, v_prefix, key_block, t
 
 
 # The entry points in native form: what each C argument is made of, in C order (fb_call.c), and where the Python order differs.  The
-# functions above stay the definition of arguments and defaults.  (A call's marshalling 1.4 -> 0.5 us.)
+# functions above stay the definition of arguments and defaults, and take what the native form does not.  (A call's marshalling 1.4 -> 0.5 us.)
 _KINDS = {
     "fb_external_partial": "SPPPPPPWH",
     "fb_external_partial_ex": "SPPPPPPIWH",
@@ -346,8 +347,9 @@ def _native_calls():
         fn = globals()[name]
         names = fn.__code__.co_varnames[:fn.__code__.co_argcount]
         kinds, order = kinds if isinstance(kinds, tuple) else (kinds, " ".join(names))
-        globals()[name] = _fbcall.Call(name, names, fn.__defaults__ or (), kinds, tuple(names.index(x) for x in order.split()),
-                                       _address, lambda: _current_stream_handle(), _check, fb_shape, fb_paged_kv)
+        call = _fbcall.Call(name, names, fn.__defaults__ or (), kinds, tuple(names.index(x) for x in order.split()),
+                            _address, lambda: _current_stream_handle(), _check, fb_shape, fb_paged_kv)
+        globals()[name] = functools.update_wrapper(call, fn)
 
 
 if _fbcall is not None:

@@ -405,3 +405,83 @@ def test_native_calls_marshal_as_the_python_ones():
             native(*args.values()) if not left_out else native(**args)
             flat = [ctypes.addressof(a._obj) if hasattr(a, "_obj") else a or 0 for a in want[0]]
             assert list(seen[-1][:len(flat)]) == flat and not any(seen[-1][len(flat):]), name
+
+
+def test_native_calls_are_used_as_functions_are():
+    """What a function of the module could be asked for, a native call can: signature, name, documentation, module, pickling, copying,
+    weak references, a class attribute of it is a method."""
+    import copy
+    import inspect
+    import pickle
+    import weakref
+    if fb._fbcall is None:
+        pytest.skip("fb_call.c is not built")
+    for name in fb._KINDS:
+        call = getattr(fb, name)
+        fn = call.__wrapped__
+        assert inspect.signature(call) == inspect.signature(fn) and list(inspect.signature(call).parameters)[0] == "shape"
+        assert call.__name__ == call.__qualname__ == name and call.__module__ == fb.__name__ and call.__doc__ == fn.__doc__
+        assert pickle.loads(pickle.dumps(call)) is call and copy.deepcopy(call) is call and copy.copy(call) is call
+        assert weakref.ref(call)() is call
+        with pytest.raises(AttributeError):
+            call.no_such_attribute
+
+    class Holder:
+        step = fb.fb_internal_merge
+    holder = Holder()
+    assert inspect.ismethod(holder.step) and holder.step.__self__ is holder and Holder.step is fb.fb_internal_merge
+
+
+def test_native_calls_take_and_refuse_what_the_python_functions_do():
+    """Arguments that are not plain integers, tensors and structures, and faulty calls, end as they do without the native form."""
+    if fb._fbcall is None:
+        pytest.skip("fb_call.c is not built")
+
+    class Tensor:
+        def __init__(self, at=4096):
+            self.at = at
+
+        def data_ptr(self):
+            return self.at
+
+        def numel(self):
+            return 1 << 20
+
+        def element_size(self):
+            return 1
+
+    class Stream:
+        cuda_stream = 12345
+
+    bad, t = _ok_shape(n_kv_heads=3), Tensor()              # a shape that is refused before anything is launched
+    splits = dict(shape=bad, q=t, k_prefix=t, v_prefix=t, o_part=t, m_part=t, lse_part=t, n_splits=1, workspace=t, stream=0)
+
+    def outcome(fn, *args, **kw):
+        try:
+            return fn(*args, **kw)
+        except Exception as e:
+            return type(e), str(e)
+    cases = [(), dict(n_splits=ctypes.c_int32(2)), dict(stream=ctypes.c_void_p(0)), dict(stream=ctypes.c_void_p(64)), dict(stream=Stream()),
+             dict(stream=2.5), dict(stream=ctypes.c_int64(3)), dict(n_splits=2.5), dict(n_splits=None), dict(n_splits=True), dict(n_splits=1 << 40),
+             dict(shape=ctypes.byref(bad)), dict(shape=None), dict(shape=fb.fb_paged_kv()), dict(q=None), dict(q=7), dict(q=Tensor(None)),
+             dict(q=Tensor(1.5)), dict(q=Tensor(ctypes.c_void_p(64))), dict(workspace=None), dict(workspace=9), dict(unknown=1)]
+    for changed in cases:
+        kw = dict(splits, **dict(changed))
+        assert outcome(fb.fb_external_partial_ex, **kw) == outcome(fb.fb_external_partial_ex.__wrapped__, **kw), changed
+    assert outcome(fb.fb_external_partial_ex, **splits)[0] is fb.FlashBlockError
+    values = list(splits.values())
+    for args, kw in ((values, {}), (values[:-1], dict(stream=0)), (values[:3], {}), (values + [1], {}), (values, dict(q=t)), ([], {}),
+                     (values[:2], dict(q=t, n_splits=1))):
+        assert outcome(fb.fb_external_partial_ex, *args, **kw) == outcome(fb.fb_external_partial_ex.__wrapped__, *args, **kw), (args, kw)
+    # a workspace that may be left out
+    args = (bad, t, t, 64, 2, t)
+    for rest in ((), (None,), (t,), (None, 0), (t, 0)):
+        kw = {} if len(rest) == 2 else dict(stream=0)
+        assert outcome(fb.fb_select_topk, *args, *rest, **kw) == outcome(fb.fb_select_topk.__wrapped__, *args, *rest, **kw)
+    # no other exception of an argument's own is taken for one of these
+
+    class Interrupted(Tensor):
+        def data_ptr(self):
+            raise KeyboardInterrupt
+    with pytest.raises(KeyboardInterrupt):
+        fb.fb_external_partial_ex(**dict(splits, q=Interrupted()))
