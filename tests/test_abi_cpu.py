@@ -485,3 +485,27 @@ def test_native_calls_take_and_refuse_what_the_python_functions_do():
             raise KeyboardInterrupt
     with pytest.raises(KeyboardInterrupt):
         fb.fb_external_partial_ex(**dict(splits, q=Interrupted()))
+
+
+def test_the_library_is_usable_without_the_native_calls(tmp_path, monkeypatch, capfd):
+    """No compiler for fb_call.c: a message, nothing stale left, and the Python functions make the calls."""
+    import subprocess
+    import sys
+    import sysconfig
+    from paper_2602_05305_amd import build as fb_build
+    assert fb_build.CALL_LIB.endswith("_fbcall" + sysconfig.get_config_var("EXT_SUFFIX"))
+    monkeypatch.setattr(fb_build, "CALL_LIB", str(tmp_path / os.path.basename(fb_build.CALL_LIB)))
+    for left in (fb_build.CALL_LIB, tmp_path / "_fbcall.so"):
+        open(left, "w").close()
+    for cc in ("/no/such/compiler", "false"):
+        monkeypatch.setenv("CC", cc)
+        fb_build._build_call()
+        assert os.listdir(tmp_path) == [] and "not built" in capfd.readouterr().err
+    code = ("import sys; sys.modules['paper_2602_05305_amd._fbcall'] = None\n"
+            "from paper_2602_05305_amd import flashblock as fb\n"
+            "import types; assert fb._fbcall is None and isinstance(fb.fb_internal_merge, types.FunctionType)\n"
+            "try: fb.fb_internal_merge(fb.make_shape(1, 4, 3, 64, 16, 256, 'f32'), None, None, None, None, None, None, None, None, 0)\n"
+            "except fb.FlashBlockError as e: assert e.status == fb.FB_ERR_SHAPE\n"
+            "else: sys.exit('no error')\n")
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120, cwd=ROOT)
+    assert r.returncode == 0, r.stderr
