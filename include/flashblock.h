@@ -116,7 +116,9 @@ const char* fb_external_kernel_name(const fb_shape* shape);
 /* Bytes of device workspace one call needs on this shape.  n_splits = 0 sizes for the
  * library's own split choice (what fb_external_partial, fb_refresh_step and fb_sparse_external_residual
  * use; a refresh step of many rows wants more than the external pass, and takes a slower route in a
- * buffer that holds only the external pass's splits and one more partial), otherwise for fb_external_partial_ex with that split count.  key_block = 0 sizes the dense
+ * buffer that holds only the external pass's splits and one more partial), otherwise for
+ * fb_external_partial_ex with that split count; that of fb_external_splits also holds
+ * fb_external_partial and fb_refresh_step (by the slower route).  key_block = 0 sizes the dense
  * external pass only; key_block > 0 sizes both sparse modes as well.  Host only.  Returns 0 on
  * invalid arguments, otherwise at least 256. */
 #define FB_MAX_SPLITS 256

@@ -320,9 +320,11 @@ fb::PassParams base_pass(const fb_shape* s, const void* q, const void* k, const 
   return p;
 }
 
-// Split partials of the dense passes, and one block-internal partial for fb_refresh_step.
+// Split partials of the dense passes, and one block-internal partial for fb_refresh_step.  The split count of fb_external_splits sizes for
+// the library's own dense passes too, which ask for a partial per reference segment (as many as there were splits before there were pieces).
 size_t pass_workspace(const fb_shape* s, int n_splits) {
-  const int ns = n_splits > 0 ? n_splits : std::max({auto_splits(s), dense_splits(s), heads_splits(s, 0)});
+  int ns = n_splits > 0 ? n_splits : std::max({auto_splits(s), dense_splits(s), heads_splits(s, 0)});
+  if (n_splits > 0 && n_splits == dense_splits(s)) ns = std::max(ns, dense_segments(s));
   return ws_layout(s, ns, 2, 0, 1).total;
 }
 

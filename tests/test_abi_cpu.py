@@ -509,3 +509,18 @@ def test_the_library_is_usable_without_the_native_calls(tmp_path, monkeypatch, c
             "else: sys.exit('no error')\n")
     r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120, cwd=ROOT)
     assert r.returncode == 0, r.stderr
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("B,Hq,Hkv,Bq,P", [(3, 8, 8, 9, 16913), (5, 8, 8, 32, 8424), (11, 4, 4, 48, 92023), (15, 16, 8, 25, 3000),
+                                           (1, 32, 8, 32, 32768), (1, 12, 12, 4680, 37440)])
+def test_workspace_of_the_librarys_split_count_holds_its_own_passes(B, Hq, Hkv, Bq, P, d):
+    """Passes in pieces ask for a partial per reference segment, more than there are pieces."""
+    shape = fb.make_shape(B, Hq, Hkv, d, Bq, P, "bf16")
+    rows = B * Hq * Bq
+    splits = fb.fb_external_splits(shape)
+    if Hq // Hkv * Bq <= 128:
+        splits = max(splits, -(-256 // (B * Hkv)))
+    held = sum(-(-n * rows * x * 4 // 256) * 256 for n in (splits, 1) for x in (d, 1, 1))
+    assert fb.fb_workspace_bytes(shape, n_splits=fb.fb_external_splits(shape)) >= held
+    assert fb.fb_workspace_bytes(shape) >= held

@@ -60,6 +60,22 @@ def test_refresh_step_of_odd_blocks(G, Bq, P, d):
         T.check_partial(ext.numpy(), want["ext"], "bf16", w.name + " ext")
 
 
+def test_workspace_sized_by_the_split_count():
+    """fb_external_splits is the number of pieces; what it sizes holds the passes that ask for a partial per segment."""
+    w = wl.Workload("sw", 3, 8, 8, 128, 64 * 88, 9, 1, 1, "bf16", 1.0)
+    Kp, Vp = wl.make_prefix(w, 607)
+    step = wl.make_block_steps(w, 607)[0]
+    want = orc.run_block_dense(Kp, Vp, [step], 1)[0]
+    q, kb, vb, k, v = (T.to_dev(x, "bf16") for x in (*step, Kp, Vp))
+    shape, ext, out = T.shape_of(w), T.Partial(w), torch.empty_like(q)
+    ws = T.workspace(shape, n_splits=fb.fb_external_splits(shape))
+    fb.fb_external_partial(shape, q, k, v, ext.o, ext.m, ext.lse, ws)
+    T.check_partial(ext.numpy(), want["ext"], "bf16", "external")
+    fb.fb_refresh_step(shape, q, k, v, kb, vb, ext.o, ext.m, ext.lse, out, None, ws)
+    T.check_partial(ext.numpy(), want["ext"], "bf16", "step ext")
+    T.assert_close(out.double().cpu().numpy(), want["out"], "bf16", "step out")
+
+
 @pytest.mark.parametrize("factor", [2.0, 8.0])
 @pytest.mark.parametrize("Bq", [8, 5])
 def test_references_that_move_between_segments(Bq, factor):
