@@ -762,7 +762,7 @@ fb_status fb_refresh_step_prof(const fb_shape* shape, const void* q, const void*
     e = launch_attn(shape, in, fb::kPassInternal, stream);
   } else if (by_parity && p.k2 == nullptr && rows_of(shape) > kFoldKernelMaxRows) {
     c.fin_out = nullptr;
-    e = fb::launch_combine(c, stream);
+    e = fb::launch_combine(c, stream, by_parity);
     if (e != hipSuccess) return hip_fail(e);
     in.fold_ns = 0;
     in.ext_o = o_part; in.ext_m = m_part; in.ext_lse = lse_part;
@@ -776,7 +776,7 @@ fb_status fb_refresh_step_prof(const fb_shape* shape, const void* q, const void*
   } else {
     c.blk_o = p.ws_o2; c.blk_m = p.ws_m2; c.blk_l = p.ws_l2;
     c.blk_ns = by_parity ? 2 : 1;
-    e = fb::launch_combine(c, stream);
+    e = fb::launch_combine(c, stream, by_parity);
   }
   if (e != hipSuccess) return hip_fail(e);
   if (ev_end && (e = hipEventRecord((hipEvent_t)ev_end, stream)) != hipSuccess) return hip_fail(e);

@@ -210,7 +210,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineParams p) {
 
 // Many splits: one workgroup per row; NSL = 256/(D/4) thread groups each fold every NSL-th split
 // (fold_strided above), then one group folds the NSL results in fixed order.
-template <int CH>
+template <int CH, bool TWO>
 __global__ __launch_bounds__(256) void combine_wide_kernel(const CombineParams p) {
   __shared__ Folded sh[2][256];
   const int per_row = p.D / 4, nsl = 256 / per_row;
@@ -229,7 +229,7 @@ __global__ __launch_bounds__(256) void combine_wide_kernel(const CombineParams p
     res = sh[1][c4];
     for (int j = 1; j < nsl; ++j) res = fold_two(res, sh[1][j * per_row + c4]);
   }
-  finish_row(p, sel, res, have_res_set, row, c4);
+  finish_row<TWO>(p, sel, res, have_res_set, row, c4);
 }
 
 // ------------------------------------------------------------------------------ refresh fold
@@ -957,20 +957,26 @@ hipError_t launch_head_similarity(const float* o_a, const float* o_b, float* sim
   return hipGetLastError();
 }
 
-hipError_t launch_combine(const CombineParams& p, hipStream_t s) {
+template <bool TWO>
+void launch_combine_wide(const CombineParams& p, hipStream_t s) {
+  // as many splits in flight per thread as it folds (one memory round trip), up to 16
+  const int per_thread = (p.nsplit + 1024 / p.D - 1) / (1024 / p.D);
+  if (per_thread <= 4) hipLaunchKernelGGL((combine_wide_kernel<4, TWO>), dim3((unsigned)p.rows), dim3(256), 0, s, p);
+  else if (per_thread <= 8) hipLaunchKernelGGL((combine_wide_kernel<8, TWO>), dim3((unsigned)p.rows), dim3(256), 0, s, p);
+  else hipLaunchKernelGGL((combine_wide_kernel<16, TWO>), dim3((unsigned)p.rows), dim3(256), 0, s, p);
+}
+
+hipError_t launch_combine(const CombineParams& p, hipStream_t s, bool streams) {
   const size_t n = (size_t)p.rows * (p.D / 4);
   if (n == 0) return hipSuccess;
-  // (one workgroup per row: not for the per-head refresh of many rows, most of whose rows are left alone, nor for the refresh step of
-  // many rows)
-  if (p.nsplit >= 8 && p.ws_o != nullptr && p.heads_cap == 0 && p.blk_ns < 2)
-  {
-    // as many splits in flight per thread as it folds (one memory round trip), up to 16
-    const int per_thread = (p.nsplit + 1024 / p.D - 1) / (1024 / p.D);
-    if (per_thread <= 4) hipLaunchKernelGGL(combine_wide_kernel<4>, dim3((unsigned)p.rows), dim3(256), 0, s, p);
-    else if (per_thread <= 8) hipLaunchKernelGGL(combine_wide_kernel<8>, dim3((unsigned)p.rows), dim3(256), 0, s, p);
-    else hipLaunchKernelGGL(combine_wide_kernel<16>, dim3((unsigned)p.rows), dim3(256), 0, s, p);
-  }
-  else if (p.blk_ns > 1)
+  // One workgroup per row: not for the per-head refresh of many rows, most of whose rows are left alone; and of the refresh steps by
+  // streams only up to 3072 rows, whose splits are many (us a step, a thread per row and four columns / a workgroup per row, head_dim 128
+  // and 64: 700 rows, 86 streams 60.7 / 45.9 and 50.2 / 37.0; 1400, 44 59.4 / 55.8 and 46.6 / 41.1; 2800, 22 58.2 / 58.3 and 44.0 /
+  // 42.2; 3600, 16 96.0 / 97.6 and 66.5 / 69.0; 5600, 12 52.4 / 55.0 and 37.4 / 40.4; 10240, 8 87.4 / 92.0 and 61.4 / 70.7)
+  const bool two = p.blk_ns > 1;
+  if (p.nsplit >= 8 && p.ws_o != nullptr && p.heads_cap == 0 && (!streams || p.rows <= 3072))
+    two ? launch_combine_wide<true>(p, s) : launch_combine_wide<false>(p, s);
+  else if (two)
     hipLaunchKernelGGL(combine_kernel<true>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p);
   else
     hipLaunchKernelGGL(combine_kernel<false>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p);

@@ -217,7 +217,8 @@ int stream_bf16_name(const PassParams& p, int D, PassMode mode, char* buf, size_
 bool internal_fold_covers(const PassParams& p, int D);
 // Name of the kernel launch_attn_bf16 runs for the dense external pass of p (profiler spelling, no namespace).
 int attn_bf16_dense_name(const PassParams& p, int D, char* buf, size_t n);
-hipError_t launch_combine(const CombineParams& p, hipStream_t s);
+// streams: of a refresh step whose splits are streams (PassParams::by_parity).
+hipError_t launch_combine(const CombineParams& p, hipStream_t s, bool streams = false);
 // Fold + block-internal attention + merge in one kernel; needs blk_q/k/v, Bq <= kMaxInlineBlock.
 hipError_t launch_refresh_fold(const CombineParams& p, hipStream_t s);
 constexpr int kMaxInlineBlock = 64;

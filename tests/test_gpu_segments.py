@@ -125,6 +125,8 @@ def test_similarity_of_partials_whose_reference_moved_down(factor, d):
     (1, 8, 8, 128, 64 * 60, 700),        # 6 splits of 10 tiles, the least; the block's 11 tiles in two streams
     (1, 8, 8, 64, 64 * 71 + 9, 641),     # a ragged last tile, a block of one row more than whole tiles
     (1, 12, 6, 128, 64 * 97 - 1, 650),   # 1300 rows per KV head, 5 splits
+    (1, 1, 1, 128, 64 * 52 * 14, 640),   # 104 streams of few rows: the combine takes a workgroup per row
+    (1, 2, 2, 64, 64 * 22 * 20 + 1, 700),
     (9, 24, 8, 128, 64 * 25 + 3, 43),    # 129 rows, 2 splits: combine and internal pass
     (4, 24, 8, 64, 64 * 144 + 31, 43),   # 4 splits: fold kernel
 ])
