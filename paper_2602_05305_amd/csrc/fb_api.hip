@@ -297,7 +297,20 @@ int step_streams(const fb_shape* s, int ns) {
   const long long a = per / 2 + 5, b = btiles / 2 + 5, na = heads * rows256 * 2 * ns, nb = heads * rows256 * 2, busy = na % 256;
   const long long fit = busy ? (256 - busy) * (a / b) : 0;
   const long long here = (na + 255) / 256 * a + (std::max(nb - fit, 0ll) + 255) / 256 * b + heads * nrows * (ns + 1) / (s->head_dim == 128 ? 6700 : 13400) ;
-  return here + here / 5 < there ? 2 * ns : 0;
+  if (here + here / 5 >= there) return 0;
+  if (s->head_dim == 64) {
+    // What the model leaves out there, with both sides measured (us, there and here).  Few heads in many splits, whose second round there
+    // is a few workgroups: one head of 640 rows, 52 splits of 10 / 14 / 20 tiles 28.9 / 35.1 / 42.8 and 31.5 / 36.3 / 41.4, two of 640, 26
+    // splits 27.9 / 34.6 / 42.1 and 30.7 / 34.8 / 40.2; from 22 splits down never slower here.
+    if (ns > 22 && per < 16) return 0;
+    // Just one round there, of fewer than 8 heads: only where the block is long beside the splits, or the splits long beside the block.  1
+    // head of 1024 rows, 64 / 80 / 96 / 128 tiles a split 55.3 / 66.2 / 78.0 / 99.3 and 59.8 / 69.3 / 76.9 / 95.0; 4 of 1024, 64 / 80 59.8 / 71.2 and
+    // 59.9 / 68.4; 1 of 2048, 10 / 16 / 96 / 128 / 200 38.8 / 40.8 / 79.5 / 102 / 152 and 41.6 / 44.1 / 88.2 / 105 / 142; 2 of 4096 (two query heads of
+    // 2048), 160 126 and 120; 2 of 4096, 16 / 32 / 96 62.8 / 69.5 / 96.5 and 61.4 / 70.0 / 105; 1 of 8192, 64 / 128 / 200 127 / 154 / 190 and 120 / 157 /
+    // 198.  (8 heads of 2048, 80 tiles: 79.7 and 70.1.)
+    if (wgs <= 256 && heads < 8 && per * 128 > btiles * btiles && per < 5 * btiles) return 0;
+  }
+  return 2 * ns;
 }
 
 fb_status check_key_block(const fb_shape* s, int32_t key_block, int32_t topk, int* nblk) {

@@ -524,3 +524,25 @@ def test_workspace_of_the_librarys_split_count_holds_its_own_passes(B, Hq, Hkv, 
     held = sum(-(-n * rows * x * 4 // 256) * 256 for n in (splits, 1) for x in (d, 1, 1))
     assert fb.fb_workspace_bytes(shape, n_splits=fb.fb_external_splits(shape)) >= held
     assert fb.fb_workspace_bytes(shape) >= held
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,Bq,ns,tiles,streams", [
+    (1, 8, 8, 128, 640, 7, 70, True), (1, 8, 8, 128, 640, 7, 69, False),        # 10 tiles a split, and one fewer altogether
+    (1, 8, 8, 128, 639, 7, 70, False), (1, 12, 6, 64, 650, 4, 56, True),        # blocks from 640 tokens on
+    (1, 1, 1, 64, 640, 52, 52 * 16, True), (1, 1, 1, 64, 640, 52, 52 * 16 - 1, False),           # head_dim 64: few heads in many splits
+    (1, 2, 2, 64, 700, 22, 220, True), (1, 1, 1, 128, 640, 52, 520, True),
+    (1, 1, 1, 64, 4096, 8, 8 * 32, True), (1, 1, 1, 64, 4096, 8, 8 * 33, False),                 # one round of fewer than 8 heads
+    (1, 4, 2, 64, 2048, 4, 4 * 96, False), (1, 4, 2, 64, 2048, 4, 4 * 160, True), (2, 4, 4, 64, 2048, 2, 2 * 80, True),
+    (1, 1, 1, 64, 1024, 32, 32 * 64, False), (1, 1, 1, 64, 1024, 32, 32 * 80, True),
+    (9, 24, 8, 64, 43, 2, 28, True), (9, 24, 8, 64, 43, 2, 27, False),          # one-tile blocks: combine and internal pass
+    (3, 24, 8, 128, 43, 6, 6 * 36, True), (3, 24, 8, 128, 43, 6, 6 * 36 - 1, False),             # fold kernel
+])
+def test_refresh_steps_by_streams(B, Hq, Hkv, d, Bq, ns, tiles, streams):
+    """Which refresh steps of many rows run as streams of even and odd tiles, on both sides of every line of the rule: they want room
+    for twice the splits and two partials of the block."""
+    shape = fb.make_shape(B, Hq, Hkv, d, Bq, 64 * tiles, "bf16")
+    rows = B * Hq * Bq
+    held = sum(-(-n * rows * x * 4 // 256) * 256 for n in (2 * ns, 2) for x in (d, 1, 1)) + 256
+    assert ns == -(-256 // (B * Hkv * -(-Hq // Hkv * Bq // 128)))
+    got = fb.fb_workspace_bytes(shape)
+    assert got == held if streams else got < held
