@@ -45,7 +45,8 @@
  *     validated on the host before the first launch, so every error except FB_ERR_HIP leaves
  *     the outputs untouched and can be provoked without a GPU.
  *   - Supported: head_dim in {64, 128}; dtype FB_F32 or FB_BF16 (accumulation, partials and the
- *     merge are always fp32); n_q_heads a multiple of n_kv_heads with at most 32 query heads
+ *     merge are always fp32; where fp32 inputs are multiplied as sums of three bf16 numbers, what of an input
+ *     lies below 2^-133 is lost); n_q_heads a multiple of n_kv_heads with at most 32 query heads
  *     per KV head; block_len >= 1; prefix_len >= 0; scale > 0, or 0 for 1/sqrt(head_dim).
  *     key_block (sparse calls) must be a positive multiple of 64.
  */
