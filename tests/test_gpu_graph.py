@@ -53,3 +53,41 @@ def test_block_replays_match_eager_bit_for_bit():
         got = outs + [ext.o, ext.lse, ext2.o, ext2.lse]
         for i, (a, b) in enumerate(zip(got, want)):
             assert torch.equal(a, b), f"replay {rep}: tensor {i} differs from the eager result"
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,P,Bq", [
+    (3, 8, 8, 128, 64 * 88, 5),           # pieces of reference segments, fold of a block of odd length
+    (1, 8, 8, 128, 64 * 60, 700),         # streams of even and odd tiles, combine of the block's two; reuse step in two streams
+    (3, 24, 8, 64, 64 * 216, 43),         # streams, fold kernel
+    (9, 24, 8, 128, 64 * 28, 43),         # streams, combine and internal pass
+])
+def test_steps_by_pieces_and_streams_replay(B, Hq, Hkv, d, P, Bq):
+    w = wl.Workload(f"gr_{B}_{Hq}_{d}_{P}_{Bq}", B, Hq, Hkv, d, P, Bq, 2, 2, "bf16", 1.0)
+    print(f"[case] graph capture {w.name}", flush=True)
+    shape, ext, ws = T.shape_of(w), T.Partial(w), T.workspace(T.shape_of(w))
+    kp, vp = (T.to_dev(x, "bf16") for x in wl.make_prefix(w, 73))
+    (q, kb, vb), (q2, kb2, vb2) = (tuple(T.to_dev(x, "bf16") for x in st) for st in wl.make_block_steps(w, 73))
+    outs = [torch.empty_like(q), torch.empty_like(q)]
+
+    def block():
+        fb.fb_refresh_step(shape, q, kp, vp, kb, vb, ext.o, ext.m, ext.lse, outs[0], None, ws)
+        fb.fb_internal_merge(shape, q2, kb2, vb2, ext.o, ext.m, ext.lse, outs[1], None)
+
+    block()
+    torch.cuda.synchronize()
+    kept = outs + [ext.o, ext.m, ext.lse]
+    want = [x.clone() for x in kept]
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=torch.cuda.Stream()):
+        block()
+    scratch = torch.empty(1 << 22, device=T.DEV)
+    for rep in range(4):
+        for x in kept:
+            x.fill_(float("nan"))
+        ws.fill_(255)
+        scratch.normal_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        for i, (a, b) in enumerate(zip(kept, want)):
+            assert torch.equal(a, b), f"replay {rep}: tensor {i} differs from the eager result"

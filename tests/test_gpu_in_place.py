@@ -21,6 +21,10 @@ pytestmark = pytest.mark.gpu
     ("bf16", 1, 16, 16, 128, 70, 449),    # beyond one tile
     ("bf16", 6, 16, 8, 128, 4000, 31),    # refresh step: splits folded by the internal pass
     ("bf16", 1, 32, 8, 128, 4200, 32),    # refresh step: one kernel folds, attends and merges
+    ("bf16", 3, 8, 8, 128, 64 * 88, 5),   # refresh step: pieces, and the same kernel over a block of odd length
+    ("bf16", 1, 8, 8, 128, 64 * 60, 700), # refresh step by streams of even and odd tiles; reuse step in two streams
+    ("bf16", 3, 24, 8, 64, 64 * 216, 43), # by streams: fold kernel
+    ("bf16", 9, 24, 8, 128, 64 * 28, 43), # by streams: combine and internal pass
     ("f32", 1, 4, 4, 64, 256, 16),
     ("f32", 1, 3, 1, 128, 70, 25),
 ])

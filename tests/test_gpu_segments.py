@@ -127,8 +127,10 @@ def test_similarity_of_partials_whose_reference_moved_down(factor, d):
     (1, 12, 6, 128, 64 * 97 - 1, 650),   # 1300 rows per KV head, 5 splits
     (1, 1, 1, 128, 64 * 52 * 14, 640),   # 104 streams of few rows: the combine takes a workgroup per row
     (1, 2, 2, 64, 64 * 22 * 20 + 1, 700),
-    (9, 24, 8, 128, 64 * 25 + 3, 43),    # 129 rows, 2 splits: combine and internal pass
-    (4, 24, 8, 64, 64 * 144 + 31, 43),   # 4 splits: fold kernel
+    (9, 24, 8, 128, 64 * 30 + 3, 43),    # 129 rows, 2 splits: combine and internal pass
+    (4, 24, 8, 64, 64 * 144 + 31, 43),   # 4 splits, more than 4096 rows: the same
+    (3, 24, 8, 64, 64 * 216 + 5, 43),    # 6 splits, 3096 rows: fold kernel
+    (3, 24, 8, 128, 64 * 216 - 9, 43),
 ])
 def test_refresh_step_in_streams_of_even_and_odd_tiles(B, Hq, Hkv, d, P, Bq):
     """More than 128 rows per KV head in several splits; a workspace without room for the streams gets the former route."""
@@ -140,9 +142,9 @@ def test_refresh_step_in_streams_of_even_and_odd_tiles(B, Hq, Hkv, d, P, Bq):
     shape = T.shape_of(w)
     ns = -(-256 // (B * Hkv * -(-(Hq // Hkv * Bq) // 128)))
     rows = B * Hq * Bq
-    small = sum(-(-n * rows * x * 4 // 256) * 256 for n in (ns, 1) for x in (d, 1, 1)) + 256
-    assert small < fb.fb_workspace_bytes(shape)
-    results = []
+    full, small = (sum(-(-n * rows * x * 4 // 256) * 256 for n in sets for x in (d, 1, 1)) + 256 for sets in ((2 * ns, 2), (ns, 1)))
+    assert fb.fb_workspace_bytes(shape) == full, "not the route of this test"
+    results, outs = [], []
     for size in (fb.fb_workspace_bytes(shape), small):
         ext, ws = T.Partial(w), torch.zeros(size, device=T.DEV, dtype=torch.uint8)
         out, lse = torch.empty_like(q), torch.empty(q.shape[:3], device=T.DEV)
@@ -151,8 +153,15 @@ def test_refresh_step_in_streams_of_even_and_odd_tiles(B, Hq, Hkv, d, P, Bq):
         T.assert_close(lse.double().cpu().numpy(), want["lse"], "bf16", w.name + " lse", lse=True)
         T.check_partial(ext.numpy(), want["ext"], "bf16", w.name + " ext")
         results.append(_normalised(ext))
+        outs.append(out.double())
+        # partials are written beyond where a route of one stream a split would put them, or not
+        written = int(ws.nonzero().max()) + 1
+        assert written > small if size == full else written <= small
     # the same references: fp32 sums only
     assert float((results[0] - results[1]).abs().max()) <= 1e-5 * float(results[1].square().mean().sqrt())
+    # and the merged output rounded to bf16 (one step of it where a sum falls on the other side of a boundary, 2^-7 at most), or with the
+    # block's weights rounded to bf16 on one route and not on the other, 2^-9 each
+    assert float((outs[0] - outs[1]).abs().max()) <= 2.0 ** -7 * float(outs[1].abs().max())
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,d,P,Bq", [
