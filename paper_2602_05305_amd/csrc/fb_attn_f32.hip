@@ -1,12 +1,13 @@
-// fp32 attention pass for gfx950: fp32 matrix instructions, softmax statistics exchanged between lanes in registers.
+// fp32 attention pass for gfx950: matrix instructions on fp32 values or on their bf16 parts, softmax statistics exchanged between lanes in
+// registers.
 //
 // Computes the per-row statistics of Eq. 3-4/6 (arxiv 2602.05305, Section 4.2) over a key range, for storage
-// type float.  This is the exactness path (max-abs 1e-5 against a float64 reference): products and sums are fp32
-// (v_mfma_f32_16x16x4_f32), the running maximum is exact, and every reduction has a fixed order, so results are
-// bit-reproducible.
+// type float.  This is the exactness path (max-abs 1e-5 against a float64 reference): sums are fp32, products are fp32
+// (v_mfma_f32_16x16x4_f32) or, in 64-row workgroups, made of exact bf16 parts (v_mfma_f32_16x16x32_bf16, off by no more than half an fp32
+// step: split_pair), the running maximum is exact, and every reduction has a fixed order, so results are bit-reproducible.
 //
-// What bounds it: the fp32 matrix rate (64 flop per clock and SIMD; 2 x 64 x 16 x D x 2 flop per 16 rows and tile), at
-// the smallest shapes the launch and one memory round trip.  Before this form the pass gave every query row a
+// What bounds it: in 16- and 32-row workgroups the fp32 matrix rate (64 flop per clock and SIMD; 2 x 64 x 16 x D x 2 flop per 16 rows and
+// tile), in 64-row ones the vector work of splitting K and V (f32_tile_parts), at the smallest shapes the launch and one memory round trip.  Before this form the pass gave every query row a
 // wavefront and accumulated values by shuffle broadcasts: 32 x 128 rows against 4111 keys, head_dim 128, took 353 us.
 //
 // Work decomposition: one workgroup = WR x 4 wavefronts = WR*RB*16 rows x one range of 64-key tiles.  Wavefront

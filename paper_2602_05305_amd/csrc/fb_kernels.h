@@ -90,7 +90,8 @@ enum PassMode : int {
   kPassSparseReuse = 3,    // only key blocks of the per-KV-group union list; selected set only
   kPassDenseHeads = 4,     // dense, but only query heads flagged in head_on take part (others keep their cache)
   kPassDensePaged = 5,     // dense over a paged KV pool with a block table and per-sequence prefix lengths
-  kPassRefreshFused = 6,   // dense over the prefix plus one extra split over the block's own keys (partial set 1)
+  kPassRefreshFused = 6,   // dense over the prefix, and the block's own keys into partial set 1: in the last split's workgroup
+                           // (register-staged), as an extra split (fp32), as two streams or not at all (by_parity)
   kPassRefreshOne = 7      // fp32: a whole refresh step in one kernel (prefix unsplit, final partial, then the block and the merge)
 };
 
@@ -142,7 +143,7 @@ struct PassParams {
   const int32_t* seq_order;   // [B] sequences by descending prefix length (longest work is dispatched first), or null
   int order_inline;           // seq_order == null and 1: each workgroup ranks the (few) sequences itself
   // fused refresh pass: the block's own K/V [B,Hkv,Bq,D] go into partial set 1 (bf16: second phase of the last
-  // split's workgroup, which gets blk_cost prefix tiles fewer; fp32: one extra split index)
+  // split's workgroup, which gets blk_cost prefix tiles fewer; fp32: one extra split index; by_parity: two streams, or null)
   const void* k2; const void* v2; int blk_cost;
   // dense / heads / paged pass with nsplit == 1: ws_o / ws_m / ws_l are the caller's final (o, m, lse)
   // arrays and the kernel emits natural-log units itself (no combine pass)
