@@ -815,7 +815,12 @@ fb_status fb_refresh_step_paged(const fb_shape* shape, const void* q, const fb_p
   fb::PassParams in = base_pass(shape, q, k_block, v_block, shape->block_len, 1);
   in.out = out; in.lse_out = lse_out;
   in.fold_ns = n_splits > 0 ? n_splits : paged_splits(shape);
-  const bool fold_kernel = shape->block_len <= fb::kMaxInlineBlock && rows_of(shape) <= kFoldKernelMaxRows;
+  // Blocks that are no multiple of that kernel's rows: only from 5 splits on and up to 896 rows, fp32 1408 (batch 11, 4026 rows, blocks of 61, 2
+  // splits 37.3 us the other way and 61.3 by it; 1008 rows, 5 splits 34.0 and 38.2; 504 rows, 10 splits 25.6 and 23.5.  Random calls, by it against
+  // the other way: inside these lines 0.97 on average and 1.01 in 95 of 100, fp32 0.93 and 1.02; outside up to 1.64, fp32 1.41).
+  const bool fours = shape->block_len % fb::kFoldRows == 0;
+  const long long fold_rows = fours ? kFoldKernelMaxRows : shape->dtype == FB_BF16 ? 896 : 1408;
+  const bool fold_kernel = shape->block_len <= fb::kMaxInlineBlock && rows_of(shape) <= fold_rows && (fours || in.fold_ns >= 5);
   const bool one_round = (long long)in.B * in.Hkv * ((in.G * in.Bq + 31) / 32) <= 256;
   const bool fold_internal = !fold_kernel && shape->dtype == FB_BF16 && in.fold_ns > 1 &&
                              (shape->head_dim == 64 || in.Bq <= 32 || one_round) &&

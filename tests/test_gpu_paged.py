@@ -205,3 +205,24 @@ def test_paged_refresh_step(dtype, B, Hq, Hkv, d, P, Bq, page, lens, n_splits):
     ora_out, ora_lse = orc.merge(ora_ext, orc.partial(Q, Kb, Vb))
     T.assert_close(out.double().cpu().numpy(), ora_out, dtype, f"{w.name} paged refresh out")
     T.assert_close(lse.double().cpu().numpy(), ora_lse, dtype, f"{w.name} paged refresh lse", lse=True)
+
+
+@pytest.mark.parametrize("Bq,n_splits,fold", [
+    (27, 8, True), (29, 8, False),          # 864 and 928 rows
+    (13, 5, True), (13, 4, False),
+])
+def test_odd_blocks_fold_in_one_kernel_up_to_896_rows_from_5_splits_on(Bq, n_splits, fold):
+    """That kernel keeps the block's weights in fp32, the internal pass rounds them to bf16: seen in how many outputs are those of the
+    two calls one by one."""
+    w = _wl("bf16", 4, 8, 4, 64, 3000, Bq)
+    seqs, Kpool, Vpool, table, lens = wl.make_paged_prefix(w, 53, 64, [3000, 2500, 2999, 1000])
+    q, kb, vb = (T.to_dev(x, "bf16") for x in wl.make_block_steps(w, 53, 1)[0])
+    kpool, vpool, tbl, ln = T.to_dev(Kpool, "bf16"), T.to_dev(Vpool, "bf16"), torch.from_numpy(table).to(T.DEV), torch.from_numpy(lens).to(T.DEV)
+    shape, kv, ext, ws = T.shape_of(w), fb.make_paged_kv(kpool, vpool, tbl, ln), T.Partial(w), T.workspace(T.shape_of(w), n_splits=n_splits)
+    one, two = torch.empty_like(q), torch.empty_like(q)
+    fb.fb_refresh_step_paged(shape, q, kv, kb, vb, ext.o, ext.m, ext.lse, one, None, ws, n_splits)
+    fb.fb_external_partial_paged(shape, q, kv, ext.o, ext.m, ext.lse, ws, n_splits)
+    fb.fb_internal_merge(shape, q, kb, vb, ext.o, ext.m, ext.lse, two, None)
+    differ = float((one != two).double().mean())
+    print(f"[case] Bq {Bq} splits {n_splits}: {differ:.4f} differ", flush=True)
+    assert differ > 0.02 if fold else differ < 0.005
