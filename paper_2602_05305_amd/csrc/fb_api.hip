@@ -279,20 +279,28 @@ int heads_ws_splits(const fb_shape* s, int active_heads) {
 // 2728 rows, 5 splits, 65 / 86 / 115 and 54 / 63 / 87).  One tile: twice the partials have to be earned where the fold kernel reads them
 // (up to 4096 rows: batch 3, 168 rows of 8 heads, 6 splits, 24 / 36 / 60 tiles 72 / 104 / 159 and 77 / 96 / 131; head_dim 64 48 / 64 / 97
 // and 51 / 62 / 87), not where combine and internal pass do (batch 7, 152 rows, 3 splits, 12 / 24 tiles 50 / 78 and 47 / 66;
-// batch 3, 212 rows, 6 splits, 14 tiles, blocks of 53, 55 and 63).
+// batch 3, 212 rows, 6 splits, 14 tiles, blocks of 53, 55 and 63), and one tile never where the streams' 256-row workgroups are a
+// round more than the 128-row ones (an odd number of those to a head: 80 heads of 344 rows, 2 splits of 15 tiles, head_dim 64, 480 and 640 workgroups,
+// 44.1 and 55.8; 84 of 360, 130 tiles 209 and 240; of 47 random such calls 37 lost, to 1.27), unless at head_dim 128 the streams are long
+// (540 rows, 26 tiles 1.07, 368 rows, 65 tiles 1.01, 344 rows, 143 tiles 0.93 times).  One round of combine and internal pass at head_dim 64:
+// from 32 tiles on (16 heads of 992 rows, 2 splits of 14 26.2 and 31.9; 928 rows, 18 1.15, 228 rows, 24 1.04, 420 rows, 35 0.98 times).
 int step_streams(const fb_shape* s, int ns) {
   const long long nrows = (long long)(s->n_q_heads / s->n_kv_heads) * s->block_len;
   const int tiles = (s->prefix_len + fb::kKeyTile - 1) / fb::kKeyTile;
   if (s->dtype != FB_BF16 || ns < 2 || nrows <= fb::kRowsPerWgBf16 || 2 * ns > FB_MAX_SPLITS) return 0;
   if (s->block_len > fb::kKeyTile && s->block_len < 640) return 0;
-  if (s->block_len <= fb::kKeyTile) return tiles >= (rows_of(s) > kFoldKernelMaxRows ? 6 + 4 * ns : 36) * ns ? 2 * ns : 0;
+  const long long heads = (long long)s->batch * s->n_kv_heads, wgs = heads * ((nrows + 127) / 128) * ns, rows256 = (nrows + 255) / 256;
+  if (s->block_len <= fb::kKeyTile) {
+    if ((heads * rows256 * 2 * ns + 255) / 256 > (wgs + 255) / 256 && !(s->head_dim == 128 && tiles >= 80 * ns)) return 0;
+    const int least = rows_of(s) <= kFoldKernelMaxRows ? 36 : s->head_dim == 64 && wgs <= 256 ? std::max(32, 6 + 4 * ns) : 6 + 4 * ns;
+    return tiles >= least * ns ? 2 * ns : 0;
+  }
   if (tiles < 10 * ns) return 0;
   // Both ways by their rounds of 256 workgroups, in tiles of 256 rows: a tile of 128 rows takes the register-staged kernel as long as one of 256
   // the row-pair kernel, a start and an end 4 and 5 tiles; the last split's workgroup runs the block too, here the block's streams
   // fill what the prefix's leave; and ns + 1 more partials are written and read.  (4 heads of 2026 rows, 11933 keys, one full round
   // there and a second one of the block's streams here: 75 us there, 80 here.)
   const int btiles = (s->block_len + fb::kKeyTile - 1) / fb::kKeyTile, per = tiles / ns;
-  const long long heads = (long long)s->batch * s->n_kv_heads, wgs = heads * ((nrows + 127) / 128) * ns, rows256 = (nrows + 255) / 256;
   const long long there = (wgs + 255) / 256 * (std::max(per, per - std::min(2 + btiles, per / 2) + btiles) + 4);
   const long long a = per / 2 + 5, b = btiles / 2 + 5, na = heads * rows256 * 2 * ns, nb = heads * rows256 * 2, busy = na % 256;
   const long long fit = busy ? (256 - busy) * (a / b) : 0;
