@@ -243,13 +243,15 @@ HeadsPlan heads_plan(const fb_shape* s, int active_heads, int ns) {
   // 3828, 7 flagged, 116 tiles 126 and 108; 8 of 4392, 4 flagged, 113 tiles 119 and 96; 9 of 4226, 7 flagged, 50 tiles 61.6 and 66.7.
   // And not where twice the splits of half the row tiles spill into one round of workgroups more (tiles of 256 rows; a start and an
   // end 5 of them, 4 there): of 5 splits and more always (4 of 1093, 3 flagged, 550 tiles, 9 splits 84 and 109; 5 of 3178, 2 flagged, 374
-  // tiles, 5 splits 98 and 131), of fewer on short streams (long ones gain all the same: 7 of 2608, 331 tiles, 3 splits 178 and 150).
+  // tiles, 5 splits 98 and 131), of fewer on short streams (long ones gain all the same: 7 of 2608, 331 tiles, 3 splits 178 and 150).  With
+  // several heads to a KV group the row tiles hold the flagged heads' rows only, but workgroups are launched for all, and a grid of more
+  // than a round costs a second one all the same: on short streams not then (12 groups of 2 x 407 rows, 22 flagged, 73 tiles, 3 splits 43.8 and
+  // 69.1; 4 of 2 x 430, 2 flagged, 467 tiles, 18 splits 46.3 and 69.2; of 28 random such calls 12 lost, to 1.57, 14 won, to 0.63).
   const long long kvg = (long long)s->batch * std::min(active_heads, s->n_kv_heads);
   const long long wgs = kvg * ((nrows + fb::kRowsPerWgBf16 - 1) / fb::kRowsPerWgBf16), wgs256 = kvg * ((nrows + 2 * fb::kRowsPerWgBf16 - 1) / (2 * fb::kRowsPerWgBf16));
-  const bool all_rows = s->n_q_heads == s->n_kv_heads;       // else row tiles are cut from flagged heads' rows, fewer than counted here
-  const bool spills = all_rows && (wgs256 * 2 * ns + 255) / 256 * (tiles / ns / 2 + 5) > (wgs * ns + 255) / 256 * (tiles / ns + 4);
+  const bool spills = (wgs256 * 2 * ns + 255) / 256 * (tiles / ns / 2 + 5) > (wgs * ns + 255) / 256 * (tiles / ns + 4);
   const bool is_long = tiles >= 48 * ns && !(ns == 1 && wgs >= 128 && tiles < 128);
-  if (tiles < (ns > 1 ? 24 * ns : wgs >= 128 ? 80 : 48) || (spills && (ns >= 5 || !is_long)) || 2 * ns > FB_MAX_SPLITS) return h;
+  if (tiles < (ns > 1 ? 24 * ns : wgs >= 128 ? 80 : 48) || (spills && ((ns >= 5 && s->n_q_heads == s->n_kv_heads) || !is_long)) || 2 * ns > FB_MAX_SPLITS) return h;
   if (nrows * s->head_dim * 2 >= (1ll << 32)) return h;      // 32-bit query offsets between the heads of a group
   h.ns = 2 * ns;
   h.cap = std::min(active_heads, s->n_kv_heads);

@@ -124,10 +124,12 @@ def test_head_wise_refresh_by_rank(Hq, Hkv, d, P, Bq, masks, hint):
     (64 * 95, 1287, [0, 1, 1, 1, 1, 1, 0, 0], 4, False),
     (64 * 300, 260, [0, 0, 0, 0, 0, 1, 0, 0], 11, True),          # 22 workgroups
     (64 * 300, 520, [0, 0, 1, 1, 1, 1, 0, 0], 12, False),         # twice 12 splits of 12 row tiles: a second round
+    (64 * 175, 145, [0] * 4 + [1] * 23 + [0] * 5, 6, False),      # four heads to a KV group: the same with 24
+    (64 * 192, 128, [0] * 4 + [1] * 23 + [0] * 5, 15, True),      # 16 (8 splits; 15 hold the partials): one round
 ])
 def test_head_wise_refresh_by_rank_or_not(P, Bq, mask, ns, by_rank):
     """Both sides of the rule's lines: by rank the first flagged group's partials stand where group 0's would."""
-    w = _wl(1, 8, 8, 128, P, Bq)
+    w = _wl(1, len(mask), 8, 128, P, Bq)
     print(f"[case] {w.name}", flush=True)
     Kp, Vp = wl.make_prefix(w, 421)
     (Q, _, _), _ = wl.make_block_steps(w, 421)
@@ -138,7 +140,7 @@ def test_head_wise_refresh_by_rank_or_not(P, Bq, mask, ns, by_rank):
     fb.fb_external_partial_heads(shape, *(T.to_dev(x, "bf16") for x in (Q, Kp, Vp)), torch.tensor([mask], dtype=torch.uint8, device=T.DEV),
                                  part.o, part.m, part.lse, ws, sum(mask))
     torch.cuda.synchronize()
-    assert bool((ws[:Bq * 128 * 4] != 0xA5).any()) == by_rank
+    assert bool((ws[:len(mask) // 8 * Bq * 128 * 4] != 0xA5).any()) == by_rank
     got, want = {k: v[:, :, ::131] for k, v in part.numpy().items()}, orc.partial(Q[:, :, ::131], Kp, Vp)
     T.check_partial({k: v[on] for k, v in got.items()}, {k: v[on] for k, v in want.items()}, "bf16", w.name)
     assert (got["o"][~on] == 7).all() and (got["m"][~on] == 8).all() and (got["lse"][~on] == 9).all()
