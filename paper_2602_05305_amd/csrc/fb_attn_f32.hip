@@ -4,7 +4,7 @@
 // Computes the per-row statistics of Eq. 3-4/6 (arxiv 2602.05305, Section 4.2) over a key range, for storage
 // type float.  This is the exactness path (max-abs 1e-5 against a float64 reference): sums are fp32, products are fp32
 // (v_mfma_f32_16x16x4_f32) or, in 64-row workgroups, made of exact bf16 parts (v_mfma_f32_16x16x32_bf16, off by no more than half an fp32
-// step: split_pair), the running maximum is exact, and every reduction has a fixed order, so results are bit-reproducible.
+// step: split_pair; not on short streams at head_dim 64), the running maximum is exact, and every reduction has a fixed order, so results are bit-reproducible.
 //
 // What bounds it: in 16- and 32-row workgroups the fp32 matrix rate (64 flop per clock and SIMD; 2 x 64 x 16 x D x 2 flop per 16 rows and
 // tile), in 64-row ones the vector work of splitting K and V (f32_tile_parts), at the smallest shapes the launch and one memory round trip.  Before this form the pass gave every query row a
@@ -148,7 +148,7 @@ __device__ __forceinline__ f32x4 mfma_parts(const u32x4& a, const u32x4& b, cons
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// 64-row workgroups: products on the bf16 matrix cores.  The fp32 ones take 32 cycles for 16 x 16 x 4, the bf16 ones 16 for 16 x 16 x
+// 64-row workgroups, but short streams at head_dim 64: products on the bf16 matrix cores.  The fp32 ones take 32 cycles for 16 x 16 x 4, the bf16 ones 16 for 16 x 16 x
 // 32, so that six of them take 3072 of 8192 cycles a tile and SIMD; what bounds the tile now is the vector work of splitting K and V
 // (11 instructions a pair of values, once for both row blocks).  128 rows of 8 KV heads, 256 workgroups, 8 / 32 tiles each, head_dim
 // 128 92 / 172 -> 72 / 132 us, 64 50 -> 41; a refresh step over 4111 keys 33 -> 28.  With one row block, or in the 32-row workgroups,
@@ -680,10 +680,10 @@ __device__ __forceinline__ bool f32_pass(const PassParams& p, unsigned char* rin
 // 64-row workgroups: an infinity has no parts (its remainder is NaN), a part of 0 must not meet one, and parts of opposite signs may
 // overflow where their sum does not.  All of it leaves a NaN in the row sums or the accumulators of the pass by parts; such a
 // workgroup does its pass over again with the fp32 products, so that a value counts for what it does in the other workgroups.
-template <int D, int MODE, int RB, int WR, int TG = 1>
+template <int D, int MODE, int RB, int WR, int TG = 1, bool PARTS = FCfg<D, RB, WR, TG>::kParts>
 __global__ __launch_bounds__(256 * WR * TG, 1) void attn_f32_kernel(const PassParams p) {
   extern __shared__ __align__(16) unsigned char ring[];
-  if constexpr (FCfg<D, RB, WR, TG>::kParts) {
+  if constexpr (PARTS) {
     if (f32_pass<D, MODE, RB, WR, TG, kProductsParts>(p, ring)) return;
     // (p is the only argument: read again from where the arguments are, instead of kept in registers throughout the first pass)
     typedef const __attribute__((address_space(4))) PassParams* Args;
@@ -982,10 +982,15 @@ hipError_t launch_f32_few(const PassParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int D, int MODE, int RB, int WR, int TG = 1>
+// head_dim 64, 64-row workgroups: tiles each up to which they keep the fp32 products.  Splitting the queries and looking for a NaN cost 3 us a
+// round of workgroups, which the tiles have not earned by then (a refresh step, fp32 products and parts: 12 heads of 464 rows, batch 6, 55 keys
+// 36.1 and 44.6 us; random calls by tiles a workgroup, parts 1 / 2 / 3 / 4 / 5: 1.18 / 1.11 / 1.08 / 0.98 / 0.92 times.  head_dim 128: 0.98 at one).
+constexpr int kFewTilesF32 = 3;
+
+template <int D, int MODE, int RB, int WR, int TG = 1, bool PARTS = FCfg<D, RB, WR, TG>::kParts>
 hipError_t launch_f32(const PassParams& p, hipStream_t s) {
   using C = FCfg<D, RB, WR, TG>;
-  auto kern = attn_f32_kernel<D, MODE, RB, WR, TG>;
+  auto kern = attn_f32_kernel<D, MODE, RB, WR, TG, PARTS>;
   static LdsLimit lim;
   hipError_t e = raise_lds_limit(kern, C::LDS, lim, C::LDS);
   if (e != hipSuccess) return e;
@@ -1039,6 +1044,10 @@ hipError_t launch_f32_rows(const PassParams& p, hipStream_t s) {
   // (32 / 8 heads of 40 rows, 4111 keys, refresh 138 us with 64 rows and 82 with 32)
   constexpr bool fits64 = !(D == 128 && MODE == kPassSparseRefresh);
   if constexpr (fits64) {
+    // (sparse reuse: how many tiles a head has is not known here, and it always takes the parts)
+    if constexpr (D == 64 && MODE != kPassSparseReuse) {
+      if (tile > 32 && (p.nkeys + kKeyTile - 1) / kKeyTile <= kFewTilesF32 * (MODE == kPassInternal ? 1 : p.nsplit)) return launch_f32<D, MODE, 2, 2, 1, false>(p, s);
+    }
     if (tile > 32) return launch_f32<D, MODE, 2, 2>(p, s);
   }
   return launch_f32<D, MODE, 2, 1>(p, s);

@@ -23,17 +23,17 @@ def _factors(rng, n):
     return np.where(rng.integers(0, 2, n) == 0, anywhere, ties).astype(np.float32)
 
 
-@pytest.mark.parametrize("B", [2, 32])                      # 16- and 64-row workgroups
+@pytest.mark.parametrize("B,Bq", [(2, 80), (32, 80), (16, 208)])           # 16- and 64-row workgroups; head_dim 64: parts in the last
 @pytest.mark.parametrize("d", [64, 128])
-def test_score_products_lose_no_more_than_fp32_rounding(B, d):
+def test_score_products_lose_no_more_than_fp32_rounding(B, Bq, d):
     """A score of one product is off by its rounding to fp32 (2^-24 of it) and, in parts, by the cross terms left out (2^-24 again; the
     rounded key has no lower parts and so none of these): the difference of the two is within 3 x 2^-24 of the score.  The sums of
     the small terms, whose roundings are 2^-8 of that, and the weights (exponents below 12, so 1e-6) come on top."""
-    w = wl.Workload(f"sp_{B}_{d}", B, 8, 4, d, 0, 80, 1, 1, "f32", 1.0)
+    w = wl.Workload(f"sp_{B}_{Bq}_{d}", B, 8, 4, d, 0, Bq, 1, 1, "f32", 1.0)
     print(f"[case] {w.name}", flush=True)
     rng = np.random.default_rng(371)
-    Q, K, V = np.zeros((B, 8, 80, d), np.float32), np.zeros((B, 4, 80, d), np.float32), np.zeros((B, 4, 80, d), np.float32)
-    Q[..., 0] = 64 * _factors(rng, B * 8 * 80).reshape(B, 8, 80)
+    Q, K, V = (np.zeros((B, h, Bq, d), np.float32) for h in (8, 4, 4))
+    Q[..., 0] = 64 * _factors(rng, B * 8 * Bq).reshape(B, 8, Bq)
     Q[..., 1] = 1.0
     K[..., 1] = -65536.0 * 16                                # all other keys: far below
     exact, rounded = 70, 5
@@ -47,7 +47,7 @@ def test_score_products_lose_no_more_than_fp32_rounding(B, d):
     got = out.double().cpu().numpy()
     got = np.log(got[..., 2]) - np.log(got[..., 3])
     pair = K[:, np.arange(8) // 2][:, :, [exact, rounded], 0].astype(np.float64)         # [B, 8, 2]
-    scores = Q[..., :1].astype(np.float64) * pair[:, :, None] * d ** -0.5               # [B, 8, 80, 2]
+    scores = Q[..., :1].astype(np.float64) * pair[:, :, None] * d ** -0.5               # [B, 8, Bq, 2]
     want = scores[..., 0] - scores[..., 1]
     bound = scores.max(-1) * (3 + 0.1) * 2.0 ** -24 + 2e-6
     over = np.abs(got - want) / bound
