@@ -985,7 +985,13 @@ hipError_t launch_f32_few(const PassParams& p, hipStream_t s) {
 // head_dim 64, 64-row workgroups: tiles each up to which they keep the fp32 products.  Splitting the queries and looking for a NaN cost 3 us a
 // round of workgroups, which the tiles have not earned by then (a refresh step, fp32 products and parts: 12 heads of 464 rows, batch 6, 55 keys
 // 36.1 and 44.6 us; random calls by tiles a workgroup, parts 1 / 2 / 3 / 4 / 5: 1.18 / 1.11 / 1.08 / 0.98 / 0.92 times.  head_dim 128: 0.98 at one).
-constexpr int kFewTilesF32 = 3;
+// In many rounds it shows longer, as two workgroups of the fp32 products share a CU and hide each other's start and end (external pass, 720
+// workgroups, 4 tiles 1.06 times; 1040, 6 1.05, 960, 8 0.98; 2856, 4 1.16, 2340, 6 1.09, 2336, 9 1.03; internal pass, 4 tiles 27.4 and 28.9 us, 5 31.9 and 33.0; 576 workgroups, 6 52.7 and 56.0, 648, 9
+// 117 and 122).
+inline int few_tiles_f32(long long workgroups, bool internal) {
+  if (internal) return workgroups > 512 ? 9 : 5;
+  return workgroups > 768 ? 8 : workgroups > 512 ? 4 : 3;
+}
 
 template <int D, int MODE, int RB, int WR, int TG = 1, bool PARTS = FCfg<D, RB, WR, TG>::kParts>
 hipError_t launch_f32(const PassParams& p, hipStream_t s) {
@@ -1046,7 +1052,9 @@ hipError_t launch_f32_rows(const PassParams& p, hipStream_t s) {
   if constexpr (fits64) {
     // (sparse reuse: how many tiles a head has is not known here, and it always takes the parts)
     if constexpr (D == 64 && MODE != kPassSparseReuse) {
-      if (tile > 32 && (p.nkeys + kKeyTile - 1) / kKeyTile <= kFewTilesF32 * (MODE == kPassInternal ? 1 : p.nsplit)) return launch_f32<D, MODE, 2, 2, 1, false>(p, s);
+      const int splits = MODE == kPassInternal ? 1 : p.nsplit;
+      const long long workgroups = (long long)p.B * (f32_per_head(MODE) ? p.Hq : p.Hkv) * splits * ((nrows + 63) / 64);
+      if (tile > 32 && (p.nkeys + kKeyTile - 1) / kKeyTile <= few_tiles_f32(workgroups, MODE == kPassInternal) * splits) return launch_f32<D, MODE, 2, 2, 1, false>(p, s);
     }
     if (tile > 32) return launch_f32<D, MODE, 2, 2>(p, s);
   }
