@@ -294,7 +294,12 @@ int step_streams(const fb_shape* s, int ns) {
   const long long heads = (long long)s->batch * s->n_kv_heads, wgs = heads * ((nrows + 127) / 128) * ns, rows256 = (nrows + 255) / 256;
   if (s->block_len <= fb::kKeyTile) {
     if ((heads * rows256 * 2 * ns + 255) / 256 > (wgs + 255) / 256 && !(s->head_dim == 128 && tiles >= 80 * ns)) return 0;
-    const int least = rows_of(s) <= kFoldKernelMaxRows ? 36 : s->head_dim == 64 && wgs <= 256 ? std::max(32, 6 + 4 * ns) : 6 + 4 * ns;
+    int least = 6 + 4 * ns;
+    // The fold kernel's line is later where one round there is a few heads of many rows each (8 splits, head_dim 128, means of random calls at
+    // 32 / 40 / 48 / 56 / 64 tiles: 16 heads of up to 256 rows 1.00 / 0.95 / 0.92 / 0.90 / 0.84 times, 8 of up to 512 1.10 / 1.02 / 0.99 / 0.95 /
+    // 0.91, 4 of up to 1024 1.17 / 1.12 / 1.08 / 1.04 / 0.96).
+    if (rows_of(s) <= kFoldKernelMaxRows) least = s->head_dim == 64 || wgs > 256 || ns > 8 || nrows <= 384 ? 36 : nrows <= 768 ? 48 : 64;
+    else if (s->head_dim == 64 && wgs <= 256) least = std::max(32, least);
     return tiles >= least * ns ? 2 * ns : 0;
   }
   if (tiles < 10 * ns) return 0;

@@ -538,6 +538,8 @@ def test_workspace_of_the_librarys_split_count_holds_its_own_passes(B, Hq, Hkv, 
     (3, 24, 8, 128, 43, 6, 6 * 36, True), (3, 24, 8, 128, 43, 6, 6 * 36 - 1, False),             # fold kernel
     (10, 64, 8, 64, 43, 2, 31, False), (8, 64, 8, 64, 43, 2, 31, True),          # 640 workgroups for 480, 512 for 384
     (4, 64, 4, 64, 62, 2, 63, False), (4, 64, 4, 64, 62, 2, 64, True), (4, 64, 4, 128, 62, 2, 28, True),       # one round of 256
+    (2, 32, 4, 128, 59, 8, 8 * 48 - 1, False), (2, 32, 4, 128, 59, 8, 8 * 48, True), (2, 32, 4, 64, 59, 8, 8 * 36, True),      # few heads of many rows
+    (1, 64, 4, 128, 59, 8, 8 * 64 - 1, False), (1, 64, 4, 128, 59, 8, 8 * 64, True),
     (7, 96, 12, 64, 45, 2, 260, False), (7, 96, 12, 128, 48, 2, 159, False), (7, 96, 12, 128, 48, 2, 160, True), (7, 72, 12, 128, 42, 2, 40, True),
 ])
 def test_refresh_steps_by_streams(B, Hq, Hkv, d, Bq, ns, tiles, streams):
